@@ -117,38 +117,57 @@ def _sequence_tokens(rng, g, n_visual, n_text, d, components, tile):
     return torch.cat(parts)
 
 
-def _layer(case, g, down_std):
-    d, E, F, shared, k, bias_std, _, _, _ = SHAPES[case["shape"]]
+def _weights(case, g, down_std):
+    """Router matrix, router bias (or None), gate / up / down projections of the experts and of the shared ones."""
+    d, E, F, shared, _, bias_std, _, _, _ = SHAPES[case["shape"]]
     td = torch.float32 if case["dtype"] == "f32" else torch.bfloat16
 
     def w(*shape, std=0.02):
         return torch.empty(shape, dtype=td, device="cuda").normal_(0.0, std, generator=g)
 
-    m = binding.FMoE(d_model=d, n_experts=E, d_ffn=F, n_shared=shared, d_ffn_shared=F if shared else 0, k_text=k,
-                     k_visual=case["k_visual"], dtype=case["dtype"])
     bias = torch.randn(E, generator=g, device="cuda") * bias_std if bias_std > 0.0 else None
     sh = [w(shared, F, d), w(shared, F, d), w(shared, d, F, std=down_std)] if shared else [None] * 3
-    m.set_weights(w(E, d), bias, w(E, F, d), w(E, F, d), w(E, d, F, std=down_std), *sh, release_packed=True)
+    return [w(E, d), bias, w(E, F, d), w(E, F, d), w(E, d, F, std=down_std), *sh]
+
+
+def _layer(case, g, down_std):
+    d, E, F, shared, k, _, _, _, _ = SHAPES[case["shape"]]
+    m = binding.FMoE(d_model=d, n_experts=E, d_ffn=F, n_shared=shared, d_ffn_shared=F if shared else 0, k_text=k,
+                     k_visual=case["k_visual"], dtype=case["dtype"])
+    m.set_weights(*_weights(case, g, down_std), release_packed=True)
     return m
 
 
-def prepare(case, seed):
-    d, E, F, shared, k, bias_std, components, tile, _ = SHAPES[case["shape"]]
-    g = torch.Generator(device="cuda")
-    g.manual_seed(seed * 7919 + 17)
-    rng = np.random.Generator(np.random.PCG64(seed))
+def _inputs(case, g, rng):
+    """Packed rows, modality mask, sequence offsets and the attention importance (or None)."""
+    d, _, _, _, _, _, components, tile, _ = SHAPES[case["shape"]]
     nv, nt = _lens(case["visual"]), _lens(case["text"])
     td = torch.float32 if case["dtype"] == "f32" else torch.bfloat16
     x = torch.cat([_sequence_tokens(rng, g, a, b, d, components, tile) for a, b in zip(nv, nt)]).to(td).contiguous()
     vis = torch.from_numpy(np.concatenate([np.repeat([1, 0], [a, b]) for a, b in zip(nv, nt)]).astype(np.uint8)).cuda()
     cu = torch.from_numpy(np.concatenate([[0], np.cumsum(np.add(nv, nt))]).astype(np.int32)).cuda()
+    # attention importance of every token: non-negative, long-tailed
+    attn = torch.empty(x.shape[0], device="cuda").exponential_(1.0, generator=g) if case["attention"] else None
+    return x, vis, cu, attn
+
+
+def _generators(seed):
+    g = torch.Generator(device="cuda")
+    g.manual_seed(seed * 7919 + 17)
+    return g, np.random.Generator(np.random.PCG64(seed))
+
+
+def prepare(case, seed):
+    d, k = SHAPES[case["shape"]][0], SHAPES[case["shape"]][4]
+    g, rng = _generators(seed)
+    nv, nt = _lens(case["visual"]), _lens(case["text"])
+    x, vis, cu, attn = _inputs(case, g, rng)
+    td = x.dtype
     T, B = x.shape[0], len(nv)
     params = None
     if case["retention"] < 1.0:
         params = binding.prune_params(retention=case["retention"], window=case["window"], alpha=case["alpha"],
                                       gamma=case["gamma"])
-    # attention importance of every token: non-negative, long-tailed
-    attn = torch.empty(T, device="cuda").exponential_(1.0, generator=g) if case["attention"] else None
     kept = binding.kept_count(nv, nt, case["retention"])
     s = {"case": case, "x": x, "vis": vis, "cu": cu, "params": params, "attn": attn, "n": kept, "nv": nv, "nt": nt,
          "out": torch.empty((T, d), dtype=td, device="cuda"),
@@ -247,3 +266,95 @@ def tolerance(case):
     # Against fp64 with the router's own decisions the listed layers are off by rel 2e-3, max 9e-3 (bf16) and rel
     # 4e-7, max 2e-6 (fp32): four times that.  Decisions (experts, kept tokens) are reproducible and stay the same.
     return {"rel": 2e-6, "max": 1e-5} if case["dtype"] == "f32" else {"rel": 8e-3, "max": 4e-2}
+
+
+def _kept(case, P, attn, x):
+    """Kept token indices and the layer input after merging: the drop rule and the window merging (token means
+    rescaled to the window's largest norm) on fp64 routing probabilities."""
+    W, r, alpha = case["window"], case["retention"], case["alpha"]
+    gamma = float(np.float32(case["gamma"]))    # a C float in the parameters
+    keep, xm, start = np.ones(P.shape[0], bool), x, 0
+    for n_visual, n_text in zip(_lens(case["visual"]), _lens(case["text"])):
+        n = (n_visual + W - 1) // W
+        if n:
+            rows = torch.zeros((n * W, P.shape[1]), dtype=torch.float64, device=P.device)
+            rows[:n_visual] = P[start:start + n_visual]
+            rows = rows.view(n, W, -1)
+            size = torch.full((n,), W, device=P.device)
+            size[-1] = n_visual - (n - 1) * W
+            mean = rows.sum(1) / size[:, None]
+            norms = rows.norm(dim=2) * mean.norm(dim=1)[:, None]
+            cos = torch.where(norms > 0, (rows * mean[:, None]).sum(2) / norms.clamp_min(1e-300), 0.0)
+            C = (cos.sum(1) / size).cpu().numpy()
+            size = size.cpu().numpy()
+            C[size == 1] = 1.0
+            A = np.zeros(n)
+            if attn is not None:
+                A = np.pad(attn[start:start + n_visual].double().cpu().numpy(), (0, n * W - n_visual)).reshape(n, W).sum(1)
+                A = A / A.max() if A.max() > 0 else A
+                C = alpha * C - (1.0 - alpha) * A
+            eta = max(1, min(n_visual, int(math.floor(r * n_visual + 0.5))))
+            u, left, merged = n_visual - eta, int(math.floor(eta * gamma)), np.zeros(n, bool)
+            for i in np.lexsort((np.arange(n), -C)):
+                if left == 0:
+                    break
+                if 2 <= size[i] <= u + 1:
+                    t = start + i * W
+                    if xm is x:
+                        xm = x.clone()
+                    m = x[t:t + size[i]].double()
+                    top, m = m.norm(dim=1).max(), m.mean(0)
+                    xm[t] = (m * (top / m.norm())).to(x.dtype)
+                    keep[t + 1:t + size[i]] = False
+                    merged[i], u, left = True, u - (size[i] - 1), left - 1
+            for i in np.lexsort((np.arange(n), -C, A)):
+                if u == 0:
+                    break
+                if not merged[i]:
+                    cut = min(u, size[i])
+                    keep[start + i * W + size[i] - cut:start + i * W + size[i]] = False
+                    u -= cut
+        start += n_visual + n_text
+    return torch.from_numpy(np.flatnonzero(keep)).cuda(), xm
+
+
+def exact(case, seed):
+    """The floating outputs in 64 bits.  Near-ties can be decided differently from the fp32 routing probabilities;
+    down a stack those differences travel, so the stack has none."""
+    if case["path"] == "stack":
+        return None
+    d, E, F, shared, k, _, _, _, _ = SHAPES[case["shape"]]
+    g, rng = _generators(seed)
+    x, vis, _, attn = _inputs(case, g, rng)
+    router, bias, w_gate, w_up, w_down, s_gate, s_up, s_down = _weights(case, g, 0.02)
+    kmax = max(k, case["k_visual"])
+
+    def route(v, visual):
+        z = v.double() @ router.double().T
+        P = torch.softmax(z if bias is None else z + bias.double(), dim=1)
+        p, e = P.topk(kmax, dim=1)
+        live = torch.arange(kmax, device=v.device)[None, :] < torch.where(visual.bool(), case["k_visual"], k)[:, None]
+        p = p * live
+        return P, p / p.sum(1, keepdim=True), torch.where(live, e, -1)
+
+    def ffn(v, a, b, c):
+        return (torch.nn.functional.silu(v @ a.double().T) * (v @ b.double().T)) @ c.double().T
+
+    P, gates, experts = route(x, vis)
+    kept, xm = torch.arange(x.shape[0], device=x.device), x
+    if case["retention"] < 1.0:
+        kept, xm = _kept(case, P, attn, x)
+    v, gk, ek = xm[kept], gates[kept], experts[kept]
+    if xm is not x:
+        _, gk, ek = route(v, vis[kept])
+    v = v.double()
+    out = v.clone() if case["residual"] else torch.zeros_like(v)
+    for i in range(shared):
+        out += ffn(v, s_gate[i], s_up[i], s_down[i])
+    for e in range(E):
+        row, slot = (ek == e).nonzero(as_tuple=True)
+        if len(row):
+            out[row] += gk[row, slot, None] * ffn(v[row], w_gate[e], w_up[e], w_down[e])
+    if case["path"] == "layer":
+        return {"out": out}
+    return {"probs": P, "gates": gates, "out": out}
