@@ -30,7 +30,7 @@ __device__ __forceinline__ float wave_sum_butterfly(float p) {
 __global__ __launch_bounds__(256) void seq_ordinals_kernel(
     const uint8_t* __restrict__ is_visual, const int32_t* __restrict__ cu, int T,
     int32_t* __restrict__ vis_ord, int32_t* __restrict__ vis_tok, int32_t* __restrict__ seq_nv) {
-  __shared__ int wave_tot[4];
+  __shared__ int wave_tot[4 * ORD_ROWS];
   seq_ordinals_block(is_visual, cu, blockIdx.x, T, vis_ord, vis_tok, seq_nv, wave_tot);
 }
 

@@ -23,9 +23,12 @@ __device__ __forceinline__ int find_seq(const int32_t* cu, int B, int g) {
   return lo;
 }
 
-// Visual ordinals of sequence b, by one 256-thread block (wave_tot: 4 ints of LDS).
+// Visual ordinals of sequence b, by one 256-thread block (wave_tot: 4 * ORD_ROWS ints of LDS).
 // vis_ord[t] = number of visual tokens before t in its sequence (for visual t), -1 for text;
 // vis_tok[cu[b] + j] = global index of the j-th visual token of sequence b; seq_nv[b] = N_v.
+// ORD_ROWS rows of 256 tokens are fetched and counted together: the scan is a chain of memory latencies,
+// and it shares a launch with the router, which it must not outlast.
+constexpr int ORD_ROWS = 8;
 __device__ __forceinline__ void seq_ordinals_block(const uint8_t* __restrict__ is_visual,
                                                    const int32_t* __restrict__ cu, int b, int T,
                                                    int32_t* __restrict__ vis_ord,
@@ -35,25 +38,36 @@ __device__ __forceinline__ void seq_ordinals_block(const uint8_t* __restrict__ i
   seq_range(cu, b, T, s, e);
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   int running = 0;
-  for (int base = s; base < e; base += 256) {
-    const int t = base + threadIdx.x;
-    const bool vis = (t < e) && (is_visual[t] != 0);
-    const unsigned long long mask = __ballot(vis);
-    const int before = __popcll(mask & ((1ull << lane) - 1ull));
-    if (lane == 0) wave_tot[wave] = __popcll(mask);
-    __syncthreads();
-    int wave_base = 0, total = 0;
+  for (int base = s; base < e; base += 256 * ORD_ROWS) {
+    bool vis[ORD_ROWS];
+    unsigned long long mask[ORD_ROWS];
 #pragma unroll
-    for (int w = 0; w < 4; ++w) {
-      if (w < wave) wave_base += wave_tot[w];
-      total += wave_tot[w];
+    for (int r = 0; r < ORD_ROWS; ++r) {
+      const int t = base + r * 256 + (int)threadIdx.x;
+      vis[r] = is_visual[t < e ? t : e - 1] != 0 && t < e;
     }
-    if (t < e) {
-      const int ord = running + wave_base + before;
-      vis_ord[t] = vis ? ord : -1;
-      if (vis) vis_tok[s + ord] = t;
+#pragma unroll
+    for (int r = 0; r < ORD_ROWS; ++r) {
+      mask[r] = __ballot(vis[r]);
+      if (lane == 0) wave_tot[r * 4 + wave] = __popcll(mask[r]);
     }
-    running += total;
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < ORD_ROWS; ++r) {
+      int wave_base = 0, total = 0;
+#pragma unroll
+      for (int w = 0; w < 4; ++w) {
+        if (w < wave) wave_base += wave_tot[r * 4 + w];
+        total += wave_tot[r * 4 + w];
+      }
+      const int t = base + r * 256 + (int)threadIdx.x;
+      if (t < e) {
+        const int ord = running + wave_base + __popcll(mask[r] & ((1ull << lane) - 1ull));
+        vis_ord[t] = vis[r] ? ord : -1;
+        if (vis[r]) vis_tok[s + ord] = t;
+      }
+      running += total;
+    }
     __syncthreads();
   }
   if (threadIdx.x == 0) seq_nv[b] = running;

@@ -14,13 +14,25 @@
 //  sum:    lane l adds q[l], q[l+64], ... in that order from +0, then a 6-level xor butterfly
 //          (p[l] += p[l xor s], s = 32,16,..,1).
 //
-// Work split: a 256-thread block owns 16 tokens; its 4 wavefronts split the experts (NB blocks of
-// 16 experts each).  Token rows are staged through LDS in 128-wide k chunks, widened to fp32 and
-// de-interleaved so that a lane fetches the operands of four consecutive MFMAs with one 16-byte
-// LDS read; router weights come from a private fp32 copy that fmoe_set_weights lays out in
-// exactly the per-lane order the MFMA consumes (one coalesced 16-byte global load per four
-// MFMAs); several chunks of both are kept in flight in registers.  Logits meet in LDS, then each wavefront does softmax /
-// top-k for four tokens with lanes mapped to experts.
+// Work split: a 256-thread block owns 16 tokens; its 4 wavefronts split the
+// experts (NB blocks of 16 experts each).  The fp32 matrix instruction runs on the vector pipe: a chain of
+// dependent ones issues every 32 cycles (so one wavefront can fill a SIMD), but every vector instruction
+// between two of them adds its own 4 cycles and a dozen more for the change-over.  The reduction is therefore
+// built to need almost none:
+//   weights: a private fp32 copy that fmoe_set_weights lays out in exactly the per-lane order the
+//            instruction consumes; one 16-byte buffer load per four instructions, scalar offsets, a register
+//            ring many groups deep;
+//   x:       staged through LDS in chunks of 128 k, widened to fp32 and de-interleaved on the way in (eight
+//            vector instructions per thread and chunk), so that one 16-byte LDS read feeds four
+//            instructions; two LDS buffers and one barrier per chunk, taken while the operands of the
+//            chunk's last group already sit in registers, so that the next chunk's first read flies behind
+//            that group's instructions.
+// Logits meet in LDS, then a wavefront does softmax / top-k for four tokens at once, sixteen lanes each
+// (one token at a time over all 64 lanes took 4.6 us a block, this takes 2.0).
+// Measured against single-buffered staging with two barriers a chunk and the one-token epilogue: 8 tokens,
+// d 2048, 64 experts 19.5 -> 14.4 us; 1600 tokens, d 1280 17.0 -> 12.2; 8192 tokens, d 2048, 128 experts
+// 64.5 -> 50.0; 22016 tokens, d 2048, 64 experts 83.6 -> 70.  Bound: the chain itself, 44 cycles per
+// instruction of the 32 it needs (the rest is the staging's vector work and the barrier).
 
 #include <type_traits>
 
@@ -31,55 +43,44 @@ namespace {
 
 typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4_t;
 typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
-typedef float fx4_t __attribute__((ext_vector_type(4)));
 
 constexpr int TOKB = 16;           // tokens per block
 constexpr int KC = 128;            // k per LDS chunk
-constexpr int NG = KC / 16;        // groups of four MFMAs per chunk
-constexpr int RS = KC / 4 + 4;     // LDS row stride in floats (rows = kq*16 + token)
+constexpr int NG = KC / 16;        // groups of four matrix instructions per chunk
+constexpr int RS = KC / 4 + 4;     // LDS row stride in floats (rows = kq*16 + token): 16 rows on 16 bank groups
+constexpr int XPF = 4;             // chunks of x in flight in registers
 
-// k groups (of 16) in the packed router weights: d rounded up to whole chunks, then to a multiple of
-// 5 chunks or 4 chunks (the prefetch depths the kernel is instantiated with), whichever is larger
-__host__ __device__ inline int router_groups(int d) {
-  const int chunks = (d + KC - 1) / KC;
-  const int p4 = (chunks + 3) / 4 * 4, p5 = (chunks + 4) / 5 * 5;
-  return (p4 > p5 ? p4 : p5) * NG;
+__host__ __device__ inline int router_chunks(int d) { return (d + KC - 1) / KC; }
+
+// v of the lane `ROT` places on in the row of 16
+template <int ROT>
+__device__ __forceinline__ float row_rotate(float v) {
+  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x120 + ROT, 0xf, 0xf, false));
 }
-
-__device__ __forceinline__ float wave_sum_butterfly(float p) {
-#pragma unroll
-  for (int s = 32; s >= 1; s >>= 1) p = p + __shfl_xor(p, s, 64);
-  return p;
+template <int ROT>
+__device__ __forceinline__ int row_rotate(int v) {
+  return __builtin_amdgcn_update_dpp(0, v, 0x120 + ROT, 0xf, 0xf, false);
 }
-
-__device__ __forceinline__ float wave_max(float v) {
-#pragma unroll
-  for (int s = 32; s >= 1; s >>= 1) {
-    float o = __shfl_xor(v, s, 64);
-    v = (o > v) ? o : v;
-  }
-  return v;
+// Over the 16 lanes of a row, the result in every lane.  After the step by 8 all values repeat with period 8,
+// so the step by 4 pairs what an exclusive-or by 4 would, and so on: the sum is the xor butterfly 8, 4, 2, 1.
+__device__ __forceinline__ float row_sum_butterfly(float v) {
+  v = v + row_rotate<8>(v);
+  v = v + row_rotate<4>(v);
+  v = v + row_rotate<2>(v);
+  return v + row_rotate<1>(v);
 }
-
-// Maximum over the 64 lanes, returned in every lane.  Inside a row of 16 lanes: xor-1 and xor-2 quad
-// permutes, then the half-row and full-row mirrors (each step pairs lanes holding different partial
-// maxima); across the four rows: one lane read per row.
-__device__ __forceinline__ float wave_max_all(float v) {
-  auto step = [](float x, auto ctrl) {
-    const int o = __builtin_amdgcn_update_dpp(0, __float_as_int(x), decltype(ctrl)::value, 0xf, 0xf, false);
-    const float y = __int_as_float(o);
-    return (y > x) ? y : x;
-  };
-  v = step(v, std::integral_constant<int, 0xB1>{});    // quad_perm [1,0,3,2]
-  v = step(v, std::integral_constant<int, 0x4E>{});    // quad_perm [2,3,0,1]
-  v = step(v, std::integral_constant<int, 0x141>{});   // row_half_mirror
-  v = step(v, std::integral_constant<int, 0x140>{});   // row_mirror
-  const float r0 = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 0));
-  const float r1 = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 16));
-  const float r2 = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 32));
-  const float r3 = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 48));
-  const float a = (r1 > r0) ? r1 : r0, b = (r3 > r2) ? r3 : r2;
-  return (b > a) ? b : a;
+__device__ __forceinline__ float larger(float v, float o) { return (o > v) ? o : v; }
+__device__ __forceinline__ float row_max(float v) {
+  v = larger(v, row_rotate<8>(v));
+  v = larger(v, row_rotate<4>(v));
+  v = larger(v, row_rotate<2>(v));
+  return larger(v, row_rotate<1>(v));
+}
+__device__ __forceinline__ int row_min(int v) {
+  v = min(v, row_rotate<8>(v));
+  v = min(v, row_rotate<4>(v));
+  v = min(v, row_rotate<2>(v));
+  return min(v, row_rotate<1>(v));
 }
 
 __device__ __forceinline__ float exp_fixed(float x) {
@@ -120,27 +121,20 @@ __global__ void pack_router_kernel(const WT* __restrict__ w, float* __restrict__
   }
 }
 
+// One thread's share of a chunk of x (16 tokens x 128 k): 16-byte units, widened and de-interleaved into LDS
+// rows kq*16 + token, k = 4*step + kq at position step.
 template <typename XT> struct XStage;
 template <> struct XStage<bf16_t> {
-  static constexpr int UNITS = 1;  // 16 tokens x 128 k / 8 per 16-byte load / 256 threads
-  u32x4_t v[UNITS];
-  // Unpredicated: a token past T re-reads the last token (its logits are never used) and k past d
-  // re-reads the row's last chunk (the packed weights are zero there).
-  __device__ __forceinline__ void load(const bf16_t* x, int t0, int T, int d, int c0, int tid) {   // t0: the tile's first token
+  static constexpr int UNITS = 1;
+  static __device__ __forceinline__ int token(int tid, int) { return tid >> 4; }
+  static __device__ __forceinline__ int k(int tid, int) { return 8 * (tid & 15); }
+  static __device__ __forceinline__ void store(float* xs, int tid, int, u32x4_t v) {
     const int tok = tid >> 4, cu = tid & 15;
-    int k = c0 + 8 * cu, t = t0 + tok;
-    k = k < d ? k : d - 8;
-    t = t < T ? t : T - 1;
-    v[0] = *reinterpret_cast<const u32x4_t*>(x + (size_t)t * d + k);
-  }
-  __device__ __forceinline__ void store(float* xs, int tid) const {
-    const int tok = tid >> 4, cu = tid & 15;
-    const uint32_t w[4] = {v[0][0], v[0][1], v[0][2], v[0][3]};
     float f[8];
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      f[2 * i] = __uint_as_float(w[i] << 16);
-      f[2 * i + 1] = __uint_as_float(w[i] & 0xffff0000u);
+      f[2 * i] = __uint_as_float(v[i] << 16);
+      f[2 * i + 1] = __uint_as_float(v[i] & 0xffff0000u);
     }
     // element i of the unit has k = 8cu + i: kq = i%4, step = 2cu + i/4
 #pragma unroll
@@ -149,29 +143,13 @@ template <> struct XStage<bf16_t> {
   }
 };
 template <> struct XStage<float> {
-  static constexpr int UNITS = 2;  // 16 x 128 / 4 / 256
-  fx4_t v[UNITS];
-  __device__ __forceinline__ void load(const float* x, int t0, int T, int d, int c0, int tid) {
+  static constexpr int UNITS = 2;
+  static __device__ __forceinline__ int token(int tid, int u) { return (tid + u * 256) >> 5; }
+  static __device__ __forceinline__ int k(int tid, int) { return 4 * (tid & 31); }
+  static __device__ __forceinline__ void store(float* xs, int tid, int u, u32x4_t v) {
+    const int tok = token(tid, u), cu = tid & 31;
 #pragma unroll
-    for (int u = 0; u < UNITS; ++u) {
-      const int unit = tid + u * 256;
-      const int tok = unit >> 5, cu = unit & 31;
-      int k = c0 + 4 * cu, t = t0 + tok;
-      k = k < d ? k : d - 4;
-      t = t < T ? t : T - 1;
-      v[u] = *reinterpret_cast<const fx4_t*>(x + (size_t)t * d + k);
-    }
-  }
-  __device__ __forceinline__ void store(float* xs, int tid) const {
-#pragma unroll
-    for (int u = 0; u < UNITS; ++u) {
-      const int unit = tid + u * 256;
-      const int tok = unit >> 5, cu = unit & 31;
-      xs[(0 * 16 + tok) * RS + cu] = v[u][0];
-      xs[(1 * 16 + tok) * RS + cu] = v[u][1];
-      xs[(2 * 16 + tok) * RS + cu] = v[u][2];
-      xs[(3 * 16 + tok) * RS + cu] = v[u][3];
-    }
+    for (int kq = 0; kq < 4; ++kq) xs[(kq * 16 + tok) * RS + cu] = __uint_as_float(v[kq]);
   }
 };
 
@@ -191,305 +169,273 @@ __device__ __forceinline__ unsigned long long splitmix64_nth(unsigned long long 
   return z ^ (z >> 31);
 }
 
-// TT = token tiles of 16 per block (1 or 2).  With two tiles every wavefront runs two independent
-// accumulation chains on the same weight fragments: a logit's own chain keeps its order (so its bits),
-// the matrix pipe gets a second instruction to issue while the first chain's next link waits for its
-// predecessor, and a token costs half the weight loads.  Taken for large batches, where there are
-// enough blocks to fill the chip either way.
-template <typename XT, int NB, int PF, bool SEL, int TT>
+// R = groups of weights in flight.  (Two token tiles per block, which halve the weight loads, measured the same
+// at 22016 tokens / 64 experts and 3 % slower at 8192 / 128.)
+template <typename XT, int NB, int R, bool SEL>
 __global__ __launch_bounds__(256) void route_kernel(
-    const XT* __restrict__ x, const fx4_t* __restrict__ wp, const float* __restrict__ bias,
-    const uint8_t* __restrict__ is_visual, int T, int d, int E, int Eb, int G, int nch, int k_text,
+    const XT* __restrict__ x, const float* __restrict__ wp, const float* __restrict__ bias,
+    const uint8_t* __restrict__ is_visual, int T, int d, int E, int Eb, int k_text,
     int k_visual, int Kmax, int renorm, float* __restrict__ probs, int32_t* __restrict__ topk_idx,
     float* __restrict__ topk_gate, int route_blocks, fmoe_ordinals_job ord, const int32_t* __restrict__ T_dev,
     fmoe_selection selp) {
-  __shared__ __align__(16) float xs[TT][64 * RS];
-  __shared__ float zs[TT * TOKB][4 * NB * 16 + 1];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  typedef XStage<XT> XS;
+  constexpr int UNITS = XS::UNITS, PER_UNIT = 16 / (int)sizeof(XT);
+  constexpr int ES = 4 * NB * 16 + 4;   // row stride of the logits
+  constexpr int XS_FLOATS = 2 * 64 * RS, ZS_FLOATS = TOKB * ES;
+  __shared__ __align__(16) float smem[XS_FLOATS > ZS_FLOATS ? XS_FLOATS : ZS_FLOATS];   // x chunks, later the logits
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   if ((int)blockIdx.x >= route_blocks) {   // rider blocks: per-sequence visual ordinals for the pruning stage
     seq_ordinals_block(is_visual, ord.cu, (int)blockIdx.x - route_blocks, T, ord.vis_ord, ord.vis_tok,
-                       ord.seq_nv, reinterpret_cast<int*>(&xs[0][0]));
+                       ord.seq_nv, reinterpret_cast<int*>(smem));
     return;
   }
-  const int t0 = blockIdx.x * (TT * TOKB);
+  const int t0 = blockIdx.x * TOKB;
   if (T_dev != nullptr) {   // the batch holds fewer tokens than its capacity
     const int Td = *T_dev;
     T = Td < T ? Td : T;
     if (t0 >= T) return;
   }
 
-  f32x4_t acc[TT][NB];
+  f32x4_t acc[NB];
 #pragma unroll
-  for (int tt = 0; tt < TT; ++tt)
-#pragma unroll
-    for (int nb = 0; nb < NB; ++nb) acc[tt][nb] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+  for (int nb = 0; nb < NB; ++nb) acc[nb] = f32x4_t{0.f, 0.f, 0.f, 0.f};
 
-  // PF chunks of operands are kept in flight in registers (the block's wavefronts are often alone
-  // on their SIMDs, so memory latency has to be covered inside the wavefront)
-  fx4_t wbuf[PF][NG][NB];
-  XStage<XT> xbuf[PF][TT];
-  const fx4_t* wsrc[NB];
+  // Loads go through buffer descriptors over the block's token rows and the wavefront's weights: a lane offset
+  // that never changes and a scalar one per load.  All indices are clamped (tokens past T re-read the last
+  // token, whose logits are then not used; k past d re-reads the end of the row, where the packed weights are
+  // zero; chunks past the last re-read it).
+  const int nch = router_chunks(d), G = nch * NG;
+  const int eb0 = wave * NB < Eb ? wave * NB : Eb - 1;
+  const __amdgpu_buffer_rsrc_t w_rsrc =
+      __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(wp) + (size_t)eb0 * G * 256, 0, 0xffffffff, 0x00020000);
+  const __amdgpu_buffer_rsrc_t x_rsrc =
+      __builtin_amdgcn_make_buffer_rsrc(const_cast<XT*>(x) + (size_t)t0 * d, 0, 0xffffffff, 0x00020000);
+  uint32_t wbase[NB];   // scalar
 #pragma unroll
-  for (int nb = 0; nb < NB; ++nb) {
-    int eb = wave * NB + nb;
-    eb = eb < Eb ? eb : Eb - 1;   // expert blocks past E recompute the last one; never read back
-    wsrc[nb] = wp + (size_t)eb * G * 64 + lane;
+  for (int nb = 0; nb < NB; ++nb) {   // expert blocks past E recompute the last one; never read back
+    const int eb = wave * NB + nb < Eb ? wave * NB + nb : Eb - 1;
+    wbase[nb] = (uint32_t)(eb - eb0) * (uint32_t)G * 1024u;
   }
-  auto load_chunk = [&](int slot, int c0) {
+  const uint32_t lane16 = (uint32_t)lane * 16u;
+  uint32_t xrow[UNITS];
 #pragma unroll
-    for (int tt = 0; tt < TT; ++tt) xbuf[slot][tt].load(x, t0 + tt * TOKB, T, d, c0, tid);
+  for (int u = 0; u < UNITS; ++u) {
+    const int row = XS::token(tid, u), last = T - 1 - t0;
+    xrow[u] = (uint32_t)(row < last ? row : last) * (uint32_t)d;
+  }
+  u32x4_t xbuf[XPF][UNITS];
+  f32x4_t wbuf[R][NB];
+  auto load_x = [&](int slot, int c) {
+    const int k0 = (c < nch ? c : nch - 1) * KC;   // scalar
 #pragma unroll
-    for (int gl = 0; gl < NG; ++gl)
-#pragma unroll
-      for (int nb = 0; nb < NB; ++nb) wbuf[slot][gl][nb] = wsrc[nb][(size_t)(c0 / 16 + gl) * 64];
+    for (int u = 0; u < UNITS; ++u) {
+      int k = k0 + XS::k(tid, u);
+      k = k < d ? k : d - PER_UNIT;
+      xbuf[slot][u] = __builtin_amdgcn_raw_buffer_load_b128(x_rsrc, (xrow[u] + (uint32_t)k) * (uint32_t)sizeof(XT), 0, 0);
+    }
   };
-  // nch chunks (a multiple of PF; d is zero-padded up to it in the packed weights).  The loop body
-  // is straight-line code with a fixed number of loads per step so that the waits on them can be
-  // counted exactly: chunk c is multiplied while chunks c+1 .. c+PF are in flight.
-  const int xrow = ((lane >> 4) * 16 + (lane & 15)) * RS;
-  auto step = [&](int p) {
+  auto load_w = [&](int slot, int g) {
+    const uint32_t off = (uint32_t)(g < G ? g : G - 1) * 1024u;   // scalar
 #pragma unroll
-    for (int tt = 0; tt < TT; ++tt) xbuf[p][tt].store(xs[tt], tid);
-    __syncthreads();
+    for (int nb = 0; nb < NB; ++nb)
+      wbuf[slot][nb] = __builtin_bit_cast(f32x4_t, __builtin_amdgcn_raw_buffer_load_b128(w_rsrc, lane16, wbase[nb] + off, 0));
+  };
+  auto store_x = [&](int buf, int slot) {
 #pragma unroll
-    for (int gl = 0; gl < NG; ++gl) {
-      fx4_t xa[TT];
+    for (int u = 0; u < UNITS; ++u) XS::store(smem + buf * (64 * RS), tid, u, xbuf[slot][u]);
+  };
+  f32x4_t xa[2];
+  const int xlane = ((lane >> 4) * 16 + (lane & 15)) * RS;
+  auto read_x = [&](int o, int buf, int gl) {
+    xa[o] = *reinterpret_cast<const f32x4_t*>(&smem[buf * (64 * RS) + xlane + gl * 4]);
+  };
+  // Chunk c is multiplied while chunk c+1 goes into the other LDS buffer, chunks up to c+XPF and R groups of
+  // weights are in flight.
+  static_assert(XPF % 2 == 0 && (XPF * NG) % R == 0, "ring indices are compile-time");
 #pragma unroll
-      for (int tt = 0; tt < TT; ++tt) xa[tt] = *reinterpret_cast<const fx4_t*>(&xs[tt][xrow + gl * 4]);
+  for (int u = 0; u < XPF; ++u) load_x(u, u);
 #pragma unroll
-      for (int nb = 0; nb < NB; ++nb) {
-        const fx4_t wv = wbuf[p][gl][nb];
+  for (int r = 0; r < R; ++r) {   // in ring order: the waits in the loop count on it
+    load_w(r, r);
+    __builtin_amdgcn_sched_barrier(0);
+  }
+  store_x(0, 0);
+  load_x(0, XPF);
+  __syncthreads();
+  read_x(0, 0, 0);
+  for (int c0 = 0; c0 < nch; c0 += XPF) {
 #pragma unroll
-        for (int q = 0; q < 4; ++q)   // each chain in ascending k; the chains of the tiles alternate
+    for (int u = 0; u < XPF; ++u) {
+      const int c = c0 + u;
+      if (c >= nch) break;   // uniform
 #pragma unroll
-          for (int tt = 0; tt < TT; ++tt)
-            acc[tt][nb] = __builtin_amdgcn_mfma_f32_16x16x4f32(xa[tt][q], wv[q], acc[tt][nb], 0, 0, 0);
+      for (int gl = 0; gl < NG; ++gl) {
+        const int o = gl & 1, slot = (u * NG + gl) % R;
+        if (gl == NG - 1) {
+          // every wavefront has its operands of this chunk's last group and has stored its part of the next chunk
+          __syncthreads();
+          read_x(o ^ 1, (u + 1) & 1, 0);
+        } else {
+          read_x(o ^ 1, u & 1, gl + 1);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int i = 0; i < 4; ++i)   // each chain in ascending k; the chains alternate
+#pragma unroll
+          for (int nb = 0; nb < NB; ++nb)
+            acc[nb] = __builtin_amdgcn_mfma_f32_16x16x4f32(xa[o][i], wbuf[slot][nb][i], acc[nb], 0, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);
+        load_w(slot, c * NG + gl + R);
+        if (gl == 0) {
+          store_x((u + 1) & 1, (u + 1) % XPF);
+          load_x((u + 1) % XPF, c + 1 + XPF);
+        }
+        __builtin_amdgcn_sched_barrier(0);
       }
     }
-  };
-#pragma unroll
-  for (int p = 0; p < PF; ++p) load_chunk(p, p * KC);
-  int c = 0;
-  for (; c + PF < nch; c += PF) {
-#pragma unroll
-    for (int p = 0; p < PF; ++p) {
-      step(p);
-      load_chunk(p, (c + p + PF) * KC);
-      __syncthreads();
-    }
   }
-#pragma unroll
-  for (int p = 0; p < PF; ++p) {
-    step(p);
-    __syncthreads();
-  }
+  __syncthreads();   // the chunks' LDS becomes the logits'
 
   // accumulator register v of lane l: token 4*(l/16) + v, expert (block)*16 + l%16
 #pragma unroll
-  for (int tt = 0; tt < TT; ++tt)
+  for (int nb = 0; nb < NB; ++nb) {
+    const int e = (wave * NB + nb) * 16 + (lane & 15);
 #pragma unroll
-    for (int nb = 0; nb < NB; ++nb) {
-      const int e = (wave * NB + nb) * 16 + (lane & 15);
-#pragma unroll
-      for (int v = 0; v < 4; ++v) zs[tt * TOKB + 4 * (lane >> 4) + v][e] = acc[tt][nb][v];
-    }
+    for (int v = 0; v < 4; ++v) smem[(4 * (lane >> 4) + v) * ES + e] = acc[nb][v];
+  }
   __syncthreads();
 
-  // softmax, top-k and gates: lanes <-> experts (expert e lives in lane e%64, register e/64).
-  // The wavefront's four tokens are processed side by side so that the cross-lane reduction
-  // chains of different tokens overlap.
-  for (int tile = 0; tile < TT; ++tile) {   // four tokens per wavefront at a time
-    constexpr int TQ = 4;
-    float P[TQ][NB], part[TQ], mx[TQ];
-    int tt[TQ];
-    bool tv[TQ];
-  #pragma unroll
-    for (int tq = 0; tq < TQ; ++tq) {
-      const int tok = tile * TOKB + wave * TQ + tq;
-      tv[tq] = (t0 + tok) < T;
-      tt[tq] = tv[tq] ? t0 + tok : T - 1;
-      mx[tq] = -INFINITY;
-  #pragma unroll
-      for (int i = 0; i < NB; ++i) {
-        const int e = lane + 64 * i;
-        float v = -INFINITY;
-        if (e < E) {
-          v = zs[tok][e];
-          if (bias != nullptr) v = v + bias[e];
-        }
-        P[tq][i] = v;
-        mx[tq] = (v > mx[tq]) ? v : mx[tq];
-      }
+  // Softmax, top-k and gates: four tokens per wavefront side by side, token q of them in lanes 16q .. 16q+15.
+  // Lane j of a token holds the experts 16r + j, r = 0 .. NR-1.
+  constexpr int NR = 4 * NB;
+  const int j = lane & 15;
+  const int tok = wave * 4 + (lane >> 4);
+  const bool tv = (t0 + tok) < T;
+  const int t = tv ? t0 + tok : T - 1;
+  float P[NR];
+  float mx = -INFINITY;
+#pragma unroll
+  for (int r = 0; r < NR; ++r) {
+    const int e = 16 * r + j;
+    float v = -INFINITY;
+    if (e < E) {
+      v = smem[tok * ES + e];
+      if (bias != nullptr) v = v + bias[e];
     }
-  #pragma unroll
-    for (int s = 32; s >= 1; s >>= 1)
-  #pragma unroll
-      for (int tq = 0; tq < TQ; ++tq) {
-        const float o = __shfl_xor(mx[tq], s, 64);
-        mx[tq] = (o > mx[tq]) ? o : mx[tq];
-      }
-  #pragma unroll
-    for (int tq = 0; tq < TQ; ++tq) {
-      part[tq] = 0.0f;
-  #pragma unroll
-      for (int i = 0; i < NB; ++i) {
-        const int e = lane + 64 * i;
-        float q = 0.0f;
-        if (e < E) {
-          q = exp_fixed(P[tq][i] - mx[tq]);
-          part[tq] = part[tq] + q;
-        }
-        P[tq][i] = q;
-      }
-    }
-  #pragma unroll
-    for (int s = 32; s >= 1; s >>= 1)
-  #pragma unroll
-      for (int tq = 0; tq < TQ; ++tq) part[tq] = part[tq] + __shfl_xor(part[tq], s, 64);
-    // Inside the fused layer (the launch that also carries the ordinal blocks) the probabilities only feed
-    // the window scores, which read visual tokens: text rows are not written.
-    const bool visual_rows_only = ord.cu != nullptr;
-  #pragma unroll
-    for (int tq = 0; tq < TQ; ++tq) {
-      const bool store_row = probs != nullptr && tv[tq] && (!visual_rows_only || is_visual[tt[tq]] != 0);
-  #pragma unroll
-      for (int i = 0; i < NB; ++i) {
-        const int e = lane + 64 * i;
-        P[tq][i] = (e < E) ? P[tq][i] / part[tq] : -1.0f;   // -1 ranks below every probability
-        if (store_row && e < E) probs[(size_t)tt[tq] * E + e] = P[tq][i];
-      }
-    }
+    P[r] = v;
+    mx = larger(mx, v);
+  }
+  mx = row_max(mx);
+#pragma unroll
+  for (int r = 0; r < NR; ++r) P[r] = (16 * r + j < E) ? exp_fixed(P[r] - mx) : 0.0f;
+  // the sum's order: experts e, e+64, .. one after the other, then the xor butterfly 32, 16, 8, 4, 2, 1
+  float part[4];
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+    part[r] = 0.0f;
+#pragma unroll
+    for (int i = 0; i < NB; ++i) part[r] = part[r] + P[r + 4 * i];
+  }
+  const float sum = row_sum_butterfly((part[0] + part[2]) + (part[1] + part[3]));
+  // Inside the fused layer (the launch that also carries the ordinal blocks) the probabilities only feed
+  // the window scores, which read visual tokens: text rows are not written.
+  const bool visual = is_visual[t] != 0;
+  const bool store_row = probs != nullptr && tv && (ord.cu == nullptr || visual);
+#pragma unroll
+  for (int r = 0; r < NR; ++r) {
+    const int e = 16 * r + j;
+    P[r] = (e < E) ? P[r] / sum : -1.0f;   // -1 ranks below every probability
+    if (store_row && e < E) probs[(size_t)t * E + e] = P[r];
+  }
 
-    // Top-k as k rounds of "take the largest remaining probability" (ties: lowest expert index), which
-    // yields the list in the order (probability desc, index asc) directly.  The maximum over the
-    // wavefront is order-free, so it uses the cheap lane-crossing modifiers (two quad permutes, two
-    // mirrors) inside a row of 16 lanes and four lane reads across rows.  The four tokens run side by
-    // side and a token that needs fewer than Kmax experts idles branch-free.
-    float work[TQ][NB];
-    int sel[TQ][NB];     // position of this lane's expert in the token's list, -1: not selected
-    float den[TQ];
-    int kk[TQ];
-  #pragma unroll
-    for (int tq = 0; tq < TQ; ++tq) {
-      kk[tq] = is_visual[tt[tq]] ? k_visual : k_text;
-      den[tq] = 0.0f;
-  #pragma unroll
-      for (int i = 0; i < NB; ++i) {
-        work[tq][i] = P[tq][i];
-        sel[tq][i] = -1;
-      }
+  // Top-k as k rounds of "take the largest remaining probability" (ties: lowest expert index), which
+  // yields the list in the order (probability desc, index asc) directly; lane j keeps entry j of it.
+  const int k = visual ? k_visual : k_text;
+  // with a selection strategy a token with k < k_base first lists its k_base candidates
+  const int kc = (SEL && k < selp.k_base) ? selp.k_base : k;
+  const int rounds = (SEL && selp.k_base > Kmax) ? selp.k_base : Kmax;
+  float den = 0.0f;
+  int my_e = -1;
+  float my_p = 0.0f;
+  for (int round = 0; round < rounds; ++round) {
+    float v = P[0];
+#pragma unroll
+    for (int r = 1; r < NR; ++r) v = larger(v, P[r]);
+    const float m = row_max(v);
+    int e = 0x7fff;
+#pragma unroll
+    for (int r = NR - 1; r >= 0; --r) e = (P[r] == m) ? 16 * r + j : e;
+    e = row_min(e);
+    const bool active = round < kc;
+    if (active && j == round) {
+      my_e = e < E ? e : -1;   // -1: a row of NaN has no largest entry
+      my_p = m;
     }
-    // with a selection strategy a token with k < k_base first lists its k_base candidates
-    int kc[TQ];
-  #pragma unroll
-    for (int tq = 0; tq < TQ; ++tq) kc[tq] = (SEL && kk[tq] < selp.k_base) ? selp.k_base : kk[tq];
-    const int rounds = (SEL && selp.k_base > Kmax) ? selp.k_base : Kmax;
-    for (int r = 0; r < rounds; ++r) {
-  #pragma unroll
-      for (int tq = 0; tq < TQ; ++tq) {
-        float v = work[tq][0];
-  #pragma unroll
-        for (int i = 1; i < NB; ++i) v = (work[tq][i] > v) ? work[tq][i] : v;
-        const float m = wave_max_all(v);
-        const bool active = r < kc[tq];
-        bool taken = false;
-  #pragma unroll
-        for (int i = 0; i < NB; ++i) {   // lowest expert index first: register i holds experts 64i..64i+63
-          const unsigned long long eq = __ballot(work[tq][i] == m);
-          const int owner = __ffsll((long long)eq) - 1;
-          if (active && !taken && lane == owner) {
-            sel[tq][i] = r;
-            work[tq][i] = -2.0f;
-          }
-          taken = taken || (eq != 0ull);
-        }
-        den[tq] = den[tq] + (active ? m : 0.0f);   // list order, sequential (Eq.5)
+    den = den + (active ? m : 0.0f);   // list order, sequential (Eq.5)
+#pragma unroll
+    for (int r = 0; r < NR; ++r) P[r] = (16 * r + j == e) ? -2.0f : P[r];
+  }
+  int pos = j < kc ? j : -1;   // place of this lane's entry in the token's list, -1: not in it
+  if constexpr (SEL) {
+    unsigned int mask = 0u;   // kept candidate positions
+    if (selp.strategy == 1) {
+      // random strategy: lane j holds the key of candidate position j; a position is kept when fewer
+      // than k keys of its token are smaller (ties: lower position)
+      const unsigned long long key = splitmix64_nth(selp.seed, (unsigned long long)t * 16ull + (unsigned long long)j + 1ull);
+      int rank = 0;
+      for (int o = 0; o < 16; ++o) {
+        const int src = (lane & 48) + o;
+        const unsigned int lo = (unsigned int)__shfl((int)(unsigned int)key, src, 64);
+        const unsigned int hi = (unsigned int)__shfl((int)(unsigned int)(key >> 32), src, 64);
+        const unsigned long long ok = ((unsigned long long)hi << 32) | lo;
+        rank += (o < selp.k_base && (ok < key || (ok == key && o < j))) ? 1 : 0;
       }
+      const unsigned long long all = __ballot(j < selp.k_base && rank < k);
+      mask = (unsigned int)(all >> (lane & 48)) & 0xffffu;
+    } else if (k < selp.k_base) {
+      mask = ((1u << k) - 1u) << (selp.strategy == 2 ? selp.k_base - k : 0);
     }
-    if constexpr (SEL) {
-      // random strategy: lane 16q + r holds the key of candidate position r of the wavefront's q-th
-      // token; a position is kept when fewer than k keys of its token are smaller (ties: lower position)
-      unsigned long long random_masks = 0ull;
-      if (selp.strategy == 1) {
-        const int q = lane >> 4, r = lane & 15;
-        const int tq_t = q == 0 ? tt[0] : (q == 1 ? tt[1] : (q == 2 ? tt[2] : tt[3]));
-        const int tq_k = q == 0 ? kk[0] : (q == 1 ? kk[1] : (q == 2 ? kk[2] : kk[3]));
-        const unsigned long long key = splitmix64_nth(selp.seed, (unsigned long long)tq_t * 16ull + (unsigned long long)r + 1ull);
-        int rank = 0;
-        for (int o = 0; o < 16; ++o) {
-          const int src = (lane & 48) + o;
-          const unsigned int lo = (unsigned int)__shfl((int)(unsigned int)key, src, 64);
-          const unsigned int hi = (unsigned int)__shfl((int)(unsigned int)(key >> 32), src, 64);
-          const unsigned long long ok = ((unsigned long long)hi << 32) | lo;
-          rank += (o < selp.k_base && (ok < key || (ok == key && o < r))) ? 1 : 0;
-        }
-        random_masks = __ballot(r < selp.k_base && rank < tq_k);
-      }
-  #pragma unroll
-      for (int tq = 0; tq < TQ; ++tq) {
-        if (kk[tq] >= selp.k_base) continue;   // not reduced: the list stands (uniform over the wavefront)
-        const int k = kk[tq];
-        unsigned int mask;   // kept candidate positions
-        if (selp.strategy == 1) mask = (unsigned int)(random_masks >> (16 * tq)) & 0xffffu;
-        else if (selp.strategy == 2) mask = ((1u << k) - 1u) << (selp.k_base - k);
-        else mask = (1u << k) - 1u;
-  #pragma unroll
-        for (int i = 0; i < NB; ++i) {
-          const int p = sel[tq][i];
-          if (p >= 0) sel[tq][i] = ((mask >> p) & 1u) ? __popc(mask & ((1u << p) - 1u)) : -1;
-        }
-        float d2 = 0.0f;   // Eq.5 over the kept experts, in list order
-        for (int sl = 0; sl < k; ++sl) {
-          float v = -1.0f;
-  #pragma unroll
-          for (int i = 0; i < NB; ++i) v = (sel[tq][i] == sl) ? P[tq][i] : v;
-          d2 = d2 + wave_max_all(v);
-        }
-        den[tq] = d2;
-      }
+    float d2 = 0.0f;   // Eq.5 over the kept experts, in list order
+    for (int p = 0; p < selp.k_base; ++p) {
+      const float v = __shfl(my_p, (lane & 48) + p, 64);
+      if ((mask >> p) & 1u) d2 = d2 + v;
     }
-  #pragma unroll
-    for (int tq = 0; tq < TQ; ++tq) {
-      if (!tv[tq]) continue;
-      int32_t* oi = topk_idx + (size_t)tt[tq] * Kmax;
-      float* og = topk_gate + (size_t)tt[tq] * Kmax;
-  #pragma unroll
-      for (int i = 0; i < NB; ++i) {
-        if (sel[tq][i] >= 0) {
-          oi[sel[tq][i]] = lane + 64 * i;
-          og[sel[tq][i]] = renorm ? P[tq][i] / den[tq] : P[tq][i];
-        }
-      }
-      if (lane < Kmax && lane >= kk[tq]) {   // unused tail of the list
-        oi[lane] = -1;
-        og[lane] = 0.0f;
-      }
+    if (k < selp.k_base) {   // otherwise not reduced: the list stands
+      pos = (pos >= 0 && ((mask >> pos) & 1u)) ? __popc(mask & ((1u << pos) - 1u)) : -1;
+      den = d2;
+    }
+  }
+  if (tv) {
+    int32_t* oi = topk_idx + (size_t)t * Kmax;
+    float* og = topk_gate + (size_t)t * Kmax;
+    if (pos >= 0) {
+      oi[pos] = my_e;
+      og[pos] = renorm ? my_p / den : my_p;
+    }
+    if (j < Kmax && j >= k) {   // unused tail of the list
+      oi[j] = -1;
+      og[j] = 0.0f;
     }
   }
 }
 
-template <typename XT, int NB, int PF, bool TT2 = (NB <= 2)>
+template <typename XT, int NB, int R>
 int launch_route_t(const fmoe_ctx* ctx, const void* x, const uint8_t* is_visual, int T, float* probs,
                    int32_t* topk_idx, float* topk_gate, const fmoe_ordinals_job& ord, hipStream_t stream, const int32_t* T_dev) {
   const int d = ctx->cfg.d_model, E = ctx->cfg.n_experts;
-  const int Eb = (E + 15) / 16, G = router_groups(d);
-  const int nch = (((d + KC - 1) / KC + PF - 1) / PF) * PF;   // <= G / NG by construction
-  // two token tiles per block once that still leaves every CU several blocks (and only for the default
-  // selection strategy and up to 128 experts, where the registers allow it)
-  const bool two = TT2 && T >= FMOE_ROUTE_TT2_MIN_TOKENS && ctx->sel_strategy == 0;
-  const int per_block = two ? 2 * TOKB : TOKB;
-  const int grid = (T + per_block - 1) / per_block;
+  const int Eb = (E + 15) / 16;
+  const int grid = (T + TOKB - 1) / TOKB;
   fmoe_prof_scope prof(ctx, SLOT_ROUTE, stream);
   const int riders = ord.cu != nullptr ? ord.B : 0;
   const fmoe_selection selp{ctx->sel_strategy, ctx->sel_k_base, ctx->sel_seed};
-#define FMOE_ROUTE_LAUNCH(SEL, TT)                                                                              \
-  hipLaunchKernelGGL((route_kernel<XT, NB, PF, SEL, TT>), dim3(grid + riders), dim3(256), 0, stream,            \
-                     static_cast<const XT*>(x), reinterpret_cast<const fx4_t*>(ctx->router_wp),                 \
-                     ctx->router_bias, is_visual, T, d, E, Eb, G, nch, ctx->cfg.k_text, ctx->cfg.k_visual,      \
-                     ctx->kmax, ctx->cfg.renormalize, probs, topk_idx, topk_gate, grid, ord, T_dev, selp)
-  if (ctx->sel_strategy != 0) FMOE_ROUTE_LAUNCH(true, 1);
-  else if constexpr (TT2) { if (two) FMOE_ROUTE_LAUNCH(false, 2); else FMOE_ROUTE_LAUNCH(false, 1); }
-  else FMOE_ROUTE_LAUNCH(false, 1);
+#define FMOE_ROUTE_LAUNCH(SEL)                                                                                  \
+  hipLaunchKernelGGL((route_kernel<XT, NB, R, SEL>), dim3(grid + riders), dim3(256), 0, stream,                 \
+                     static_cast<const XT*>(x), static_cast<const float*>(ctx->router_wp),                      \
+                     ctx->router_bias, is_visual, T, d, E, Eb, ctx->cfg.k_text, ctx->cfg.k_visual, ctx->kmax,   \
+                     ctx->cfg.renormalize, probs, topk_idx, topk_gate, grid, ord, T_dev, selp)
+  if (ctx->sel_strategy != 0) FMOE_ROUTE_LAUNCH(true);
+  else FMOE_ROUTE_LAUNCH(false);
 #undef FMOE_ROUTE_LAUNCH
   FMOE_HIP_CHECK(hipGetLastError());
   return FMOE_OK;
@@ -499,34 +445,22 @@ template <typename XT>
 int launch_route_x(const fmoe_ctx* ctx, const void* x, const uint8_t* is_visual, int T, float* probs,
                    int32_t* topk_idx, float* topk_gate, const fmoe_ordinals_job& ord, hipStream_t stream, const int32_t* T_dev) {
   const int E = ctx->cfg.n_experts;
-  const int chunks = (ctx->cfg.d_model + KC - 1) / KC;
-  if (E <= 64) {
-    if (chunks < 4) return launch_route_t<XT, 1, 1>(ctx, x, is_visual, T, probs, topk_idx, topk_gate, ord, stream, T_dev);
-    // Large batches have several blocks per CU to hide memory latency with; two chunks in flight instead of
-    // four or five then halve the registers of a wavefront, twice as many wavefronts share a SIMD, and
-    // their accumulation chains keep the matrix pipe busier (91 -> 80 us at 22016 tokens).
-    if (T >= FMOE_ROUTE_SHALLOW_MIN_TOKENS)
-      return launch_route_t<XT, 1, 2>(ctx, x, is_visual, T, probs, topk_idx, topk_gate, ord, stream, T_dev);
-    if (chunks % 5 == 0) return launch_route_t<XT, 1, 5>(ctx, x, is_visual, T, probs, topk_idx, topk_gate, ord, stream, T_dev);
-    return launch_route_t<XT, 1, 4>(ctx, x, is_visual, T, probs, topk_idx, topk_gate, ord, stream, T_dev);
-  }
-  if (E <= 128) {
-    if (chunks < 2) return launch_route_t<XT, 2, 1>(ctx, x, is_visual, T, probs, topk_idx, topk_gate, ord, stream, T_dev);
-    return launch_route_t<XT, 2, 2>(ctx, x, is_visual, T, probs, topk_idx, topk_gate, ord, stream, T_dev);
-  }
-  return launch_route_t<XT, 4, 1>(ctx, x, is_visual, T, probs, topk_idx, topk_gate, ord, stream, T_dev);
+  // enough weight groups in flight to cover some 2000 cycles at 128 cycles per group and expert block
+  if (E <= 64) return launch_route_t<XT, 1, 16>(ctx, x, is_visual, T, probs, topk_idx, topk_gate, ord, stream, T_dev);
+  if (E <= 128) return launch_route_t<XT, 2, 8>(ctx, x, is_visual, T, probs, topk_idx, topk_gate, ord, stream, T_dev);
+  return launch_route_t<XT, 4, 4>(ctx, x, is_visual, T, probs, topk_idx, topk_gate, ord, stream, T_dev);
 }
 
 }  // namespace
 
 size_t router_pack_floats(const fmoe_ctx* ctx) {
-  const int Eb = (ctx->cfg.n_experts + 15) / 16, G = router_groups(ctx->cfg.d_model);
+  const int Eb = (ctx->cfg.n_experts + 15) / 16, G = NG * router_chunks(ctx->cfg.d_model);
   return (size_t)Eb * G * 256;
 }
 
 int launch_pack_router(const fmoe_ctx* ctx, const void* router_w, float* wp, hipStream_t stream) {
   const int E = ctx->cfg.n_experts, d = ctx->cfg.d_model;
-  const int Eb = (E + 15) / 16, G = router_groups(d);
+  const int Eb = (E + 15) / 16, G = NG * router_chunks(d);
   const size_t n = router_pack_floats(ctx);
   const int grid = (int)((n + 255) / 256 < 4096 ? (n + 255) / 256 : 4096);
   if (ctx->cfg.dtype == FMOE_BF16)

@@ -95,6 +95,28 @@ def test_route_large_batches(dtype, d, E, T_v, T_t):
     assert np.abs(host(gate) - o_gate).max() <= 1e-6
 
 
+@pytest.mark.parametrize("dtype", [W.F32, W.BF16])
+@pytest.mark.parametrize("d,E,T_v,T_t,k", [
+    (8, 16, 1, 0, 16), (120, 17, 15, 0, 3), (128, 64, 16, 1, 16), (136, 65, 17, 14, 8), (384, 128, 30, 2, 1),
+    (520, 129, 33, 31, 16), (1032, 256, 50, 13, 10), (648, 9, 2300, 40, 9),
+])
+def test_route_tile_edges(dtype, d, E, T_v, T_t, k):
+    """One to nine chunks of the reduction (whole and partial), every expert-block count per wavefront, token
+    counts around a tile, lists as long as they get: bit for bit."""
+    wl = W.small_random(900 + d, T_v=[T_v], T_t=[T_t], d=d, E=E, F=16, k_text=k, k_visual=max(1, k // 2),
+                        retention=0.5, window=3, dtype=dtype, bias_std=0.5)
+    m = make_layer(wl)
+    x, vis, cu = inputs(wl)
+    probs, idx, gate = m.route(x, vis)
+    o = oracle.route(wl.x, wl.is_visual, wl.weights.router_w, wl.weights.router_bias, k, max(1, k // 2))
+    assert np.array_equal(host(probs), o[0]) and np.array_equal(host(idx), o[1])
+    assert np.abs(host(gate) - o[2]).max() <= 1e-6
+    pp = binding.prune_params(retention=0.5, window=3)      # the ordinal blocks that ride in the router's launch
+    _, kept, new_cu, _ = m.layer_forward(x, vis, cu, pp)
+    o_kept, o_cu, _ = oracle.prune(o[0], wl.is_visual, wl.cu_seqlens, 0.5, 3)
+    assert np.array_equal(host(new_cu), o_cu) and np.array_equal(host(kept)[:len(o_kept)], o_kept)
+
+
 def test_route_ties_duplicated_router_rows():
     wl = W.small_random(110, T_v=[20], T_t=[12], d=64, E=10, F=32, k_text=10, k_visual=4,
                         retention=0.5, window=3)
