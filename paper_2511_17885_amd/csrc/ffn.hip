@@ -27,8 +27,7 @@
 //    the linear block id is decoded as (batch of 8 row tiles, column tile, tile within the batch
 //    = XCD); all column tiles of one row tile run on one XCD and its activation rows are fetched
 //    from HBM once.
-// The fp32 storage type (a correctness configuration) uses a plain LDS-tiled kernel on the fp32
-// MFMA with the caller's weight layout.
+// The fp32 storage type has a kernel of its own on the fp32 matrix instruction, reading the caller's weights.
 
 #include <type_traits>
 
@@ -38,7 +37,6 @@
 namespace {
 
 typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8_t;
-typedef __attribute__((__vector_size__(16 * sizeof(float)))) float f32x16_t;
 typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4_t;
 typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));   // one 16-byte chunk
 
@@ -799,27 +797,40 @@ __global__ void pack_weights_kernel(const bf16_t* __restrict__ src0, const bf16_
   }
 }
 
-// ======================================================================== fp32: LDS-tiled kernel
-constexpr int BNW = 128;  // weight rows per block: 64 gate + 64 up columns, or 128 down columns
-
-template <typename T> struct Traits;
-template <> struct Traits<float> {
-  static constexpr int VEC = 4;
-  static constexpr int BK = 32;
-  static constexpr int LDK = BK + 4;
-};
+// ======================================================================== fp32 kernel
+// fp32 storage.  The fp32 matrix instruction (16x16x4: 32 cycles, 154 TFLOP/s over the chip) is a sixteenth of
+// the bf16 rate and shares the vector pipe, so from some forty rows per expert on the kernel is bound by it and
+// below by the weight stream; both want a k loop with next to no vector instructions and rows cut finely:
+//  * a block owns a 64-row tile and 64 features (or 128 output columns), a wavefront all rows of the tile and
+//    two blocks of 16 columns (gate and up of the same features, or two neighbours); only the tile's live 16-row
+//    blocks are computed;
+//  * k order inside 16 is free (a sum), so one 16-byte piece per lane is an operand of four instructions: lane
+//    (row or column l%16, quarter q) holds k = 4q..4q+3 and instruction i takes element i on both sides.
+//    Weights therefore come straight from the caller's rows into registers, rows from LDS without a
+//    transposition;
+//  * weights: F_SLOTS-1 k tiles (32 wide, one 128-byte line per column) in flight per wavefront, addressed by a
+//    descriptor over the wavefront's rows, a constant lane offset and a scalar one; gathered rows: 64-bit
+//    pointers (fp32 tensors may exceed 4 GiB), F_SLOTS-1 tiles in flight, through registers into one of two
+//    LDS buffers in the swizzled layout of the bf16 kernels; one barrier per k tile.
+// Measured against an LDS-tiled kernel on the 32x32x2 instruction (both operands through LDS, one tile of
+// loads in flight, one operand per LDS read): 1600 tokens, d 1280, 64 experts of 896, 42 rows per expert:
+// gate/up 572 -> 238 us, down 286 -> 133 us; 3000 tokens, 280 rows per expert: 1890 -> 972 and 960 -> 507 us
+// (111 TFLOP/s); 64 tokens, d 128, 8 experts of 256: 19.2 -> 8.1 and 33.2 -> 10.1 us.
+constexpr int FBM = 64;        // rows per tile
+constexpr int FBK = 32;        // k per tile: 128 bytes of a row
+constexpr int F_SLOTS = 4;     // register rings, in k tiles
 
 struct GemmProblem {
-  const void* A;            // [*, lda]
+  const float* A;           // [*, lda]
   int lda;
   const int32_t* map1;      // row -> index (perm_src) or null
   const int32_t* map2;      // index -> token (kept_idx) or null
   int map1_limit;           // clamp for map1 values (exclusive), <= 0: none
-  const void* B0;           // [G, N, K] gate / down
-  const void* B1;           // [G, N, K] up (SwiGLU only)
+  const float* B0;          // [G, N, K] gate / down
+  const float* B1;          // [G, N, K] up (SwiGLU only)
   long long group_stride;   // elements between groups (0 for the shared group)
   int ldb;                  // elements between consecutive weight rows
-  void* C;                  // [*, ldc]
+  float* C;                 // [*, ldc]
   int ldc;
   int N, K;
   int n_col_tiles;
@@ -836,25 +847,183 @@ struct GemmArgs {
   int n_col_tiles_max;
 };
 
-template <typename T, bool SWIGLU, int MT>
-__global__ __launch_bounds__(256) void grouped_gemm_kernel(GemmArgs a) {
-  using TR = Traits<T>;
-  constexpr int VEC = TR::VEC, BK = TR::BK, LDK = TR::LDK;
-  constexpr int BM = 64 * MT;
-  constexpr int CPR = BK / VEC;                 // 16-byte chunks per tile row (8)
-  constexpr int A_IT = BM * CPR / 256;          // chunks per thread
-  constexpr int B_IT = BNW * CPR / 256;
-  __shared__ __align__(16) T As[BM * LDK];
-  __shared__ __align__(16) T Bs[BNW * LDK];
+template <bool SWIGLU, int NRB>   // NRB: live 16-row blocks of the tile
+__device__ __forceinline__ void f32_tile(const GemmProblem& P, const fmoe_tile& tile, int group, bool shared, int nt,
+                                         float* As) {
+  constexpr int A_IT = (NRB + 1) / 2;   // 16-byte pieces of a k tile per thread
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int N = P.N, K = P.K;
+  const int NT = K / FBK;               // whole k tiles
 
-  // XCD-aware decode of the linear block id
+  // weights of this wavefront: fragment f holds columns n0[f] .. n0[f]+15 (past N the last one again, never stored)
+  __amdgpu_buffer_rsrc_t b_rsrc[2];
+  uint32_t b_off[2];
+#pragma unroll
+  for (int f = 0; f < 2; ++f) {
+    const int n0 = SWIGLU ? nt * 64 + wave * 16 : nt * 128 + wave * 32 + f * 16;
+    const int base = n0 < N ? n0 : N - 1, n = n0 + (lane & 15);
+    const float* B = (SWIGLU && f ? P.B1 : P.B0) + (size_t)group * P.group_stride + (size_t)base * P.ldb;
+    b_rsrc[f] = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(B), 0, 0xffffffff, 0x00020000);
+    b_off[f] = ((uint32_t)((n < N ? n : N - 1) - base) * (uint32_t)P.ldb + (uint32_t)(lane >> 4) * 4u) * 4u;
+  }
+  f32x4_t breg[F_SLOTS][2][2];          // [ring slot][16 k][fragment]
+  auto load_b = [&](int slot, int t) {
+    const uint32_t off = (uint32_t)(t < NT ? t : NT - 1) * (FBK * 4);   // scalar
+#pragma unroll
+    for (int g = 0; g < 2; ++g)
+#pragma unroll
+      for (int f = 0; f < 2; ++f)
+        breg[slot][g][f] = __builtin_bit_cast(f32x4_t, __builtin_amdgcn_raw_buffer_load_b128(b_rsrc[f], b_off[f], off + g * 64, 0));
+  };
+  if (NT > 0) {   // uniform; the weights do not wait for the row indices
+#pragma unroll
+    for (int t = 0; t < F_SLOTS; ++t) {   // in ring order: the waits in the loop count on it
+      load_b(t, t);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  }
+
+  // rows: thread -> row 32*it + tid/8, 16-byte chunk tid%8 of its k tile, kept at chunk ^ ((row >> 1) & 7).
+  // Rows past the tile reuse its last row: their products land in accumulator rows that are never stored.
+  const int chunk = tid & 7;
+  const float* a_src[A_IT];
+  int a_dst[A_IT];
+#pragma unroll
+  for (int it = 0; it < A_IT; ++it) {
+    const int r = 32 * it + (tid >> 3);
+    int src = tile.row0 + (r < tile.rows ? r : tile.rows - 1);
+    if (P.map1) {
+      src = P.map1[src];
+      if (P.map1_limit > 0) src = src < 0 ? 0 : (src >= P.map1_limit ? P.map1_limit - 1 : src);
+    }
+    if (P.map2) src = P.map2[src];
+    a_src[it] = P.A + (shared ? (size_t)group * P.a_group_off : 0) + (size_t)src * P.lda + chunk * 4;
+    a_dst[it] = r * FBK + (chunk ^ ((r >> 1) & 7)) * 4;
+  }
+  f32x4_t areg[F_SLOTS][A_IT];
+  auto load_a = [&](int slot, int t) {
+    const int off = (t < NT ? t : NT - 1) * FBK;   // scalar
+#pragma unroll
+    for (int it = 0; it < A_IT; ++it) areg[slot][it] = *reinterpret_cast<const f32x4_t*>(a_src[it] + off);
+  };
+  auto store_a = [&](int buf, int slot) {
+#pragma unroll
+    for (int it = 0; it < A_IT; ++it) *reinterpret_cast<f32x4_t*>(&As[buf * (FBM * FBK) + a_dst[it]]) = areg[slot][it];
+  };
+
+  f32x4_t acc[NRB][2];
+#pragma unroll
+  for (int rb = 0; rb < NRB; ++rb)
+#pragma unroll
+    for (int f = 0; f < 2; ++f) acc[rb][f] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+  const int frow = (lane & 15) * FBK;
+  const int fpos[2] = {frow + (((lane >> 4)) ^ ((lane & 15) >> 1)) * 4, frow + (((lane >> 4) + 4) ^ ((lane & 15) >> 1)) * 4};
+  auto multiply = [&](int buf, int slot) {
+    f32x4_t fa[2][NRB];
+#pragma unroll
+    for (int g = 0; g < 2; ++g)
+#pragma unroll
+      for (int rb = 0; rb < NRB; ++rb)
+        fa[g][rb] = *reinterpret_cast<const f32x4_t*>(&As[buf * (FBM * FBK) + rb * (16 * FBK) + fpos[g]]);
+#pragma unroll
+    for (int g = 0; g < 2; ++g)
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int rb = 0; rb < NRB; ++rb)
+#pragma unroll
+          for (int f = 0; f < 2; ++f)
+            acc[rb][f] = __builtin_amdgcn_mfma_f32_16x16x4f32(fa[g][rb][i], breg[slot][g][f][i], acc[rb][f], 0, 0, 0);
+  };
+
+  // Step t multiplies tile t, puts tile t+1's rows into the other LDS buffer and issues the weights of tile
+  // t+F_SLOTS and the rows of tile t+1+F_SLOTS (past the last tile the last one again).
+  static_assert(F_SLOTS % 2 == 0, "ring slots and LDS buffers are compile-time");
+  if (NT > 0) {   // uniform
+#pragma unroll
+    for (int t = 0; t < F_SLOTS; ++t) {
+      load_a(t, t);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    store_a(0, 0);
+    load_a(0, F_SLOTS);
+    __syncthreads();
+    for (int t0 = 0;; t0 += F_SLOTS) {
+#pragma unroll
+      for (int u = 0; u < F_SLOTS; ++u) {
+        const int t = t0 + u;
+        if (t >= NT) goto whole_tiles_done;   // uniform
+        store_a((u + 1) & 1, (u + 1) % F_SLOTS);
+        load_a((u + 1) % F_SLOTS, t + 1 + F_SLOTS);
+        multiply(u & 1, u);
+        __builtin_amdgcn_sched_barrier(0);
+        load_b(u, t + F_SLOTS);
+        __syncthreads();   // tile t+1 is in LDS, all are done with tile t
+      }
+    }
+  }
+whole_tiles_done:
+  if (NT * FBK < K) {   // uniform: the last, partial tile; what lies past K counts as zero on both sides
+    const f32x4_t zero = {0.f, 0.f, 0.f, 0.f};
+    const int k0 = NT * FBK;
+#pragma unroll
+    for (int it = 0; it < A_IT; ++it) {
+      const bool in = k0 + chunk * 4 < K;
+      const f32x4_t v = *reinterpret_cast<const f32x4_t*>(a_src[it] + (in ? k0 : K - 4 - chunk * 4));
+      areg[0][it] = in ? v : zero;
+    }
+#pragma unroll
+    for (int g = 0; g < 2; ++g) {
+      const int k = k0 + 16 * g + 4 * (lane >> 4);
+      const bool in = k < K;
+#pragma unroll
+      for (int f = 0; f < 2; ++f) {
+        const uint32_t off = b_off[f] + (uint32_t)((in ? k : K - 4) - 4 * (lane >> 4)) * 4u;
+        const f32x4_t v = __builtin_bit_cast(f32x4_t, __builtin_amdgcn_raw_buffer_load_b128(b_rsrc[f], off, 0, 0));
+        breg[0][g][f] = in ? v : zero;
+      }
+    }
+    store_a(0, 0);   // the loop's last barrier is behind every reader of the buffers
+    __syncthreads();
+    multiply(0, 0);
+  }
+
+  // accumulator register v of lane l holds row 4*(l/16) + v, column l%16 of a 16x16 block
+  float* C = P.C + (shared ? (size_t)group * P.c_group_off : 0);
+#pragma unroll
+  for (int rb = 0; rb < NRB; ++rb)
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      const int row = rb * 16 + 4 * (lane >> 4) + v;
+      if (row >= tile.rows) continue;
+      float* crow = C + (size_t)(tile.row0 + row) * P.ldc;
+      if (SWIGLU) {
+        const int col = nt * 64 + wave * 16 + (lane & 15);
+        if (col < N) crow[col] = silu_mul(acc[rb][0][v], acc[rb][1][v]);
+      } else {
+        const int col = nt * 128 + wave * 32 + (lane & 15);
+        if (col < N) crow[col] = acc[rb][0][v];
+        if (col + 16 < N) crow[col + 16] = acc[rb][1][v];
+      }
+    }
+}
+
+template <bool SWIGLU>
+__global__ __launch_bounds__(256, 2) void grouped_gemm_kernel(GemmArgs a) {
+  __shared__ __align__(16) float As[2 * FBM * FBK];
+
+  // XCD-aware decode of the linear block id, as in the weight-stream kernel: row tiles dealt round-robin over
+  // the XCDs, the blocks of a group with several row tiles re-dealt column-major so that one XCD fetches a
+  // weight column block
+  const int n_tiles = *a.n_tiles;
   const int xcd = blockIdx.x & 7;
   const int rr = blockIdx.x >> 3;
   const int batch = rr / a.n_col_tiles_max;
-  const int nt_launch = rr - batch * a.n_col_tiles_max;
-  const int ti = batch * 8 + xcd;
-  if (ti >= *a.n_tiles) return;
-  const fmoe_tile tile = a.tiles[ti];
+  int nt_launch = rr - batch * a.n_col_tiles_max;
+  int ti = batch * 8 + xcd;
+  if (ti >= n_tiles) return;
+  fmoe_tile tile = a.tiles[ti];
   const bool shared = tile.group >= a.E;
   // field-by-field select keeps the descriptors in scalar registers (indexing the kernel argument
   // dynamically would spill it to scratch memory)
@@ -865,154 +1034,23 @@ __global__ __launch_bounds__(256) void grouped_gemm_kernel(GemmArgs a) {
   FMOE_SEL(C); FMOE_SEL(ldc); FMOE_SEL(N); FMOE_SEL(K); FMOE_SEL(n_col_tiles);
   FMOE_SEL(a_group_off); FMOE_SEL(c_group_off);
 #undef FMOE_SEL
+  // column tiles this entry really has
+  const int c_eff = (P.n_col_tiles - tile.col0 < a.n_col_tiles_max) ? (P.n_col_tiles - tile.col0) : a.n_col_tiles_max;
+  if (nt_launch >= c_eff) return;
+  if (tile.nrt > 1) {
+    const int w = tile.rt * c_eff + nt_launch;
+    const int r2 = w % tile.nrt;
+    nt_launch = w / tile.nrt;
+    ti = ti - tile.rt + r2;
+    tile = a.tiles[ti];
+  }
   const int nt = tile.col0 + nt_launch;
-  if (nt >= P.n_col_tiles) return;
   const int group = shared ? tile.group - a.E : tile.group;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int wm = wave >> 1, wn = wave & 1;
-  const int N = P.N, K = P.K;
-
-  const T* Ag = static_cast<const T*>(P.A) + (shared ? (size_t)group * P.a_group_off : 0);
-  const T* B0g = static_cast<const T*>(P.B0) + (size_t)group * P.group_stride;
-  const T* B1g = SWIGLU ? static_cast<const T*>(P.B1) + (size_t)group * P.group_stride : nullptr;
-
-  // per-thread chunk sources (fixed over the K loop)
-  const T* a_src[A_IT];
-  const T* b_src[B_IT];
-  int a_lo[A_IT], b_lo[B_IT], a_k[A_IT], b_k[B_IT];
-#pragma unroll
-  for (int it = 0; it < A_IT; ++it) {
-    const int chunk = tid + it * 256;
-    const int r = chunk / CPR, kc = (chunk % CPR) * VEC;
-    a_lo[it] = r * LDK + kc;
-    a_k[it] = kc;
-    // rows past the tile reuse its last row: their products land in accumulator rows that are
-    // never stored, and the loads stay unconditional (no branches in the pipelined loop)
-    int src = tile.row0 + (r < tile.rows ? r : tile.rows - 1);
-    if (P.map1) {
-      src = P.map1[src];
-      if (P.map1_limit > 0) src = src < 0 ? 0 : (src >= P.map1_limit ? P.map1_limit - 1 : src);
-    }
-    if (P.map2) src = P.map2[src];
-    a_src[it] = Ag + (size_t)src * P.lda;
-  }
-#pragma unroll
-  for (int it = 0; it < B_IT; ++it) {
-    const int chunk = tid + it * 256;
-    const int wr = chunk / CPR, kc = (chunk % CPR) * VEC;
-    b_lo[it] = wr * LDK + kc;
-    b_k[it] = kc;
-    int n;
-    const T* base;
-    if (SWIGLU) {
-      n = nt * 64 + (wr & 63);
-      base = (wr < 64) ? B0g : B1g;
-    } else {
-      n = nt * BNW + wr;
-      base = B0g;
-    }
-    b_src[it] = base + (size_t)(n < N ? n : N - 1) * P.ldb;   // same trick for columns past N
-  }
-  f32x16_t acc[MT][2];
-#pragma unroll
-  for (int r = 0; r < MT; ++r)
-#pragma unroll
-    for (int c = 0; c < 2; ++c)
-#pragma unroll
-      for (int v = 0; v < 16; ++v) acc[r][c][v] = 0.0f;
-
-  // which 32-row groups of this wavefront hold any valid row (uniform per wavefront)
-  bool live[MT];
-#pragma unroll
-  for (int r = 0; r < MT; ++r) live[r] = (wm * 32 * MT + 32 * r) < tile.rows;
-
-  u32x4_t ra[A_IT], rb[B_IT];
-  const u32x4_t zero4 = {0u, 0u, 0u, 0u};
-  // k past K (ragged last k-tile) must contribute zeros: the address is clamped into the row and
-  // the loaded value replaced by a select, so the load itself is never predicated
-  auto load_tile = [&](int k0) {
-#pragma unroll
-    for (int it = 0; it < A_IT; ++it) {
-      const int k = k0 + a_k[it];
-      const int kk = k < K ? k : K - VEC;
-      const u32x4_t v = *reinterpret_cast<const u32x4_t*>(a_src[it] + kk);
-      ra[it] = k < K ? v : zero4;
-    }
-#pragma unroll
-    for (int it = 0; it < B_IT; ++it) {
-      const int k = k0 + b_k[it];
-      const int kk = k < K ? k : K - VEC;
-      const u32x4_t v = *reinterpret_cast<const u32x4_t*>(b_src[it] + kk);
-      rb[it] = k < K ? v : zero4;
-    }
-  };
-
-  load_tile(0);
-  for (int k0 = 0; k0 < K; k0 += BK) {
-#pragma unroll
-    for (int it = 0; it < A_IT; ++it) *reinterpret_cast<u32x4_t*>(&As[a_lo[it]]) = ra[it];
-#pragma unroll
-    for (int it = 0; it < B_IT; ++it) *reinterpret_cast<u32x4_t*>(&Bs[b_lo[it]]) = rb[it];
-    __syncthreads();
-    if (k0 + BK < K) load_tile(k0 + BK);   // in flight while the matrix cores work
-
-    const int brow0 = SWIGLU ? (wn * 32 + (lane & 31)) : (wn * 64 + (lane & 31));
-    const int brow1 = SWIGLU ? (64 + wn * 32 + (lane & 31)) : (wn * 64 + 32 + (lane & 31));
-    if constexpr (sizeof(T) == 2) {
-#pragma unroll
-      for (int ks = 0; ks < BK; ks += 16) {
-        const int ko = ks + (lane >> 5) * 8;
-        const bf16x8_t fb0 = *reinterpret_cast<const bf16x8_t*>(&Bs[brow0 * LDK + ko]);
-        const bf16x8_t fb1 = *reinterpret_cast<const bf16x8_t*>(&Bs[brow1 * LDK + ko]);
-#pragma unroll
-        for (int r = 0; r < MT; ++r) {
-          if (live[r]) {
-            const int arow = wm * 32 * MT + 32 * r + (lane & 31);
-            const bf16x8_t fa = *reinterpret_cast<const bf16x8_t*>(&As[arow * LDK + ko]);
-            acc[r][0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa, fb0, acc[r][0], 0, 0, 0);
-            acc[r][1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa, fb1, acc[r][1], 0, 0, 0);
-          }
-        }
-      }
-    } else {
-#pragma unroll
-      for (int ks = 0; ks < BK; ks += 2) {
-        const int ko = ks + (lane >> 5);
-        const float fb0 = Bs[brow0 * LDK + ko];
-        const float fb1 = Bs[brow1 * LDK + ko];
-#pragma unroll
-        for (int r = 0; r < MT; ++r) {
-          if (live[r]) {
-            const int arow = wm * 32 * MT + 32 * r + (lane & 31);
-            const float fa = As[arow * LDK + ko];
-            acc[r][0] = __builtin_amdgcn_mfma_f32_32x32x2f32(fa, fb0, acc[r][0], 0, 0, 0);
-            acc[r][1] = __builtin_amdgcn_mfma_f32_32x32x2f32(fa, fb1, acc[r][1], 0, 0, 0);
-          }
-        }
-      }
-    }
-    __syncthreads();
-  }
-
-  // epilogue: accumulator register v of lane l holds row 8*(v/4) + 4*(l/32) + v%4, column l%32
-  T* Cg = static_cast<T*>(P.C) + (shared ? (size_t)group * P.c_group_off : 0);
-#pragma unroll
-  for (int r = 0; r < MT; ++r) {
-    if (!live[r]) continue;
-#pragma unroll
-    for (int v = 0; v < 16; ++v) {
-      const int row = wm * 32 * MT + 32 * r + 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3);
-      if (row >= tile.rows) continue;
-      T* crow = Cg + (size_t)(tile.row0 + row) * P.ldc;
-      if (SWIGLU) {
-        const int col = nt * 64 + wn * 32 + (lane & 31);
-        if (col < N) crow[col] = from_f32<T>(silu_mul(acc[r][0][v], acc[r][1][v]));
-      } else {
-        const int col = nt * BNW + wn * 64 + (lane & 31);
-        if (col < N) crow[col] = from_f32<T>(acc[r][0][v]);
-        if (col + 32 < N) crow[col + 32] = from_f32<T>(acc[r][1][v]);
-      }
-    }
+  switch ((tile.rows + 15) >> 4) {   // live 16-row blocks of the tile, uniform per block
+    case 1: f32_tile<SWIGLU, 1>(P, tile, group, shared, nt, As); break;
+    case 2: f32_tile<SWIGLU, 2>(P, tile, group, shared, nt, As); break;
+    case 3: f32_tile<SWIGLU, 3>(P, tile, group, shared, nt, As); break;
+    default: f32_tile<SWIGLU, 4>(P, tile, group, shared, nt, As); break;
   }
 }
 
@@ -1037,7 +1075,7 @@ inline size_t packed_units(int nbw, int ks) { return (size_t)((nbw + 3) / 4) * 4
 fmoe_ffn_geom fmoe_geom(const fmoe_ctx* ctx, int n_cap) {
   const fmoe_config& c = ctx->cfg;
   fmoe_ffn_geom g;
-  g.bm = (c.dtype == FMOE_BF16) ? SBM : 64;
+  g.bm = (c.dtype == FMOE_BF16) ? SBM : FBM;
   const int Ft = c.n_shared * c.d_ffn_shared;
   g.cols1 = (c.d_ffn + 63) / 64;           // 64 hidden columns per block
   g.scols1 = (Ft + 63) / 64;
@@ -1103,37 +1141,37 @@ int run_ffn_f32(const fmoe_ctx* ctx, const void* x, const int32_t* kept_idx, int
   g2.n_tiles = tile_count + 1;
   {
     GemmProblem& p = g1.p0;
-    p.A = x; p.lda = d; p.map1 = perm_src; p.map2 = kept_idx; p.map1_limit = n_cap;
-    p.B0 = ctx->w_gate; p.B1 = ctx->w_up; p.group_stride = (long long)F * d; p.ldb = d;
-    p.C = base + L.h; p.ldc = F; p.N = F; p.K = d; p.n_col_tiles = geo.cols1;
+    p.A = static_cast<const float*>(x); p.lda = d; p.map1 = perm_src; p.map2 = kept_idx; p.map1_limit = n_cap;
+    p.B0 = static_cast<const float*>(ctx->w_gate); p.B1 = static_cast<const float*>(ctx->w_up); p.group_stride = (long long)F * d; p.ldb = d;
+    p.C = reinterpret_cast<float*>(base + L.h); p.ldc = F; p.N = F; p.K = d; p.n_col_tiles = geo.cols1;
     GemmProblem& q = g1.p1;
     q = p;
     q.map1 = nullptr; q.map1_limit = 0;
-    q.B0 = ctx->ws_gate; q.B1 = ctx->ws_up; q.group_stride = 0;
-    q.C = base + L.h_shared; q.ldc = Ft; q.N = Ft; q.n_col_tiles = geo.scols1;
+    q.B0 = static_cast<const float*>(ctx->ws_gate); q.B1 = static_cast<const float*>(ctx->ws_up); q.group_stride = 0;
+    q.C = reinterpret_cast<float*>(base + L.h_shared); q.ldc = Ft; q.N = Ft; q.n_col_tiles = geo.scols1;
     g1.n_col_tiles_max = geo.cols1;
   }
   {
     GemmProblem& p = g2.p0;
-    p.A = base + L.h; p.lda = F; p.map1 = nullptr; p.map2 = nullptr; p.map1_limit = 0;
-    p.B0 = ctx->w_down; p.B1 = nullptr; p.group_stride = (long long)d * F; p.ldb = F;
-    p.C = y; p.ldc = d; p.N = d; p.K = F; p.n_col_tiles = geo.cols2;
+    p.A = reinterpret_cast<const float*>(base + L.h); p.lda = F; p.map1 = nullptr; p.map2 = nullptr; p.map1_limit = 0;
+    p.B0 = static_cast<const float*>(ctx->w_down); p.B1 = nullptr; p.group_stride = (long long)d * F; p.ldb = F;
+    p.C = static_cast<float*>(y); p.ldc = d; p.N = d; p.K = F; p.n_col_tiles = geo.cols2;
     GemmProblem& q = g2.p1;
     q = p;
-    q.A = base + L.h_shared; q.lda = Ft; q.a_group_off = Fs;
-    q.B0 = ctx->ws_down; q.group_stride = (long long)d * Fs; q.ldb = Fs;
-    q.C = y_shared; q.c_group_off = (long long)n_cap * d; q.K = Fs; q.n_col_tiles = geo.scols2;
+    q.A = reinterpret_cast<const float*>(base + L.h_shared); q.lda = Ft; q.a_group_off = Fs;
+    q.B0 = static_cast<const float*>(ctx->ws_down); q.group_stride = (long long)d * Fs; q.ldb = Fs;
+    q.C = static_cast<float*>(y_shared); q.c_group_off = (long long)n_cap * d; q.K = Fs; q.n_col_tiles = geo.scols2;
     g2.n_col_tiles_max = geo.cols2;
   }
   const unsigned batches = (unsigned)((geo.tile_cap + 7) / 8);
   {
     fmoe_prof_scope prof(ctx, SLOT_GEMM1, stream);
-    hipLaunchKernelGGL((grouped_gemm_kernel<float, true, 1>), dim3(batches * 8 * g1.n_col_tiles_max),
+    hipLaunchKernelGGL(grouped_gemm_kernel<true>, dim3(batches * 8 * g1.n_col_tiles_max),
                        dim3(256), 0, stream, g1);
   }
   {
     fmoe_prof_scope prof(ctx, SLOT_GEMM2, stream);
-    hipLaunchKernelGGL((grouped_gemm_kernel<float, false, 1>), dim3(batches * 8 * g2.n_col_tiles_max),
+    hipLaunchKernelGGL(grouped_gemm_kernel<false>, dim3(batches * 8 * g2.n_col_tiles_max),
                        dim3(256), 0, stream, g2);
   }
   return FMOE_OK;

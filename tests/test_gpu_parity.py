@@ -1376,3 +1376,36 @@ def test_expert_ffn_k_loop_lengths(d, F, shape):
     M = int(o["expert_offsets"][-1])
     assert max_rel_err(host(y)[:M], o["y"]) <= TOL[W.BF16]
     assert max_rel_err(host(ysh).astype(np.float64).sum(0)[:n], o["y_shared"]) <= TOL[W.BF16]
+
+
+@pytest.mark.parametrize("d,F", [(8, 8), (24, 40), (32, 72), (136, 64), (160, 264), (296, 24)])
+def test_expert_ffn_fp32_tile_edges(d, F):
+    """The fp32 expert GEMMs at every count of live 16-row blocks of a tile and around its edges, reductions
+    shorter than a k tile, of whole tiles (fewer and more than the register rings hold) and with a partial
+    one, column counts that end inside a block; against fp64 at the fp32 bound (TOL)."""
+    counts = [0, 1, 15, 16, 17, 31, 33, 48, 49, 63, 64, 65, 130]
+    E, n, M = len(counts), 150, sum(counts)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(d * 1000 + F)
+    rnd = lambda *s: torch.randn(s, generator=g, device="cuda")
+    x, wr = rnd(n, d), rnd(E, d)
+    w = [rnd(E, F, d) * 0.1, rnd(E, F, d) * 0.1, rnd(E, d, F) * 0.1]
+    sh = [rnd(2, F, d) * 0.1, rnd(2, F, d) * 0.1, rnd(2, d, F) * 0.1]
+    m = binding.FMoE(d_model=d, n_experts=E, d_ffn=F, n_shared=2, d_ffn_shared=F, k_text=4, k_visual=4, dtype="f32")
+    m.set_weights(wr, None, *w, *sh)
+    kept = torch.randperm(n, generator=g, device="cuda").int()
+    perm = torch.randint(0, n, (M,), generator=g, device="cuda").int()
+    offs = torch.tensor(np.concatenate([[0], np.cumsum(counts)]), dtype=torch.int32, device="cuda")
+    y, ysh = m.expert_ffn(x, kept, n, offs, perm)
+
+    def ffn(v, a, b, c):
+        v, a, b, c = (t.double() for t in (v, a, b, c))
+        return ((torch.nn.functional.silu(v @ a.T) * (v @ b.T)) @ c.T).cpu().numpy()
+
+    rows = x[kept.long()]
+    for e, (lo, c) in enumerate(zip(np.cumsum([0] + counts), counts)):
+        if c:
+            ref = ffn(rows[perm[lo:lo + c].long()], w[0][e], w[1][e], w[2][e])
+            assert max_rel_err(host(y)[lo:lo + c], ref) <= TOL[W.F32], (e, c)
+    for s in range(2):
+        assert max_rel_err(host(ysh)[s], ffn(rows, sh[0][s], sh[1][s], sh[2][s])) <= TOL[W.F32], s
