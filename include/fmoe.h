@@ -129,7 +129,8 @@ int fmoe_set_selection(fmoe_ctx* ctx, int32_t strategy, int32_t k_base, uint64_t
 /* Tuning knob of the bf16 expert GEMMs (Eq.4).  The kernel has two shapes: the weight-stream shape (a
  * workgroup = 128 rows x 4 column blocks) for calls that route few rows per expert, and the dense
  * shape (128 rows x 8 column blocks, half the on-chip traffic per flop) from a capacity of 256 routed
- * rows per expert (T * Kmax / E) on.  Both add the products of a dot product in ascending k, so their
+ * rows per expert (T * Kmax / E) on.  Calls of at most 16 tokens take a third, thin shape (a wavefront per
+ * column block).  All add the products of a dot product in ascending k, so their
  * outputs are bit-identical.  shape 0 = choose by that rule (default), 1 = always weight-stream,
  * 2 = always dense; anything else is FMOE_ERR_INVALID_ARG.  No effect on fp32 contexts. */
 int fmoe_set_ffn_shape(fmoe_ctx* ctx, int32_t shape);

@@ -767,6 +767,140 @@ __global__ __launch_bounds__(256, 2) void ffn_dense_kernel(StreamArgs a) {
   }
 }
 
+// ---- the thin shape, for calls of at most THIN_ROWS tokens (decoding steps, short turns), where no expert sees
+// more rows than that and the weights are all there is to move.  One wavefront per workgroup and per column
+// block: four times as many, four times shorter work items than the weight-stream shape, dealt over all XCDs
+// column block by column block, so that every CU streams about the same number of bytes (a CU sustains some
+// 13 bytes/ns whatever it runs; with 418 items of 512 KB over 256 CUs the CUs holding two of them finished
+// last by half the launch).  No LDS and no barrier: the rows' operands come straight from memory in matrix
+// order (lane: row l%16, k = 8*(l/16)..+7), a few KB that every wavefront finds in L2.
+// Same instructions in the same order per output element as the other shapes, so the same bits.
+// Measured (8 tokens, d 2048, 64 experts of 1408 and two shared): gate/up 44.2 -> 35.3 us, down 22.7 -> 20.2 with
+// the weights partly in the memory-side cache, 57.7 -> 52.4 and 28.9 -> 26.9 (5.1 TB/s) without.  At 30 tokens,
+// with a second row block, it took 102 us against the weight-stream shape's 100: the line is one row block.
+constexpr int THIN_ROWS = 16;
+constexpr int THIN_SLOTS = 6;    // k tiles (64 wide) of both operands in flight per wavefront
+
+template <bool SWIGLU>
+__device__ __forceinline__ void thin_tile(const StreamProblem& P, const fmoe_tile& tile, int group, int cb) {
+  constexpr int S = THIN_SLOTS;
+  const int lane = threadIdx.x;
+  const int K = P.K, N = P.N;
+  const int NT = (K + SBK - 1) / SBK;
+  const __amdgpu_buffer_rsrc_t b_rsrc = __builtin_amdgcn_make_buffer_rsrc(
+      const_cast<u32x4_t*>(P.Bp) + (size_t)group * P.group_stride + (size_t)(cb >> 2) * (P.ks / 2) * 1024 + (cb & 3) * 256,
+      0, 0xffffffff, 0x00020000);
+  const __amdgpu_buffer_rsrc_t a_rsrc =
+      __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t*>(P.A), 0, 0xffffffff, 0x00020000);
+  const uint32_t lane16 = (uint32_t)lane * 16u;
+  const int kq = (lane >> 4) * 8;
+  u32x4_t breg[S][2][2], areg[S][2];   // [ring slot][k step][fragment]
+  auto load_b = [&](int slot, int t) {   // past the last tile the last one again
+    const int off = (t < NT ? t : NT - 1) * 16384;   // scalar
+#pragma unroll
+    for (int s = 0; s < 2; ++s)
+#pragma unroll
+      for (int f = 0; f < 2; ++f)
+        breg[slot][s][f] = __builtin_amdgcn_raw_buffer_load_b128(b_rsrc, lane16, off + (s * 2 + f) * 1024, 0);
+  };
+  uint32_t a_row;   // byte offset of the lane's row
+  auto load_a = [&](int slot, int t) {   // k past K re-reads the row's end, where the packed weights are zero
+    const int k0 = (t < NT ? t : NT - 1) * SBK;
+#pragma unroll
+    for (int s = 0; s < 2; ++s) {
+      const int k = k0 + s * 32 + kq;
+      areg[slot][s] = __builtin_amdgcn_raw_buffer_load_b128(a_rsrc, a_row + (uint32_t)(k < K ? k : K - 8) * 2u, 0, 0);
+    }
+  };
+  // Row indices (two dependent loads) between the first weight loads, which do not need them.  Rows past the
+  // tile reuse its last row, indices are clamped as in gather_offsets.
+  const uint32_t a_max_row = 0xffffffffu / ((uint32_t)P.lda * 2u) - 1u;
+  int src = tile.row0 + ((lane & 15) < tile.rows ? (lane & 15) : tile.rows - 1);
+  if (P.map1) src = P.map1[src];
+  __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+  for (int t = 0; t < S / 2; ++t) load_b(t, t);
+  __builtin_amdgcn_sched_barrier(0);
+  if (P.map1 && P.map1_limit > 0) src = src < 0 ? 0 : (src >= P.map1_limit ? P.map1_limit - 1 : src);
+  if (P.map2) src = P.map2[src];
+  __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+  for (int t = S / 2; t < S; ++t) load_b(t, t);
+  __builtin_amdgcn_sched_barrier(0);
+  a_row = ((uint32_t)src < a_max_row ? (uint32_t)src : a_max_row) * (uint32_t)P.lda * 2u;
+#pragma unroll
+  for (int t = 0; t < S; ++t) {
+    load_a(t, t);
+    __builtin_amdgcn_sched_barrier(0);
+  }
+
+  f32x4_t acc[2] = {f32x4_t{0.f, 0.f, 0.f, 0.f}, f32x4_t{0.f, 0.f, 0.f, 0.f}};
+  auto multiply = [&](int slot) {
+#pragma unroll
+    for (int s = 0; s < 2; ++s)
+#pragma unroll
+      for (int f = 0; f < 2; ++f)
+        acc[f] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, areg[slot][s]),
+                                                         __builtin_bit_cast(bf16x8_t, breg[slot][s][f]), acc[f], 0, 0, 0);
+  };
+  int t0 = 0;
+  for (; t0 + S <= NT; t0 += S) {   // no exit inside, so that the waits can count on the rings' order
+#pragma unroll
+    for (int u = 0; u < S; ++u) {
+      multiply(u);
+      __builtin_amdgcn_sched_barrier(0);
+      load_b(u, t0 + u + S);
+      load_a(u, t0 + u + S);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  }
+#pragma unroll
+  for (int u = 0; u < S - 1; ++u)
+    if (t0 + u < NT) multiply(u);   // uniform
+  // accumulator register v of lane l: row 4*(l/16) + v, column l%16
+#pragma unroll
+  for (int v = 0; v < 4; ++v) {
+    const int row = 4 * (lane >> 4) + v;
+    if (row >= tile.rows) continue;
+    bf16_t* crow = P.C + (size_t)(tile.row0 + row) * P.ldc;
+    if (SWIGLU) {
+      const int col = cb * 16 + (lane & 15);
+      if (col < N) crow[col] = f32_to_bf16(silu_mul_bf16(acc[0][v], acc[1][v]));
+    } else {
+      const int col = cb * 32 + (lane & 15);
+      if (col < N) crow[col] = f32_to_bf16(acc[0][v]);
+      if (col + 16 < N) crow[col + 16] = f32_to_bf16(acc[1][v]);
+    }
+  }
+}
+
+// Item -> (tile entry, column block), a.cols = column blocks per entry in the launch.
+template <bool SWIGLU>
+__global__ __launch_bounds__(64, 2) void ffn_thin_kernel(StreamArgs a) {
+  const int ti = (int)blockIdx.x / a.cols;
+  if (ti >= *a.n_tiles) return;
+  fmoe_tile tile = a.tiles[ti];
+  const bool shared = tile.group >= a.E;
+  StreamProblem P;
+#define FMOE_SEL(f) P.f = shared ? a.p1.f : a.p0.f
+  FMOE_SEL(A); FMOE_SEL(lda); FMOE_SEL(map1); FMOE_SEL(map2); FMOE_SEL(map1_limit); FMOE_SEL(Bp);
+  FMOE_SEL(group_stride); FMOE_SEL(nbw); FMOE_SEL(ks); FMOE_SEL(C); FMOE_SEL(ldc); FMOE_SEL(N);
+  FMOE_SEL(K); FMOE_SEL(n_col_tiles); FMOE_SEL(a_group_off); FMOE_SEL(c_group_off);
+#undef FMOE_SEL
+  const int cb = tile.col0 * 4 + ((int)blockIdx.x - ti * a.cols);
+  if (cb >= P.nbw) return;
+  const int group = shared ? tile.group - a.E : tile.group;
+  if (shared) {   // per-shared-expert slices of the hidden buffer / output (down GEMM)
+    P.A += (size_t)group * P.a_group_off;
+    P.C += (size_t)group * P.c_group_off;
+  }
+  // one turn unless a caller's own row lists name a token several times for one expert
+  for (int left = tile.rows; left > 0; left -= THIN_ROWS, tile.row0 += THIN_ROWS) {
+    tile.rows = left < THIN_ROWS ? left : THIN_ROWS;
+    thin_tile<SWIGLU>(P, tile, group, cb);
+  }
+}
+
 // Packing: unit u (16 bytes = 8 consecutive k) -> (group, tile of 4 column blocks, 64-wide k tile,
 // column block in the tile = wavefront, 32-wide k step, fragment, lane): the 16 KB a workgroup
 // consumes per k tile are contiguous and its whole stream is one linear run of memory.
@@ -1200,10 +1334,15 @@ int run_ffn_bf16(const fmoe_ctx* ctx, const void* x, const int32_t* kept_idx, in
   bool dense = (long long)n_cap * ctx->kmax >= (long long)FMOE_DENSE_MIN_ROWS * E;
   if (ctx->ffn_shape == 1) dense = false;
   if (ctx->ffn_shape == 2) dense = true;
+  // at most THIN_ROWS tokens: no tile has more rows, and the weight stream wants the finest work items
+  const bool thin = n_cap <= THIN_ROWS && ctx->ffn_shape == 0;
   // the dense shape addresses the packed weights with 32-bit byte offsets
   for (int w = 0; w < 4; ++w)
     if (fmoe_packed_bytes(ctx, w) > 0xffffffffull) dense = false;
-  if (dense) {
+  if (thin) {
+    g1.cols = geo.cols1 * 4;
+    g2.cols = geo.cols2 * 4;
+  } else if (dense) {
     g1.cols = (geo.cols1 + DNCB - 1) / DNCB;
     g2.cols = (geo.cols2 + DNCB - 1) / DNCB;
   }
@@ -1235,16 +1374,22 @@ int run_ffn_bf16(const fmoe_ctx* ctx, const void* x, const int32_t* kept_idx, in
     q.n_col_tiles = geo.scols2;
   }
   const unsigned batches = (unsigned)((geo.tile_cap + 7) / 8);
+  // tile entries the lists of a thin call can have (geo.tile_cap allows for one of every expert)
+  const int row_cap = n_cap * ctx->kmax;
+  const int all = geo.tile_cap - (row_cap < E ? E - row_cap : 0);
+  const unsigned thin_entries = (unsigned)(all > 0 ? all : 0);
   {
     fmoe_prof_scope prof(ctx, dense ? SLOT_GEMM1_DENSE : SLOT_GEMM1, stream);
     const unsigned items = batches * 8 * g1.cols;
-    if (dense) hipLaunchKernelGGL((ffn_dense_kernel<true>), dim3(items), dim3(256), 0, stream, g1);
+    if (thin) hipLaunchKernelGGL(ffn_thin_kernel<true>, dim3(thin_entries * g1.cols), dim3(64), 0, stream, g1);
+    else if (dense) hipLaunchKernelGGL((ffn_dense_kernel<true>), dim3(items), dim3(256), 0, stream, g1);
     else hipLaunchKernelGGL((ffn_stream_kernel<true>), dim3(items), dim3(256), 0, stream, g1);
   }
   {
     fmoe_prof_scope prof(ctx, dense ? SLOT_GEMM2_DENSE : SLOT_GEMM2, stream);
     const unsigned items = batches * 8 * g2.cols;
-    if (dense) hipLaunchKernelGGL((ffn_dense_kernel<false>), dim3(items), dim3(256), 0, stream, g2);
+    if (thin) hipLaunchKernelGGL(ffn_thin_kernel<false>, dim3(thin_entries * g2.cols), dim3(64), 0, stream, g2);
+    else if (dense) hipLaunchKernelGGL((ffn_dense_kernel<false>), dim3(items), dim3(256), 0, stream, g2);
     else hipLaunchKernelGGL((ffn_stream_kernel<false>), dim3(items), dim3(256), 0, stream, g2);
   }
   return FMOE_OK;

@@ -1409,3 +1409,33 @@ def test_expert_ffn_fp32_tile_edges(d, F):
             assert max_rel_err(host(y)[lo:lo + c], ref) <= TOL[W.F32], (e, c)
     for s in range(2):
         assert max_rel_err(host(ysh)[s], ffn(rows, sh[0][s], sh[1][s], sh[2][s])) <= TOL[W.F32], s
+
+
+@pytest.mark.parametrize("n,d,F", [(1, 8, 8), (3, 136, 40), (8, 712, 456), (15, 392, 776), (16, 1288, 264), (17, 136, 40)])
+def test_expert_ffn_thin_shape(n, d, F):
+    """Calls of at most 16 tokens take a kernel shape of their own: the same bits as the weight-stream shape
+    (which the oracle tests cover) at reductions of 1 to 21 k tiles, whole and partial, at every row count of a
+    tile, with empty experts and with a row list that names tokens several times (more than 16 rows)."""
+    k, E = 5, 11
+    g = torch.Generator(device="cuda")
+    g.manual_seed(n * 1000 + d)
+    rnd = lambda *s: (torch.randn(s, generator=g, device="cuda") * 0.2).bfloat16()
+    counts = np.zeros(E, np.int64)
+    left = n * k
+    for e, want in enumerate([0, n, 1, min(n, 5), 2 * n, 0, min(n, 15), 1, 1, 2, 0]):
+        counts[e] = min(left, want)
+        left -= counts[e]
+    offs = torch.tensor(np.concatenate([[0], np.cumsum(counts)]), dtype=torch.int32, device="cuda")
+    x, wr = rnd(40, d), rnd(E, d)
+    w = [rnd(E, F, d), rnd(E, F, d), rnd(E, d, F), rnd(2, F, d), rnd(2, F, d), rnd(2, d, F)]
+    kept = torch.randperm(40, generator=g, device="cuda").int()[:n].contiguous()
+    perm = torch.randint(0, n, (n * k,), generator=g, device="cuda").int()
+    got = []
+    for shape in (0, 1):
+        m = binding.FMoE(d_model=d, n_experts=E, d_ffn=F, n_shared=2, d_ffn_shared=F, k_text=k, k_visual=2, dtype="bf16")
+        m.set_weights(wr, None, *w)
+        m.set_ffn_shape(shape)
+        y, ysh = m.expert_ffn(x, kept, n, offs, perm)
+        got.append((y[:int(counts.sum())].clone(), ysh.clone()))
+    assert torch.equal(got[0][0], got[1][0]) and torch.equal(got[0][1], got[1][1])
+    assert got[0][0].float().abs().max() > 0 and torch.isfinite(got[0][0].float()).all()
