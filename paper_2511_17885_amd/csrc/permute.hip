@@ -67,6 +67,127 @@ __global__ __launch_bounds__(PB) void permute_count_kernel(
   }
 }
 
+// Exclusive scan of the E (at most 256) totals into offsets[0..E] by the block's first wavefront, four per lane.
+__device__ __forceinline__ void scan_totals(const int* total, int E, int32_t* offsets) {
+  if (threadIdx.x < 64) {
+    const int lane = threadIdx.x;
+    int c[4], sum = 0;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int i = 4 * lane + q;
+      c[q] = (i < E) ? total[i] : 0;
+      sum += c[q];
+    }
+    int incl = sum;
+#pragma unroll
+    for (int sh = 1; sh < 64; sh <<= 1) {
+      const int o = __shfl_up(incl, sh, 64);
+      if (lane >= sh) incl += o;
+    }
+    int excl = incl - sum;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int i = 4 * lane + q;
+      if (i < E) offsets[i] = excl;
+      excl += c[q];
+    }
+    if (lane == 63) offsets[E] = incl;
+  }
+}
+
+// ---- P2 + P3 in one launch, up to FMOE_PERM_JOIN_BLOCKS blocks of positions: every block sums the per-block
+// counts itself (totals over all blocks, bases over those before it; E counts per block, from L2), scans the
+// totals and scatters its own positions.  One more block writes the offsets and builds the GEMM work lists, so
+// that neither waits for the other.  A launch less and no walk by a single block: at 22016 tokens / 64 experts
+// the scan and the scatter took 22 + 6 us, this takes 17.5; at 4224 of 8192 tokens / 128 experts 10 + 6 us, now
+// 10.9; at 2176 of 4096 / 64 7 + 5, now 8.6.  The reads grow with the square of the block count, which is
+// why longer batches keep the two launches.
+__global__ __launch_bounds__(PB) void permute_scan_scatter_kernel(
+    const int32_t* __restrict__ topk_idx, const int32_t* __restrict__ kept_idx, int n_cap,
+    const int32_t* __restrict__ n_dev, int E, int Kmax, const int32_t* __restrict__ slot_rank,
+    const int32_t* __restrict__ blk_count, int32_t* __restrict__ expert_offsets,
+    int32_t* __restrict__ perm_src, int32_t* __restrict__ inv_perm, fmoe_ffn_geom geom, int build, int n_shared,
+    fmoe_tile* __restrict__ tiles1, fmoe_tile* __restrict__ tiles2, int32_t* __restrict__ tile_count) {
+  __shared__ int s_tot[PB], s_pre[PB], s_off[FMOE_MAX_EXPERTS + 1];
+  __shared__ __align__(8) int scratch[513];
+  const int n = resolve_count(n_cap, n_dev);
+  const int nblk = (n + PB - 1) / PB;
+  const int blk = blockIdx.x;
+  const bool lists = blk == (int)gridDim.x - 1;   // the extra block
+  if (!lists && blk >= nblk) return;
+  const int tid = threadIdx.x;
+  int ep = 1;
+  while (ep < E) ep <<= 1;                        // experts side by side, PB/ep shares of the blocks
+  const int e = tid & (ep - 1), share = tid / ep, shares = PB / ep;
+  int tot = 0, pre = 0;
+  if (e < E) {
+    constexpr int SC = 8;                         // independent loads at a time
+    for (int b0 = share; b0 < nblk; b0 += SC * shares) {
+      int c[SC];
+#pragma unroll
+      for (int i = 0; i < SC; ++i) {
+        const int b = b0 + i * shares;
+        c[i] = b < nblk ? blk_count[(size_t)b * E + e] : 0;
+      }
+#pragma unroll
+      for (int i = 0; i < SC; ++i) {
+        tot += c[i];
+        pre += b0 + i * shares < blk ? c[i] : 0;
+      }
+    }
+  }
+  // the block's own positions meanwhile
+  const int p = blk * PB + tid;
+  const bool mine = !lists && p < n;
+  int ex[FMOE_MAX_TOPK], rank[FMOE_MAX_TOPK];
+  if (mine) {
+    const int t = kept_idx ? kept_idx[p] : p;
+#pragma unroll
+    for (int s = 0; s < FMOE_MAX_TOPK; ++s) {
+      if (s < Kmax) {
+        ex[s] = topk_idx[(size_t)t * Kmax + s];
+        rank[s] = slot_rank[(size_t)p * Kmax + s];
+      }
+    }
+  }
+  s_tot[tid] = tot;
+  s_pre[tid] = pre;
+  __syncthreads();
+  if (tid < ep) {
+    for (int q = 1; q < shares; ++q) {
+      tot += s_tot[q * ep + tid];
+      pre += s_pre[q * ep + tid];
+    }
+  }
+  __syncthreads();
+  if (tid < ep) {
+    s_tot[tid] = tot;
+    s_pre[tid] = pre;
+  }
+  __syncthreads();
+  scan_totals(s_tot, E, s_off);
+  __syncthreads();
+  if (lists) {
+    for (int i = tid; i <= E; i += PB) expert_offsets[i] = s_off[i];
+    if (build)   // fused layer path
+      fmoe_build_tiles(s_off, E, n_cap * Kmax, n, n_shared, geom.bm, geom.tile_cap, geom.cols1, geom.scols1,
+                       tiles1, tiles2, tile_count, scratch);
+    return;
+  }
+  if (!mine) return;
+#pragma unroll
+  for (int s = 0; s < FMOE_MAX_TOPK; ++s) {
+    if (s < Kmax) {
+      int row = -1;
+      if (ex[s] >= 0 && ex[s] < E) {
+        row = s_off[ex[s]] + s_pre[ex[s]] + rank[s];
+        perm_src[row] = p;
+      }
+      inv_perm[(size_t)p * Kmax + s] = row;
+    }
+  }
+}
+
 // ---- P2: one block; thread e scans its expert's per-block counts (turning them into block
 // bases in place), then the per-expert totals are scanned into expert_offsets.
 __global__ __launch_bounds__(256) void permute_scan_kernel(int n_cap, const int32_t* __restrict__ n_dev,
@@ -99,30 +220,7 @@ __global__ __launch_bounds__(256) void permute_scan_kernel(int n_cap, const int3
     total[e] = running;
   }
   __syncthreads();
-  if (threadIdx.x < 64) {   // exclusive scan of the (at most 256) totals by one wavefront, four per lane
-    const int lane = threadIdx.x;
-    int c[4], sum = 0;
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const int i = 4 * lane + q;
-      c[q] = (i < E) ? total[i] : 0;
-      sum += c[q];
-    }
-    int incl = sum;
-#pragma unroll
-    for (int sh = 1; sh < 64; sh <<= 1) {
-      const int o = __shfl_up(incl, sh, 64);
-      if (lane >= sh) incl += o;
-    }
-    int excl = incl - sum;
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const int i = 4 * lane + q;
-      if (i < E) expert_offsets[i] = excl;
-      excl += c[q];
-    }
-    if (lane == 63) expert_offsets[E] = incl;
-  }
+  scan_totals(total, E, expert_offsets);
   if (build) {   // fused layer path: the grouped-GEMM work lists come out of the same scan
     __threadfence_block();
     __syncthreads();
@@ -168,6 +266,16 @@ int launch_permute(const fmoe_ctx* ctx, const int32_t* topk_idx, const int32_t* 
     fmoe_prof_scope prof(ctx, SLOT_PERM_COUNT, stream);
     hipLaunchKernelGGL(permute_count_kernel, dim3(nblk), dim3(PB), 0, stream, topk_idx, kept_idx,
                        n_cap, n_dev, E, Kmax, slot_rank, blk_count);
+  }
+  if (nblk > 0 && nblk <= FMOE_PERM_JOIN_BLOCKS && Kmax > 0) {
+    fmoe_prof_scope prof(ctx, SLOT_PERM_SCATTER, stream);
+    hipLaunchKernelGGL(permute_scan_scatter_kernel, dim3(nblk + 1), dim3(PB), 0, stream, topk_idx, kept_idx,
+                       n_cap, n_dev, E, Kmax, slot_rank, blk_count, expert_offsets, perm_src, inv_perm,
+                       fmoe_geom(ctx, n_cap), build_tiles ? 1 : 0, ctx->cfg.n_shared,
+                       reinterpret_cast<fmoe_tile*>(base + L.tiles), reinterpret_cast<fmoe_tile*>(base + L.tiles2),
+                       reinterpret_cast<int32_t*>(base + L.tile_count));
+    FMOE_HIP_CHECK(hipGetLastError());
+    return FMOE_OK;
   }
   {
     fmoe_prof_scope prof(ctx, SLOT_PERM_SCAN, stream);

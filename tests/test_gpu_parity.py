@@ -1439,3 +1439,23 @@ def test_expert_ffn_thin_shape(n, d, F):
         got.append((y[:int(counts.sum())].clone(), ysh.clone()))
     assert torch.equal(got[0][0], got[1][0]) and torch.equal(got[0][1], got[1][1])
     assert got[0][0].float().abs().max() > 0 and torch.isfinite(got[0][0].float()).all()
+
+
+@pytest.mark.parametrize("n,E,k", [(1, 3, 3), (255, 256, 16), (256, 64, 6), (257, 100, 8), (2049, 1, 1), (5003, 128, 8),
+                                   (65536, 33, 2), (65537, 33, 2)])
+def test_permute_block_counts(n, E, k):
+    """One launch for scan and scatter up to 256 blocks of positions, two beyond: around a block, at expert counts
+    that are no power of two, with padded slots, with and without an index list and a device count."""
+    rng = np.random.default_rng(n + E)
+    idx = np.argsort(rng.random((n, max(E, k))), axis=1)[:, :k].astype(np.int32)
+    idx[rng.random((n, k)) < 0.2] = -1
+    m = binding.FMoE(d_model=8, n_experts=E, d_ffn=8, k_text=k, k_visual=k, dtype="f32")
+    kept = np.flatnonzero(rng.random(n) < 0.7).astype(np.int32)
+    for lst in (None, kept):
+        c = n if lst is None else len(lst)
+        o_offs, o_perm, o_inv = oracle.permute(idx, lst, E)
+        padded = None if lst is None else dev(np.concatenate([lst, np.zeros(n - c, np.int32)]))
+        offs, perm, inv = m.permute(dev(idx), padded, n, n_kept_dev=dev(np.array([c], np.int32)))   # capacity n >= c
+        M = int(o_offs[-1])
+        assert np.array_equal(host(offs), o_offs) and np.array_equal(host(perm)[:M], o_perm[:M])
+        assert np.array_equal(host(inv)[:c], o_inv[:c])
