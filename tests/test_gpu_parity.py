@@ -1459,3 +1459,22 @@ def test_permute_block_counts(n, E, k):
         M = int(o_offs[-1])
         assert np.array_equal(host(offs), o_offs) and np.array_equal(host(perm)[:M], o_perm[:M])
         assert np.array_equal(host(inv)[:c], o_inv[:c])
+
+
+@pytest.mark.parametrize("T_v,T_t,k", [([1990, 50], [6, 2], 8), ([1990, 50], [6, 3], 8), ([2900, 1100], [60, 36], 8),
+                                       ([2900, 1100], [60, 36], 9)])
+@pytest.mark.parametrize("gamma", [0.0, 0.1])
+def test_small_dispatch_register_sizes(T_v, T_t, k, gamma):
+    """The single-workgroup dispatch at the edges of its register-array sizes: 2048 and 2049 tokens, 4096 tokens,
+    eight and nine experts per token, with pruning inside it and (merging) as permutation only."""
+    wl = W.small_random(700 + k, T_v=T_v, T_t=T_t, d=32, E=24, F=16, k_text=k, k_visual=3, retention=0.5, window=5,
+                        bias_std=1.0, n_components=12)
+    m = make_layer(wl)
+    x, vis, cu = inputs(wl)
+    pp = binding.prune_params(retention=0.5, window=5, gamma=gamma)
+    out, kept, new_cu, _ = m.layer_forward(x, vis, cu, pp, add_residual=True)
+    o = oracle.layer_forward(wl.x, wl.is_visual, wl.cu_seqlens, wl.weights, k_text=k, k_visual=3, is_bf16=False,
+                             retention=0.5, window=5, gamma=gamma, add_residual=True)
+    n = len(o["kept_idx"])
+    assert int(host(new_cu)[-1]) == n and np.array_equal(host(kept)[:n], o["kept_idx"])
+    assert max_rel_err(host(out)[:n], o["out_f64"]) <= TOL[W.F32]
