@@ -1478,3 +1478,25 @@ def test_small_dispatch_register_sizes(T_v, T_t, k, gamma):
     n = len(o["kept_idx"])
     assert int(host(new_cu)[-1]) == n and np.array_equal(host(kept)[:n], o["kept_idx"])
     assert max_rel_err(host(out)[:n], o["out_f64"]) <= TOL[W.F32]
+
+
+@pytest.mark.parametrize("dtype", [W.F32, W.BF16])
+@pytest.mark.parametrize("d,window", [(8, 2), (2040, 5), (2048, 4), (2056, 7), (4104, 9)])
+def test_prune_merge_row_widths(dtype, d, window):
+    """The merged layer input around the widths a thread keeps in registers (2048 columns a block) and the rows
+    whose norms are reduced together (four), copied rows bit for bit."""
+    wl = W.small_random(640 + d, T_v=[61, 40], T_t=[5, 3], d=d, E=16, F=16, k_text=2, k_visual=1, retention=0.5,
+                        window=window, dtype=dtype, n_components=6)
+    o_probs, _, _ = oracle.route(wl.x, wl.is_visual, wl.weights.router_w, None, 2, 1)
+    m = make_layer(wl)
+    x, vis, cu = inputs(wl)
+    o_kept, o_cu, _, o_mrg, o_xm = oracle.prune(o_probs, wl.is_visual, wl.cu_seqlens, 0.5, window, gamma=0.2, x=wl.x,
+                                                is_bf16=dtype == W.BF16)
+    kept, new_cu, _, mrg, x_m = m.prune(binding.prune_params(retention=0.5, window=window, gamma=0.2), dev(o_probs),
+                                        vis, cu, x=x)
+    n = int(host(new_cu)[-1])
+    assert np.array_equal(host(new_cu), o_cu) and np.array_equal(host(kept)[:n], o_kept)
+    assert np.array_equal(host(mrg)[:n], o_mrg) and o_mrg.sum() > 0
+    plain = o_mrg == 0
+    assert np.array_equal(host(x_m)[:n][plain], o_xm[plain])
+    _check_merged_rows(host(x_m)[:n], o_xm, o_mrg, wl.dtype)
