@@ -411,6 +411,18 @@ int fmoe_layer_forward(fmoe_ctx* ctx, const fmoe_prune_params* params, const voi
     ord = fmoe_ordinals_job{cu_seqlens, B, reinterpret_cast<int32_t*>(base + L.vis_ord),
                             reinterpret_cast<int32_t*>(base + L.vis_tok),
                             reinterpret_cast<int32_t*>(base + L.seq_nv)};
+  if (small && !do_prune && T <= FMOE_ROUTE_DISPATCH_TOKENS && ctx->sel_strategy == 0) {
+    // a decoding step: the router's one block writes the permutation and the work lists as well
+    const fmoe_dispatch_job job{cu_seqlens, B, kept_idx, new_cu_seqlens, is_visual_out, expert_offsets, perm_src,
+                                inv_perm, fmoe_geom(ctx, T), ctx->cfg.n_shared, T * ctx->kmax,
+                                reinterpret_cast<fmoe_tile*>(base + L.tiles), reinterpret_cast<fmoe_tile*>(base + L.tiles2),
+                                reinterpret_cast<int32_t*>(base + L.tile_count)};
+    if ((rc = launch_route(ctx, x, is_visual, T, nullptr, topk_idx, topk_gate, ord, s, nullptr, &job)) != FMOE_OK)
+      return rc;
+    if ((rc = launch_expert_ffn(ctx, x, nullptr, T, nullptr, expert_offsets, perm_src, y, y_shared, ws, L, true, s)) != FMOE_OK)
+      return rc;
+    return launch_combine(ctx, y, y_shared, inv_perm, topk_gate, nullptr, T, nullptr, add_residual ? x : nullptr, out, s);
+  }
   if ((rc = launch_route(ctx, x, is_visual, T, do_prune ? probs : nullptr, topk_idx, topk_gate, ord, s)) != FMOE_OK)
     return rc;
   const int32_t* kept = nullptr;

@@ -11,6 +11,7 @@
 #define FMOE_MAX_TOPK 16
 #define FMOE_MAX_WINDOW 64
 #define FMOE_PERM_BLOCK 256   // kept positions per block in the permutation kernels
+#define FMOE_ROUTE_DISPATCH_TOKENS 16   // tokens up to which the router's one block does the dispatch too
 #define FMOE_PERM_JOIN_BLOCKS 256   // blocks of positions up to which scan and scatter are one launch
 #define FMOE_TILE_M 64        // rows per grouped-GEMM tile (tile list granularity)
 #define FMOE_TILE_RUN 8       // row tiles per run of a group in the tile lists
@@ -114,10 +115,23 @@ struct fmoe_ordinals_job {
   int B;
   int32_t *vis_ord, *vis_tok, *seq_nv;
 };
-// T_dev (nullable): device count of the tokens actually present (<= T, the capacity).
+// What the dispatch step writes when every token is kept, for a router launch of one block to write as well
+// (at most FMOE_ROUTE_DISPATCH_TOKENS tokens, default selection strategy).
+struct fmoe_dispatch_job {
+  const int32_t* cu;
+  int B;
+  int32_t *kept_idx, *new_cu;
+  uint8_t* is_visual_out;      // or nullptr
+  int32_t *expert_offsets, *perm_src, *inv_perm;
+  fmoe_ffn_geom geom;
+  int n_shared, row_cap;
+  fmoe_tile *tiles1, *tiles2;
+  int32_t* tile_count;
+};
+// T_dev (nullable): device count of the tokens actually present (<= T, the capacity).  dispatch (nullable): see above.
 int launch_route(const fmoe_ctx* ctx, const void* x, const uint8_t* is_visual, int T, float* probs,
                  int32_t* topk_idx, float* topk_gate, const fmoe_ordinals_job& ord, hipStream_t stream,
-                 const int32_t* T_dev = nullptr);
+                 const int32_t* T_dev = nullptr, const fmoe_dispatch_job* dispatch = nullptr);
 
 int launch_prune(const fmoe_ctx* ctx, const fmoe_prune_params* pp, const float* probs,
                  const uint8_t* is_visual, const int32_t* cu_seqlens, int B, int T,

@@ -1500,3 +1500,24 @@ def test_prune_merge_row_widths(dtype, d, window):
     plain = o_mrg == 0
     assert np.array_equal(host(x_m)[:n][plain], o_xm[plain])
     _check_merged_rows(host(x_m)[:n], o_xm, o_mrg, wl.dtype)
+
+
+@pytest.mark.parametrize("dtype", [W.F32, W.BF16])
+@pytest.mark.parametrize("T_v,T_t,E,k,kv,shared", [
+    ([0], [1], 8, 2, 1, 0), ([0, 0, 0], [1, 1, 1], 64, 6, 3, 1), ([3, 0, 2], [4, 0, 7], 256, 16, 5, 0),
+    ([9], [6], 129, 8, 8, 2), ([5], [11], 16, 4, 0, 1), ([0, 8], [8, 0], 3, 3, 3, 0), ([6], [11], 24, 5, 2, 1),
+])
+def test_layer_forward_up_to_sixteen_tokens(dtype, T_v, T_t, E, k, kv, shared):
+    """Layers of at most 16 tokens that keep all of them take the dispatch from the router's launch (the last case,
+    17 tokens, does not): empty sequences, every expert touched or none by a modality, more lists than experts."""
+    wl = W.small_random(330 + E, T_v=T_v, T_t=T_t, d=136, E=E, F=40, k_text=k, k_visual=kv, retention=1.0, window=3,
+                        dtype=dtype, n_shared=shared, F_shared=24 if shared else 0, bias_std=1.0)
+    m = make_layer(wl)
+    x, vis, cu = inputs(wl)
+    o = oracle.layer_forward(wl.x, wl.is_visual, wl.cu_seqlens, wl.weights, k_text=k, k_visual=kv,
+                             is_bf16=dtype == W.BF16, do_prune=False)
+    for _ in range(2):      # scratch left by the first call does not matter
+        out, kept, new_cu, mask = m.layer_forward(x, vis, cu, None, want_mask=True)
+        assert np.array_equal(host(kept)[:wl.T], np.arange(wl.T)) and np.array_equal(host(new_cu), wl.cu_seqlens)
+        assert np.array_equal(host(mask)[:wl.T], wl.is_visual)
+        assert max_rel_err(host(out)[:wl.T], o["out_f64"]) <= TOL[dtype]
