@@ -599,7 +599,8 @@ int fmoe_flops_ratios(const fmoe_flops_model* m, double* ratios) {
 int fmoe_profile_slots(void) { return SLOT_COUNT; }
 
 const char* fmoe_profile_name(int slot) {
-  // kernel symbols (the two expert GEMMs: bf16 symbol; fp32 contexts run grouped_gemm_kernel)
+  // kernel symbols (the two expert GEMMs: bf16 symbol; fp32 contexts run grouped_gemm_kernel, calls of at most 16
+  // tokens ffn_thin_kernel; scan and scatter in one launch are timed as the scatter)
   static const char* names[SLOT_COUNT] = {
       "route_kernel", "seq_ordinals_kernel", "window_score_kernel", "select_kernel", "compact_flag_kernel+compact_write_kernel",
       "prune_dispatch_small_kernel", "permute_count_kernel", "permute_scan_kernel",
