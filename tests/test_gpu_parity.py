@@ -1331,6 +1331,37 @@ def test_layer_forward_merge_after_the_layer_over_several_compaction_blocks(with
     _check_after_layer_rows(host(out)[:n], o, wl.x, wl.dtype, f"attention {with_attention}")
 
 
+@pytest.mark.parametrize("dtype", [W.F32, W.BF16])
+@pytest.mark.parametrize("T_v,T_t,window,prune", [
+    ([4070], [40], 3, None),                                        # more tokens than the single-workgroup kernel takes
+    ([4070], [40], 3, dict()),
+    ([2600, 2, 1900], [30, 0, 9], 5, dict(gamma=0.1)),
+    ([1400, 7], [11, 3], 1, dict()),                                # more windows than it takes
+    ([90, 30], [6, 2], 3, dict(gamma=0.1, prune_mode=2)),           # merging after the layer
+    ([90, 30], [6, 2], 3, dict()),                                  # the single-workgroup kernel
+    ([4], [5], 3, None),                                            # dispatch from the router's launch
+])
+def test_layer_forward_shared_experts_only(dtype, T_v, T_t, window, prune):
+    """No routed expert at all (k = 0 for both modalities): the shared experts still run on every kept token, on
+    each chain of kernels a layer can take.  The workspace starts as NaN, so a product left out shows."""
+    wl = W.small_random(540 + window, T_v=T_v, T_t=T_t, d=72, E=12, F=16, k_text=0, k_visual=0, retention=0.5,
+                        window=window, dtype=dtype, n_shared=2, F_shared=40, bias_std=1.0, n_components=12)
+    pp = None if prune is None else binding.prune_params(retention=0.5, window=window, **prune)
+    kw = dict(do_prune=False) if prune is None else dict(gamma=prune.get("gamma", 0.0),
+                                                         after_layer=prune.get("prune_mode") == 2)
+    o = _oracle(wl, **kw)
+    m = make_layer(wl)
+    x, vis, cu = inputs(wl)
+    m.workspace(wl.T, len(T_v)).fill_(0xff)
+    out, kept, new_cu, _ = m.layer_forward(x, vis, cu, pp)
+    n = int(host(new_cu)[-1])
+    assert np.array_equal(host(new_cu), o["new_cu_seqlens"]) and np.array_equal(host(kept)[:n], o["kept_idx"])
+    if kw.get("after_layer"):
+        _check_after_layer_rows(host(out)[:n], o, None, dtype, "shared experts only")
+    else:
+        assert_outputs_close(host(out)[:n], o["out_f64"], dtype, "shared experts only")
+
+
 @pytest.mark.parametrize("shape", SHAPES)
 def test_layer_forward_general_chain_at_the_widest_routing(shape):
     """The largest expert count and top-k the library takes (256 experts, 16 per text token), shared experts,
