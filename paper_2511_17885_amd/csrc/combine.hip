@@ -41,24 +41,30 @@ template <> struct Vec<float> {
 
 // A small batch is a chain of memory latencies, so the block's indices are fetched in two steps, by scalar
 // loads that depend on nothing but the step before: the count, the token and the rows of its slots, then the
-// gates (with the first of the data); 8 tokens, d 2048: 7.4 -> 5.3 us; 22016 tokens: 167.7 -> 164.3 us, 5.5 TB/s,
-// which is what a large copy reaches.  KM: slots a token can have.
+// gates (with the first of the data).  KM is the number of slots itself, so that a step is one or two wide
+// scalar loads; with arrays of eight or sixteen and a load per entry the scalar cache was the bound of narrow
+// rows (22016 tokens of d 128, two slots: 24.9 us, now 11.0; 13.1 through LDS, one thread a slot, behind a
+// barrier).  Wavefronts without columns leave at once.  Eight blocks a CU (what the scalar registers of sixteen
+// slots would not allow): 1600 tokens of d 2048 in fp32, sixteen slots, 43.8 -> 38.1 us.  8 tokens, d 2048, eight
+// slots, through LDS and now: 4.4 -> 4.0 us; 22016 tokens, d 2048: 179 us both, 5.5 TB/s, which is what a large
+// copy reaches.
 template <typename T, int KM>
-__global__ __launch_bounds__(256) void combine_kernel(
+__global__ __launch_bounds__(256, 8) void combine_kernel(
     const T* __restrict__ y, const T* __restrict__ y_shared, const int32_t* __restrict__ inv_perm,
     const float* __restrict__ topk_gate, const int32_t* __restrict__ kept_idx, int n_cap,
-    const int32_t* __restrict__ n_dev, int row_cap, int Kmax, int d, int n_shared,
-    const T* __restrict__ residual, T* __restrict__ out) {
+    const int32_t* __restrict__ n_dev, int row_cap, int d, int n_shared, const T* __restrict__ residual,
+    T* __restrict__ out) {
   constexpr int N = Vec<T>::N;
+  if ((int)(threadIdx.x & ~63u) * N >= d) return;   // uniform over the wavefront
   const int p = blockIdx.x;
-  int rows[KM];
+  int rows[KM > 0 ? KM : 1];
 #pragma unroll
-  for (int s = 0; s < KM; ++s) rows[s] = Kmax > 0 ? inv_perm[(size_t)p * Kmax + (s < Kmax ? s : Kmax - 1)] : -1;
+  for (int s = 0; s < KM; ++s) rows[s] = inv_perm[(size_t)p * KM + s];
   const int t = kept_idx ? kept_idx[p] : p;
   if (p >= resolve_count(n_cap, n_dev)) return;
-  float gates[KM];
+  float gates[KM > 0 ? KM : 1];
 #pragma unroll
-  for (int s = 0; s < KM; ++s) gates[s] = Kmax > 0 ? topk_gate[(size_t)t * Kmax + (s < Kmax ? s : Kmax - 1)] : 0.0f;
+  for (int s = 0; s < KM; ++s) gates[s] = topk_gate[(size_t)t * KM + s];
   for (int c = threadIdx.x * N; c < d; c += 256 * N) {
     float acc[N], v[N];
 #pragma unroll
@@ -78,7 +84,7 @@ __global__ __launch_bounds__(256) void combine_kernel(
 #pragma unroll
     for (int s = 0; s < KM; ++s) {
       const int r = rows[s];
-      if (s >= Kmax || r < 0 || r >= row_cap) continue;   // uniform
+      if (r < 0 || r >= row_cap) continue;   // uniform
       Vec<T>::load(y + (size_t)r * d + c, v);
 #pragma unroll
       for (int i = 0; i < N; ++i) acc[i] = fmaf(gates[s], v[i], acc[i]);
@@ -87,18 +93,17 @@ __global__ __launch_bounds__(256) void combine_kernel(
   }
 }
 
-template <typename T>
+template <typename T, int KM>
 void launch_combine_t(const fmoe_ctx* ctx, const void* y, const void* y_shared, const int32_t* inv_perm,
                       const float* topk_gate, const int32_t* kept_idx, int n_cap, const int32_t* n_dev,
                       const void* residual, void* out, hipStream_t stream) {
-  const int d = ctx->cfg.d_model, Kmax = ctx->kmax;
-#define FMOE_COMBINE_LAUNCH(KM)                                                                              \
-  hipLaunchKernelGGL((combine_kernel<T, KM>), dim3(n_cap), dim3(256), 0, stream, static_cast<const T*>(y),   \
-                     static_cast<const T*>(y_shared), inv_perm, topk_gate, kept_idx, n_cap, n_dev,           \
-                     n_cap * Kmax, Kmax, d, ctx->cfg.n_shared, static_cast<const T*>(residual), static_cast<T*>(out))
-  if (Kmax <= 8) FMOE_COMBINE_LAUNCH(8);
-  else FMOE_COMBINE_LAUNCH(FMOE_MAX_TOPK);
-#undef FMOE_COMBINE_LAUNCH
+  if constexpr (KM < FMOE_MAX_TOPK) {
+    if (ctx->kmax > KM)
+      return launch_combine_t<T, KM + 1>(ctx, y, y_shared, inv_perm, topk_gate, kept_idx, n_cap, n_dev, residual, out, stream);
+  }
+  hipLaunchKernelGGL((combine_kernel<T, KM>), dim3(n_cap), dim3(256), 0, stream, static_cast<const T*>(y),
+                     static_cast<const T*>(y_shared), inv_perm, topk_gate, kept_idx, n_cap, n_dev, n_cap * KM,
+                     ctx->cfg.d_model, ctx->cfg.n_shared, static_cast<const T*>(residual), static_cast<T*>(out));
 }
 
 }  // namespace
@@ -109,9 +114,9 @@ int launch_combine(const fmoe_ctx* ctx, const void* y, const void* y_shared, con
   if (n_cap == 0) return FMOE_OK;
   fmoe_prof_scope prof(ctx, SLOT_COMBINE, stream);
   if (ctx->cfg.dtype == FMOE_BF16)
-    launch_combine_t<bf16_t>(ctx, y, y_shared, inv_perm, topk_gate, kept_idx, n_cap, n_dev, residual, out, stream);
+    launch_combine_t<bf16_t, 0>(ctx, y, y_shared, inv_perm, topk_gate, kept_idx, n_cap, n_dev, residual, out, stream);
   else
-    launch_combine_t<float>(ctx, y, y_shared, inv_perm, topk_gate, kept_idx, n_cap, n_dev, residual, out, stream);
+    launch_combine_t<float, 0>(ctx, y, y_shared, inv_perm, topk_gate, kept_idx, n_cap, n_dev, residual, out, stream);
   FMOE_HIP_CHECK(hipGetLastError());
   return FMOE_OK;
 }

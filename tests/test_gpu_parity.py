@@ -1472,6 +1472,42 @@ def test_expert_ffn_thin_shape(n, d, F):
     assert got[0][0].float().abs().max() > 0 and torch.isfinite(got[0][0].float()).all()
 
 
+@pytest.mark.parametrize("dtype", [W.F32, W.BF16])
+@pytest.mark.parametrize("k", range(17))
+def test_combine_slot_counts(k, dtype):
+    """The combine has a form for every number of slots, and wavefronts without columns leave it: rows of one
+    16-byte piece, of one and of all wavefronts of a block, and past it; unused slots, shared experts, an index
+    list, fewer tokens than the capacity (rows past them stay untouched).  Against fp64: at most k + 3 terms
+    added in fp32, one rounding to the storage type."""
+    td = torch.bfloat16 if dtype == W.BF16 else torch.float32
+    g = torch.Generator(device="cuda")
+    g.manual_seed(k)
+    for d in (8, 520, 1032, 2056):
+        n, T, kept_n = 23, 40, 19
+        m = binding.FMoE(d_model=d, n_experts=16, d_ffn=8, n_shared=2, d_ffn_shared=8, k_text=k, k_visual=k, dtype=dtype)
+        rnd = lambda *s: torch.randn(s, generator=g, device="cuda").to(td)
+        y, ysh, res = rnd(max(n * k, 1), d), rnd(2, n, d), rnd(T, d)
+        inv = torch.randperm(max(n * k, 1), generator=g, device="cuda").int()[:n * k].view(n, k)
+        inv = torch.where(torch.rand((n, k), generator=g, device="cuda") < 0.2, -1, inv).contiguous()
+        gate = torch.rand((T, k), generator=g, device="cuda")
+        kept = torch.randperm(T, generator=g, device="cuda").int()[:n].contiguous()
+        count = torch.tensor([kept_n], dtype=torch.int32, device="cuda")
+        ref = res[kept.long()].double() + ysh.double().sum(0)
+        size = res[kept.long()].double().abs() + ysh.double().abs().sum(0)
+        for s in range(k):
+            live = (inv[:, s] >= 0).double() * gate[kept.long(), s].double()
+            row = y[inv[:, s].clamp(min=0).long()].double()
+            ref += live[:, None] * row
+            size += live[:, None] * row.abs()
+        out = torch.full((n, d), 7.0, dtype=td, device="cuda")
+        rc = m.lib.fmoe_combine(m._ctx, *[binding._ptr(t) for t in (y, ysh, inv, gate, kept)], n, binding._ptr(count),
+                                binding._ptr(res), binding._ptr(out), binding._stream())
+        assert rc == 0
+        bound = (k + 3) * 2.0 ** -24 * size + HALF_ULP[dtype] * (ref.abs() + (k + 3) * 2.0 ** -24 * size)
+        assert ((out.double() - ref).abs()[:kept_n] <= bound[:kept_n]).all(), d
+        assert (out[kept_n:] == 7.0).all()
+
+
 @pytest.mark.parametrize("n,E,k", [(1, 3, 3), (255, 256, 16), (256, 64, 6), (257, 100, 8), (2049, 1, 1), (5003, 128, 8),
                                    (65536, 33, 2), (65537, 33, 2)])
 def test_permute_block_counts(n, E, k):
