@@ -189,19 +189,22 @@ __global__ __launch_bounds__(PB) void permute_scan_scatter_kernel(
 }
 
 // ---- P2: one block; thread e scans its expert's per-block counts (turning them into block
-// bases in place), then the per-expert totals are scanned into expert_offsets.  counted == 0: no slot is routed
-// anywhere (Kmax == 0) and there are no counts; the work lists still get the n rows of the shared experts.
+// bases in place), then the per-expert totals are scanned into expert_offsets.  n_cap / n_dev: the positions that
+// have been counted, none if no slot is routed anywhere (Kmax == 0); rows_cap / rows_dev: those kept, which is what
+// the work lists give the shared experts.
 __global__ __launch_bounds__(256) void permute_scan_kernel(int n_cap, const int32_t* __restrict__ n_dev,
-                                                           int counted, int E, int32_t* __restrict__ blk_count,
+                                                           int E, int32_t* __restrict__ blk_count,
                                                            int32_t* __restrict__ expert_offsets,
                                                            fmoe_ffn_geom geom, int build, int n_shared,
-                                                           int row_cap, fmoe_tile* __restrict__ tiles1,
+                                                           int row_cap, int rows_cap,
+                                                           const int32_t* __restrict__ rows_dev,
+                                                           fmoe_tile* __restrict__ tiles1,
                                                            fmoe_tile* __restrict__ tiles2,
                                                            int32_t* __restrict__ tile_count) {
   __shared__ int total[FMOE_MAX_EXPERTS];
   __shared__ __align__(8) int scratch[513];
   const int n = resolve_count(n_cap, n_dev);
-  const int nblk = counted ? (n + PB - 1) / PB : 0;
+  const int nblk = (n + PB - 1) / PB;
   const int e = threadIdx.x;
   if (e < E) {
     // SC blocks at a time: their counts are fetched together (independent loads), then turned into
@@ -225,8 +228,8 @@ __global__ __launch_bounds__(256) void permute_scan_kernel(int n_cap, const int3
   if (build) {   // fused layer path: the grouped-GEMM work lists come out of the same scan
     __threadfence_block();
     __syncthreads();
-    fmoe_build_tiles(expert_offsets, E, row_cap, n, n_shared, geom.bm, geom.tile_cap, geom.cols1,
-                     geom.scols1, tiles1, tiles2, tile_count, scratch);
+    fmoe_build_tiles(expert_offsets, E, row_cap, resolve_count(rows_cap, rows_dev), n_shared, geom.bm,
+                     geom.tile_cap, geom.cols1, geom.scols1, tiles1, tiles2, tile_count, scratch);
   }
 }
 
@@ -280,10 +283,10 @@ int launch_permute(const fmoe_ctx* ctx, const int32_t* topk_idx, const int32_t* 
   }
   {
     fmoe_prof_scope prof(ctx, SLOT_PERM_SCAN, stream);
-    hipLaunchKernelGGL(permute_scan_kernel, dim3(1), dim3(256), 0, stream, n_cap, n_dev, Kmax > 0 ? 1 : 0, E,
-                       blk_count, expert_offsets,
+    hipLaunchKernelGGL(permute_scan_kernel, dim3(1), dim3(256), 0, stream, Kmax > 0 ? n_cap : 0,
+                       Kmax > 0 ? n_dev : nullptr, E, blk_count, expert_offsets,
                        fmoe_geom(ctx, n_cap), build_tiles ? 1 : 0, ctx->cfg.n_shared,
-                       n_cap * Kmax, reinterpret_cast<fmoe_tile*>(base + L.tiles),
+                       n_cap * Kmax, n_cap, n_dev, reinterpret_cast<fmoe_tile*>(base + L.tiles),
                        reinterpret_cast<fmoe_tile*>(base + L.tiles2),
                        reinterpret_cast<int32_t*>(base + L.tile_count));
   }
