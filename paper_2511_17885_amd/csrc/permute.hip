@@ -95,13 +95,10 @@ __device__ __forceinline__ void scan_totals(const int* total, int E, int32_t* of
   }
 }
 
-// ---- P2 + P3 in one launch, up to FMOE_PERM_JOIN_BLOCKS blocks of positions: every block sums the per-block
-// counts itself (totals over all blocks, bases over those before it; E counts per block, from L2), scans the
-// totals and scatters its own positions.  One more block writes the offsets and builds the GEMM work lists, so
-// that neither waits for the other.  A launch less and no walk by a single block: at 22016 tokens / 64 experts
-// the scan and the scatter took 22 + 6 us, this takes 17.5; at 4224 of 8192 tokens / 128 experts 10 + 6 us, now
-// 10.9; at 2176 of 4096 / 64 7 + 5, now 8.6.  The reads grow with the square of the block count, which is
-// why longer batches keep the two launches.
+// ---- P2 + P3 in one launch: every block sums the per-block counts itself (totals over all blocks, bases over
+// those before it; E counts per block, from L2), scans the totals and scatters its own positions.  One more block
+// writes the offsets and builds the GEMM work lists, so that neither waits for the other.  A launch less and no
+// walk by a single block.
 __global__ __launch_bounds__(PB) void permute_scan_scatter_kernel(
     const int32_t* __restrict__ topk_idx, const int32_t* __restrict__ kept_idx, int n_cap,
     const int32_t* __restrict__ n_dev, int E, int Kmax, const int32_t* __restrict__ slot_rank,
@@ -188,6 +185,20 @@ __global__ __launch_bounds__(PB) void permute_scan_scatter_kernel(
   }
 }
 
+// Up to which size the joined launch is the faster one.  Every block walks all counts, a thread at least
+// nblk / (256 / E rounded up to a power of two) of them, while the scan's one block walks nblk a thread whatever E is.
+// Whole permutation, two launches after the count -> one, us:
+//   experts 64, 8 slots:   8192 positions 15.4 -> 12.6, 22016 18.4 -> 14.1, 65536 27.7 -> 18.8
+//   experts 128, 8 slots:  8192 15.7 -> 13.4, 22016 19.0 -> 15.9, 65536 28.7 -> 24.1; 16 slots, 65536: 40.7 -> 36.7
+//   experts 256, 1 slot:   8192 9.0 -> 8.75, 16384 10.7 -> 11.1, 65536 20.9 -> 25.8
+//   experts 256, 8 slots:  16384 18.0 -> 17.3, 22016 19.5 -> 19.2, 32768 21.9 -> 22.5, 65536 29.7 -> 33.9
+//   experts 256, 16 slots: 32768 32.8 -> 32.2, 49152 37.3 -> 38.9
+// With more than 128 experts a thread walks all blocks, and the lines cross where a position's own slots (whose
+// loads the walk hides) no longer pay for it: some 40 / 100 / 150 blocks at 1 / 8 / 16 slots.
+bool join_scan_scatter(int nblk, int E, int Kmax) {
+  return nblk <= (E <= 128 ? 256 : 32 + 8 * Kmax);
+}
+
 // ---- P2: one block; thread e scans its expert's per-block counts (turning them into block
 // bases in place), then the per-expert totals are scanned into expert_offsets.  n_cap / n_dev: the positions that
 // have been counted, none if no slot is routed anywhere (Kmax == 0); rows_cap / rows_dev: those kept, which is what
@@ -271,7 +282,7 @@ int launch_permute(const fmoe_ctx* ctx, const int32_t* topk_idx, const int32_t* 
     hipLaunchKernelGGL(permute_count_kernel, dim3(nblk), dim3(PB), 0, stream, topk_idx, kept_idx,
                        n_cap, n_dev, E, Kmax, slot_rank, blk_count);
   }
-  if (nblk > 0 && nblk <= FMOE_PERM_JOIN_BLOCKS && Kmax > 0) {
+  if (nblk > 0 && Kmax > 0 && join_scan_scatter(nblk, E, Kmax)) {
     fmoe_prof_scope prof(ctx, SLOT_PERM_SCATTER, stream);
     hipLaunchKernelGGL(permute_scan_scatter_kernel, dim3(nblk + 1), dim3(PB), 0, stream, topk_idx, kept_idx,
                        n_cap, n_dev, E, Kmax, slot_rank, blk_count, expert_offsets, perm_src, inv_perm,

@@ -1509,10 +1509,12 @@ def test_combine_slot_counts(k, dtype):
 
 
 @pytest.mark.parametrize("n,E,k", [(1, 3, 3), (255, 256, 16), (256, 64, 6), (257, 100, 8), (2049, 1, 1), (5003, 128, 8),
-                                   (65536, 33, 2), (65537, 33, 2)])
+                                   (65536, 33, 2), (65537, 33, 2), (65536, 128, 3), (10240, 256, 1), (10241, 256, 1),
+                                   (24577, 129, 8), (40960, 200, 16)])
 def test_permute_block_counts(n, E, k):
-    """One launch for scan and scatter up to 256 blocks of positions, two beyond: around a block, at expert counts
-    that are no power of two, with padded slots, with and without an index list and a device count."""
+    """One launch for scan and scatter up to 256 blocks of positions (more than 128 experts: 32 + 8k), two beyond:
+    around a block and around those lines, at expert counts that are no power of two, with padded slots, with and
+    without an index list and a device count."""
     rng = np.random.default_rng(n + E)
     idx = np.argsort(rng.random((n, max(E, k))), axis=1)[:, :k].astype(np.int32)
     idx[rng.random((n, k)) < 0.2] = -1
