@@ -20,7 +20,7 @@
 // is about what one XCD runs at a time.
 // counts[0], counts[1] = number of entries in list 1 / list 2.  Experts whose offsets are malformed
 // (negative, decreasing or past row_cap) are skipped so that no tile can index outside the row
-// buffers.  `scratch` is 513 ints of LDS (8-byte aligned); bm is a power of two.
+// buffers; without room for rows (row_cap 0) the offsets are not read and may be null.  `scratch` is 513 ints of LDS (8-byte aligned); bm is a power of two.
 __device__ __forceinline__ void fmoe_build_tiles(const int32_t* expert_offsets, int E, int row_cap,
                                                  int n, int n_shared, int bm, int tile_cap, int cols1,
                                                  int scols1, fmoe_tile* tiles1, fmoe_tile* tiles2,
@@ -28,7 +28,7 @@ __device__ __forceinline__ void fmoe_build_tiles(const int32_t* expert_offsets, 
   const int e = threadIdx.x;
   const int sh = 31 - __clz(bm);   // bm is a power of two
   int r0 = 0, cnt = 0;
-  if (e < E) {
+  if (e < E && row_cap > 0) {
     r0 = expert_offsets[e];
     const int r1 = expert_offsets[e + 1];
     cnt = r1 - r0;

@@ -1508,6 +1508,26 @@ def test_combine_slot_counts(k, dtype):
         assert (out[kept_n:] == 7.0).all()
 
 
+@pytest.mark.parametrize("dtype", [W.F32, W.BF16])
+@pytest.mark.parametrize("n", [3, 16, 17, 300])
+def test_expert_ffn_without_routed_experts(dtype, n):
+    """k = 0 for both modalities: fmoe_expert_ffn takes NULL for everything that describes routed rows."""
+    wl = W.small_random(560 + n, T_v=[n], T_t=[5], d=72, E=12, F=16, k_text=0, k_visual=0, retention=1.0, window=1,
+                        dtype=dtype, n_shared=2, F_shared=40)
+    m = make_layer(wl)
+    x, _, _ = inputs(wl)
+    kept = np.arange(n + 5, dtype=np.int32)[::-1][:n].copy()
+    kept_dev = dev(kept)
+    ysh = torch.full((2, n, wl.d), float("nan"), dtype=torch_dtype(wl), device="cuda")
+    ws = m.workspace(n, 1)
+    rc = m.lib.fmoe_expert_ffn(m._ctx, binding._ptr(x), binding._ptr(kept_dev), n, None, None, None, None,
+                               binding._ptr(ysh), binding._ptr(ws), ws.numel(), binding._stream())
+    assert rc == 0
+    w = wl.weights
+    ref = oracle.shared_ffn(wl.x, kept, n, w.ws_gate, w.ws_up, w.ws_down, dtype == W.BF16)
+    assert_outputs_close(host(ysh).astype(np.float64).sum(0), ref, dtype, "shared experts")
+
+
 @pytest.mark.parametrize("n,E,k", [(1, 3, 3), (255, 256, 16), (256, 64, 6), (257, 100, 8), (2049, 1, 1), (5003, 128, 8),
                                    (65536, 33, 2), (65537, 33, 2), (65536, 128, 3), (10240, 256, 1), (10241, 256, 1),
                                    (24577, 129, 8), (40960, 200, 16)])
