@@ -427,6 +427,7 @@ __global__ __launch_bounds__(256) void route_kernel(
   }
 
   if constexpr (DISPATCH) {
+    static_assert(FMOE_ROUTE_DISPATCH_TOKENS <= TOKB, "one block has all tokens");
     static_assert(TOKB <= 31, "the token masks are ints");
     int* s_mask = reinterpret_cast<int*>(smem);          // [FMOE_MAX_EXPERTS] tokens of the expert
     int* s_off = s_mask + FMOE_MAX_EXPERTS;              // [FMOE_MAX_EXPERTS + 1] exclusive scan of their numbers
