@@ -74,15 +74,15 @@ def test_route(seed, kw):
 
 
 @pytest.mark.parametrize("dtype,d,E,T_v,T_t", [
-    (W.F32, 512, 24, [4100], [37]),        # fp32, four chunks of 128: the shallow operand pipeline from 4096 tokens on
-    (W.BF16, 1280, 64, [3000, 1200], [50, 13]),   # bf16, ten chunks (five in flight below 4096 tokens)
-    (W.BF16, 640, 40, [4095], [0]),        # five chunks: an odd count, one token below the switch
-    (W.BF16, 640, 40, [4096], [3]),        # ... and above it (the chunk count is rounded up to an even one)
-    (W.F32, 384, 16, [16500], [20]),       # three chunks, two token tiles per block
+    (W.F32, 512, 24, [4100], [37]),        # fp32, four chunks of 128: one turn of the ring of x chunks
+    (W.BF16, 1280, 64, [3000, 1200], [50, 13]),   # bf16, ten chunks: the loop ends inside a turn
+    (W.BF16, 640, 40, [4095], [0]),        # five chunks, a last block of fifteen tokens
+    (W.BF16, 640, 40, [4096], [3]),        # ... and of three
+    (W.F32, 384, 16, [16500], [20]),       # three chunks (less than a turn), a thousand blocks
 ])
 def test_route_large_batches(dtype, d, E, T_v, T_t):
-    """The router's launch shapes for large batches (operand pipeline two chunks deep from 4096 tokens on,
-    two token tiles per block from 16384): probabilities and expert lists bit for bit, gates to 1e-6."""
+    """The router over several hundred blocks of sixteen tokens, at chunk counts that end anywhere in the ring of
+    four and with partial last blocks: probabilities and expert lists bit for bit, gates to 1e-6."""
     wl = W.small_random(620 + d, T_v=T_v, T_t=T_t, d=d, E=E, F=16, k_text=4, k_visual=2, retention=0.5, window=3,
                         dtype=dtype, bias_std=1.0, n_components=12)
     m = make_layer(wl)
@@ -115,6 +115,27 @@ def test_route_tile_edges(dtype, d, E, T_v, T_t, k):
     _, kept, new_cu, _ = m.layer_forward(x, vis, cu, pp)
     o_kept, o_cu, _ = oracle.prune(o[0], wl.is_visual, wl.cu_seqlens, 0.5, 3)
     assert np.array_equal(host(new_cu), o_cu) and np.array_equal(host(kept)[:len(o_kept)], o_kept)
+
+
+@pytest.mark.parametrize("T,E", [(9, 9), (9, 64), (40, 65), (40, 200), (4200, 33)])
+def test_a_row_without_a_largest_probability(T, E):
+    """A token that holds a NaN has no ranking: its list entries are -1 and it goes to no expert, on each way the
+    permutation is made; all other tokens come out as they would without it."""
+    wl = W.small_random(130 + E, T_v=[T - 3], T_t=[3], d=72, E=E, F=24, k_text=4, k_visual=2, retention=1.0, window=1,
+                        bias_std=0.5)
+    m = make_layer(wl)
+    x, vis, cu = inputs(wl)
+    bad = [1, T - 2]
+    good = np.setdiff1d(np.arange(T), bad)
+    want = [host(t) for t in m.route(x, vis)]
+    want_out = host(m.layer_forward(x, vis, cu, None)[0])[good]
+    x[bad, 5] = float("nan")
+    probs, idx, gate = (host(t) for t in m.route(x, vis))
+    assert (idx[bad] == -1).all() and np.isnan(probs[bad]).all()
+    for got, ref in zip((probs, idx, gate), want):
+        assert np.array_equal(got[good], ref[good])
+    out = host(m.layer_forward(x, vis, cu, None)[0])
+    assert np.array_equal(out[good], want_out) and not out[bad].any()
 
 
 def test_route_ties_duplicated_router_rows():
@@ -1442,20 +1463,19 @@ def test_expert_ffn_fp32_tile_edges(d, F):
         assert max_rel_err(host(ysh)[s], ffn(rows, sh[0][s], sh[1][s], sh[2][s])) <= TOL[W.F32], s
 
 
-@pytest.mark.parametrize("n,d,F", [(1, 8, 8), (3, 136, 40), (8, 712, 456), (15, 392, 776), (16, 1288, 264), (17, 136, 40)])
+@pytest.mark.parametrize("n,d,F", [(1, 8, 8), (3, 136, 40), (8, 712, 456), (15, 392, 776), (16, 1288, 264), (16, 616, 248)])
 def test_expert_ffn_thin_shape(n, d, F):
     """Calls of at most 16 tokens take a kernel shape of their own: the same bits as the weight-stream shape
-    (which the oracle tests cover) at reductions of 1 to 21 k tiles, whole and partial, at every row count of a
-    tile, with empty experts and with a row list that names tokens several times (more than 16 rows)."""
-    k, E = 5, 11
+    (which the oracle tests cover) at reductions of 1 to 21 k tiles, whole and partial, that leave 0 to 5 of them
+    behind the last whole turn of the ring of six, with experts of 1, 2, .. n rows, empty ones and a row list that
+    names tokens several times (more than 16 rows at n > 8)."""
+    E = n + 3
+    k = min(E, 10)
     g = torch.Generator(device="cuda")
     g.manual_seed(n * 1000 + d)
     rnd = lambda *s: (torch.randn(s, generator=g, device="cuda") * 0.2).bfloat16()
-    counts = np.zeros(E, np.int64)
-    left = n * k
-    for e, want in enumerate([0, n, 1, min(n, 5), 2 * n, 0, min(n, 15), 1, 1, 2, 0]):
-        counts[e] = min(left, want)
-        left -= counts[e]
+    counts = np.array([0, *range(1, n + 1), 0, 0])
+    counts[-1] = min(2 * n, n * k - counts.sum())
     offs = torch.tensor(np.concatenate([[0], np.cumsum(counts)]), dtype=torch.int32, device="cuda")
     x, wr = rnd(40, d), rnd(E, d)
     w = [rnd(E, F, d), rnd(E, F, d), rnd(E, d, F), rnd(2, F, d), rnd(2, F, d), rnd(2, d, F)]
@@ -1605,7 +1625,10 @@ def test_layer_forward_up_to_sixteen_tokens(dtype, T_v, T_t, E, k, kv, shared):
     x, vis, cu = inputs(wl)
     o = oracle.layer_forward(wl.x, wl.is_visual, wl.cu_seqlens, wl.weights, k_text=k, k_visual=kv,
                              is_bf16=dtype == W.BF16, do_prune=False)
-    for _ in range(2):      # scratch left by the first call does not matter
+    m.workspace(wl.T, len(T_v)).fill_(0xff)
+    for turn in range(2):
+        if turn:      # lists, offsets and permutation of another batch in the workspace
+            m.layer_forward(torch.randn_like(x), 1 - vis, cu, None)
         out, kept, new_cu, mask = m.layer_forward(x, vis, cu, None, want_mask=True)
         assert np.array_equal(host(kept)[:wl.T], np.arange(wl.T)) and np.array_equal(host(new_cu), wl.cu_seqlens)
         assert np.array_equal(host(mask)[:wl.T], wl.is_visual)
