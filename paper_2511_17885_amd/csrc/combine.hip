@@ -46,8 +46,8 @@ template <> struct Vec<float> {
 // rows (22016 tokens of d 128, two slots: 24.9 us, now 11.0; 13.1 through LDS, one thread a slot, behind a
 // barrier).  Wavefronts without columns leave at once.  Eight blocks a CU (what the scalar registers of sixteen
 // slots would not allow): 1600 tokens of d 2048 in fp32, sixteen slots, 43.8 -> 38.1 us.  8 tokens, d 2048, eight
-// slots, through LDS and now: 4.4 -> 4.0 us; 22016 tokens, d 2048: 179 us both, 5.5 TB/s, which is what a large
-// copy reaches.
+// slots, through LDS and now: 4.4 -> 4.0 us; 22016 tokens, d 2048, six slots, two shared experts: 165 us both,
+// 5.5 TB/s, which is what a large copy reaches.
 template <typename T, int KM>
 __global__ __launch_bounds__(256, 8) void combine_kernel(
     const T* __restrict__ y, const T* __restrict__ y_shared, const int32_t* __restrict__ inv_perm,

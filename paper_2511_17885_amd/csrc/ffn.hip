@@ -770,14 +770,16 @@ __global__ __launch_bounds__(256, 2) void ffn_dense_kernel(StreamArgs a) {
 // ---- the thin shape, for calls of at most THIN_ROWS tokens (decoding steps, short turns), where no expert sees
 // more rows than that and the weights are all there is to move.  One wavefront per workgroup and per column
 // block: four times as many, four times shorter work items than the weight-stream shape, dealt over all XCDs
-// column block by column block, so that every CU streams about the same number of bytes (a CU sustains some
-// 13 bytes/ns whatever it runs; with 418 items of 512 KB over 256 CUs the CUs holding two of them finished
-// last by half the launch).  No LDS and no barrier: the rows' operands come straight from memory in matrix
-// order (lane: row l%16, k = 8*(l/16)..+7), a few KB that every wavefront finds in L2.
+// column block by column block, so that every CU streams about the same number of bytes (with 418 items of
+// 512 KB over 256 CUs the CUs holding two of them finish last).  No LDS and no barrier: the rows' operands come
+// straight from memory in matrix order (lane: row l%16, k = 8*(l/16)..+7), a few KB that every wavefront finds in L2.
 // Same instructions in the same order per output element as the other shapes, so the same bits.
-// Measured (8 tokens, d 2048, 64 experts of 1408 and two shared): gate/up 44.2 -> 35.3 us, down 22.7 -> 20.2 with
-// the weights partly in the memory-side cache, 57.7 -> 52.4 and 28.9 -> 26.9 (5.1 TB/s) without.  At 30 tokens,
-// with a second row block, it took 102 us against the weight-stream shape's 100: the line is one row block.
+// Measured against the weight-stream shape, weights from memory, whole expert FFN: 8 tokens, d 2048, 64 experts of
+// 1408 and two shared 77.1 -> 71.9 us; one token there x0.95, 8 experts of 1408 x0.71 (one token) to x0.98
+// (sixteen), 8 of 14336 with d 4096 x0.49 to x1.04, 128 of 768 x0.84 to x1.02.  It gains where a launch of the other
+// shape has too few items for the chip; where there are several per CU the two are equal, and the down product of
+// short rows (F 768, hundreds of items) is 2 to 10 % slower in this one.  At 30 tokens, with a second row block, it
+// took 102 us against the weight-stream shape's 100: the line is one row block.
 constexpr int THIN_ROWS = 16;
 constexpr int THIN_SLOTS = 6;    // k tiles (64 wide) of both operands in flight per wavefront
 
@@ -948,8 +950,8 @@ __global__ void pack_weights_kernel(const bf16_t* __restrict__ src0, const bf16_
 //    LDS buffers in the swizzled layout of the bf16 kernels; one barrier per k tile.
 // Measured against an LDS-tiled kernel on the 32x32x2 instruction (both operands through LDS, one tile of
 // loads in flight, one operand per LDS read): 1600 tokens, d 1280, 64 experts of 896, 42 rows per expert:
-// gate/up 572 -> 238 us, down 286 -> 133 us; 3000 tokens, 280 rows per expert: 1890 -> 972 and 960 -> 507 us
-// (111 TFLOP/s); 64 tokens, d 128, 8 experts of 256: 19.2 -> 8.1 and 33.2 -> 10.1 us.
+// gate/up 539 -> 231 us, down 280 -> 123 us; 3000 tokens, 280 rows per expert: 1989 -> 1018 and 1031 -> 525 us
+// (108 and 105 TFLOP/s); 64 tokens, d 128, 8 experts of 256: 19.5 -> 7.9 and 33.5 -> 10.0 us.
 constexpr int FBM = 64;        // rows per tile
 constexpr int FBK = 32;        // k per tile: 128 bytes of a row
 constexpr int F_SLOTS = 4;     // register rings, in k tiles

@@ -452,8 +452,8 @@ __global__ __launch_bounds__(CP_BLOCK) void compact_write_kernel(CompactArgs a) 
 // type, so that the routing decisions taken on them afterwards see the correctly rounded token; a thread
 // keeps the columns' sums in registers between the norm and the store (columns past MG_COLS * 256 are summed
 // a second time), and the row norms share one block reduction, since it is the chain of reductions and row
-// reads that a merged row costs.  1216 kept rows of d 1280, 57 merged: 14.1 -> 11.0 us; 4000 of d 2048: 27.7 ->
-// 18.3 (element copies, three passes over a window and a reduction per row before).
+// reads that a merged row costs.  1216 kept rows of d 1280, 57 merged: 13.6 -> 10.4 us; 4250 of d 2048: 23.9 ->
+// 15.6 (element copies, three passes over a window and a reduction per row before).
 constexpr int MG_COLS = 8;
 constexpr int MG_ROWS = 4;    // rows of the window whose norms are reduced together
 template <int NV>
@@ -1083,7 +1083,7 @@ int launch_prune_dispatch_small(const fmoe_ctx* ctx, const fmoe_prune_params* pp
       hipLaunchKernelGGL((prune_dispatch_small_kernel<TP, KM, true>), dim3(1), dim3(SB_THREADS), 0, stream, a);  \
   } while (0)
     // the register arrays as small as the call allows: with those for sixteen experts per token a batch of 3000
-    // tokens and six took 39.0 us (pruning) and 32.7 us (not), with those for eight 31.1 and 24.2
+    // tokens and six took 34.6 us (pruning) and 25.8 us (not), with those for eight 29.2 and 20.8
     if (ctx->kmax > 8) FMOE_DISPATCH_LAUNCH(SB_MAX_TP, FMOE_MAX_TOPK);
     else if (T > 2 * SB_THREADS) FMOE_DISPATCH_LAUNCH(SB_MAX_TP, 8);
     else FMOE_DISPATCH_LAUNCH(2, 8);

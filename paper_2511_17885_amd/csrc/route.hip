@@ -29,10 +29,11 @@
 //            that group's instructions.
 // Logits meet in LDS, then a wavefront does softmax / top-k for four tokens at once, sixteen lanes each
 // (one token at a time over all 64 lanes took 4.6 us a block, this takes 2.0).
-// Measured against single-buffered staging with two barriers a chunk and the one-token epilogue: 8 tokens,
-// d 2048, 64 experts 19.5 -> 14.4 us; 1600 tokens, d 1280 17.0 -> 12.2; 8192 tokens, d 2048, 128 experts
-// 64.5 -> 50.0; 22016 tokens, d 2048, 64 experts 83.6 -> 70.  Bound: the chain itself, 44 cycles per
-// instruction of the 32 it needs (the rest is the staging's vector work and the barrier).
+// Measured against single-buffered staging with two barriers a chunk and the one-token epilogue (average kernel
+// times under the profiler): 8 tokens, d 2048, 64 experts 18.5 -> 13.1 us; 1600 tokens, d 1280 17.3 -> 12.3; 8192
+// tokens, d 2048, 128 experts 63.0 -> 49.2; 22016 tokens, d 2048, 64 experts 84.8 -> 74.6; 256 experts, 8 tokens
+// 55.3 -> 41.4, 8192 101 -> 83, 22016 278 -> 224.  Bound: the chain itself, 44 cycles per instruction where 32
+// are needed (the rest is the staging's vector work and the barrier).
 
 #include <type_traits>
 
@@ -177,7 +178,7 @@ __device__ __forceinline__ unsigned long long splitmix64_nth(unsigned long long 
 // DISPATCH: one block has all tokens and none is dropped, so it goes on to write what the dispatch step would
 // (kept list, permutation by expert, GEMM work lists): an expert's rows are the set bits of its token mask.  A
 // launch less for a decoding step, where the dispatch kernel took 9 us for a few hundred bytes (8 tokens, 64
-// experts: router 14.2 + dispatch 9.0 us, now 17.6; the layer 108.0 -> 102.9 us).
+// experts: router 13.1 + dispatch 9.3 us, together 19.2; the layer 108.0 -> 102.9 us).
 template <typename XT, int NB, int R, bool SEL, bool DISPATCH>
 __global__ __launch_bounds__(256) void route_kernel(
     const XT* __restrict__ x, const float* __restrict__ wp, const float* __restrict__ bias,
