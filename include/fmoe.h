@@ -126,7 +126,7 @@ int fmoe_set_topk(fmoe_ctx* ctx, int32_t k_text, int32_t k_visual);
  * FMOE_ERR_INVALID_ARG unless 0 <= strategy <= 2 and 0 <= k_base <= min(E, 16). */
 int fmoe_set_selection(fmoe_ctx* ctx, int32_t strategy, int32_t k_base, uint64_t seed);
 
-/* Tuning knob of the bf16 expert GEMMs (Eq.4).  The kernel has two shapes: the weight-stream shape (a
+/* Tuning knob of the bf16 expert GEMMs (Eq.4).  The kernel has two shapes for batches: the weight-stream shape (a
  * workgroup = 128 rows x 4 column blocks) for calls that route few rows per expert, and the dense
  * shape (128 rows x 8 column blocks, half the on-chip traffic per flop) from a capacity of 256 routed
  * rows per expert (T * Kmax / E) on.  Calls of at most 16 tokens take a third, thin shape (a wavefront per

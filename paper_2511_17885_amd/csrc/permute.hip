@@ -98,7 +98,8 @@ __device__ __forceinline__ void scan_totals(const int* total, int E, int32_t* of
 // ---- P2 + P3 in one launch: every block sums the per-block counts itself (totals over all blocks, bases over
 // those before it; E counts per block, from L2), scans the totals and scatters its own positions.  One more block
 // writes the offsets and builds the GEMM work lists, so that neither waits for the other.  A launch less and no
-// walk by a single block.
+// walk by a single block: inside a layer, scan + scatter -> this, 22016 tokens / 64 experts 20.7 + 5.8 -> 19.9 us;
+// 4224 of 8192 tokens / 128 experts 9.7 + 5.5 -> 10.2; 2176 of 4096 / 64 6.9 + 4.8 -> 7.5.
 __global__ __launch_bounds__(PB) void permute_scan_scatter_kernel(
     const int32_t* __restrict__ topk_idx, const int32_t* __restrict__ kept_idx, int n_cap,
     const int32_t* __restrict__ n_dev, int E, int Kmax, const int32_t* __restrict__ slot_rank,
@@ -187,7 +188,7 @@ __global__ __launch_bounds__(PB) void permute_scan_scatter_kernel(
 
 // Up to which size the joined launch is the faster one.  Every block walks all counts, a thread at least
 // nblk / (256 / E rounded up to a power of two) of them, while the scan's one block walks nblk a thread whatever E is.
-// Whole permutation, two launches after the count -> one, us:
+// Whole permutation (without work lists, ten calls in a graph), two launches after the count -> one, us:
 //   experts 64, 8 slots:   8192 positions 15.4 -> 12.6, 22016 18.4 -> 14.1, 65536 27.7 -> 18.8
 //   experts 128, 8 slots:  8192 15.7 -> 13.4, 22016 19.0 -> 15.9, 65536 28.7 -> 24.1; 16 slots, 65536: 40.7 -> 36.7
 //   experts 256, 1 slot:   8192 9.0 -> 8.75, 16384 10.7 -> 11.1, 65536 20.9 -> 25.8
