@@ -14,8 +14,13 @@
 #define FMOE_ROUTE_DISPATCH_TOKENS 16   // tokens up to which the router's one block does the dispatch too
 #define FMOE_TILE_M 64        // rows per grouped-GEMM tile (tile list granularity)
 #define FMOE_TILE_RUN 8       // row tiles per run of a group in the tile lists
+#define FMOE_DENSE_TILE_RUN 64   // the same for the dense shape
 #define FMOE_SEG_MIN_TILES 256   // tile entries from which each XCD takes a contiguous segment of the list
-#define FMOE_DENSE_MIN_ROWS 256  // routed-row capacity per expert from which the expert GEMMs take their dense shape
+// Routed-row capacity per expert from which the expert GEMMs take their dense shape.  Both GEMMs, stream / dense, us:
+//   capacity  98: d 2048, 64 experts of 1408, half kept 172 / 181, all kept 221 / 217; d 1280, experts of 896 74 / 80, 93 / 88
+//   capacity 125: d 2048, 128 experts of 768, half kept 134 / 135, all kept 175 / 163
+//   capacity 188: d 2048, 64 experts of 1408 240 / 240, 310 / 277; d 1280, experts of 896 101 / 103, 134 / 131
+#define FMOE_DENSE_MIN_ROWS 112
 
 // ---- optional per-kernel timing (instrumentation; off by default)
 enum fmoe_kernel_slot {
@@ -95,6 +100,8 @@ struct fmoe_tile {  // one M-tile of the grouped GEMM
 // launch geometry of the two grouped GEMMs for a call with capacity n_cap
 struct fmoe_ffn_geom {
   int bm;              // rows per tile
+  int run;             // row tiles per run
+  bool dense;          // bf16: by size, the dense shape of the expert GEMMs
   int cols1, scols1;   // column tiles per launch entry / of the shared group, gate-up GEMM
   int cols2, scols2;   // same, down GEMM
   int tile_cap;        // capacity of each tile list

@@ -107,7 +107,7 @@ __global__ __launch_bounds__(PB) void permute_scan_scatter_kernel(
     int32_t* __restrict__ perm_src, int32_t* __restrict__ inv_perm, fmoe_ffn_geom geom, int build, int n_shared,
     fmoe_tile* __restrict__ tiles1, fmoe_tile* __restrict__ tiles2, int32_t* __restrict__ tile_count) {
   __shared__ int s_tot[PB], s_pre[PB], s_off[FMOE_MAX_EXPERTS + 1];
-  __shared__ __align__(8) int scratch[513];
+  __shared__ __align__(8) int scratch[FMOE_TILES_SCRATCH];
   const int n = resolve_count(n_cap, n_dev);
   const int nblk = (n + PB - 1) / PB;
   const int blk = blockIdx.x;
@@ -168,7 +168,7 @@ __global__ __launch_bounds__(PB) void permute_scan_scatter_kernel(
   if (lists) {
     for (int i = tid; i <= E; i += PB) expert_offsets[i] = s_off[i];
     if (build)   // fused layer path
-      fmoe_build_tiles(s_off, E, n_cap * Kmax, n, n_shared, geom.bm, geom.tile_cap, geom.cols1, geom.scols1,
+      fmoe_build_tiles(s_off, E, n_cap * Kmax, n, n_shared, geom.bm, geom.run, geom.tile_cap, geom.cols1, geom.scols1,
                        tiles1, tiles2, tile_count, scratch);
     return;
   }
@@ -214,7 +214,7 @@ __global__ __launch_bounds__(256) void permute_scan_kernel(int n_cap, const int3
                                                            fmoe_tile* __restrict__ tiles2,
                                                            int32_t* __restrict__ tile_count) {
   __shared__ int total[FMOE_MAX_EXPERTS];
-  __shared__ __align__(8) int scratch[513];
+  __shared__ __align__(8) int scratch[FMOE_TILES_SCRATCH];
   const int n = resolve_count(n_cap, n_dev);
   const int nblk = (n + PB - 1) / PB;
   const int e = threadIdx.x;
@@ -241,7 +241,7 @@ __global__ __launch_bounds__(256) void permute_scan_kernel(int n_cap, const int3
     __threadfence_block();
     __syncthreads();
     fmoe_build_tiles(expert_offsets, E, row_cap, resolve_count(rows_cap, rows_dev), n_shared, geom.bm,
-                     geom.tile_cap, geom.cols1, geom.scols1, tiles1, tiles2, tile_count, scratch);
+                     geom.run, geom.tile_cap, geom.cols1, geom.scols1, tiles1, tiles2, tile_count, scratch);
   }
 }
 

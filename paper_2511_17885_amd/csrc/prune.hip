@@ -643,7 +643,7 @@ __global__ __launch_bounds__(SB_THREADS) void prune_dispatch_small_kernel(SmallA
   __shared__ __align__(16) unsigned char s_u[U_BYTES];
   __shared__ int s_off[FMOE_MAX_EXPERTS + 1], s_base[FMOE_MAX_EXPERTS];
   __shared__ int s_cu[SB_MAX_B + 1], s_nv[SB_MAX_B];
-  __shared__ __align__(8) int s_scr[513];
+  __shared__ __align__(8) int s_scr[FMOE_TILES_SCRATCH];
   __shared__ uint16_t s_pfx[FMOE_MAX_EXPERTS * 16];   // rows of an expert ahead of each wavefront's tokens
   __shared__ int wave_tot[16];
   __shared__ float red[16];
@@ -884,7 +884,7 @@ __global__ __launch_bounds__(SB_THREADS) void prune_dispatch_small_kernel(SmallA
   __syncthreads();
 
   // ---- grouped-GEMM tile lists
-  fmoe_build_tiles(s_off, E, a.row_cap, n, a.n_shared, a.geom.bm, a.geom.tile_cap, a.geom.cols1,
+  fmoe_build_tiles(s_off, E, a.row_cap, n, a.n_shared, a.geom.bm, a.geom.run, a.geom.tile_cap, a.geom.cols1,
                    a.geom.scols1, a.tiles1, a.tiles2, a.tile_count, s_scr);
 
   // ---- outputs

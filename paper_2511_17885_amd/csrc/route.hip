@@ -432,8 +432,8 @@ __global__ __launch_bounds__(256) void route_kernel(
     static_assert(TOKB <= 31, "the token masks are ints");
     int* s_mask = reinterpret_cast<int*>(smem);          // [FMOE_MAX_EXPERTS] tokens of the expert
     int* s_off = s_mask + FMOE_MAX_EXPERTS;              // [FMOE_MAX_EXPERTS + 1] exclusive scan of their numbers
-    int* scratch = s_off + FMOE_MAX_EXPERTS + 2;         // 513, 8-byte aligned
-    static_assert((2 * FMOE_MAX_EXPERTS + 2 + 513) * 4 <= sizeof(smem), "fits where x and the logits were");
+    int* scratch = s_off + FMOE_MAX_EXPERTS + 2;         // 8-byte aligned
+    static_assert((2 * FMOE_MAX_EXPERTS + 2 + FMOE_TILES_SCRATCH) * 4 <= sizeof(smem), "fits where x and the logits were");
     static_assert(FMOE_MAX_EXPERTS == 256, "a mask per thread");
     __syncthreads();   // the logits have been read
     s_mask[tid] = 0;
@@ -479,7 +479,7 @@ __global__ __launch_bounds__(256) void route_kernel(
     if (tid <= E) job.expert_offsets[tid] = s_off[tid];
     if (tid == 0 && E == FMOE_MAX_EXPERTS) job.expert_offsets[E] = s_off[E];
     for (int b = tid; b <= job.B; b += 256) job.new_cu[b] = clampi(job.cu[b], 0, T);
-    fmoe_build_tiles(s_off, E, job.row_cap, T, job.n_shared, job.geom.bm, job.geom.tile_cap, job.geom.cols1,
+    fmoe_build_tiles(s_off, E, job.row_cap, T, job.n_shared, job.geom.bm, job.geom.run, job.geom.tile_cap, job.geom.cols1,
                      job.geom.scols1, job.tiles1, job.tiles2, job.tile_count, scratch);
   }
 }

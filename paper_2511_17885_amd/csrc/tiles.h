@@ -4,6 +4,8 @@
 
 #include "common.h"
 
+#define FMOE_TILES_SCRATCH 514
+
 #if defined(__HIPCC__)
 // Builds, with one 256-thread block, the two row-tile lists of the expert FFN (`bm` rows per tile):
 //   list 1 (gate/up GEMM): the dense shared-expert group (group id E, all n kept tokens, hidden
@@ -15,14 +17,14 @@
 // fill the tail of the launch.  A launch gives every entry `cols1` column tiles; the shared group
 // of list 1 may have more (`scols1`): its row tiles are then repeated with a column-tile offset in
 // `col0`.  The row tiles of one group (one replica) are consecutive entries, cut into runs of at most
-// FMOE_TILE_RUN row tiles (rt / nrt number a tile within its run): a run is the unit within which
-// the GEMM kernel re-deals its workgroups column-major, and eight row tiles by eight column tiles
-// is about what one XCD runs at a time.
-// counts[0], counts[1] = number of entries in list 1 / list 2.  Experts whose offsets are malformed
+// `run` row tiles (rt / nrt number a tile within its run): a run is the unit within which
+// the GEMM kernels order their workgroups.
+// counts[0], counts[1] = number of entries in list 1 / list 2; counts[2], counts[3] = how many of them, the first
+// ones, belong to groups of several row tiles.  Experts whose offsets are malformed
 // (negative, decreasing or past row_cap) are skipped so that no tile can index outside the row
-// buffers; without room for rows (row_cap 0) the offsets are not read and may be null.  `scratch` is 513 ints of LDS (8-byte aligned); bm is a power of two.
+// buffers; without room for rows (row_cap 0) the offsets are not read and may be null.  `scratch` is FMOE_TILES_SCRATCH ints of LDS (8-byte aligned); bm and run are powers of two.
 __device__ __forceinline__ void fmoe_build_tiles(const int32_t* expert_offsets, int E, int row_cap,
-                                                 int n, int n_shared, int bm, int tile_cap, int cols1,
+                                                 int n, int n_shared, int bm, int run, int tile_cap, int cols1,
                                                  int scols1, fmoe_tile* tiles1, fmoe_tile* tiles2,
                                                  int32_t* counts, int* scratch) {
   const int e = threadIdx.x;
@@ -37,6 +39,7 @@ __device__ __forceinline__ void fmoe_build_tiles(const int32_t* expert_offsets, 
   __syncthreads();
   // order key: more rows first, then the lower expert id (rows < 2^24, ids < 2^8)
   const unsigned key = ((unsigned)cnt << 8) | (unsigned)(255 - (e & 255));
+  if (e == 0) scratch[513] = 0;
   if (e < 256) {
     scratch[2 * e] = (e < E) ? (int)key : 0;
     scratch[2 * e + 1] = (e < E) ? ((cnt + bm - 1) >> sh) : 0;
@@ -52,9 +55,12 @@ __device__ __forceinline__ void fmoe_build_tiles(const int32_t* expert_offsets, 
       start += ((unsigned)kn.x > key) ? kn.y : 0;
     }
     if (e == 0) scratch[512] = routed;
+    const int nt = (cnt + bm - 1) >> sh;
+    if (nt > 1) atomicMax(&scratch[513], start + nt);   // experts of several tiles are the first ones
   }
   __syncthreads();
   routed = scratch[512];
+  const int several = scratch[513];
 
   const int ns = (n_shared > 0) ? (n + bm - 1) / bm : 0;
   const int rep1 = (ns > 0 && cols1 > 0) ? (scols1 + cols1 - 1) / cols1 : 0;
@@ -63,8 +69,8 @@ __device__ __forceinline__ void fmoe_build_tiles(const int32_t* expert_offsets, 
     fmoe_tile t;
     t.row0 = j * bm;
     t.rows = (n - j * bm < bm) ? (n - j * bm) : bm;
-    t.rt = j % FMOE_TILE_RUN;
-    t.nrt = (ns - (j - t.rt) < FMOE_TILE_RUN) ? (ns - (j - t.rt)) : FMOE_TILE_RUN;
+    t.rt = j & (run - 1);
+    t.nrt = (ns - (j - t.rt) < run) ? (ns - (j - t.rt)) : run;
     t.group = E;
     for (int c = 0; c < rep1; ++c) {   // replica-major: the row tiles of one replica are consecutive
       const int slot = c * ns + j;
@@ -88,8 +94,8 @@ __device__ __forceinline__ void fmoe_build_tiles(const int32_t* expert_offsets, 
       t.row0 = r0 + j * bm;
       t.rows = (cnt - j * bm < bm) ? (cnt - j * bm) : bm;
       t.col0 = 0;
-      t.rt = j % FMOE_TILE_RUN;
-      t.nrt = (nt - (j - t.rt) < FMOE_TILE_RUN) ? (nt - (j - t.rt)) : FMOE_TILE_RUN;
+      t.rt = j & (run - 1);
+      t.nrt = (nt - (j - t.rt) < run) ? (nt - (j - t.rt)) : run;
       if (sh1 + start + j < tile_cap) tiles1[sh1 + start + j] = t;
       if (sh2 + start + j < tile_cap) tiles2[sh2 + start + j] = t;
     }
@@ -98,6 +104,9 @@ __device__ __forceinline__ void fmoe_build_tiles(const int32_t* expert_offsets, 
     const int t1 = routed + sh1, t2 = routed + sh2;
     counts[0] = t1 < tile_cap ? t1 : tile_cap;
     counts[1] = t2 < tile_cap ? t2 : tile_cap;
+    const int s1 = several + (ns > 1 ? sh1 : 0), s2 = several + (ns > 1 ? sh2 : 0);
+    counts[2] = s1 < tile_cap ? s1 : tile_cap;
+    counts[3] = s2 < tile_cap ? s2 : tile_cap;
   }
 }
 #endif

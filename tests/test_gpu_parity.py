@@ -746,6 +746,42 @@ def test_expert_gemm_shapes_agree_bit_for_bit(cfg):
         m.set_ffn_shape(3)
 
 
+@pytest.mark.parametrize("rows,d,F,n_shared", [
+    ([129, 1, 0, 128, 127, 16, 17, 256, 257, 40], 136, 520, 0),   # both kinds, column groups 5 (strips 3 + 2) and 1
+    ([1, 128, 0, 31, 32, 33, 96, 97], 520, 136, 1),               # single tiles only (a shared group of several)
+    ([60, 40], 72, 1032, 2),                                      # the shared group a single tile too
+    ([129, 300, 1000, 2049], 1288, 200, 2),                       # several row tiles each, strips of 3 + 3
+    ([8193, 70, 130, 5], 264, 72, 0),                             # a group of 65 row tiles: two runs
+])
+def test_dense_shape_covers_every_work_item(rows, d, F, n_shared):
+    """The dense shape cuts its work lists into eight shares of either kind (single row tiles, several row tiles),
+    mixes them and walks runs in strips of three column groups: every output element is written, and to the bits
+    of the weight-stream shape, whatever the mix (outputs and workspace start as NaN)."""
+    E, n = len(rows), sum(rows)
+    rng = np.random.Generator(np.random.PCG64(sum(rows) + d))
+    m = binding.FMoE(d_model=d, n_experts=E, d_ffn=F, n_shared=n_shared, d_ffn_shared=F if n_shared else 0, k_text=1,
+                     k_visual=1, dtype="bf16")
+    w = lambda *s: dev(rng.standard_normal(s, dtype=np.float32) * 0.05, torch.bfloat16)
+    m.set_weights(w(E, d), None, w(E, F, d), w(E, F, d), w(E, d, F),
+                  *([w(n_shared, F, d), w(n_shared, F, d), w(n_shared, d, F)] if n_shared else [None] * 3))
+    x = w(n, d)
+    idx = dev(rng.permutation(np.repeat(np.arange(E), rows)).astype(np.int32)[:, None])
+    offs, perm, _ = m.permute(idx, None, n)
+    outs = []
+    for shape in (1, 2):
+        m.set_ffn_shape(shape)
+        m.workspace(n, 1).fill_(255)
+        # blocks the outputs are likely to be given again; the assertions below hold for any contents
+        del_later = [torch.full((n, d), float("nan"), dtype=torch.bfloat16, device="cuda") for _ in range(1 + n_shared)]
+        del del_later
+        y, ysh = m.expert_ffn(x, None, n, offs, perm)
+        outs.append((y, ysh))
+    for a, b in zip(*outs):
+        if a is not None:
+            assert torch.isfinite(b.float()).all()
+            assert torch.equal(a, b)
+
+
 def test_config2_dsvl2_tiny_dense_shape():
     wl = W.config2()
     m = make_layer(wl, ffn_shape=2)
