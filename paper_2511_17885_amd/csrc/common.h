@@ -88,13 +88,14 @@ struct fmoe_ws_layout {
 };
 fmoe_ws_layout fmoe_layout(const fmoe_ctx* ctx, int32_t max_tokens, int32_t max_seqs);
 
-struct fmoe_tile {  // one M-tile of the grouped GEMM
+struct fmoe_tile {  // one M-tile of the grouped GEMM.  The rows are given for its run of consecutive entries (row tiles
+                    // of one group), so that every tile of the run follows from any of the run's entries
   int32_t group;    // expert id
-  int32_t row0;     // first row (in the permuted row space)
-  int32_t rows;     // valid rows in the tile
+  int32_t row0;     // first row of the run (in the permuted row space)
+  int32_t rows;     // valid rows from there to the end of the group
   int32_t col0;     // first column tile this entry covers (shared group split over entries)
-  int32_t rt;       // index of this row tile within its group's run of consecutive entries
-  int32_t nrt;      // number of row tiles in that run
+  int32_t rt;       // index of this row tile within the run
+  int32_t nrt;      // number of row tiles in the run
 };
 
 // launch geometry of the two grouped GEMMs for a call with capacity n_cap

@@ -96,6 +96,21 @@ struct StreamArgs {
   int cols_entry;             // column tiles per tile entry
 };
 
+// A list entry, by scalar loads of all its words at once (the lists are read-only in these kernels, which the
+// compiler cannot see past their stores).
+__device__ __forceinline__ fmoe_tile load_entry(const fmoe_tile* tiles, int ti) {
+  typedef const __attribute__((address_space(4))) int32_t* const_ptr;
+  const const_ptr p = (const_ptr)(uintptr_t)(tiles + ti);
+  fmoe_tile t;
+  t.group = p[0]; t.row0 = p[1]; t.rows = p[2]; t.col0 = p[3]; t.rt = p[4]; t.nrt = p[5];
+  return t;
+}
+// Narrows an entry to row tile r of its run (bm rows per tile).
+__device__ __forceinline__ void take_row_tile(fmoe_tile& t, int r, int bm) {
+  t.row0 += r * bm;
+  t.rows = t.rows - r * bm < bm ? t.rows - r * bm : bm;
+}
+
 // s_waitcnt vmcnt(n) with the other counters left alone (gfx9 encoding: vmcnt = bits 15:14 | 3:0)
 #define FMOE_WAIT_VM(n) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(n) : "memory")
 __device__ __forceinline__ void wait_vm_upto(int n) {   // n not known at compile time (loop tails)
@@ -212,22 +227,33 @@ __device__ __forceinline__ void static_for(F&& f) {   // f(integral_constant<int
 
 // Byte offsets (into the buffer descriptor over P.A) of the activation rows this lane fetches: rows
 // 32*it + 8*wave + lane/8 of the tile, through the two-level gather; rows past the tile reuse its last row.
+// In two halves, a load each, so that the first weights can be requested in between.
 template <int NAB>
-__device__ __forceinline__ void gather_offsets(const StreamProblem& P, const fmoe_tile& tile, uint32_t (&a_src)[NAB]) {
+__device__ __forceinline__ void gather_first(const StreamProblem& P, const fmoe_tile& tile, int (&src)[NAB]) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const uint32_t a_max_row = 0xffffffffu / ((uint32_t)P.lda * 2u) - 1u;
 #pragma unroll
   for (int it = 0; it < NAB; ++it) {
     const int r = 32 * it + 8 * wave + (lane >> 3);
-    int src = tile.row0 + (r < tile.rows ? r : tile.rows - 1);
-    if (P.map1) {
-      src = P.map1[src];
-      if (P.map1_limit > 0) src = src < 0 ? 0 : (src >= P.map1_limit ? P.map1_limit - 1 : src);
-    }
-    if (P.map2) src = P.map2[src];
-    src = (uint32_t)src < a_max_row ? src : (int)a_max_row;   // offsets stay below 4 GiB whatever the input
-    a_src[it] = (uint32_t)src * (uint32_t)P.lda * 2u;
+    src[it] = tile.row0 + (r < tile.rows ? r : tile.rows - 1);
+    if (P.map1) src[it] = P.map1[src[it]];
   }
+}
+template <int NAB>
+__device__ __forceinline__ void gather_offsets(const StreamProblem& P, const int (&src)[NAB], uint32_t (&a_src)[NAB]) {
+  const uint32_t a_max_row = 0xffffffffu / ((uint32_t)P.lda * 2u) - 1u;
+#pragma unroll
+  for (int it = 0; it < NAB; ++it) {
+    int s = src[it];
+    if (P.map1 && P.map1_limit > 0) s = s < 0 ? 0 : (s >= P.map1_limit ? P.map1_limit - 1 : s);
+    if (P.map2) s = P.map2[s];
+    s = (uint32_t)s < a_max_row ? s : (int)a_max_row;   // offsets stay below 4 GiB whatever the input
+    a_src[it] = (uint32_t)s * (uint32_t)P.lda * 2u;
+  }
+}
+// Nothing is moved across: what is requested before is requested first.
+__device__ __forceinline__ void order_loads() {
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_sched_barrier(0);
 }
 
 // Epilogue of one 128-row x 4-column-block output tile (column tile nt of the packing): accumulator
@@ -303,7 +329,8 @@ __device__ __forceinline__ void stream_tile(const StreamProblem& P, const fmoe_t
   const __amdgpu_buffer_rsrc_t a_rsrc =
       __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t*>(P.A), 0, 0xffffffff, 0x00020000);
   const int a_kc = ((lane & 7) ^ ((4 * wave + (lane >> 4)) & 7)) * 8;
-  gather_offsets<NAB>(P, tile, a_src);
+  int src[NAB];
+  gather_first<NAB>(P, tile, src);
 
   f32x4_t acc[NRB][2];
 #pragma unroll
@@ -377,24 +404,32 @@ __device__ __forceinline__ void stream_tile(const StreamProblem& P, const fmoe_t
   };
 
   // Step t issues the activations of tile t + A_AHEAD and the weights of tile t + B_AHEAD (in an
-  // order the compiler may choose, but never across the barrier that opens a step); the prologue
-  // replays the steps before 0 the same way.  Loads land in issue order, so "all but the newest
-  // (A_AHEAD-1)*PER_STEP loads have landed" implies "tile t's activations are in LDS".
+  // order the compiler may choose, but never across the barrier that opens a step).  Loads land in issue order, so
+  // "all but the newest (A_AHEAD-1)*PER_STEP loads have landed" implies "tile t's activations are in LDS".  The
+  // prologue requests all its weights before its activations (they do not need the row indices), so the
+  // activations of the first two tiles have fewer loads behind them and are waited for before the first step.
   constexpr int A_AHEAD = A_STAGES - 1, B_AHEAD = B_SLOTS - 1;
   constexpr int NEWER = (A_AHEAD - 1) * PER_STEP;
   constexpr int UNROLL = 4;    // a multiple of both ring sizes: slots and stages are compile-time
   static_assert(UNROLL % A_STAGES == 0 && UNROLL % B_SLOTS == 0, "ring indices must be static");
-  static_assert(A_AHEAD <= B_AHEAD, "the prologue below starts with the weights");
+  static_assert(A_AHEAD == 3 && B_AHEAD == 3, "two tiles are waited for before the first step");
   int t = 0;
   if (UNROLL + B_AHEAD <= NT) {
     // the steady loop will run: an unconditional prologue, so that the compiler's own count of the
     // loads in flight at the loop head is exact (a conditional one makes it wait for all of them)
+    order_loads();
 #pragma unroll
-    for (int q = -B_AHEAD; q < 0; ++q) {
-      if (q + A_AHEAD >= 0) loadA((q + A_AHEAD) % A_STAGES, q + A_AHEAD);
-      loadB(q + B_AHEAD, q + B_AHEAD);
-      asm volatile("" ::: "memory");   // keeps the steps' loads apart
+    for (int q = 0; q < B_AHEAD; ++q) {
+      loadB(q, q);
+      order_loads();
     }
+    gather_offsets<NAB>(P, src, a_src);
+#pragma unroll
+    for (int q = 0; q < A_AHEAD; ++q) {
+      loadA(q, q);
+      order_loads();
+    }
+    FMOE_WAIT_VM((A_AHEAD - 2) * NAB);
     for (; t + UNROLL + B_AHEAD <= NT; t += UNROLL) {   // steady state: every load is unconditional
 #pragma unroll
       for (int u = 0; u < UNROLL; ++u) {
@@ -405,12 +440,19 @@ __device__ __forceinline__ void stream_tile(const StreamProblem& P, const fmoe_t
       }
     }
   } else {
+    order_loads();
 #pragma unroll
-    for (int q = -B_AHEAD; q < 0; ++q) {
-      if (q + A_AHEAD >= 0 && q + A_AHEAD < NT) loadA((q + A_AHEAD) % A_STAGES, q + A_AHEAD);
-      if (q + B_AHEAD < NT) loadB(q + B_AHEAD, q + B_AHEAD);
-      asm volatile("" ::: "memory");
+    for (int q = 0; q < B_AHEAD; ++q) {
+      if (q < NT) loadB(q, q);
+      order_loads();
     }
+    gather_offsets<NAB>(P, src, a_src);
+#pragma unroll
+    for (int q = 0; q < A_AHEAD; ++q) {
+      if (q < NT) loadA(q, q);
+      order_loads();
+    }
+    FMOE_WAIT_VM(0);
   }
   // Tail: 3..6 steps are left after the steady loop (1..6 when it did not run).  Every count gets its
   // own straight-line code, so that which steps still issue loads, and how many loads are newer than
@@ -480,7 +522,7 @@ __global__ __launch_bounds__(256, 2) void ffn_stream_kernel(StreamArgs a) {
     ti = batch * 8 + xcd;
     if (ti >= n_tiles) return;
   }
-  fmoe_tile tile = a.tiles[ti];
+  fmoe_tile tile = load_entry(a.tiles, ti);
   const bool shared = tile.group >= a.E;
   // field-by-field select keeps the descriptors in scalar registers (indexing the kernel argument
   // dynamically would spill it to scratch memory)
@@ -500,13 +542,13 @@ __global__ __launch_bounds__(256, 2) void ffn_stream_kernel(StreamArgs a) {
   // outweigh the activation rows, which every XCD then reads).
   // (runs are at most FMOE_TILE_RUN row tiles long; in a long list the whole run sits on this XCD and
   // the re-deal makes it walk the run column-major, about eight row tiles by eight column tiles at a time)
+  int row_tile = tile.rt;
   if (tile.nrt > 1) {
     const int w = tile.rt * c_eff + nt_launch;
-    const int r2 = w % tile.nrt;
+    row_tile = w % tile.nrt;
     nt_launch = w / tile.nrt;
-    ti = ti - tile.rt + r2;
-    tile = a.tiles[ti];
   }
+  take_row_tile(tile, row_tile, SBM);
   const int nt = tile.col0 + nt_launch;
   const int group = shared ? tile.group - a.E : tile.group;
   if (shared) {   // per-shared-expert slices of the hidden buffer / output (down GEMM)
@@ -587,7 +629,6 @@ __device__ __forceinline__ void dense_tile(const StreamProblem& P, const fmoe_ti
   const __amdgpu_buffer_rsrc_t a_rsrc =
       __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t*>(P.A), 0, 0xffffffff, 0x00020000);
   const int a_kc = ((lane & 7) ^ ((4 * wave + (lane >> 4)) & 7)) * 8;
-  gather_offsets<NAB>(P, tile, a_src);
 
   dense_claim_acc();   // accumulator (j, rb, f) is number (j*NRB + rb)*2 + f, all zero now
 
@@ -676,21 +717,27 @@ __device__ __forceinline__ void dense_tile(const StreamProblem& P, const fmoe_ti
     });
   };
 
-  // prologue: what the steps before the first would have issued, in their order (activations reach
-  // 2*A_AHEAD steps back, weights B_AHEAD)
-  static_for<0, 2 * A_AHEAD>([&](auto qc) {
-    constexpr int q = decltype(qc)::value - 2 * A_AHEAD;   // step number, negative
-    if constexpr ((q + 2 * A_AHEAD) % 2 == 0) {            // an even step: activations of tile q/2 + A_AHEAD
-      constexpr int t = q / 2 + A_AHEAD;
+  // prologue: the first weights, between the two loads of the row indices, then the first activations
+  int src[NAB];
+  gather_first<NAB>(P, tile, src);
+  order_loads();
+  static_for<0, B_AHEAD>([&](auto tc) {
+    constexpr int t = decltype(tc)::value;
 #pragma unroll
-      for (int it = 0; it < NAB; ++it) loadA1(t % DA_STAGES, t, it);
-    }
-    if constexpr (q + B_AHEAD >= 0) {
-#pragma unroll
-      for (int i = 0; i < 2 * DNCB; ++i) loadB1((q + B_AHEAD) % DB_SLOTS, q + B_AHEAD, i);
-    }
-    asm volatile("" ::: "memory");
+    for (int i = 0; i < 2 * DNCB; ++i) loadB1(t % DB_SLOTS, t, i);
+    order_loads();
   });
+  gather_offsets<NAB>(P, src, a_src);
+  static_for<0, A_AHEAD>([&](auto tc) {
+    constexpr int t = decltype(tc)::value;
+#pragma unroll
+    for (int it = 0; it < NAB; ++it) loadA1(t % DA_STAGES, t, it);
+    order_loads();
+  });
+  // The steps count on a tile's activations being older than its weights.  Here they are younger: the first tile
+  // is waited for here, the second one by the third step (which waits for all but NEWER_EVEN loads, and no more
+  // than A_AHEAD-1 tiles and the loads of two steps are younger than the second tile).
+  FMOE_WAIT_VM((A_AHEAD - 1) * NAB);
   int ks0 = 0;
   for (; ks0 + UNROLL <= NKS; ks0 += UNROLL)
     static_for<0, UNROLL>([&](auto uc) { kstep(uc, ks0 + decltype(uc)::value); });
@@ -760,7 +807,7 @@ __global__ __launch_bounds__(256, 2) void ffn_dense_kernel(StreamArgs a) {
   bool single;
   int ti = dense_entry(a, nt_launch, single);
   if (ti < 0) return;
-  fmoe_tile tile = a.tiles[ti];
+  fmoe_tile tile = load_entry(a.tiles, ti);
   const bool shared = tile.group >= a.E;
   StreamProblem P;
 #define FMOE_SEL(f) P.f = shared ? a.p1.f : a.p0.f
@@ -772,16 +819,16 @@ __global__ __launch_bounds__(256, 2) void ffn_dense_kernel(StreamArgs a) {
   const int ct_here = (P.n_col_tiles - tile.col0 < a.cols_entry) ? (P.n_col_tiles - tile.col0) : a.cols_entry;
   const int c_eff = (ct_here + DNCB - 1) / DNCB;
   if (nt_launch >= c_eff) return;
+  int row_tile = tile.rt;
   if (tile.nrt > 1) {   // the items of a run in strips
     const int w = tile.rt * c_eff + nt_launch;
     const int strip = w / (DENSE_STRIP * tile.nrt), in_strip = w - strip * (DENSE_STRIP * tile.nrt);
     const int left = c_eff - strip * DENSE_STRIP;
     const int width = left < DENSE_STRIP ? left : DENSE_STRIP;
-    const int r2 = in_strip / width;
-    nt_launch = strip * DENSE_STRIP + (in_strip - r2 * width);
-    ti = ti - tile.rt + r2;
-    tile = a.tiles[ti];
+    row_tile = in_strip / width;
+    nt_launch = strip * DENSE_STRIP + (in_strip - row_tile * width);
   }
+  take_row_tile(tile, row_tile, SBM);
   const int nt4 = tile.col0 + nt_launch * DNCB;
   const int ct_limit = tile.col0 + ct_here;
   const int group = shared ? tile.group - a.E : tile.group;
@@ -915,7 +962,8 @@ template <bool SWIGLU>
 __global__ __launch_bounds__(64, 2) void ffn_thin_kernel(StreamArgs a) {
   const int ti = (int)blockIdx.x / a.cols;
   if (ti >= *a.n_tiles) return;
-  fmoe_tile tile = a.tiles[ti];
+  fmoe_tile tile = load_entry(a.tiles, ti);
+  take_row_tile(tile, tile.rt, SBM);
   const bool shared = tile.group >= a.E;
   StreamProblem P;
 #define FMOE_SEL(f) P.f = shared ? a.p1.f : a.p0.f
@@ -1193,7 +1241,7 @@ __global__ __launch_bounds__(256, 2) void grouped_gemm_kernel(GemmArgs a) {
   int nt_launch = rr - batch * a.n_col_tiles_max;
   int ti = batch * 8 + xcd;
   if (ti >= n_tiles) return;
-  fmoe_tile tile = a.tiles[ti];
+  fmoe_tile tile = load_entry(a.tiles, ti);
   const bool shared = tile.group >= a.E;
   // field-by-field select keeps the descriptors in scalar registers (indexing the kernel argument
   // dynamically would spill it to scratch memory)
@@ -1207,13 +1255,13 @@ __global__ __launch_bounds__(256, 2) void grouped_gemm_kernel(GemmArgs a) {
   // column tiles this entry really has
   const int c_eff = (P.n_col_tiles - tile.col0 < a.n_col_tiles_max) ? (P.n_col_tiles - tile.col0) : a.n_col_tiles_max;
   if (nt_launch >= c_eff) return;
+  int row_tile = tile.rt;
   if (tile.nrt > 1) {
     const int w = tile.rt * c_eff + nt_launch;
-    const int r2 = w % tile.nrt;
+    row_tile = w % tile.nrt;
     nt_launch = w / tile.nrt;
-    ti = ti - tile.rt + r2;
-    tile = a.tiles[ti];
   }
+  take_row_tile(tile, row_tile, FBM);
   const int nt = tile.col0 + nt_launch;
   const int group = shared ? tile.group - a.E : tile.group;
   switch ((tile.rows + 15) >> 4) {   // live 16-row blocks of the tile, uniform per block

@@ -67,10 +67,10 @@ __device__ __forceinline__ void fmoe_build_tiles(const int32_t* expert_offsets, 
   const int sh1 = ns * rep1, sh2 = ns * n_shared;
   for (int j = threadIdx.x; j < ns; j += blockDim.x) {
     fmoe_tile t;
-    t.row0 = j * bm;
-    t.rows = (n - j * bm < bm) ? (n - j * bm) : bm;
     t.rt = j & (run - 1);
     t.nrt = (ns - (j - t.rt) < run) ? (ns - (j - t.rt)) : run;
+    t.row0 = (j - t.rt) * bm;
+    t.rows = n - t.row0;
     t.group = E;
     for (int c = 0; c < rep1; ++c) {   // replica-major: the row tiles of one replica are consecutive
       const int slot = c * ns + j;
@@ -91,11 +91,11 @@ __device__ __forceinline__ void fmoe_build_tiles(const int32_t* expert_offsets, 
     for (int j = 0; j < nt; ++j) {
       fmoe_tile t;
       t.group = e;
-      t.row0 = r0 + j * bm;
-      t.rows = (cnt - j * bm < bm) ? (cnt - j * bm) : bm;
       t.col0 = 0;
       t.rt = j & (run - 1);
       t.nrt = (nt - (j - t.rt) < run) ? (nt - (j - t.rt)) : run;
+      t.row0 = r0 + (j - t.rt) * bm;
+      t.rows = cnt - (j - t.rt) * bm;
       if (sh1 + start + j < tile_cap) tiles1[sh1 + start + j] = t;
       if (sh2 + start + j < tile_cap) tiles2[sh2 + start + j] = t;
     }
