@@ -36,7 +36,8 @@ def check_accumulation_registers(asm_path):
     registers that the kernel names itself, which the compiler's register allocator does not see.  This
     reads the device assembly the compiler wrote for ffn.hip and fails if, inside those kernels, the
     compiler placed anything of its own in an accumulation register (any a<N> operand outside the
-    kernel's own inline-assembly blocks)."""
+    kernel's own inline-assembly blocks), or spilled a register (their LDS reads are inline assembly and
+    land later than the compiler believes)."""
     import re
     inside = in_asm = False
     kernels = 0
@@ -54,6 +55,8 @@ def check_accumulation_registers(asm_path):
             in_asm = True
         elif "ASMEND" in line:
             in_asm = False
+        elif "Spill" in line:
+            raise RuntimeError(f"{asm_path}:{n}: the compiler spills a register inside {name}: {line.strip()}")
         elif not in_asm and re.search(r"\ba\[?\d", line.split(";")[0]):
             raise RuntimeError(f"{asm_path}:{n}: the compiler uses an accumulation register inside {name}, which "
                                f"keeps hand-placed accumulators there: {line.strip()}")

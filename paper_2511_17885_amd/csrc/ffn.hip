@@ -741,13 +741,14 @@ __device__ __forceinline__ void dense_tile(const StreamProblem& P, const fmoe_ti
   int ks0 = 0;
   for (; ks0 + UNROLL <= NKS; ks0 += UNROLL)
     static_for<0, UNROLL>([&](auto uc) { kstep(uc, ks0 + decltype(uc)::value); });
-  switch (NKS - ks0) {   // left-over steps (an even number below UNROLL), uniform
-    case 2: static_for<0, 2>([&](auto uc) { kstep(uc, ks0 + decltype(uc)::value); }); break;
-    case 4: static_for<0, 4>([&](auto uc) { kstep(uc, ks0 + decltype(uc)::value); }); break;
-    case 6: static_for<0, 6>([&](auto uc) { kstep(uc, ks0 + decltype(uc)::value); }); break;
-    default: break;
+  const int left = NKS - ks0;   // left-over steps: an even number below UNROLL, uniform
+  if (left == 2) {
+    static_for<0, 2>([&](auto uc) { kstep(uc, ks0 + decltype(uc)::value); });
+  } else if (left >= 4) {
+    static_for<0, 4>([&](auto uc) { kstep(uc, ks0 + decltype(uc)::value); });
+    if (left == 6) static_for<4, 6>([&](auto uc) { kstep(uc, ks0 + decltype(uc)::value); });
   }
-  static_assert(UNROLL == 8, "the switch above covers 2, 4 and 6 left-over steps");
+  static_assert(UNROLL == 8, "2, 4 or 6 steps can be left over");
   FMOE_WAIT_VM(0);   // the loads issued past the end have landed before the ring is reused
   // the last matrix instructions have retired before their accumulators are read (24 idle cycles
   // cover the longest read-after-write distance of a 16x16x32 instruction)
@@ -1167,21 +1168,30 @@ __device__ __forceinline__ void f32_tile(const GemmProblem& P, const fmoe_tile& 
     store_a(0, 0);
     load_a(0, F_SLOTS);
     __syncthreads();
-    for (int t0 = 0;; t0 += F_SLOTS) {
+    auto step = [&](int u, int t) {
+      store_a((u + 1) & 1, (u + 1) % F_SLOTS);
+      load_a((u + 1) % F_SLOTS, t + 1 + F_SLOTS);
+      multiply(u & 1, u);
+      __builtin_amdgcn_sched_barrier(0);
+      load_b(u, t + F_SLOTS);
+      __syncthreads();   // tile t+1 is in LDS, all are done with tile t
+    };
+    // No exit inside the loop: with one after every step the compiler sees a way from each of them to the loop's
+    // head and drains all loads there, once per turn of the rings.
+    int t0 = 0;
+    for (; t0 + F_SLOTS <= NT; t0 += F_SLOTS) {
 #pragma unroll
-      for (int u = 0; u < F_SLOTS; ++u) {
-        const int t = t0 + u;
-        if (t >= NT) goto whole_tiles_done;   // uniform
-        store_a((u + 1) & 1, (u + 1) % F_SLOTS);
-        load_a((u + 1) % F_SLOTS, t + 1 + F_SLOTS);
-        multiply(u & 1, u);
-        __builtin_amdgcn_sched_barrier(0);
-        load_b(u, t + F_SLOTS);
-        __syncthreads();   // tile t+1 is in LDS, all are done with tile t
+      for (int u = 0; u < F_SLOTS; ++u) step(u, t0 + u);
+    }
+    static_assert(F_SLOTS == 4, "up to three tiles are left");
+    if (t0 < NT) {   // uniform
+      step(0, t0);
+      if (t0 + 1 < NT) {
+        step(1, t0 + 1);
+        if (t0 + 2 < NT) step(2, t0 + 2);
       }
     }
   }
-whole_tiles_done:
   if (NT * FBK < K) {   // uniform: the last, partial tile; what lies past K counts as zero on both sides
     const f32x4_t zero = {0.f, 0.f, 0.f, 0.f};
     const int k0 = NT * FBK;
