@@ -1027,9 +1027,9 @@ __global__ void pack_weights_kernel(const bf16_t* __restrict__ src0, const bf16_
 //    (row or column l%16, quarter q) holds k = 4q..4q+3 and instruction i takes element i on both sides.
 //    Weights therefore come straight from the caller's rows into registers, rows from LDS without a
 //    transposition;
-//  * weights: F_SLOTS-1 k tiles (32 wide, one 128-byte line per column) in flight per wavefront, addressed by a
+//  * weights: one or three k tiles (32 wide, one 128-byte line per column) in flight per wavefront, addressed by a
 //    descriptor over the wavefront's rows, a constant lane offset and a scalar one; gathered rows: 64-bit
-//    pointers (fp32 tensors may exceed 4 GiB), F_SLOTS-1 tiles in flight, through registers into one of two
+//    pointers (fp32 tensors may exceed 4 GiB), as many tiles in flight, through registers into one of two
 //    LDS buffers in the swizzled layout of the bf16 kernels; one barrier per k tile.
 // Measured against an LDS-tiled kernel on the 32x32x2 instruction (both operands through LDS, one tile of
 // loads in flight, one operand per LDS read): 1600 tokens, d 1280, 64 experts of 896, 42 rows per expert:
@@ -1037,7 +1037,10 @@ __global__ void pack_weights_kernel(const bf16_t* __restrict__ src0, const bf16_
 // (108 and 105 TFLOP/s); 64 tokens, d 128, 8 experts of 256: 19.5 -> 7.9 and 33.5 -> 10.0 us.
 constexpr int FBM = 64;        // rows per tile
 constexpr int FBK = 32;        // k per tile: 128 bytes of a row
-constexpr int F_SLOTS = 4;     // register rings, in k tiles
+// Register rings, in k tiles.  Tiles of up to 32 rows are chains of latencies, where what a shorter prologue and
+// fewer registers give counts for more than two more tiles in flight: 64 tokens, d 128, 8 experts of 256 9.4 + 10.7 ->
+// 8.5 + 9.8 us; 2600 tokens of it 13.8 + 17.2 -> 12.6 + 15.7; tiles of more rows measured 1 to 3 % slower with two.
+constexpr int f32_slots(int row_blocks) { return row_blocks <= 2 ? 2 : 4; }
 
 struct GemmProblem {
   const float* A;           // [*, lda]
@@ -1069,6 +1072,7 @@ struct GemmArgs {
 template <bool SWIGLU, int NRB>   // NRB: live 16-row blocks of the tile
 __device__ __forceinline__ void f32_tile(const GemmProblem& P, const fmoe_tile& tile, int group, bool shared, int nt,
                                          float* As) {
+  constexpr int SLOTS = f32_slots(NRB);
   constexpr int A_IT = (NRB + 1) / 2;   // 16-byte pieces of a k tile per thread
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -1086,7 +1090,7 @@ __device__ __forceinline__ void f32_tile(const GemmProblem& P, const fmoe_tile& 
     b_rsrc[f] = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(B), 0, 0xffffffff, 0x00020000);
     b_off[f] = ((uint32_t)((n < N ? n : N - 1) - base) * (uint32_t)P.ldb + (uint32_t)(lane >> 4) * 4u) * 4u;
   }
-  f32x4_t breg[F_SLOTS][2][2];          // [ring slot][16 k][fragment]
+  f32x4_t breg[SLOTS][2][2];          // [ring slot][16 k][fragment]
   auto load_b = [&](int slot, int t) {
     const uint32_t off = (uint32_t)(t < NT ? t : NT - 1) * (FBK * 4);   // scalar
 #pragma unroll
@@ -1097,7 +1101,7 @@ __device__ __forceinline__ void f32_tile(const GemmProblem& P, const fmoe_tile& 
   };
   if (NT > 0) {   // uniform; the weights do not wait for the row indices
 #pragma unroll
-    for (int t = 0; t < F_SLOTS; ++t) {   // in ring order: the waits in the loop count on it
+    for (int t = 0; t < SLOTS; ++t) {   // in ring order: the waits in the loop count on it
       load_b(t, t);
       __builtin_amdgcn_sched_barrier(0);
     }
@@ -1120,7 +1124,7 @@ __device__ __forceinline__ void f32_tile(const GemmProblem& P, const fmoe_tile& 
     a_src[it] = P.A + (shared ? (size_t)group * P.a_group_off : 0) + (size_t)src * P.lda + chunk * 4;
     a_dst[it] = r * FBK + (chunk ^ ((r >> 1) & 7)) * 4;
   }
-  f32x4_t areg[F_SLOTS][A_IT];
+  f32x4_t areg[SLOTS][A_IT];
   auto load_a = [&](int slot, int t) {
     const int off = (t < NT ? t : NT - 1) * FBK;   // scalar
 #pragma unroll
@@ -1157,41 +1161,46 @@ __device__ __forceinline__ void f32_tile(const GemmProblem& P, const fmoe_tile& 
   };
 
   // Step t multiplies tile t, puts tile t+1's rows into the other LDS buffer and issues the weights of tile
-  // t+F_SLOTS and the rows of tile t+1+F_SLOTS (past the last tile the last one again).
-  static_assert(F_SLOTS % 2 == 0, "ring slots and LDS buffers are compile-time");
+  // t+SLOTS and the rows of tile t+1+SLOTS (past the last tile the last one again).
+  static_assert(SLOTS % 2 == 0, "ring slots and LDS buffers are compile-time");
   if (NT > 0) {   // uniform
 #pragma unroll
-    for (int t = 0; t < F_SLOTS; ++t) {
+    for (int t = 0; t < SLOTS; ++t) {
       load_a(t, t);
       __builtin_amdgcn_sched_barrier(0);
     }
     store_a(0, 0);
-    load_a(0, F_SLOTS);
+    load_a(0, SLOTS);
     __syncthreads();
     auto step = [&](int u, int t) {
-      store_a((u + 1) & 1, (u + 1) % F_SLOTS);
-      load_a((u + 1) % F_SLOTS, t + 1 + F_SLOTS);
+      store_a((u + 1) & 1, (u + 1) % SLOTS);
+      load_a((u + 1) % SLOTS, t + 1 + SLOTS);
       multiply(u & 1, u);
       __builtin_amdgcn_sched_barrier(0);
-      load_b(u, t + F_SLOTS);
+      load_b(u, t + SLOTS);
       __syncthreads();   // tile t+1 is in LDS, all are done with tile t
     };
-    // No exit inside the loop: with one after every step the compiler sees a way from each of them to the loop's
-    // head and drains all loads there, once per turn of the rings.
     int t0 = 0;
-    for (; t0 + F_SLOTS <= NT; t0 += F_SLOTS) {
+    if constexpr (SLOTS == 2) {
+      // No exit inside the loop: with one after every step the compiler sees a way from each of them to the loop's
+      // head and drains all loads there, once per turn of the rings, which a short step does not hide ...
+      for (; t0 + SLOTS <= NT; t0 += SLOTS) {
 #pragma unroll
-      for (int u = 0; u < F_SLOTS; ++u) step(u, t0 + u);
-    }
-    static_assert(F_SLOTS == 4, "up to three tiles are left");
-    if (t0 < NT) {   // uniform
-      step(0, t0);
-      if (t0 + 1 < NT) {
-        step(1, t0 + 1);
-        if (t0 + 2 < NT) step(2, t0 + 2);
+        for (int u = 0; u < SLOTS; ++u) step(u, t0 + u);
+      }
+      if (t0 < NT) step(0, t0);   // uniform
+    } else {
+      // ... and a long one does.
+      for (;; t0 += SLOTS) {
+#pragma unroll
+        for (int u = 0; u < SLOTS; ++u) {
+          if (t0 + u >= NT) goto whole_tiles_done;   // uniform
+          step(u, t0 + u);
+        }
       }
     }
   }
+whole_tiles_done:
   if (NT * FBK < K) {   // uniform: the last, partial tile; what lies past K counts as zero on both sides
     const f32x4_t zero = {0.f, 0.f, 0.f, 0.f};
     const int k0 = NT * FBK;
