@@ -18,10 +18,24 @@
 
 namespace {
 
+// v of the lane `ROT` places on in the row of 16
+template <int ROT>
+__device__ __forceinline__ float row_rotate(float v) {
+  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x120 + ROT, 0xf, 0xf, false));
+}
+// The xor butterfly 32, 16, 8, 4, 2, 1 without the LDS crossbar: the halves and the rows of 16 are exchanged by lane
+// swaps (a swap of v with itself leaves v of the lower partner in one result and of the upper one in the other),
+// and once the values repeat every 8 lanes, a rotation inside the row pairs what the exclusive-or would.
+// (Eleven sums one after the other per window of five: 7936 tokens, 128 experts 11.0 -> 10.2 us; 48 tokens 4.9 -> 4.2.)
 __device__ __forceinline__ float wave_sum_butterfly(float p) {
-#pragma unroll
-  for (int s = 32; s >= 1; s >>= 1) p = p + __shfl_xor(p, s, 64);
-  return p;
+  const auto h = __builtin_amdgcn_permlane32_swap(__float_as_uint(p), __float_as_uint(p), false, false);
+  p = __uint_as_float(h[0]) + __uint_as_float(h[1]);
+  const auto q = __builtin_amdgcn_permlane16_swap(__float_as_uint(p), __float_as_uint(p), false, false);
+  p = __uint_as_float(q[0]) + __uint_as_float(q[1]);
+  p = p + row_rotate<8>(p);
+  p = p + row_rotate<4>(p);
+  p = p + row_rotate<2>(p);
+  return p + row_rotate<1>(p);
 }
 
 // ---- A: visual ordinals.  One block per sequence.
@@ -563,27 +577,18 @@ __global__ void identity_kept_kernel(const uint8_t* __restrict__ is_visual,
   if (i <= B && new_cu != nullptr) new_cu[i] = clampi(cu[i], 0, T);
 }
 
-// v of lane (l xor 2^jb).  jb is a constant after unrolling: distances 1 and 2 are quad permutes,
-// 4 and 8 a pair of row shifts (lanes with the bit clear read upwards, the others downwards), all
-// executed inside the ALU; 16 and 32 cross rows and go through the LDS crossbar.
-template <int CTRL>
-__device__ __forceinline__ uint32_t dpp_mov(uint32_t v) {
-  return (uint32_t)__builtin_amdgcn_update_dpp((int)v, (int)v, CTRL, 0xf, 0xf, false);
+// Inclusive prefix sum over the wavefront's lanes, inside the vector unit: within rows of 16, then the rows' totals.
+template <int CTRL, int ROWS>
+__device__ __forceinline__ int dpp_or_zero(int v) {   // lanes without a source, or in other rows, get 0
+  return __builtin_amdgcn_update_dpp(0, v, CTRL, ROWS, 0xf, false);
 }
-__device__ __forceinline__ uint32_t lane_xor_pow2(int jb, uint32_t v, int lane) {
-  switch (jb) {
-    case 0: return dpp_mov<0xB1>(v);    // quad_perm [1,0,3,2]
-    case 1: return dpp_mov<0x4E>(v);    // quad_perm [2,3,0,1]
-    case 2: {
-      const uint32_t up = dpp_mov<0x104>(v), dn = dpp_mov<0x114>(v);   // row_shl:4, row_shr:4
-      return (lane & 4) ? dn : up;
-    }
-    case 3: {
-      const uint32_t up = dpp_mov<0x108>(v), dn = dpp_mov<0x118>(v);   // row_shl:8, row_shr:8
-      return (lane & 8) ? dn : up;
-    }
-    default: return (uint32_t)__shfl_xor((int)v, 1 << jb, 64);
-  }
+__device__ __forceinline__ int wave_scan(int v) {
+  v += dpp_or_zero<0x111, 0xf>(v);   // row_shr:1
+  v += dpp_or_zero<0x112, 0xf>(v);   // row_shr:2
+  v += dpp_or_zero<0x114, 0xf>(v);   // row_shr:4
+  v += dpp_or_zero<0x118, 0xf>(v);   // row_shr:8
+  v += dpp_or_zero<0x142, 0xa>(v);   // the last lane of rows 0 and 2 to rows 1 and 3
+  return v + dpp_or_zero<0x143, 0xc>(v);   // lane 31 to rows 2 and 3
 }
 
 // ---- E: small batches.  One 1024-thread block takes the whole chain after the window scores:
@@ -592,15 +597,15 @@ __device__ __forceinline__ uint32_t lane_xor_pow2(int jb, uint32_t v, int lane) 
 // of work and the launches between them cost more than the steps themselves.
 //   * every global input is fetched up front (thread i owns tokens i, i+1024, ...), every global
 //     output is stored at the very end, so no barrier in between waits on memory;
-//   * drop order: the order (normalised attention asc, score desc, index asc) is total, so a
-//     bitonic sort of the integer keys (one window per thread; exchanges inside a wavefront by
-//     lane shuffles, across wavefronts through LDS) gives every window its number of predecessors;
+//   * drop order: the order (normalised attention asc, score desc, index asc) is total, and of the places in it
+//     only one matters, that of the window at which the budget ends: a radix selection finds it, one window
+//     per thread (with a bitonic sort for all places 1600 tokens took 19.9 us in this kernel, so they take 16.9);
 //   * permutation: as in the stand-alone kernels (per-expert position masks, popcount ranks), one
 //     pass per 1024 tokens, one 64-bit mask word per wavefront.
 constexpr int SB_THREADS = 1024;
 constexpr int SB_MAX_TP = 4;                       // tokens per thread, at most
 constexpr int SB_MAX_T = SB_THREADS * SB_MAX_TP;   // tokens
-constexpr int SB_MAX_NW = 1024;                // windows of one sequence: one sort element per thread
+constexpr int SB_MAX_NW = 1024;                // windows of one sequence: one per thread
 constexpr int SB_MROW = 17;                    // 64-bit mask words per expert (16 + 1 against bank conflicts)
 constexpr int SB_MAX_B = 512;                  // sequences whose bounds are cached in LDS
 
@@ -636,10 +641,10 @@ struct SmallArgs {
 template <int SB_TP, int KM, bool PERM_ONLY>
 __global__ __launch_bounds__(SB_THREADS) void prune_dispatch_small_kernel(SmallArgs a) {
   __shared__ uint16_t s_kept[SB_MAX_T];
-  // phase 1: precede u16[SB_MAX_T] | 2 x sort keys u64[SB_MAX_NW] | 2 x sort keys u32[SB_MAX_NW]
+  // phase 1: leading tokens kept per window u16[SB_MAX_T] | 3 x counts per byte value [256]
   // phase 2: position masks u64[FMOE_MAX_EXPERTS][SB_MROW]
   constexpr int U_BYTES = FMOE_MAX_EXPERTS * SB_MROW * 8;
-  static_assert(SB_MAX_T * 2 + SB_MAX_NW * 24 <= U_BYTES, "phase-1 arrays fit");
+  static_assert(SB_MAX_T * 2 + 3 * 256 * 4 <= U_BYTES, "phase-1 arrays fit");
   __shared__ __align__(16) unsigned char s_u[U_BYTES];
   __shared__ int s_off[FMOE_MAX_EXPERTS + 1], s_base[FMOE_MAX_EXPERTS];
   __shared__ int s_cu[SB_MAX_B + 1], s_nv[SB_MAX_B];
@@ -647,10 +652,9 @@ __global__ __launch_bounds__(SB_THREADS) void prune_dispatch_small_kernel(SmallA
   __shared__ uint16_t s_pfx[FMOE_MAX_EXPERTS * 16];   // rows of an expert ahead of each wavefront's tokens
   __shared__ int wave_tot[16];
   __shared__ float red[16];
-  __shared__ int s_last;
+  __shared__ uint32_t s_last[2], s_cut[3];   // keys of a shorter last window; of the window at which the budget ends
   uint16_t* s_pre = reinterpret_cast<uint16_t*>(s_u);
-  unsigned long long* sK = reinterpret_cast<unsigned long long*>(s_u + SB_MAX_T * 2);
-  uint32_t* sA = reinterpret_cast<uint32_t*>(s_u + SB_MAX_T * 2 + SB_MAX_NW * 16);
+  int* const hist = reinterpret_cast<int*>(s_u + SB_MAX_T * 2);
   unsigned long long* mask = reinterpret_cast<unsigned long long*>(s_u);
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -716,57 +720,94 @@ __global__ __launch_bounds__(SB_THREADS) void prune_dispatch_small_kernel(SmallA
 #pragma unroll
         for (int w = 1; w < 16; ++w) amax = (red[w] > amax) ? red[w] : amax;
       }
-      uint32_t ka = ~0u;               // padding sorts behind every window
-      unsigned long long kk = ~0ull;
+      uint32_t ka = 0u, kc = 0u;   // sort keys, ascending = drop order (ties: lower index)
       if (tid < n) {
         float A;
         const float c = redundancy_score(ws_r, has_attn, wa_r, amax, a.alpha, one_minus_alpha, A);
-        kk = ((unsigned long long)(~float_order_key(c)) << 32) | (uint32_t)tid;
+        kc = ~float_order_key(c);
         ka = float_order_key(A);
       }
-      int N = 64;
-      while (N < n) N <<= 1;
-      const bool active = tid < N;   // whole wavefronts; the others only keep the barriers company
-      int buf = 0;
-      for (int k = 2; k <= N; k <<= 1) {
+      // How many full-size windows are dropped whole (q), what the next one loses (part), what the last window
+      // keeps if it is shorter: that one's turn comes behind `ahead` full windows.
+      const int w_last = nv - (n - 1) * W, n_full = w_last < W ? n - 1 : n;
+      const bool full = tid < n_full;
+      const int eps = nv - token_budget(nv, a.retention);
+      int q = eps / W, part = eps - q * W, last_keeps = w_last;
+      if (n_full < n) {   // uniform
+        if (tid == n - 1) {
+          s_last[0] = ka;
+          s_last[1] = kc;
+        }
+        __syncthreads();
+        const unsigned long long m = __ballot(full && (ka < s_last[0] || (ka == s_last[0] && kc <= s_last[1])));
+        if (lane == 0) wave_tot[wave] = __popcll(m);
+        __syncthreads();
+        int ahead = 0;
 #pragma unroll
-        for (int jb = 9; jb >= 0; --jb) {   // partner distances 512 .. 1, those below k
-          const int j = 1 << jb;
-          if (j >= k) continue;             // uniform
-          uint32_t pa = ka;
-          unsigned long long pk = kk;
-          if (j >= 64) {   // partner in another wavefront: through LDS, buffers alternate
-            if (active) {
-              sK[buf * SB_MAX_NW + tid] = kk;
-              if (has_attn) sA[buf * SB_MAX_NW + tid] = ka;
-            }
-            __syncthreads();
-            if (active) {
-              pk = sK[buf * SB_MAX_NW + (tid ^ j)];
-              if (has_attn) pa = sA[buf * SB_MAX_NW + (tid ^ j)];
-            }
-            buf ^= 1;
-          } else if (active) {
-            const uint32_t lo = lane_xor_pow2(jb, (uint32_t)kk, lane);
-            const uint32_t hi = lane_xor_pow2(jb, (uint32_t)(kk >> 32), lane);
-            pk = ((unsigned long long)hi << 32) | lo;
-            if (has_attn) pa = lane_xor_pow2(jb, ka, lane);
-          }
-          if (active) {
-            const bool partner_first = (pa < ka) || (pa == ka && pk < kk);
-            const bool want_min = (((tid & j) == 0) == ((tid & k) == 0));
-            if (want_min == partner_first) {
-              ka = pa;
-              kk = pk;
-            }
-          }
+        for (int w = 0; w < 16; ++w) ahead += wave_tot[w];
+        if (q >= ahead) {
+          const int u = eps - ahead * W;
+          last_keeps = u < w_last ? w_last - u : 0;
+          q = u < w_last ? ahead : ahead + (u - w_last) / W;
+          part = u < w_last ? 0 : (u - w_last) % W;
         }
       }
-      // thread r < n now holds the window at place r of the drop order
-      const int wi = (int)(kk & 0xffffffffu);
-      if (tid < n && wi == n - 1) s_last = tid;
+      // The full window at place q, by its key's bytes from the highest on: counts of the candidates per byte value,
+      // summed by every wavefront for itself; one barrier a byte, the tables take turns.
+      bool candidate = full;
+      int place = q;
+      bool single = false;
+      if (q < n_full) {   // uniform
+        for (int i = tid; i < 256; i += SB_THREADS) hist[i] = 0;
+        __syncthreads();
+        int table = 0;
+        for (int byte = has_attn ? 0 : 4; byte < 8 && !single; ++byte) {   // uniform
+          int* const h = hist + table * 256;
+          table = table == 2 ? 0 : table + 1;
+          for (int i = tid; i < 256; i += SB_THREADS) hist[table * 256 + i] = 0;
+          const int digit = (int)((byte < 4 ? ka : kc) >> (24 - 8 * (byte & 3))) & 255;
+          if (candidate) atomicAdd(&h[digit], 1);
+          __syncthreads();
+          const int4 c4 = *reinterpret_cast<const int4*>(&h[4 * lane]);
+          const int sum4 = c4.x + c4.y + c4.z + c4.w;
+          const int excl = wave_scan(sum4) - sum4;
+          const int src = __builtin_ctzll(__ballot(excl <= place && place < excl + sum4));   // exactly one lane
+          int before = excl, val = 4 * lane, here = c4.x;
+          if (before + here <= place) { before += here; here = c4.y; ++val; }
+          if (val > 4 * lane && before + here <= place) { before += here; here = c4.z; ++val; }
+          if (val > 4 * lane + 1 && before + here <= place) { before += here; here = c4.w; ++val; }
+          place -= __builtin_amdgcn_readlane(before, src);
+          candidate = candidate && digit == __builtin_amdgcn_readlane(val, src);
+          single = __builtin_amdgcn_readlane(here, src) == 1;
+        }
+        if (!single) {   // equal keys: by index
+          const unsigned long long m = __ballot(candidate);
+          if (lane == 0) wave_tot[wave] = __popcll(m);
+          __syncthreads();
+          int pos = __popcll(m & ((1ull << lane) - 1ull));
+#pragma unroll
+          for (int w = 0; w < 16; ++w) pos += w < wave ? wave_tot[w] : 0;
+          candidate = candidate && pos == place;
+        }
+        if (candidate) {
+          s_cut[0] = ka;
+          s_cut[1] = kc;
+          s_cut[2] = (uint32_t)tid;
+        }
+      }
       __syncthreads();
-      if (tid < n) s_pre[s + wi] = (uint16_t)(tid | ((s_last < tid) ? 0x8000 : 0));
+      if (tid < n) {   // leading tokens that stay
+        int lead = last_keeps;
+        if (full && q < n_full) {
+          const uint32_t ca = s_cut[0], cc = s_cut[1];
+          const int ci = (int)s_cut[2];
+          const bool ahead = ka != ca ? ka < ca : (kc != cc ? kc < cc : tid < ci);
+          lead = ahead ? 0 : (tid == ci ? W - part : W);
+        } else if (full) {
+          lead = 0;
+        }
+        s_pre[s + tid] = (uint16_t)lead;
+      }
       __syncthreads();
     }
   }
@@ -784,9 +825,7 @@ __global__ __launch_bounds__(SB_THREADS) void prune_dispatch_small_kernel(SmallA
       } else {
         const int b = find_seq(cu, B, t);
         const int s = clampi(cu[b], 0, T);
-        const int pc = s_pre[s + ord / W];
-        keep = (ord % W) < window_keep_lead(ord, seq_nv[b], W, a.retention,
-                                            (pc & 0x7fff) | ((pc >> 15) << 30));
+        keep = (ord % W) < s_pre[s + ord / W];
       }
     }
     keep_r[k] = keep;

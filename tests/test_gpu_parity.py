@@ -746,6 +746,40 @@ def test_expert_gemm_shapes_agree_bit_for_bit(cfg):
         m.set_ffn_shape(3)
 
 
+@pytest.mark.parametrize("T_v,T_t,win,retention,copies,attn", [
+    ([1], [0], 3, 0.5, 1, False), ([2], [1], 3, 0.25, 1, False), ([61], [3], 4, 0.75, 1, False),
+    ([192], [0], 3, 0.5, 1, False),                        # 64 windows, none of them short
+    ([2043], [5], 2, 0.5, 1, True),                        # 1022 windows, the last one short
+    ([1024], [0], 1, 0.999, 1, False),                     # 1024 windows of one token: equal scores
+    ([700, 0, 40, 3], [9, 4, 0, 1], 5, 0.37, 1, True),
+    ([900, 31], [2, 0], 3, 0.5, 90, False), ([900, 31], [2, 0], 3, 0.06, 90, True),   # runs of equal windows
+    ([4000], [50], 7, 0.9, 50, False),
+    ([100, 100, 100], [1, 1, 1], 6, 1.0 - 1e-7, 1, False),  # nothing to drop
+    ([333], [0], 64, 0.01, 1, True),
+])
+def test_one_block_prune_keeps_what_the_general_chain_keeps(T_v, T_t, win, retention, copies, attn):
+    """The single-workgroup form finds the window at which the budget ends by selection, the general chain counts the
+    predecessors of every window: the same tokens, with equal scores, short last windows, attention (with equal
+    sums), and up to as many windows as it takes."""
+    wl = W.small_random(4100 + sum(T_v) + win, T_v=T_v, T_t=T_t, d=64, E=12, F=16, k_text=2, k_visual=1,
+                            retention=0.5, window=win, dtype=W.F32, n_components=4)
+    x = wl.x.copy()
+    if copies > 1:
+        x = x[(np.arange(len(x)) // copies) * copies]      # equal rows: equal probabilities
+    m = make_layer(wl)
+    x, vis, cu = dev(x, torch.float32), dev(wl.is_visual), dev(wl.cu_seqlens)
+    a = None
+    if attn:
+        a = dev(np.random.Generator(np.random.PCG64(5)).integers(0, 3, wl.T).astype(np.float32))
+    pp = binding.prune_params(retention=retention, window=win, alpha=0.5 if attn else 1.0)
+    _, kept, new_cu, _ = m.layer_forward(x, vis, cu, pp, attn=a)
+    probs, _, _ = m.route(x, vis)
+    g_kept, g_cu, _ = m.prune(pp, probs, vis, cu, attn=a)
+    n = int(host(g_cu)[-1])
+    assert np.array_equal(host(new_cu), host(g_cu))
+    assert np.array_equal(host(kept)[:n], host(g_kept)[:n])
+
+
 @pytest.mark.parametrize("rows,d,F,n_shared", [
     ([129, 1, 0, 128, 127, 16, 17, 256, 257, 40], 136, 520, 0),   # both kinds, column groups 5 (strips 3 + 2) and 1
     ([1, 128, 0, 31, 32, 33, 96, 97], 520, 136, 1),               # single tiles only (a shared group of several)
