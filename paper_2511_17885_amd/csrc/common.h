@@ -225,6 +225,23 @@ template <> __device__ __forceinline__ bf16_t from_f64<bf16_t>(double v) {
   return f32_to_bf16(__uint_as_float(u));
 }
 
+// Inclusive prefix sum over the wavefront's lanes, inside the vector unit: within rows of 16, then the rows' totals.
+template <int CTRL, int ROWS>
+__device__ __forceinline__ int dpp_or_zero(int v) {   // lanes without a source, or in other rows, get 0
+  return __builtin_amdgcn_update_dpp(0, v, CTRL, ROWS, 0xf, false);
+}
+__device__ __forceinline__ int row_scan(int v) {   // over the lanes of each row of 16
+  v += dpp_or_zero<0x111, 0xf>(v);   // row_shr:1
+  v += dpp_or_zero<0x112, 0xf>(v);   // row_shr:2
+  v += dpp_or_zero<0x114, 0xf>(v);   // row_shr:4
+  return v + dpp_or_zero<0x118, 0xf>(v);   // row_shr:8
+}
+__device__ __forceinline__ int wave_scan(int v) {
+  v = row_scan(v);
+  v += dpp_or_zero<0x142, 0xa>(v);   // the last lane of rows 0 and 2 to rows 1 and 3
+  return v + dpp_or_zero<0x143, 0xc>(v);   // lane 31 to rows 2 and 3
+}
+
 // number of valid entries: the device-side count if given (clamped to the capacity), else cap
 __device__ __forceinline__ int resolve_count(int cap, const int32_t* n_dev) {
   if (n_dev == nullptr) return cap;

@@ -78,12 +78,7 @@ __device__ __forceinline__ void scan_totals(const int* total, int E, int32_t* of
       c[q] = (i < E) ? total[i] : 0;
       sum += c[q];
     }
-    int incl = sum;
-#pragma unroll
-    for (int sh = 1; sh < 64; sh <<= 1) {
-      const int o = __shfl_up(incl, sh, 64);
-      if (lane >= sh) incl += o;
-    }
+    const int incl = wave_scan(sum);
     int excl = incl - sum;
 #pragma unroll
     for (int q = 0; q < 4; ++q) {

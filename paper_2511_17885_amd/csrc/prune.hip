@@ -577,20 +577,6 @@ __global__ void identity_kept_kernel(const uint8_t* __restrict__ is_visual,
   if (i <= B && new_cu != nullptr) new_cu[i] = clampi(cu[i], 0, T);
 }
 
-// Inclusive prefix sum over the wavefront's lanes, inside the vector unit: within rows of 16, then the rows' totals.
-template <int CTRL, int ROWS>
-__device__ __forceinline__ int dpp_or_zero(int v) {   // lanes without a source, or in other rows, get 0
-  return __builtin_amdgcn_update_dpp(0, v, CTRL, ROWS, 0xf, false);
-}
-__device__ __forceinline__ int wave_scan(int v) {
-  v += dpp_or_zero<0x111, 0xf>(v);   // row_shr:1
-  v += dpp_or_zero<0x112, 0xf>(v);   // row_shr:2
-  v += dpp_or_zero<0x114, 0xf>(v);   // row_shr:4
-  v += dpp_or_zero<0x118, 0xf>(v);   // row_shr:8
-  v += dpp_or_zero<0x142, 0xa>(v);   // the last lane of rows 0 and 2 to rows 1 and 3
-  return v + dpp_or_zero<0x143, 0xc>(v);   // lane 31 to rows 2 and 3
-}
-
 // ---- E: small batches.  One 1024-thread block takes the whole chain after the window scores:
 // drop order, budget, compaction, permutation by expert and the grouped-GEMM tile lists, with the
 // intermediate arrays in LDS.  At a few thousand tokens each of those steps is a few microseconds
@@ -867,12 +853,7 @@ __global__ __launch_bounds__(SB_THREADS) void prune_dispatch_small_kernel(SmallA
         const int e = it >> 4, w = it & 15;
         const int c = __popcll(mask[e * SB_MROW + w]);
         const int base = s_base[e];
-        int incl = c;
-#pragma unroll
-        for (int sh = 1; sh < 16; sh <<= 1) {
-          const int o = __shfl_up(incl, sh, 16);
-          if (w >= sh) incl += o;
-        }
+        const int incl = row_scan(c);
         s_pfx[it] = (uint16_t)(base + incl - c);
         if (w == 15) s_base[e] = base + incl;   // same wavefront: every lane has read the old value
       }
@@ -906,12 +887,7 @@ __global__ __launch_bounds__(SB_THREADS) void prune_dispatch_small_kernel(SmallA
       c[q] = (e < E) ? s_base[e] : 0;
       sum += c[q];
     }
-    int incl = sum;
-#pragma unroll
-    for (int sh = 1; sh < 64; sh <<= 1) {
-      const int o = __shfl_up(incl, sh, 64);
-      if (lane >= sh) incl += o;
-    }
+    const int incl = wave_scan(sum);
     int excl = incl - sum;
 #pragma unroll
     for (int q = 0; q < 4; ++q) {

@@ -100,9 +100,9 @@ __device__ __forceinline__ float exp_fixed(float x) {
   p = fmaf(p, r, 0.5f);
   p = fmaf(p, r, 1.0f);
   p = fmaf(p, r, 1.0f);
-  if (!(n >= -125.0f)) return 0.0f;
-  float scale = __uint_as_float((uint32_t)((int)n + 127) << 23);
-  return p * scale;
+  const bool in = n >= -125.0f;   // not for NaN
+  const float scale = __uint_as_float((uint32_t)((int)(in ? n : 0.0f) + 127) << 23);
+  return in ? p * scale : 0.0f;
 }
 
 // Private router-weight layout: for expert block eb (16 experts) and k group g (16 k), lane l
@@ -258,6 +258,15 @@ __global__ __launch_bounds__(256) void route_kernel(
   auto read_x = [&](int o, int buf, int gl) {
     xa[o] = *reinterpret_cast<const f32x4_t*>(&smem[buf * (64 * RS) + xlane + gl * 4]);
   };
+  // Four tokens per wavefront side by side, token q of them in lanes 16q .. 16q+15; lane j of a token holds the
+  // experts 16r + j, r = 0 .. NR-1.
+  constexpr int NR = 4 * NB;
+  const int j = lane & 15;
+  const int tok = wave * 4 + (lane >> 4);
+  const bool tv = (t0 + tok) < T;
+  const int t = tv ? t0 + tok : T - 1;
+  const bool visual = is_visual[t] != 0;
+  const bool biased = bias != nullptr;
   // Chunk c is multiplied while chunk c+1 goes into the other LDS buffer, chunks up to c+XPF and R groups of
   // weights are in flight.
   static_assert(XPF % 2 == 0 && (XPF * NG) % R == 0, "ring indices are compile-time");
@@ -303,6 +312,11 @@ __global__ __launch_bounds__(256) void route_kernel(
       }
     }
   }
+  // all biases at once, on their way while the logits go through LDS: fetched where they are added, each was a
+  // memory latency of its own (8192 tokens, 128 experts 46.4 -> 45.4 us; 1600 tokens, 64 experts 13.3 -> 12.9)
+  float bias_r[NR];
+#pragma unroll
+  for (int r = 0; r < NR; ++r) bias_r[r] = biased ? bias[16 * r + j < E ? 16 * r + j : E - 1] : 0.0f;
   __syncthreads();   // the chunks' LDS becomes the logits'
 
   // accumulator register v of lane l: token 4*(l/16) + v, expert (block)*16 + l%16
@@ -314,29 +328,19 @@ __global__ __launch_bounds__(256) void route_kernel(
   }
   __syncthreads();
 
-  // Softmax, top-k and gates: four tokens per wavefront side by side, token q of them in lanes 16q .. 16q+15.
-  // Lane j of a token holds the experts 16r + j, r = 0 .. NR-1.
-  constexpr int NR = 4 * NB;
-  const int j = lane & 15;
-  const int tok = wave * 4 + (lane >> 4);
-  const bool tv = (t0 + tok) < T;
-  const int t = tv ? t0 + tok : T - 1;
+  // Softmax, top-k and gates
   float P[NR];
   float mx = -INFINITY;
 #pragma unroll
   for (int r = 0; r < NR; ++r) {
-    const int e = 16 * r + j;
-    float v = -INFINITY;
-    if (e < E) {
-      v = smem[tok * ES + e];
-      if (bias != nullptr) v = v + bias[e];
-    }
-    P[r] = v;
-    mx = larger(mx, v);
+    const float z = smem[tok * ES + 16 * r + j];   // (past E the last block's logits again)
+    const float v = biased ? z + bias_r[r] : z;
+    P[r] = 16 * r + j < E ? v : -INFINITY;
+    mx = larger(mx, P[r]);
   }
   mx = row_max(mx);
 #pragma unroll
-  for (int r = 0; r < NR; ++r) P[r] = (16 * r + j < E) ? exp_fixed(P[r] - mx) : 0.0f;
+  for (int r = 0; r < NR; ++r) P[r] = exp_fixed(P[r] - mx);   // 0 past E, without a branch
   // the sum's order: experts e, e+64, .. one after the other, then the xor butterfly 32, 16, 8, 4, 2, 1
   float part[4];
 #pragma unroll
@@ -348,7 +352,6 @@ __global__ __launch_bounds__(256) void route_kernel(
   const float sum = row_sum_butterfly((part[0] + part[2]) + (part[1] + part[3]));
   // Inside the fused layer (the launch that also carries the ordinal blocks) the probabilities only feed
   // the window scores, which read visual tokens: text rows are not written.
-  const bool visual = is_visual[t] != 0;
   const bool store_row = probs != nullptr && tv && (ord.cu == nullptr || visual);
 #pragma unroll
   for (int r = 0; r < NR; ++r) {
@@ -448,12 +451,7 @@ __global__ __launch_bounds__(256) void route_kernel(
         c[q] = __popc(s_mask[4 * lane + q]);
         sum += c[q];
       }
-      int incl = sum;
-#pragma unroll
-      for (int sh = 1; sh < 64; sh <<= 1) {
-        const int o = __shfl_up(incl, sh, 64);
-        if (lane >= sh) incl += o;
-      }
+      const int incl = wave_scan(sum);
       int excl = incl - sum;
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
