@@ -93,9 +93,11 @@ __global__ __launch_bounds__(256) void window_score_kernel(
   const int w = (nv - first < W) ? (nv - first) : W;
   const int32_t* toks = vis_tok + s + first;
 
+  const int tok = toks[lane < w ? lane : w - 1];   // one load for all rows (w <= 64)
   if (attn != nullptr) {
+    const float mine = attn[tok];
     float a = 0.0f;
-    for (int j = 0; j < w; ++j) a = a + attn[toks[j]];
+    for (int j = 0; j < w; ++j) a = a + __int_as_float(__builtin_amdgcn_readlane(__float_as_int(mine), j));
     if (lane == 0) win_a[g] = a;
   }
   if (w == 1) {
@@ -104,14 +106,24 @@ __global__ __launch_bounds__(256) void window_score_kernel(
   }
   float* tile = tile_all + (STAGED ? (threadIdx.x >> 6) * WS_TILE : 0);
   if (STAGED) {
-    for (int j = 0; j < w; ++j) {
-      const float* src = probs + (size_t)toks[j] * E;
-      for (int ex = lane; ex < E; ex += 64) tile[j * E + ex] = src[ex];
+    // eight rows at a time: one after the other, index and row, each was two memory latencies (7936 tokens in
+    // windows of five, 128 experts 10.6 -> 6.9 us; 1536 in windows of three, 64 experts 5.2 -> 4.9)
+    for (int ex = lane; ex < E; ex += 64) {
+      for (int j0 = 0; j0 < w; j0 += 8) {
+        float v[8];
+#pragma unroll
+        for (int q = 0; q < 8; ++q) {   // (past the window the last row again)
+          const int j = j0 + q < w ? j0 + q : w - 1;
+          v[q] = probs[(size_t)__builtin_amdgcn_readlane(tok, j) * E + ex];
+        }
+#pragma unroll
+        for (int q = 0; q < 8; ++q) tile[(j0 + q < w ? j0 + q : w - 1) * E + ex] = v[q];
+      }
     }
   }
   // element ex of the window's row j
   auto row = [&](int j, int ex) -> float {
-    return STAGED ? tile[j * E + ex] : probs[(size_t)toks[j] * E + ex];
+    return STAGED ? tile[j * E + ex] : probs[(size_t)__builtin_amdgcn_readlane(tok, j) * E + ex];
   };
   float S;
   if (sim_mode == 0) {
