@@ -11,8 +11,8 @@ namespace {
 template <typename T> struct Vec;
 template <> struct Vec<bf16_t> {
   static constexpr int N = 8;
-  static __device__ __forceinline__ void load(const bf16_t* p, float* f) {
-    const uint4 v = *reinterpret_cast<const uint4*>(p);
+  static __device__ __forceinline__ void load(const bf16_t* p, float* f) { widen(*reinterpret_cast<const uint4*>(p), f); }
+  static __device__ __forceinline__ void widen(uint4 v, float* f) {
     const uint32_t w[4] = {v.x, v.y, v.z, v.w};
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
@@ -34,6 +34,9 @@ template <> struct Vec<float> {
     const float4 v = *reinterpret_cast<const float4*>(p);
     f[0] = v.x; f[1] = v.y; f[2] = v.z; f[3] = v.w;
   }
+  static __device__ __forceinline__ void widen(uint4 v, float* f) {
+    f[0] = __uint_as_float(v.x); f[1] = __uint_as_float(v.y); f[2] = __uint_as_float(v.z); f[3] = __uint_as_float(v.w);
+  }
   static __device__ __forceinline__ void store(float* p, const float* f) {
     *reinterpret_cast<float4*>(p) = make_float4(f[0], f[1], f[2], f[3]);
   }
@@ -48,8 +51,16 @@ template <> struct Vec<float> {
 // slots would not allow): 1600 tokens of d 2048 in fp32, sixteen slots, 43.8 -> 38.1 us.  8 tokens, d 2048, eight
 // slots, through LDS and now: 4.4 -> 4.0 us; 22016 tokens, d 2048, six slots, two shared experts: 165 us both,
 // 5.5 TB/s, which is what a large copy reaches.
-template <typename T, int KM>
-__global__ __launch_bounds__(256, 8) void combine_kernel(
+// TOGETHER: all rows of a token on their way before the first is added.  Otherwise a wavefront waits for each row
+// before it asks for the next (the test for a row that counts stands between), and only the other wavefronts of the
+// CU keep the memory busy: with eight to a SIMD and tens of megabytes they do, and the registers then count for more.
+// The line is drawn at the size of one row set (tokens x d), separate / together, us, bf16, six slots, two shared
+// experts: 832 tokens of d 1280 (2 MB) 8.5 / 7.7, 2176 of d 2048 (9 MB) 23.2 / 20.0, 4096 (17 MB) 27.8 / 29.2, 22016
+// 173 / 175; eight slots, none shared: 3838 of d 2048 (16 MB) 31.8 / 32.2; six, 20000 of d 128 (5 MB) 21.5 / 14.4;
+// fp32, 832 of d 1280 (4 MB) 11.6 / 10.5; sixteen, 1600 of d 2048 (13 MB) 50.4 / 52.1.
+constexpr size_t COMBINE_TOGETHER_BYTES = 10u << 20;
+template <typename T, int KM, bool TOGETHER>
+__global__ __launch_bounds__(256, TOGETHER ? 4 : 8) void combine_kernel(
     const T* __restrict__ y, const T* __restrict__ y_shared, const int32_t* __restrict__ inv_perm,
     const float* __restrict__ topk_gate, const int32_t* __restrict__ kept_idx, int n_cap,
     const int32_t* __restrict__ n_dev, int row_cap, int d, int n_shared, const T* __restrict__ residual,
@@ -69,6 +80,38 @@ __global__ __launch_bounds__(256, 8) void combine_kernel(
     float acc[N], v[N];
 #pragma unroll
     for (int i = 0; i < N; ++i) acc[i] = 0.0f;
+    if constexpr (TOGETHER) {
+      uint4 vr = make_uint4(0u, 0u, 0u, 0u), vs[2] = {vr, vr}, vk[KM > 0 ? KM : 1];
+      if (residual) vr = *reinterpret_cast<const uint4*>(residual + (size_t)t * d + c);
+      if (y_shared) {
+#pragma unroll
+        for (int s = 0; s < 2; ++s)
+          vs[s] = *reinterpret_cast<const uint4*>(y_shared + ((size_t)(s < n_shared ? s : 0) * n_cap + p) * d + c);
+      }
+#pragma unroll
+      for (int s = 0; s < KM; ++s) {   // a row that does not count: the first one, not added
+        const int r = rows[s] < 0 || rows[s] >= row_cap ? 0 : rows[s];
+        vk[s] = *reinterpret_cast<const uint4*>(y + (size_t)r * d + c);
+      }
+      if (residual) Vec<T>::widen(vr, acc);
+      if (y_shared) {
+        for (int s = 0; s < n_shared; ++s) {
+          if (s < 2) Vec<T>::widen(vs[s & 1], v);
+          else Vec<T>::load(y_shared + ((size_t)s * n_cap + p) * d + c, v);
+#pragma unroll
+          for (int i = 0; i < N; ++i) acc[i] += v[i];
+        }
+      }
+#pragma unroll
+      for (int s = 0; s < KM; ++s) {
+        if (rows[s] < 0 || rows[s] >= row_cap) continue;   // uniform
+        Vec<T>::widen(vk[s], v);
+#pragma unroll
+        for (int i = 0; i < N; ++i) acc[i] = fmaf(gates[s], v[i], acc[i]);
+      }
+      Vec<T>::store(out + (size_t)p * d + c, acc);
+      continue;
+    }
     if (residual) {
       Vec<T>::load(residual + (size_t)t * d + c, v);
 #pragma unroll
@@ -101,9 +144,15 @@ void launch_combine_t(const fmoe_ctx* ctx, const void* y, const void* y_shared, 
     if (ctx->kmax > KM)
       return launch_combine_t<T, KM + 1>(ctx, y, y_shared, inv_perm, topk_gate, kept_idx, n_cap, n_dev, residual, out, stream);
   }
-  hipLaunchKernelGGL((combine_kernel<T, KM>), dim3(n_cap), dim3(256), 0, stream, static_cast<const T*>(y),
-                     static_cast<const T*>(y_shared), inv_perm, topk_gate, kept_idx, n_cap, n_dev, n_cap * KM,
-                     ctx->cfg.d_model, ctx->cfg.n_shared, static_cast<const T*>(residual), static_cast<T*>(out));
+#define FMOE_COMBINE_LAUNCH(TOGETHER)                                                                            \
+  hipLaunchKernelGGL((combine_kernel<T, KM, TOGETHER>), dim3(n_cap), dim3(256), 0, stream, static_cast<const T*>(y), \
+                     static_cast<const T*>(y_shared), inv_perm, topk_gate, kept_idx, n_cap, n_dev, n_cap * KM,       \
+                     ctx->cfg.d_model, ctx->cfg.n_shared, static_cast<const T*>(residual), static_cast<T*>(out))
+  // a count on the device is what pruning left of the capacity: half of it, say
+  const size_t bytes = (size_t)n_cap * ctx->cfg.d_model * sizeof(T) / (n_dev != nullptr ? 2 : 1);
+  if (bytes <= COMBINE_TOGETHER_BYTES) FMOE_COMBINE_LAUNCH(true);
+  else FMOE_COMBINE_LAUNCH(false);
+#undef FMOE_COMBINE_LAUNCH
 }
 
 }  // namespace

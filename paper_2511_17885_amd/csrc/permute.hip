@@ -16,12 +16,14 @@ namespace {
 constexpr int PB = FMOE_PERM_BLOCK;
 constexpr int PW = PB / 32;  // mask words per expert
 
-// ---- P1: per-block expert masks -> in-block ranks and per-block counts
+// ---- P1: per-block expert masks -> in-block ranks and per-block counts.  KM: at most so many slots.
+template <int KM>
 __global__ __launch_bounds__(PB) void permute_count_kernel(
     const int32_t* __restrict__ topk_idx, const int32_t* __restrict__ kept_idx, int n_cap,
     const int32_t* __restrict__ n_dev, int E, int Kmax, int32_t* __restrict__ slot_rank,
     int32_t* __restrict__ blk_count) {
-  __shared__ uint32_t mask[FMOE_MAX_EXPERTS * PW];
+  __shared__ __align__(16) uint32_t mask[FMOE_MAX_EXPERTS * PW];
+  static_assert(PW == 8, "a position's words are two 16-byte reads");
   const int n = resolve_count(n_cap, n_dev);
   const int blk = blockIdx.x;
   for (int i = threadIdx.x; i < E * PW; i += PB) mask[i] = 0u;
@@ -33,29 +35,31 @@ __global__ __launch_bounds__(PB) void permute_count_kernel(
   for (int s = 0; s < FMOE_MAX_TOPK; ++s) ex[s] = -1;
   if (p < n) {
     const int t = kept_idx ? kept_idx[p] : p;
+    // all slots' experts on their way at once (past Kmax the last one again): asked for where they are used, each
+    // was a memory latency of its own
+#pragma unroll
+    for (int s = 0; s < FMOE_MAX_TOPK; ++s)
+      if (s < KM) ex[s] = topk_idx[(size_t)t * Kmax + (s < Kmax ? s : Kmax - 1)];
 #pragma unroll
     for (int s = 0; s < FMOE_MAX_TOPK; ++s) {
-      if (s < Kmax) {
-        const int e = topk_idx[(size_t)t * Kmax + s];
-        if (e >= 0 && e < E) {
-          ex[s] = e;
-          atomicOr(&mask[e * PW + (lp >> 5)], 1u << (lp & 31));
-        }
-      }
+      if (s >= KM || s >= Kmax || ex[s] < 0 || ex[s] >= E) ex[s] = -1;
+      else atomicOr(&mask[ex[s] * PW + (lp >> 5)], 1u << (lp & 31));
     }
   }
   __syncthreads();
   if (p < n) {
 #pragma unroll
     for (int s = 0; s < FMOE_MAX_TOPK; ++s) {
-      if (s < Kmax) {
-        int rank = -1;
-        if (ex[s] >= 0) {
-          const uint32_t* m = &mask[ex[s] * PW];
-          rank = __popc(m[lp >> 5] & ((1u << (lp & 31)) - 1u));
-          for (int w = 0; w < (lp >> 5); ++w) rank += __popc(m[w]);
-        }
-        slot_rank[(size_t)p * Kmax + s] = rank;
+      if (s < KM && s < Kmax) {
+        // set bits below the position: the words before its own whole, its own up to it
+        const uint4* m = reinterpret_cast<const uint4*>(&mask[(ex[s] >= 0 ? ex[s] : 0) * PW]);
+        const uint4 a = m[0], b = m[1];
+        const uint32_t w[PW] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
+        int rank = 0;
+#pragma unroll
+        for (int i = 0; i < PW; ++i)
+          rank += __popc(w[i] & (i < (lp >> 5) ? ~0u : (i == (lp >> 5) ? (1u << (lp & 31)) - 1u : 0u)));
+        slot_rank[(size_t)p * Kmax + s] = ex[s] >= 0 ? rank : -1;
       }
     }
   }
@@ -275,8 +279,12 @@ int launch_permute(const fmoe_ctx* ctx, const int32_t* topk_idx, const int32_t* 
   const int nblk = (n_cap + PB - 1) / PB;
   if (nblk > 0 && Kmax > 0) {
     fmoe_prof_scope prof(ctx, SLOT_PERM_COUNT, stream);
-    hipLaunchKernelGGL(permute_count_kernel, dim3(nblk), dim3(PB), 0, stream, topk_idx, kept_idx,
-                       n_cap, n_dev, E, Kmax, slot_rank, blk_count);
+    if (Kmax <= 8)
+      hipLaunchKernelGGL(permute_count_kernel<8>, dim3(nblk), dim3(PB), 0, stream, topk_idx, kept_idx,
+                         n_cap, n_dev, E, Kmax, slot_rank, blk_count);
+    else
+      hipLaunchKernelGGL(permute_count_kernel<FMOE_MAX_TOPK>, dim3(nblk), dim3(PB), 0, stream, topk_idx, kept_idx,
+                         n_cap, n_dev, E, Kmax, slot_rank, blk_count);
   }
   if (nblk > 0 && Kmax > 0 && join_scan_scatter(nblk, E, Kmax)) {
     fmoe_prof_scope prof(ctx, SLOT_PERM_SCATTER, stream);

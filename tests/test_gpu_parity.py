@@ -1562,6 +1562,29 @@ def test_expert_ffn_thin_shape(n, d, F):
     assert got[0][0].float().abs().max() > 0 and torch.isfinite(got[0][0].float()).all()
 
 
+@pytest.mark.parametrize("k,n_shared", [(0, 2), (1, 1), (6, 3), (16, 0)])
+@pytest.mark.parametrize("dtype,n", [(W.F32, 1300), (W.BF16, 2600)])
+def test_combine_forms_agree_bit_for_bit(dtype, n, k, n_shared):
+    """Rows fetched together (small calls) and one after the other (here from 10 MB a row set on) are added in one
+    order: a few tokens on their own give the bits they have in the large call, unused slots included."""
+    td = torch.bfloat16 if dtype == W.BF16 else torch.float32
+    d, few = 2056, 33
+    g = torch.Generator(device="cuda")
+    g.manual_seed(100 * k + n)
+    m = binding.FMoE(d_model=d, n_experts=16, d_ffn=8, n_shared=n_shared, d_ffn_shared=8 if n_shared else 0, k_text=k,
+                     k_visual=k, dtype=dtype)
+    rnd = lambda *s: torch.randn(s, generator=g, device="cuda").to(td)
+    y, res = rnd(max(few * k, 1), d), rnd(n, d)
+    ysh = rnd(n_shared, n, d) if n_shared else None
+    inv = torch.randint(0, max(few * k, 1), (n, max(k, 1)), generator=g, device="cuda").int()
+    inv[torch.rand(inv.shape, generator=g, device="cuda") < 0.2] = -1
+    gate = torch.rand((n, max(k, 1)), generator=g, device="cuda")
+    large = m.combine(y, ysh, inv, gate, None, n, residual=res)
+    small = m.combine(y, ysh[:, :few].contiguous() if n_shared else None, inv[:few].contiguous(), gate[:few].contiguous(),
+                      None, few, residual=res)
+    assert torch.equal(large[:few], small)
+
+
 @pytest.mark.parametrize("dtype", [W.F32, W.BF16])
 @pytest.mark.parametrize("k", range(17))
 def test_combine_slot_counts(k, dtype):
