@@ -16,11 +16,22 @@
 #define FMOE_TILE_RUN 8       // row tiles per run of a group in the tile lists
 #define FMOE_DENSE_TILE_RUN 64   // the same for the dense shape
 #define FMOE_SEG_MIN_TILES 256   // tile entries from which each XCD takes a contiguous segment of the list
-// Routed-row capacity per expert from which the expert GEMMs take their dense shape.  Both GEMMs, stream / dense, us:
-//   capacity  98: d 2048, 64 experts of 1408, half kept 172 / 181, all kept 221 / 217; d 1280, experts of 896 74 / 80, 93 / 88
-//   capacity 125: d 2048, 128 experts of 768, half kept 134 / 135, all kept 175 / 163
-//   capacity 188: d 2048, 64 experts of 1408 240 / 240, 310 / 277; d 1280, experts of 896 101 / 103, 134 / 131
-#define FMOE_DENSE_MIN_ROWS 112
+// Routed-row capacity per expert from which the expert GEMMs take their dense shape, by how much there is to do with one
+// row tile an expert: work items (column groups of the narrower GEMM) and length of the shorter reduction.  The dense
+// shape's items are twice as long and half as many; where they leave the chip half idle the weight-stream shape wins
+// until experts have several row tiles.  Gate/up + down, stream / dense, us, half of the visual tokens kept, all kept:
+//   704 and 512 items (d 2048, 64 experts of 1408): capacity 98 172 / 181, 221 / 217; 121 213 / 216, 257 / 246; 188
+//     240 / 240, 310 / 277;  128 experts of 768: 125 134 / 135, 175 / 163
+//   448 and 320 (d 1280, 64 of 896): 117 80 / 86, 105 / 101; 150 89 / 91, 114 / 108; 197 105 / 104, 136 / 138
+//   512 and 512, but short (d 1024, 128 of 512): 166 56 / 63, 74 / 69; 230 71 / 67, 96 / 91
+//   256 (d 2048, 32 of 1024): 166 98 / 112, 122 / 118; 231 109 / 113, 137 / 127
+//   96 and 128 (d 4096, 8 of 1536): 167 78 / 99, 103 / 102; 232 103 / 100, 109 / 106
+#define FMOE_DENSE_MIN_ROWS 112        // from FMOE_DENSE_ITEMS items on
+#define FMOE_DENSE_MIN_ROWS_SOME 144   // from FMOE_DENSE_ITEMS_SOME on
+#define FMOE_DENSE_MIN_ROWS_FEW 256    // fewer, or shorter reductions than FMOE_DENSE_MIN_K
+#define FMOE_DENSE_ITEMS 512
+#define FMOE_DENSE_ITEMS_SOME 320
+#define FMOE_DENSE_MIN_K 768
 
 // ---- optional per-kernel timing (instrumentation; off by default)
 enum fmoe_kernel_slot {

@@ -778,11 +778,23 @@ __device__ __forceinline__ void dense_tile(const StreamProblem& P, const fmoe_ti
 // 8192 tokens, 128 experts of 768 160 + 97 -> 149 + 90; 22016 tokens, six experts 1526 + 883 -> 1493 + 864.  Strips of
 // one or two groups and runs of 8 or 16 row tiles: within 1 % of this, one group 1 % slower at 22016 tokens.
 constexpr int DENSE_STRIP = 3;
+// Up to so many items, a round and a half of two workgroups a CU, the launch takes as long as its fullest XCD: entries go
+// round the XCDs, long and short ones alike, and a run's items in strips of one column group, so that a weight
+// tile enters one or two L2s (layer of 1600 tokens, d 1280, 64 experts of 896, half kept: 118.1 -> 114.9 us).
+constexpr int DENSE_ONE_ROUND = 768;
 __device__ __forceinline__ int eighth(int n, int x) { return (n >> 3) * x + (((n & 7) * x) >> 3); }   // n*x/8
-// list entry of this workgroup, -1: none; its column group; whether the entry counts as a single tile
-__device__ __forceinline__ int dense_entry(const StreamArgs& a, int& group, bool& single) {
+// list entry of this workgroup, -1: none; its column group; whether the entry counts as a single tile; columns per strip
+__device__ __forceinline__ int dense_entry(const StreamArgs& a, int& group, bool& single, int& strip) {
   const int n = a.n_tiles[0], n_several = a.n_tiles[2];
   const int xcd = blockIdx.x & 7, b = blockIdx.x >> 3;
+  if (n * a.cols <= DENSE_ONE_ROUND) {
+    const int batch = b / a.cols, e = batch * 8 + xcd;
+    group = b - batch * a.cols;
+    single = e >= n_several;
+    strip = 1;
+    return e < n ? e : -1;
+  }
+  strip = DENSE_STRIP;
   const int i0 = n_several * a.cols, i1 = (n - n_several) * a.cols;   // items of the two kinds
   const int f0 = eighth(i0, xcd), nf = eighth(i0, xcd + 1) - f0;
   const int s0 = eighth(i1, xcd), ns = eighth(i1, xcd + 1) - s0;
@@ -804,9 +816,9 @@ __device__ __forceinline__ int dense_entry(const StreamArgs& a, int& group, bool
 template <bool SWIGLU>
 __global__ __launch_bounds__(256, 2) void ffn_dense_kernel(StreamArgs a) {
   __shared__ __align__(16) bf16_t As[DA_STAGES * SBM * SBK];
-  int nt_launch;
+  int nt_launch, strip_cols;
   bool single;
-  int ti = dense_entry(a, nt_launch, single);
+  int ti = dense_entry(a, nt_launch, single, strip_cols);
   if (ti < 0) return;
   fmoe_tile tile = load_entry(a.tiles, ti);
   const bool shared = tile.group >= a.E;
@@ -823,11 +835,11 @@ __global__ __launch_bounds__(256, 2) void ffn_dense_kernel(StreamArgs a) {
   int row_tile = tile.rt;
   if (tile.nrt > 1) {   // the items of a run in strips
     const int w = tile.rt * c_eff + nt_launch;
-    const int strip = w / (DENSE_STRIP * tile.nrt), in_strip = w - strip * (DENSE_STRIP * tile.nrt);
-    const int left = c_eff - strip * DENSE_STRIP;
-    const int width = left < DENSE_STRIP ? left : DENSE_STRIP;
+    const int strip = w / (strip_cols * tile.nrt), in_strip = w - strip * (strip_cols * tile.nrt);
+    const int left = c_eff - strip * strip_cols;
+    const int width = left < strip_cols ? left : strip_cols;
     row_tile = in_strip / width;
-    nt_launch = strip * DENSE_STRIP + (in_strip - row_tile * width);
+    nt_launch = strip * strip_cols + (in_strip - row_tile * width);
   }
   take_row_tile(tile, row_tile, SBM);
   const int nt4 = tile.col0 + nt_launch * DNCB;
@@ -1313,10 +1325,15 @@ fmoe_ffn_geom fmoe_geom(const fmoe_ctx* ctx, int n_cap) {
   const fmoe_config& c = ctx->cfg;
   fmoe_ffn_geom g;
   g.bm = (c.dtype == FMOE_BF16) ? SBM : FBM;
-  // Shape of the bf16 kernel: the dense one when the rows this call can route average FMOE_DENSE_MIN_ROWS per
-  // expert or more, else the weight-stream one; fmoe_set_ffn_shape overrides the rule.  The dense shape addresses
-  // the packed weights with 32-bit byte offsets.
-  g.dense = c.dtype == FMOE_BF16 && (long long)n_cap * ctx->kmax >= (long long)FMOE_DENSE_MIN_ROWS * c.n_experts;
+  // Shape of the bf16 kernel: the dense one when the rows this call can route average so many per expert or more,
+  // else the weight-stream one; fmoe_set_ffn_shape overrides the rule.  The dense shape addresses the packed
+  // weights with 32-bit byte offsets.
+  const int groups1 = (c.d_ffn + 127) / 128, groups2 = (c.d_model + 255) / 256;
+  const long long work = (long long)c.n_experts * (groups1 < groups2 ? groups1 : groups2);
+  long long min_rows = FMOE_DENSE_MIN_ROWS_FEW;
+  if (c.d_model >= FMOE_DENSE_MIN_K && c.d_ffn >= FMOE_DENSE_MIN_K && work >= FMOE_DENSE_ITEMS_SOME)
+    min_rows = work >= FMOE_DENSE_ITEMS ? FMOE_DENSE_MIN_ROWS : FMOE_DENSE_MIN_ROWS_SOME;
+  g.dense = c.dtype == FMOE_BF16 && (long long)n_cap * ctx->kmax >= min_rows * c.n_experts;
   if (ctx->ffn_shape == 1) g.dense = false;
   if (ctx->ffn_shape == 2) g.dense = c.dtype == FMOE_BF16;
   for (int w = 0; w < 4; ++w)
@@ -1486,14 +1503,14 @@ int run_ffn_bf16(const fmoe_ctx* ctx, const void* x, const int32_t* kept_idx, in
   const unsigned thin_entries = (unsigned)(all > 0 ? all : 0);
   {
     fmoe_prof_scope prof(ctx, dense ? SLOT_GEMM1_DENSE : SLOT_GEMM1, stream);
-    const unsigned items = dense ? ((unsigned)geo.tile_cap * g1.cols / 8 + 2) * 8 : batches * 8 * g1.cols;
+    const unsigned items = dense ? (((unsigned)geo.tile_cap + 7) / 8 * g1.cols + 2) * 8 : batches * 8 * g1.cols;
     if (thin) hipLaunchKernelGGL(ffn_thin_kernel<true>, dim3(thin_entries * g1.cols), dim3(64), 0, stream, g1);
     else if (dense) hipLaunchKernelGGL((ffn_dense_kernel<true>), dim3(items), dim3(256), 0, stream, g1);
     else hipLaunchKernelGGL((ffn_stream_kernel<true>), dim3(items), dim3(256), 0, stream, g1);
   }
   {
     fmoe_prof_scope prof(ctx, dense ? SLOT_GEMM2_DENSE : SLOT_GEMM2, stream);
-    const unsigned items = dense ? ((unsigned)geo.tile_cap * g2.cols / 8 + 2) * 8 : batches * 8 * g2.cols;
+    const unsigned items = dense ? (((unsigned)geo.tile_cap + 7) / 8 * g2.cols + 2) * 8 : batches * 8 * g2.cols;
     if (thin) hipLaunchKernelGGL(ffn_thin_kernel<false>, dim3(thin_entries * g2.cols), dim3(64), 0, stream, g2);
     else if (dense) hipLaunchKernelGGL((ffn_dense_kernel<false>), dim3(items), dim3(256), 0, stream, g2);
     else hipLaunchKernelGGL((ffn_stream_kernel<false>), dim3(items), dim3(256), 0, stream, g2);
