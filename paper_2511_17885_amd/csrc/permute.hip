@@ -23,7 +23,7 @@ __global__ __launch_bounds__(PB) void permute_count_kernel(
     const int32_t* __restrict__ n_dev, int E, int Kmax, int32_t* __restrict__ slot_rank,
     int32_t* __restrict__ blk_count) {
   __shared__ __align__(16) uint32_t mask[FMOE_MAX_EXPERTS * PW];
-  static_assert(PW == 8, "a position's words are two 16-byte reads");
+  static_assert(PB == 256 && PW == 8, "a wavefront's 64 positions end with a pair of words");
   const int n = resolve_count(n_cap, n_dev);
   const int blk = blockIdx.x;
   for (int i = threadIdx.x; i < E * PW; i += PB) mask[i] = 0u;
@@ -47,20 +47,33 @@ __global__ __launch_bounds__(PB) void permute_count_kernel(
     }
   }
   __syncthreads();
-  if (p < n) {
+  // set bits below the position: the words before its own whole, its own up to it; PAIRS = pairs of words up to the
+  // wavefront's own (a few positions with sixteen slots: all four pairs cost 2 us more than the one)
+  auto ranks = [&](auto pairs) {
+    constexpr int PAIRS = decltype(pairs)::value;
 #pragma unroll
     for (int s = 0; s < FMOE_MAX_TOPK; ++s) {
       if (s < KM && s < Kmax) {
-        // set bits below the position: the words before its own whole, its own up to it
-        const uint4* m = reinterpret_cast<const uint4*>(&mask[(ex[s] >= 0 ? ex[s] : 0) * PW]);
-        const uint4 a = m[0], b = m[1];
-        const uint32_t w[PW] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
+        const uint2* m = reinterpret_cast<const uint2*>(&mask[(ex[s] >= 0 ? ex[s] : 0) * PW]);
         int rank = 0;
 #pragma unroll
-        for (int i = 0; i < PW; ++i)
-          rank += __popc(w[i] & (i < (lp >> 5) ? ~0u : (i == (lp >> 5) ? (1u << (lp & 31)) - 1u : 0u)));
+        for (int i = 0; i < PAIRS - 1; ++i) {
+          const uint2 w = m[i];
+          rank += __popc(w.x) + __popc(w.y);
+        }
+        const uint2 w = m[PAIRS - 1];
+        const uint32_t below = (1u << (lp & 31)) - 1u;
+        rank += (lp & 32) ? __popc(w.x) + __popc(w.y & below) : __popc(w.x & below);
         slot_rank[(size_t)p * Kmax + s] = ex[s] >= 0 ? rank : -1;
       }
+    }
+  };
+  if (p < n) {
+    switch (__builtin_amdgcn_readfirstlane(lp >> 6)) {
+      case 0: ranks(std::integral_constant<int, 1>{}); break;
+      case 1: ranks(std::integral_constant<int, 2>{}); break;
+      case 2: ranks(std::integral_constant<int, 3>{}); break;
+      default: ranks(std::integral_constant<int, 4>{}); break;
     }
   }
   for (int e = threadIdx.x; e < E; e += PB) {
@@ -98,7 +111,8 @@ __device__ __forceinline__ void scan_totals(const int* total, int E, int32_t* of
 // those before it; E counts per block, from L2), scans the totals and scatters its own positions.  One more block
 // writes the offsets and builds the GEMM work lists, so that neither waits for the other.  A launch less and no
 // walk by a single block: inside a layer, scan + scatter -> this, 22016 tokens / 64 experts 20.7 + 5.8 -> 19.9 us;
-// 4224 of 8192 tokens / 128 experts 9.7 + 5.5 -> 10.2; 2176 of 4096 / 64 6.9 + 4.8 -> 7.5.
+// 4224 of 8192 tokens / 128 experts 9.7 + 5.5 -> 10.2; 2176 of 4096 / 64 6.9 + 4.8 -> 7.5; with the work lists shared
+// out over the whole block (tiles.h) 11.7, 9.0 and 6.7.  (Every row's loads before the first store: 12.2 -> 12.9.)
 __global__ __launch_bounds__(PB) void permute_scan_scatter_kernel(
     const int32_t* __restrict__ topk_idx, const int32_t* __restrict__ kept_idx, int n_cap,
     const int32_t* __restrict__ n_dev, int E, int Kmax, const int32_t* __restrict__ slot_rank,
