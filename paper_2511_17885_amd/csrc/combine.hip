@@ -57,7 +57,8 @@ template <> struct Vec<float> {
 // The line is drawn at the size of one row set (tokens x d), separate / together, us, bf16, six slots, two shared
 // experts: 832 tokens of d 1280 (2 MB) 8.5 / 7.7, 2176 of d 2048 (9 MB) 23.2 / 20.0, 4096 (17 MB) 27.8 / 29.2, 22016
 // 173 / 175; eight slots, none shared: 3838 of d 2048 (16 MB) 31.8 / 32.2; six, 20000 of d 128 (5 MB) 21.5 / 14.4;
-// fp32, 832 of d 1280 (4 MB) 11.6 / 10.5; sixteen, 1600 of d 2048 (13 MB) 50.4 / 52.1.
+// fp32, 832 of d 1280 (4 MB) 11.6 / 10.5; sixteen, 1600 of d 2048 (13 MB) 50.4 / 52.1.  One or two fp32 rows a token
+// are nothing to gather: 8192 of d 128 (4 MB) 5.1 / 5.5, one token 2.8 / 3.0.
 constexpr size_t COMBINE_TOGETHER_BYTES = 10u << 20;
 template <typename T, int KM, bool TOGETHER>
 __global__ __launch_bounds__(256, TOGETHER ? 4 : 8) void combine_kernel(
@@ -89,9 +90,9 @@ __global__ __launch_bounds__(256, TOGETHER ? 4 : 8) void combine_kernel(
           vs[s] = *reinterpret_cast<const uint4*>(y_shared + ((size_t)(s < n_shared ? s : 0) * n_cap + p) * d + c);
       }
 #pragma unroll
-      for (int s = 0; s < KM; ++s) {   // a row that does not count: the first one, not added
-        const int r = rows[s] < 0 || rows[s] >= row_cap ? 0 : rows[s];
-        vk[s] = *reinterpret_cast<const uint4*>(y + (size_t)r * d + c);
+      for (int s = 0; s < KM; ++s) {   // a row that does not count: what stands in the output, not added
+        const T* const src = rows[s] < 0 || rows[s] >= row_cap ? out + (size_t)p * d : y + (size_t)rows[s] * d;
+        vk[s] = *reinterpret_cast<const uint4*>(src + c);
       }
       if (residual) Vec<T>::widen(vr, acc);
       if (y_shared) {
@@ -150,7 +151,8 @@ void launch_combine_t(const fmoe_ctx* ctx, const void* y, const void* y_shared, 
                      ctx->cfg.d_model, ctx->cfg.n_shared, static_cast<const T*>(residual), static_cast<T*>(out))
   // a count on the device is what pruning left of the capacity: half of it, say
   const size_t bytes = (size_t)n_cap * ctx->cfg.d_model * sizeof(T) / (n_dev != nullptr ? 2 : 1);
-  if (bytes <= COMBINE_TOGETHER_BYTES) FMOE_COMBINE_LAUNCH(true);
+  const bool few = sizeof(T) == 4 && KM <= 2 && y_shared == nullptr;
+  if (bytes <= COMBINE_TOGETHER_BYTES && !few) FMOE_COMBINE_LAUNCH(true);
   else FMOE_COMBINE_LAUNCH(false);
 #undef FMOE_COMBINE_LAUNCH
 }
