@@ -93,7 +93,8 @@ __global__ __launch_bounds__(256) void window_score_kernel(
   const int w = (nv - first < W) ? (nv - first) : W;
   const int32_t* toks = vis_tok + s + first;
 
-  const int tok = toks[lane < w ? lane : w - 1];   // one load for all rows (w <= 64)
+  int tok = toks[lane < w ? lane : w - 1];   // one load for all rows (w <= 64)
+  asm volatile("" : "+v"(tok));   // by all lanes, here: read across lanes below, where those without an expert are off
   if (attn != nullptr) {
     const float mine = attn[tok];
     float a = 0.0f;
@@ -1110,7 +1111,8 @@ int launch_prune_dispatch_small(const fmoe_ctx* ctx, const fmoe_prune_params* pp
       hipLaunchKernelGGL((prune_dispatch_small_kernel<TP, KM, true>), dim3(1), dim3(SB_THREADS), 0, stream, a);  \
   } while (0)
     // the register arrays as small as the call allows: with those for sixteen experts per token a batch of 3000
-    // tokens and six took 34.6 us (pruning) and 25.8 us (not), with those for eight 29.2 and 20.8
+    // tokens and six took 34.6 us (pruning, the drop order then still sorted) and 25.8 us (not), with those for eight
+    // 29.2 and 20.8
     if (ctx->kmax > 8) FMOE_DISPATCH_LAUNCH(SB_MAX_TP, FMOE_MAX_TOPK);
     else if (T > 2 * SB_THREADS) FMOE_DISPATCH_LAUNCH(SB_MAX_TP, 8);
     else FMOE_DISPATCH_LAUNCH(2, 8);

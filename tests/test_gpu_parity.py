@@ -231,6 +231,32 @@ def test_prune_windows_around_the_size_of_the_staging_tile(E, window, sim_mode):
     assert np.array_equal(np.concatenate(got), o_scores)
 
 
+@pytest.mark.parametrize("E,window", [(8, 8), (8, 9), (8, 64), (70, 17), (32, 64)])
+def test_prune_windows_of_more_rows_than_fetched_together(E, window):
+    """The scoring kernel takes a staged window's rows eight at a time, their token ids from the lanes of one load, also
+    from lanes that hold no expert (window > E): a full group, a remainder, the widest window, ragged last windows;
+    without an attention term; scores, kept set and bounds bit for bit."""
+    wl = W.small_random(160 + window, T_v=[3 * window + 2, 1, 5 * window, window - 1], T_t=[3, 2, 0, 5], d=32, E=E,
+                        F=16, k_text=4, k_visual=2, retention=0.6, window=window, n_components=7, bias_std=1.0,
+                        interleave=True)
+    o_probs, _, _ = oracle.route(wl.x, wl.is_visual, wl.weights.router_w, wl.weights.router_bias, 4, 2)
+    o_kept, o_cu, o_scores = oracle.prune(o_probs, wl.is_visual, wl.cu_seqlens, wl.retention, window)
+    m = make_layer(wl)
+    pp = binding.prune_params(retention=wl.retention, window=window)
+    kept, new_cu, scores = m.prune(pp, dev(o_probs), dev(wl.is_visual), dev(wl.cu_seqlens), want_scores=True)
+    torch.cuda.synchronize()
+    new_cu = host(new_cu)
+    assert np.array_equal(new_cu, o_cu)
+    assert np.array_equal(host(kept)[:new_cu[-1]], o_kept)
+    scores = host(scores)
+    got = []
+    for b in range(wl.B):
+        s, e = wl.cu_seqlens[b], wl.cu_seqlens[b + 1]
+        nv = int(wl.is_visual[s:e].sum())
+        got.append(scores[s:s + (nv + window - 1) // window])
+    assert np.array_equal(np.concatenate(got), o_scores)
+
+
 @pytest.mark.parametrize("T_v,T_t", [([1023], [0]), ([1000], [24]), ([1024], [1]), ([700, 0, 2500, 1, 1900], [30, 5, 0, 0, 9])])
 @pytest.mark.parametrize("gamma", [0.0, 0.2])
 def test_prune_over_several_compaction_blocks(T_v, T_t, gamma):
@@ -786,6 +812,11 @@ def test_one_block_prune_keeps_what_the_general_chain_keeps(T_v, T_t, win, reten
     ([60, 40], 72, 1032, 2),                                      # the shared group a single tile too
     ([129, 300, 1000, 2049], 1288, 200, 2),                       # several row tiles each, strips of 3 + 3
     ([8193, 70, 130, 5], 264, 72, 0),                             # a group of 65 row tiles: two runs
+    # the same with more items than are dealt entry by entry (768)
+    ([129, 1, 0, 128, 127, 16, 17, 256, 257, 40], 136, 10248, 0),
+    ([1, 128, 0, 31, 32, 33, 96, 97], 136, 10248, 1),
+    ([129, 300, 1000, 2049], 8200, 200, 2),
+    ([8193, 70, 130, 5], 264, 2056, 0),
 ])
 def test_dense_shape_covers_every_work_item(rows, d, F, n_shared):
     """The dense shape cuts its work lists into eight shares of either kind (single row tiles, several row tiles),
