@@ -90,11 +90,12 @@ __global__ __launch_bounds__(256) void window_score_kernel(
   if (i < 0 || (long long)i * W >= nv) return;  // not a window of this sequence
   const int g = s + i;                          // < s + nv <= T
   const int first = i * W;
-  const int w = (nv - first < W) ? (nv - first) : W;
+  const int w = __builtin_amdgcn_readfirstlane((nv - first < W) ? (nv - first) : W);
   const int32_t* toks = vis_tok + s + first;
 
-  int tok = toks[lane < w ? lane : w - 1];   // one load for all rows (w <= 64)
-  asm volatile("" : "+v"(tok));   // by all lanes, here: read across lanes below, where those without an expert are off
+  // One load for all rows (w <= 64).  The token ids are read across the lanes, so that from here on every loop and
+  // branch is uniform: all lanes stay on, those without an expert take the last one's column and add nothing.
+  const int tok = toks[lane < w ? lane : w - 1];
   if (attn != nullptr) {
     const float mine = attn[tok];
     float a = 0.0f;
@@ -109,7 +110,8 @@ __global__ __launch_bounds__(256) void window_score_kernel(
   if (STAGED) {
     // eight rows at a time: one after the other, index and row, each was two memory latencies (7936 tokens in
     // windows of five, 128 experts 10.6 -> 6.9 us; 1536 in windows of three, 64 experts 5.2 -> 4.9)
-    for (int ex = lane; ex < E; ex += 64) {
+    for (int e0 = 0; e0 < E; e0 += 64) {
+      const int ex = e0 + lane < E ? e0 + lane : E - 1;
       for (int j0 = 0; j0 < w; j0 += 8) {
         float v[8];
 #pragma unroll
@@ -122,9 +124,11 @@ __global__ __launch_bounds__(256) void window_score_kernel(
       }
     }
   }
-  // element ex of the window's row j
+  // element ex of the window's row j, 0 past the experts
   auto row = [&](int j, int ex) -> float {
-    return STAGED ? tile[j * E + ex] : probs[(size_t)__builtin_amdgcn_readlane(tok, j) * E + ex];
+    const int e = ex < E ? ex : E - 1;
+    const float v = STAGED ? tile[j * E + e] : probs[(size_t)__builtin_amdgcn_readlane(tok, j) * E + e];
+    return ex < E ? v : 0.0f;
   };
   float S;
   if (sim_mode == 0) {
@@ -134,7 +138,7 @@ __global__ __launch_bounds__(256) void window_score_kernel(
     for (int r = 0; r < 4; ++r) {
       const int ex = lane + 64 * r;
       float acc = 0.0f;
-      if (ex < E) {
+      if (64 * r < E) {
         acc = row(0, ex);
         for (int j = 1; j < w; ++j) acc = acc + row(j, ex);
         acc = acc / (float)w;
@@ -144,7 +148,7 @@ __global__ __launch_bounds__(256) void window_score_kernel(
     float pm = 0.0f;
 #pragma unroll
     for (int r = 0; r < 4; ++r)
-      if (lane + 64 * r < E) pm = fmaf(mean[r], mean[r], pm);
+      if (64 * r < E) pm = fmaf(mean[r], mean[r], pm);
     const float norm_mean = sqrtf(wave_sum_butterfly(pm));
     float acc = 0.0f;
     for (int j = 0; j < w; ++j) {
@@ -152,7 +156,7 @@ __global__ __launch_bounds__(256) void window_score_kernel(
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
         const int ex = lane + 64 * r;
-        if (ex < E) {
+        if (64 * r < E) {
           const float v = row(j, ex);
           pd = fmaf(v, mean[r], pd);
           pn = fmaf(v, v, pn);
@@ -173,8 +177,8 @@ __global__ __launch_bounds__(256) void window_score_kernel(
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
         const int ex = lane + 64 * r;
-        rj[r] = (ex < E) ? row(j, ex) : 0.0f;
-        if (ex < E) pn = fmaf(rj[r], rj[r], pn);
+        rj[r] = 64 * r < E ? row(j, ex) : 0.0f;
+        if (64 * r < E) pn = fmaf(rj[r], rj[r], pn);
       }
       const float nj = sqrtf(wave_sum_butterfly(pn));
       for (int q = 0; q < j; ++q) {
@@ -182,7 +186,7 @@ __global__ __launch_bounds__(256) void window_score_kernel(
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
           const int ex = lane + 64 * r;
-          if (ex < E) {
+          if (64 * r < E) {
             const float v = row(q, ex);
             pd = fmaf(rj[r], v, pd);
             pq = fmaf(v, v, pq);

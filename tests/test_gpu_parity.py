@@ -257,6 +257,35 @@ def test_prune_windows_of_more_rows_than_fetched_together(E, window):
     assert np.array_equal(np.concatenate(got), o_scores)
 
 
+@pytest.mark.parametrize("sim_mode", [0, 1])
+@pytest.mark.parametrize("E,window", [(48, 60), (70, 40), (65, 33), (34, 64), (200, 13)])
+def test_prune_wide_windows_with_lanes_past_the_experts(E, window, sim_mode):
+    """Windows too large for the LDS tile (window * E > 2048) of more tokens than the last round of 64 experts has
+    lanes for: the token ids of such rows come from lanes without an expert.  Both scores, with attention."""
+    wl = W.small_random(190 + window, T_v=[2 * window + 3, 1, 3 * window, window - 1], T_t=[3, 2, 0, 5], d=32, E=E,
+                        F=16, k_text=4, k_visual=2, retention=0.6, window=window, n_components=7, bias_std=1.0,
+                        interleave=True)
+    attn = np.random.Generator(np.random.PCG64(window)).random(wl.T).astype(np.float32)
+    o_probs, _, _ = oracle.route(wl.x, wl.is_visual, wl.weights.router_w, wl.weights.router_bias, 4, 2)
+    o_kept, o_cu, o_scores = oracle.prune(o_probs, wl.is_visual, wl.cu_seqlens, wl.retention, window, alpha=0.7,
+                                          attn=attn, sim_mode=sim_mode)
+    m = make_layer(wl)
+    pp = binding.prune_params(retention=wl.retention, window=window, alpha=0.7, sim_mode=sim_mode)
+    kept, new_cu, scores = m.prune(pp, dev(o_probs), dev(wl.is_visual), dev(wl.cu_seqlens), attn=dev(attn),
+                                   want_scores=True)
+    torch.cuda.synchronize()
+    new_cu = host(new_cu)
+    assert np.array_equal(new_cu, o_cu)
+    assert np.array_equal(host(kept)[:new_cu[-1]], o_kept)
+    scores = host(scores)
+    got = []
+    for b in range(wl.B):
+        s, e = wl.cu_seqlens[b], wl.cu_seqlens[b + 1]
+        nv = int(wl.is_visual[s:e].sum())
+        got.append(scores[s:s + (nv + window - 1) // window])
+    assert np.array_equal(np.concatenate(got), o_scores)
+
+
 @pytest.mark.parametrize("T_v,T_t", [([1023], [0]), ([1000], [24]), ([1024], [1]), ([700, 0, 2500, 1, 1900], [30, 5, 0, 0, 9])])
 @pytest.mark.parametrize("gamma", [0.0, 0.2])
 def test_prune_over_several_compaction_blocks(T_v, T_t, gamma):
