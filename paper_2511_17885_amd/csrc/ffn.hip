@@ -735,8 +735,10 @@ __device__ __forceinline__ void dense_tile(const StreamProblem& P, const fmoe_ti
     order_loads();
   });
   // The steps count on a tile's activations being older than its weights.  Here they are younger: the first tile
-  // is waited for here, the second one by the third step (which waits for all but NEWER_EVEN loads, and no more
-  // than A_AHEAD-1 tiles and the loads of two steps are younger than the second tile).
+  // is waited for here, the others by their first steps, which wait for all but NEWER_EVEN loads: at least so many
+  // are younger than the tile.  Fewest are younger than the second one: the prologue's later tiles, a tile of
+  // activations and the weights of two steps.
+  static_assert(A_AHEAD >= 2 && NEWER_EVEN <= (A_AHEAD - 2) * NAB + NAB + 2 * 2 * DNCB, "the second tile is waited for");
   FMOE_WAIT_VM((A_AHEAD - 1) * NAB);
   int ks0 = 0;
   for (; ks0 + UNROLL <= NKS; ks0 += UNROLL)
