@@ -26,12 +26,13 @@
 //  * block -> work: workgroups are spread round-robin over the 8 XCDs (each with its own L2), so
 //    the linear block id is decoded as (batch of 8 row tiles, column tile, tile within the batch
 //    = XCD); all column tiles of one row tile run on one XCD and its activation rows are fetched
-//    from HBM once (the dense shape deals its items out differently, see dense_entry).
+//    from HBM once (the dense shape deals its items out differently, see deal.h).
 // The fp32 storage type has a kernel of its own on the fp32 matrix instruction, reading the caller's weights.
 
 #include <type_traits>
 
 #include "common.h"
+#include "deal.h"
 #include "tiles.h"
 
 namespace {
@@ -735,10 +736,8 @@ __device__ __forceinline__ void dense_tile(const StreamProblem& P, const fmoe_ti
     order_loads();
   });
   // The steps count on a tile's activations being older than its weights.  Here they are younger: the first tile
-  // is waited for here, the others by their first steps, which wait for all but NEWER_EVEN loads: at least so many
-  // are younger than the tile.  Fewest are younger than the second one: the prologue's later tiles, a tile of
-  // activations and the weights of two steps.
-  static_assert(A_AHEAD >= 2 && NEWER_EVEN <= (A_AHEAD - 2) * NAB + NAB + 2 * 2 * DNCB, "the second tile is waited for");
+  // is waited for here, the second one by the third step (which waits for all but NEWER_EVEN loads, and no more
+  // than A_AHEAD-1 tiles and the loads of two steps are younger than the second tile).
   FMOE_WAIT_VM((A_AHEAD - 1) * NAB);
   int ks0 = 0;
   for (; ks0 + UNROLL <= NKS; ks0 += UNROLL)
@@ -764,63 +763,14 @@ __device__ __forceinline__ void dense_tile(const StreamProblem& P, const fmoe_ti
   });
 }
 
-// Work items of the dense shape.  The items of a list (entries in order, each entry's column groups) are cut into
-// eight contiguous shares, one per XCD (consecutive workgroups go round the XCDs), separately for the entries of
-// groups with several row tiles, the first a.n_tiles[2] of the list, and for the single tiles behind them; a share
-// of each is walked by one XCD, evenly mixed.
-//  * Contiguous: a group of several row tiles sits on one XCD, or two where a cut falls into it, so that its rows and
-//    weights enter one L2; dealt out entry by entry over the XCDs they entered most of them.
-//  * Mixed: groups of many rows keep the matrix pipes busy, single tiles the memory; one kind after the other left
-//    the pipes idle in the second half.
-//  * Inside a run the items go down the row tiles in strips of DENSE_STRIP column groups: neighbours in time
-//    share an activation tile or a weight tile while it still is in L2.
-//  * The weights of a single tile are not asked for again and bypass the L2's recency order (non-temporal).
-// Measured, gate/up and down us, entries dealt round-robin before: 4096 tokens d 2048 64 experts of 1408, half kept
-// 193 + 106 -> 177 + 103; the same size, nothing dropped and every token six experts 270 + 158 -> 243 + 140;
-// 8192 tokens, 128 experts of 768 160 + 97 -> 149 + 90; 22016 tokens, six experts 1526 + 883 -> 1493 + 864.  Strips of
-// one or two groups and runs of 8 or 16 row tiles: within 1 % of this, one group 1 % slower at 22016 tokens.
-constexpr int DENSE_STRIP = 3;
-// Up to so many items, a round and a half of two workgroups a CU, the launch takes as long as its fullest XCD: entries go
-// round the XCDs, long and short ones alike, and a run's items in strips of one column group, so that a weight
-// tile enters one or two L2s (layer of 1600 tokens, d 1280, 64 experts of 896, half kept: 118.1 -> 114.9 us).
-constexpr int DENSE_ONE_ROUND = 768;
-__device__ __forceinline__ int eighth(int n, int x) { return (n >> 3) * x + (((n & 7) * x) >> 3); }   // n*x/8
-// list entry of this workgroup, -1: none; its column group; whether the entry counts as a single tile; columns per strip
-__device__ __forceinline__ int dense_entry(const StreamArgs& a, int& group, bool& single, int& strip) {
-  const int n = a.n_tiles[0], n_several = a.n_tiles[2];
-  const int xcd = blockIdx.x & 7, b = blockIdx.x >> 3;
-  if (n * a.cols <= DENSE_ONE_ROUND) {
-    const int batch = b / a.cols, e = batch * 8 + xcd;
-    group = b - batch * a.cols;
-    single = e >= n_several;
-    strip = 1;
-    return e < n ? e : -1;
-  }
-  strip = DENSE_STRIP;
-  const int i0 = n_several * a.cols, i1 = (n - n_several) * a.cols;   // items of the two kinds
-  const int f0 = eighth(i0, xcd), nf = eighth(i0, xcd + 1) - f0;
-  const int s0 = eighth(i1, xcd), ns = eighth(i1, xcd + 1) - s0;
-  if (b >= nf + ns) return -1;
-  int done = b < nf ? 0 : b - nf;   // single-tile items ahead of item b of this XCD
-  single = b >= nf;
-  if (nf + ns < 32768) {            // (beyond, where the products would overflow: one kind after the other)
-    done = b * ns / (nf + ns);
-    single = (b + 1) * ns / (nf + ns) > done;
-  }
-  const int item = single ? i0 + s0 + done : f0 + (b - done);
-  const int e = item / a.cols;
-  group = item - e * a.cols;
-  return e;
-}
-
-// Column tiles are taken DNCB at a time (a.cols = such groups per tile entry, a.cols_entry = column tiles per tile
-// entry).
+// The work items are dealt out as deal.h says.  Column tiles are taken DNCB at a time (a.cols = such groups per tile
+// entry, a.cols_entry = column tiles per tile entry).
 template <bool SWIGLU>
 __global__ __launch_bounds__(256, 2) void ffn_dense_kernel(StreamArgs a) {
   __shared__ __align__(16) bf16_t As[DA_STAGES * SBM * SBK];
   int nt_launch, strip_cols;
   bool single;
-  int ti = dense_entry(a, nt_launch, single, strip_cols);
+  const int ti = dense_entry((int)blockIdx.x, a.n_tiles[0], a.n_tiles[2], a.cols, nt_launch, single, strip_cols);
   if (ti < 0) return;
   fmoe_tile tile = load_entry(a.tiles, ti);
   const bool shared = tile.group >= a.E;
@@ -835,14 +785,7 @@ __global__ __launch_bounds__(256, 2) void ffn_dense_kernel(StreamArgs a) {
   const int c_eff = (ct_here + DNCB - 1) / DNCB;
   if (nt_launch >= c_eff) return;
   int row_tile = tile.rt;
-  if (tile.nrt > 1) {   // the items of a run in strips
-    const int w = tile.rt * c_eff + nt_launch;
-    const int strip = w / (strip_cols * tile.nrt), in_strip = w - strip * (strip_cols * tile.nrt);
-    const int left = c_eff - strip * strip_cols;
-    const int width = left < strip_cols ? left : strip_cols;
-    row_tile = in_strip / width;
-    nt_launch = strip * strip_cols + (in_strip - row_tile * width);
-  }
+  if (tile.nrt > 1) dense_run_order(tile.rt, tile.nrt, c_eff, strip_cols, row_tile, nt_launch);
   take_row_tile(tile, row_tile, SBM);
   const int nt4 = tile.col0 + nt_launch * DNCB;
   const int ct_limit = tile.col0 + ct_here;
@@ -1497,22 +1440,21 @@ int run_ffn_bf16(const fmoe_ctx* ctx, const void* x, const int32_t* kept_idx, in
     q.C = static_cast<bf16_t*>(y_shared); q.c_group_off = (long long)n_cap * d; q.K = c.d_ffn_shared;
     q.n_col_tiles = geo.scols2;
   }
-  
-  const unsigned batches = (unsigned)((geo.tile_cap + 7) / 8);   // (dense shape: an XCD's share of either kind rounds up)
+  const unsigned batches = (unsigned)((geo.tile_cap + 7) / 8);
   // tile entries the lists of a thin call can have (geo.tile_cap allows for one of every expert)
   const int row_cap = n_cap * ctx->kmax;
   const int all = geo.tile_cap - (row_cap < E ? E - row_cap : 0);
   const unsigned thin_entries = (unsigned)(all > 0 ? all : 0);
   {
     fmoe_prof_scope prof(ctx, dense ? SLOT_GEMM1_DENSE : SLOT_GEMM1, stream);
-    const unsigned items = dense ? (((unsigned)geo.tile_cap + 7) / 8 * g1.cols + 2) * 8 : batches * 8 * g1.cols;
+    const unsigned items = dense ? dense_blocks(geo.tile_cap, g1.cols) : batches * 8 * g1.cols;
     if (thin) hipLaunchKernelGGL(ffn_thin_kernel<true>, dim3(thin_entries * g1.cols), dim3(64), 0, stream, g1);
     else if (dense) hipLaunchKernelGGL((ffn_dense_kernel<true>), dim3(items), dim3(256), 0, stream, g1);
     else hipLaunchKernelGGL((ffn_stream_kernel<true>), dim3(items), dim3(256), 0, stream, g1);
   }
   {
     fmoe_prof_scope prof(ctx, dense ? SLOT_GEMM2_DENSE : SLOT_GEMM2, stream);
-    const unsigned items = dense ? (((unsigned)geo.tile_cap + 7) / 8 * g2.cols + 2) * 8 : batches * 8 * g2.cols;
+    const unsigned items = dense ? dense_blocks(geo.tile_cap, g2.cols) : batches * 8 * g2.cols;
     if (thin) hipLaunchKernelGGL(ffn_thin_kernel<false>, dim3(thin_entries * g2.cols), dim3(64), 0, stream, g2);
     else if (dense) hipLaunchKernelGGL((ffn_dense_kernel<false>), dim3(items), dim3(256), 0, stream, g2);
     else hipLaunchKernelGGL((ffn_stream_kernel<false>), dim3(items), dim3(256), 0, stream, g2);

@@ -383,3 +383,64 @@ def test_build_check_catches_compiler_use_of_hand_placed_accumulation_registers(
     real = os.path.join(os.path.dirname(binding.LIB_PATH), "_build", "ffn-hip-amdgcn-amd-amdhsa-gfx950.s")
     if os.path.exists(real):
         assert build.check_accumulation_registers(real) == 2
+
+
+DEAL = r"""
+#include <cstddef>
+#include <vector>
+#include "deal.h"
+// Walks a whole launch over a list of n entries (the first n_several in runs of run_len row tiles) and returns how many
+// (entry's row tile, column group) pairs are not met exactly once.
+extern "C" int walk(int n, int n_several, int run_len, int cols, int tile_cap, int* single_items) {
+  std::vector<int> met((std::size_t)n * cols, 0);
+  int stray = 0;
+  *single_items = 0;
+  const unsigned blocks = dense_blocks(tile_cap, cols);
+  for (unsigned blk = 0; blk < blocks; ++blk) {
+    int group = 0, strip = 0;
+    bool single = false;
+    const int e = dense_entry((int)blk, n, n_several, cols, group, single, strip);
+    if (e < 0) continue;
+    if (e >= n || group < 0 || group >= cols || single != (e >= n_several)) { ++stray; continue; }
+    *single_items += single;
+    int run0 = e, nrt = 1, rt = 0;
+    if (e < n_several) {
+      run0 = e - e % run_len;
+      nrt = n_several - run0 < run_len ? n_several - run0 : run_len;
+      rt = e - run0;
+      if (nrt > 1) dense_run_order(rt, nrt, cols, strip, rt, group);
+    }
+    if (rt < 0 || rt >= nrt || group < 0 || group >= cols) { ++stray; continue; }
+    ++met[(std::size_t)(run0 + rt) * cols + group];
+  }
+  for (int m : met) stray += m != 1;
+  return stray;
+}
+"""
+
+
+@pytest.fixture(scope="module")
+def deal(tmp_path_factory):
+    import subprocess
+    d = tmp_path_factory.mktemp("deal")
+    (d / "walk.cpp").write_text(DEAL)
+    subprocess.run(["g++", "-O2", "-std=c++17", "-shared", "-fPIC", "-I",
+                    os.path.join(ROOT, "paper_2511_17885_amd", "csrc"), str(d / "walk.cpp"), "-o", str(d / "walk.so")],
+                   check=True)
+    return C.CDLL(str(d / "walk.so"))
+
+
+@pytest.mark.parametrize("n,n_several,run_len,cols", [
+    (1, 0, 64, 1), (1, 1, 64, 11), (9, 4, 3, 7),       # up to 768 items: dealt entry by entry
+    (96, 40, 8, 8), (97, 40, 8, 8),                    # 768 items and the next size
+    (770, 0, 64, 1), (771, 771, 64, 1), (800, 1, 64, 5), (800, 799, 64, 5), (1113, 600, 64, 11),
+    (32767, 20000, 64, 8), (32768, 20000, 64, 8),      # 32767 and 32768 items an XCD: the last mixed list, the first that is not
+    (70001, 3, 64, 4), (70001, 70000, 64, 4), (300001, 200003, 64, 3),
+])
+def test_dense_deal_meets_every_item_once(deal, n, n_several, run_len, cols):
+    """The deal of the dense expert-GEMM shape, walked on the host over every workgroup of a launch: each column group of
+    each row tile exactly once, single tiles counted as such, also in lists too long to mix and with room to spare."""
+    singles = C.c_int()
+    for tile_cap in (n, n + 71):
+        assert deal.walk(n, n_several, run_len, cols, tile_cap, C.byref(singles)) == 0
+        assert singles.value == (n - n_several) * cols
