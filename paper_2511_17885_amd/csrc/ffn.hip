@@ -984,7 +984,7 @@ __global__ void pack_weights_kernel(const bf16_t* __restrict__ src0, const bf16_
 //    (row or column l%16, quarter q) holds k = 4q..4q+3 and instruction i takes element i on both sides.
 //    Weights therefore come straight from the caller's rows into registers, rows from LDS without a
 //    transposition;
-//  * weights: one or three k tiles (32 wide, one 128-byte line per column) in flight per wavefront, addressed by a
+//  * weights: up to three k tiles (32 wide, one 128-byte line per column) in flight per wavefront, addressed by a
 //    descriptor over the wavefront's rows, a constant lane offset and a scalar one; gathered rows: 64-bit
 //    pointers (fp32 tensors may exceed 4 GiB), as many tiles in flight, through registers into one of two
 //    LDS buffers in the swizzled layout of the bf16 kernels; one barrier per k tile.
@@ -994,10 +994,16 @@ __global__ void pack_weights_kernel(const bf16_t* __restrict__ src0, const bf16_
 // (108 and 105 TFLOP/s); 64 tokens, d 128, 8 experts of 256: 19.5 -> 7.9 and 33.5 -> 10.0 us.
 constexpr int FBM = 64;        // rows per tile
 constexpr int FBK = 32;        // k per tile: 128 bytes of a row
-// Register rings, in k tiles.  Tiles of up to 32 rows are chains of latencies, where what a shorter prologue and
-// fewer registers give counts for more than two more tiles in flight: 64 tokens, d 128, 8 experts of 256 9.4 + 10.7 ->
-// 8.5 + 9.8 us; 2600 tokens of it 13.8 + 17.2 -> 12.6 + 15.7; tiles of more rows measured 1 to 3 % slower with two.
-constexpr int f32_slots(int row_blocks) { return row_blocks <= 2 ? 2 : 4; }
+// Register rings, in k tiles: four, and two for tiles of up to 32 rows where either the reduction is short or the chip
+// has several workgroups a CU.  Those are chains of latencies, where a shorter prologue counts for more than two more
+// tiles in flight: 64 tokens, d 128, 8 experts of 256 9.4 + 10.7 -> 8.5 + 9.8 us; 2600 tokens of it 13.8 + 17.2 ->
+// 12.6 + 15.7; 416 tokens, d 512, 256 experts of 512 196 -> 188.  With a workgroup a CU or less and a long reduction the
+// weights in flight are all that the memory has to do (both GEMMs, two / four): 8 tokens, d 4096, 8 experts of 1536
+// 162 / 141 us; 64 tokens 181 / 156; one token, d 1288, 16 experts of 904 51 / 45; one token, d 2048, 64 experts of 1408
+// and two shared ones 93 / 80; against it 64 tokens, d 64, 4 experts of 2048 48.2 / 49.1.
+// Tiles of more rows measured 1 to 3 % slower with two.
+constexpr int F_DEEP_ITEMS = 256;   // work items up to which such tiles take the deep ring,
+constexpr int F_DEEP_K = 512;       // from this length of the reduction on
 
 struct GemmProblem {
   const float* A;           // [*, lda]
@@ -1026,10 +1032,9 @@ struct GemmArgs {
   int n_col_tiles_max;
 };
 
-template <bool SWIGLU, int NRB>   // NRB: live 16-row blocks of the tile
+template <bool SWIGLU, int NRB, int SLOTS>   // NRB: live 16-row blocks of the tile; SLOTS: k tiles in a register ring
 __device__ __forceinline__ void f32_tile(const GemmProblem& P, const fmoe_tile& tile, int group, bool shared, int nt,
                                          float* As) {
-  constexpr int SLOTS = f32_slots(NRB);
   constexpr int A_IT = (NRB + 1) / 2;   // 16-byte pieces of a k tile per thread
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -1138,14 +1143,17 @@ __device__ __forceinline__ void f32_tile(const GemmProblem& P, const fmoe_tile& 
       __syncthreads();   // tile t+1 is in LDS, all are done with tile t
     };
     int t0 = 0;
-    if constexpr (SLOTS == 2) {
+    if constexpr (NRB <= 2) {
       // No exit inside the loop: with one after every step the compiler sees a way from each of them to the loop's
-      // head and drains all loads there, once per turn of the rings, which a short step does not hide ...
+      // head and drains all loads there, once per turn of the rings, which a short step does not hide (64 tokens,
+      // d 4096, 8 experts of 1536, rings of four: 166 -> 156 us) ...
       for (; t0 + SLOTS <= NT; t0 += SLOTS) {
 #pragma unroll
         for (int u = 0; u < SLOTS; ++u) step(u, t0 + u);
       }
-      if (t0 < NT) step(0, t0);   // uniform
+      static_for<0, SLOTS - 1>([&](auto u) {
+        if (t0 + decltype(u)::value < NT) step(decltype(u)::value, t0 + decltype(u)::value);   // uniform
+      });
     } else {
       // ... and a long one does.
       for (;; t0 += SLOTS) {
@@ -1240,11 +1248,18 @@ __global__ __launch_bounds__(256, 2) void grouped_gemm_kernel(GemmArgs a) {
   take_row_tile(tile, row_tile, FBM);
   const int nt = tile.col0 + nt_launch;
   const int group = shared ? tile.group - a.E : tile.group;
+  const bool deep = n_tiles * a.n_col_tiles_max <= F_DEEP_ITEMS && P.K >= F_DEEP_K;   // uniform
   switch ((tile.rows + 15) >> 4) {   // live 16-row blocks of the tile, uniform per block
-    case 1: f32_tile<SWIGLU, 1>(P, tile, group, shared, nt, As); break;
-    case 2: f32_tile<SWIGLU, 2>(P, tile, group, shared, nt, As); break;
-    case 3: f32_tile<SWIGLU, 3>(P, tile, group, shared, nt, As); break;
-    default: f32_tile<SWIGLU, 4>(P, tile, group, shared, nt, As); break;
+    case 1:
+      if (deep) f32_tile<SWIGLU, 1, 4>(P, tile, group, shared, nt, As);
+      else f32_tile<SWIGLU, 1, 2>(P, tile, group, shared, nt, As);
+      break;
+    case 2:
+      if (deep) f32_tile<SWIGLU, 2, 4>(P, tile, group, shared, nt, As);
+      else f32_tile<SWIGLU, 2, 2>(P, tile, group, shared, nt, As);
+      break;
+    case 3: f32_tile<SWIGLU, 3, 4>(P, tile, group, shared, nt, As); break;
+    default: f32_tile<SWIGLU, 4, 4>(P, tile, group, shared, nt, As); break;
   }
 }
 

@@ -1593,6 +1593,32 @@ def test_expert_ffn_fp32_tile_edges(d, F):
         assert max_rel_err(host(ysh)[s], ffn(rows, sh[0][s], sh[1][s], sh[2][s])) <= TOL[W.F32], s
 
 
+@pytest.mark.parametrize("E", [8, 72])   # fewer and more work items than CUs: the deep and the shallow register rings
+@pytest.mark.parametrize("d,F", [(512, 544), (520, 576), (616, 608), (640, 584)])
+def test_expert_ffn_fp32_long_reductions_of_few_rows(d, F, E):
+    """The fp32 expert GEMMs on tiles of at most 32 rows with reductions of 16 to 20 k tiles, whole and with a partial
+    one, that leave 0 to 3 behind the last whole turn of a ring of four; against fp64 at the fp32 bound (TOL)."""
+    counts = [(1, 15, 16, 17, 31, 32, 0, 8)[e % 8] for e in range(E)]
+    k = 4
+    M = sum(counts)
+    n = (M + k - 1) // k
+    g = torch.Generator(device="cuda")
+    g.manual_seed(d * 1000 + E)
+    rnd = lambda *s: torch.randn(s, generator=g, device="cuda")
+    x, wr = rnd(n, d), rnd(E, d)
+    w = [rnd(E, F, d) * 0.1, rnd(E, F, d) * 0.1, rnd(E, d, F) * 0.1]
+    m = binding.FMoE(d_model=d, n_experts=E, d_ffn=F, k_text=k, k_visual=k, dtype="f32")
+    m.set_weights(wr, None, *w)
+    perm = torch.randint(0, n, (M,), generator=g, device="cuda").int()
+    offs = torch.tensor(np.concatenate([[0], np.cumsum(counts)]), dtype=torch.int32, device="cuda")
+    y, _ = m.expert_ffn(x, None, n, offs, perm)
+    for e, (lo, c) in enumerate(zip(np.cumsum([0] + counts), counts)):
+        if c:
+            v, ga, up, dn = (t.double() for t in (x[perm[lo:lo + c].long()], w[0][e], w[1][e], w[2][e]))
+            ref = ((torch.nn.functional.silu(v @ ga.T) * (v @ up.T)) @ dn.T).cpu().numpy()
+            assert max_rel_err(host(y)[lo:lo + c], ref) <= TOL[W.F32], (e, c)
+
+
 @pytest.mark.parametrize("n,d,F", [(1, 8, 8), (3, 136, 40), (8, 712, 456), (15, 392, 776), (16, 1288, 264), (16, 616, 248)])
 def test_expert_ffn_thin_shape(n, d, F):
     """Calls of at most 16 tokens take a kernel shape of their own: the same bits as the weight-stream shape
