@@ -18,7 +18,12 @@
 //    the pipes idle in the second half.
 //  * Inside a run the items go down the row tiles in strips of DENSE_STRIP column groups: neighbours in time
 //    share an activation tile or a weight tile while it still is in L2.
-//  * The weights of a single tile are not asked for again and bypass the L2's recency order (non-temporal).
+//  * The weights of a single tile are not asked for again and bypass the L2's recency order (non-temporal), if the
+//    layer's weights are more than the memory-side cache (256 MB) keeps for the next call: non-temporal loads miss that
+//    too.  Layer after layer, or 440 MB and more of weights, with / without the hint: 1600 tokens, d 1280, 64 experts of
+//    896 115.5 / 121.2 us, 4096 tokens, d 2048, 64 experts of 1408 347 / 356.  One layer over and over, very uneven rows:
+//    1200 tokens, d 1288, 16 experts of 904 and a shared one (119 MB) 94 / 78, 1600 tokens, d 4096, 8 experts of 1536 (302 MB) 156 / 138.
+//    The line is drawn between, at one and a half times the cache.
 // Measured, gate/up and down us, entries dealt round-robin before: 4096 tokens d 2048 64 experts of 1408, half kept
 // 193 + 106 -> 177 + 103; the same size, nothing dropped and every token six experts 270 + 158 -> 243 + 140;
 // 8192 tokens, 128 experts of 768 160 + 97 -> 149 + 90; 22016 tokens, six experts 1526 + 883 -> 1493 + 864.  Strips of

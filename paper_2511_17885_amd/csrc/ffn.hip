@@ -68,6 +68,7 @@ constexpr int DNCB = 2;         // column blocks per wavefront
 constexpr int DA_STAGES = 4;    // LDS ring of activation k tiles (64 wide)
 constexpr int DB_SLOTS = 4;     // register ring of weight k steps (32 wide)
 constexpr int NON_TEMPORAL = 2; // cache hint of a buffer load
+constexpr size_t WEIGHTS_PASS_BYTES = 384u << 20;   // one and a half times the memory-side cache, see deal.h
 
 struct StreamProblem {
   const bf16_t* A;            // [*, lda]
@@ -95,6 +96,7 @@ struct StreamArgs {
   const int32_t* n_tiles;     // device
   int cols;                   // work items per tile entry in this launch (column tiles, or groups of them)
   int cols_entry;             // column tiles per tile entry
+  int weights_pass;           // dense shape: the layer's weights do not stay in the memory-side cache anyway
 };
 
 // A list entry, by scalar loads of all its words at once (the lists are read-only in these kernels, which the
@@ -795,7 +797,7 @@ __global__ __launch_bounds__(256, 2) void ffn_dense_kernel(StreamArgs a) {
     P.C += (size_t)group * P.c_group_off;
   }
   auto by_rows = [&](auto nab) {
-    if (single) dense_tile<SWIGLU, decltype(nab)::value, NON_TEMPORAL>(P, tile, group, nt4, ct_limit, As);
+    if (single && a.weights_pass) dense_tile<SWIGLU, decltype(nab)::value, NON_TEMPORAL>(P, tile, group, nt4, ct_limit, As);
     else dense_tile<SWIGLU, decltype(nab)::value, 0>(P, tile, group, nt4, ct_limit, As);
   };
   switch ((tile.rows + 31) >> 5) {   // live 32-row bands of the tile, uniform per block
@@ -1419,6 +1421,9 @@ int run_ffn_bf16(const fmoe_ctx* ctx, const void* x, const int32_t* kept_idx, in
   g1.cols = g1.cols_entry = geo.cols1;
   g2.cols = g2.cols_entry = geo.cols2;
   const bool dense = geo.dense;
+  size_t packed = 0;
+  for (int w = 0; w < 4; ++w) packed += fmoe_packed_bytes(ctx, w);
+  g1.weights_pass = g2.weights_pass = packed > WEIGHTS_PASS_BYTES;
   // at most THIN_ROWS tokens: no tile has more rows, and the weight stream wants the finest work items
   const bool thin = n_cap <= THIN_ROWS && ctx->ffn_shape == 0;
   if (thin) {
