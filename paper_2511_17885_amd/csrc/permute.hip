@@ -16,12 +16,13 @@ namespace {
 constexpr int PB = FMOE_PERM_BLOCK;
 constexpr int PW = PB / 32;  // mask words per expert
 
-// ---- P1: per-block expert masks -> in-block ranks and per-block counts.  KM: at most so many slots.
+// ---- P1: per-block expert masks -> in-block ranks and per-block counts.  KM slots: one or few blocks fetch the code from
+// memory, so that code for slots that are not there, or a copy of it for each wavefront's pairs of words, costs more
+// than what it computes (16 positions, 256 experts, sixteen slots 5.3 -> 2.6 us; 256 positions, one slot 1.84 -> 1.44).
 template <int KM>
 __global__ __launch_bounds__(PB) void permute_count_kernel(
     const int32_t* __restrict__ topk_idx, const int32_t* __restrict__ kept_idx, int n_cap,
-    const int32_t* __restrict__ n_dev, int E, int Kmax, int32_t* __restrict__ slot_rank,
-    int32_t* __restrict__ blk_count) {
+    const int32_t* __restrict__ n_dev, int E, int32_t* __restrict__ slot_rank, int32_t* __restrict__ blk_count) {
   __shared__ __align__(16) uint32_t mask[FMOE_MAX_EXPERTS * PW];
   static_assert(PB == 256 && PW == 8, "a wavefront's 64 positions end with a pair of words");
   const int n = resolve_count(n_cap, n_dev);
@@ -30,51 +31,40 @@ __global__ __launch_bounds__(PB) void permute_count_kernel(
   __syncthreads();
   const int lp = threadIdx.x;
   const int p = blk * PB + lp;
-  int ex[FMOE_MAX_TOPK];
+  int ex[KM];
 #pragma unroll
-  for (int s = 0; s < FMOE_MAX_TOPK; ++s) ex[s] = -1;
+  for (int s = 0; s < KM; ++s) ex[s] = -1;
   if (p < n) {
     const int t = kept_idx ? kept_idx[p] : p;
-    // all slots' experts on their way at once (past Kmax the last one again): asked for where they are used, each
-    // was a memory latency of its own
+    // all slots' experts on their way at once: asked for where they are used, each was a memory latency of its own
 #pragma unroll
-    for (int s = 0; s < FMOE_MAX_TOPK; ++s)
-      if (s < KM) ex[s] = topk_idx[(size_t)t * Kmax + (s < Kmax ? s : Kmax - 1)];
+    for (int s = 0; s < KM; ++s) ex[s] = topk_idx[(size_t)t * KM + s];
 #pragma unroll
-    for (int s = 0; s < FMOE_MAX_TOPK; ++s) {
-      if (s >= KM || s >= Kmax || ex[s] < 0 || ex[s] >= E) ex[s] = -1;
+    for (int s = 0; s < KM; ++s) {
+      if (ex[s] < 0 || ex[s] >= E) ex[s] = -1;
       else atomicOr(&mask[ex[s] * PW + (lp >> 5)], 1u << (lp & 31));
     }
   }
   __syncthreads();
-  // set bits below the position: the words before its own whole, its own up to it; PAIRS = pairs of words up to the
-  // wavefront's own (a few positions with sixteen slots: all four pairs cost 2 us more than the one)
-  auto ranks = [&](auto pairs) {
-    constexpr int PAIRS = decltype(pairs)::value;
+  // set bits below the position, in pairs of words: its own up to it, those before it whole
+  if (p < n) {
+    const int pair = __builtin_amdgcn_readfirstlane(lp >> 6);
+    const uint32_t below = (1u << (lp & 31)) - 1u;
+    int rank[KM];
 #pragma unroll
-    for (int s = 0; s < FMOE_MAX_TOPK; ++s) {
-      if (s < KM && s < Kmax) {
-        const uint2* m = reinterpret_cast<const uint2*>(&mask[(ex[s] >= 0 ? ex[s] : 0) * PW]);
-        int rank = 0;
+    for (int s = 0; s < KM; ++s) {
+      const uint2 w = reinterpret_cast<const uint2*>(&mask[(ex[s] >= 0 ? ex[s] : 0) * PW])[pair];
+      rank[s] = (lp & 32) ? __popc(w.x) + __popc(w.y & below) : __popc(w.x & below);
+    }
+    for (int i = 0; i < pair; ++i) {
 #pragma unroll
-        for (int i = 0; i < PAIRS - 1; ++i) {
-          const uint2 w = m[i];
-          rank += __popc(w.x) + __popc(w.y);
-        }
-        const uint2 w = m[PAIRS - 1];
-        const uint32_t below = (1u << (lp & 31)) - 1u;
-        rank += (lp & 32) ? __popc(w.x) + __popc(w.y & below) : __popc(w.x & below);
-        slot_rank[(size_t)p * Kmax + s] = ex[s] >= 0 ? rank : -1;
+      for (int s = 0; s < KM; ++s) {
+        const uint2 w = reinterpret_cast<const uint2*>(&mask[(ex[s] >= 0 ? ex[s] : 0) * PW])[i];
+        rank[s] += __popc(w.x) + __popc(w.y);
       }
     }
-  };
-  if (p < n) {
-    switch (__builtin_amdgcn_readfirstlane(lp >> 6)) {
-      case 0: ranks(std::integral_constant<int, 1>{}); break;
-      case 1: ranks(std::integral_constant<int, 2>{}); break;
-      case 2: ranks(std::integral_constant<int, 3>{}); break;
-      default: ranks(std::integral_constant<int, 4>{}); break;
-    }
+#pragma unroll
+    for (int s = 0; s < KM; ++s) slot_rank[(size_t)p * KM + s] = ex[s] >= 0 ? rank[s] : -1;
   }
   for (int e = threadIdx.x; e < E; e += PB) {
     int c = 0;
@@ -280,6 +270,17 @@ __global__ __launch_bounds__(PB) void permute_scatter_kernel(
   }
 }
 
+template <int KM = 1>
+void launch_count(int Kmax, int nblk, hipStream_t stream, const int32_t* topk_idx, const int32_t* kept_idx, int n_cap,
+                  const int32_t* n_dev, int E, int32_t* slot_rank, int32_t* blk_count) {
+  if constexpr (KM < FMOE_MAX_TOPK) {
+    if (Kmax > KM)
+      return launch_count<KM + 1>(Kmax, nblk, stream, topk_idx, kept_idx, n_cap, n_dev, E, slot_rank, blk_count);
+  }
+  hipLaunchKernelGGL(permute_count_kernel<KM>, dim3(nblk), dim3(PB), 0, stream, topk_idx, kept_idx, n_cap, n_dev, E,
+                     slot_rank, blk_count);
+}
+
 }  // namespace
 
 int launch_permute(const fmoe_ctx* ctx, const int32_t* topk_idx, const int32_t* kept_idx, int n_cap,
@@ -293,12 +294,7 @@ int launch_permute(const fmoe_ctx* ctx, const int32_t* topk_idx, const int32_t* 
   const int nblk = (n_cap + PB - 1) / PB;
   if (nblk > 0 && Kmax > 0) {
     fmoe_prof_scope prof(ctx, SLOT_PERM_COUNT, stream);
-    if (Kmax <= 8)
-      hipLaunchKernelGGL(permute_count_kernel<8>, dim3(nblk), dim3(PB), 0, stream, topk_idx, kept_idx,
-                         n_cap, n_dev, E, Kmax, slot_rank, blk_count);
-    else
-      hipLaunchKernelGGL(permute_count_kernel<FMOE_MAX_TOPK>, dim3(nblk), dim3(PB), 0, stream, topk_idx, kept_idx,
-                         n_cap, n_dev, E, Kmax, slot_rank, blk_count);
+    launch_count(Kmax, nblk, stream, topk_idx, kept_idx, n_cap, n_dev, E, slot_rank, blk_count);
   }
   if (nblk > 0 && Kmax > 0 && join_scan_scatter(nblk, E, Kmax)) {
     fmoe_prof_scope prof(ctx, SLOT_PERM_SCATTER, stream);

@@ -1749,6 +1749,22 @@ def test_permute_block_counts(n, E, k):
         assert np.array_equal(host(inv)[:c], o_inv[:c])
 
 
+@pytest.mark.parametrize("k", range(1, 17))
+def test_permute_every_number_of_slots(k):
+    """The counting kernel has a form for each number of slots; positions on both sides of a mask word, of a
+    wavefront's pair of words and of a block, a fifth of the slots padding."""
+    rng = np.random.default_rng(50 + k)
+    m = binding.FMoE(d_model=8, n_experts=40, d_ffn=8, k_text=k, k_visual=k, dtype="f32")
+    for n in (1, 32, 33, 64, 65, 128, 193, 256, 257):
+        idx = np.argsort(rng.random((n, 40)), axis=1)[:, :k].astype(np.int32)
+        idx[rng.random((n, k)) < 0.2] = -1
+        o_offs, o_perm, o_inv = oracle.permute(idx, None, 40)
+        offs, perm, inv = m.permute(dev(idx), None, n)
+        M = int(o_offs[-1])
+        assert np.array_equal(host(offs), o_offs) and np.array_equal(host(perm)[:M], o_perm[:M])
+        assert np.array_equal(host(inv)[:n], o_inv[:n])
+
+
 @pytest.mark.parametrize("T_v,T_t,k", [([1990, 50], [6, 2], 8), ([1990, 50], [6, 3], 8), ([2900, 1100], [60, 36], 8),
                                        ([2900, 1100], [60, 36], 9)])
 @pytest.mark.parametrize("gamma", [0.0, 0.1])
