@@ -1266,8 +1266,8 @@ __global__ __launch_bounds__(256) void build_tiles_kernel(const int32_t* __restr
                                                           fmoe_tile* __restrict__ tiles2,
                                                           int32_t* __restrict__ counts) {
   __shared__ __align__(8) int scratch[FMOE_TILES_SCRATCH];
-  fmoe_build_tiles(expert_offsets, E, row_cap, resolve_count(n_cap, n_dev), n_shared, geom.bm,
-                   geom.run, geom.tile_cap, geom.cols1, geom.scols1, tiles1, tiles2, counts, scratch);
+  fmoe_build_tiles<false>(expert_offsets, E, row_cap, resolve_count(n_cap, n_dev), n_shared, geom.bm,
+                          geom.run, geom.tile_cap, geom.cols1, geom.scols1, tiles1, tiles2, counts, scratch);
 }
 
 inline int ks_steps(int K) { return ((K + SBK - 1) / SBK) * 2; }

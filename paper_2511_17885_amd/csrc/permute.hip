@@ -171,8 +171,8 @@ __global__ __launch_bounds__(PB) void permute_scan_scatter_kernel(
   if (lists) {
     for (int i = tid; i <= E; i += PB) expert_offsets[i] = s_off[i];
     if (build)   // fused layer path
-      fmoe_build_tiles(s_off, E, n_cap * Kmax, n, n_shared, geom.bm, geom.run, geom.tile_cap, geom.cols1, geom.scols1,
-                       tiles1, tiles2, tile_count, scratch);
+      fmoe_build_tiles<true>(s_off, E, n_cap * Kmax, n, n_shared, geom.bm, geom.run, geom.tile_cap, geom.cols1,
+                             geom.scols1, tiles1, tiles2, tile_count, scratch);
     return;
   }
   if (!mine) return;
@@ -243,8 +243,8 @@ __global__ __launch_bounds__(256) void permute_scan_kernel(int n_cap, const int3
   if (build) {   // fused layer path: the grouped-GEMM work lists come out of the same scan
     __threadfence_block();
     __syncthreads();
-    fmoe_build_tiles(expert_offsets, E, row_cap, resolve_count(rows_cap, rows_dev), n_shared, geom.bm,
-                     geom.run, geom.tile_cap, geom.cols1, geom.scols1, tiles1, tiles2, tile_count, scratch);
+    fmoe_build_tiles<true>(expert_offsets, E, row_cap, resolve_count(rows_cap, rows_dev), n_shared, geom.bm,
+                           geom.run, geom.tile_cap, geom.cols1, geom.scols1, tiles1, tiles2, tile_count, scratch);
   }
 }
 

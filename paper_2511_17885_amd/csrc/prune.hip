@@ -916,8 +916,8 @@ __global__ __launch_bounds__(SB_THREADS) void prune_dispatch_small_kernel(SmallA
   __syncthreads();
 
   // ---- grouped-GEMM tile lists
-  fmoe_build_tiles(s_off, E, a.row_cap, n, a.n_shared, a.geom.bm, a.geom.run, a.geom.tile_cap, a.geom.cols1,
-                   a.geom.scols1, a.tiles1, a.tiles2, a.tile_count, s_scr);
+  fmoe_build_tiles<true>(s_off, E, a.row_cap, n, a.n_shared, a.geom.bm, a.geom.run, a.geom.tile_cap, a.geom.cols1,
+                         a.geom.scols1, a.tiles1, a.tiles2, a.tile_count, s_scr);
 
   // ---- outputs
   if (tid <= E) a.expert_offsets[tid] = s_off[tid];

@@ -477,8 +477,8 @@ __global__ __launch_bounds__(256) void route_kernel(
     if (tid <= E) job.expert_offsets[tid] = s_off[tid];
     if (tid == 0 && E == FMOE_MAX_EXPERTS) job.expert_offsets[E] = s_off[E];
     for (int b = tid; b <= job.B; b += 256) job.new_cu[b] = clampi(job.cu[b], 0, T);
-    fmoe_build_tiles(s_off, E, job.row_cap, T, job.n_shared, job.geom.bm, job.geom.run, job.geom.tile_cap, job.geom.cols1,
-                     job.geom.scols1, job.tiles1, job.tiles2, job.tile_count, scratch);
+    fmoe_build_tiles<false>(s_off, E, job.row_cap, T, job.n_shared, job.geom.bm, job.geom.run, job.geom.tile_cap,
+                            job.geom.cols1, job.geom.scols1, job.tiles1, job.tiles2, job.tile_count, scratch);
   }
 }
 

@@ -4,7 +4,7 @@
 
 #include "common.h"
 
-#define FMOE_TILES_SCRATCH 770
+#define FMOE_TILES_SCRATCH 768
 
 #if defined(__HIPCC__)
 // Builds, with one block of 256 threads or a multiple, the two row-tile lists of the expert FFN (`bm` rows per tile):
@@ -24,18 +24,20 @@
 // (negative, decreasing or past row_cap) are skipped so that no tile can index outside the row
 // buffers; without room for rows (row_cap 0) the offsets are not read and may be null.  `scratch` is
 // FMOE_TILES_SCRATCH ints of LDS (8-byte aligned); bm and run are powers of two.
+template <bool SPLIT>
 __device__ __forceinline__ void fmoe_build_tiles(const int32_t* expert_offsets, int E, int row_cap,
                                                  int n, int n_shared, int bm, int run, int tile_cap, int cols1,
                                                  int scols1, fmoe_tile* tiles1, fmoe_tile* tiles2,
                                                  int32_t* counts, int* scratch) {
   const int sh = 31 - __clz(bm);   // bm is a power of two
-  // the experts side by side, as often as the block holds them: every share takes its part of the comparisons and
-  // of an expert's tiles (64 experts, 256 threads, some 1000 tiles at 20000 tokens: the joined scan and scatter, whose
-  // longest block this is, 12.3 -> 8.1 us)
+  // the experts side by side, as often as the block holds them: every share takes its part of an expert's tiles and, with
+  // SPLIT, of the comparisons (64 experts, 256 threads, some 1000 tiles at 20000 tokens: the joined scan and scatter,
+  // whose longest block this is, 12.3 -> 8.1 us).  Alone in a launch, or for a handful of tokens, it does not split: the
+  // code comes from memory, and the additions and the barrier behind them take longer than the comparisons they
+  // save (8 experts 1.84 -> 1.56 us, 256 experts 6.40 -> 6.16)
   const int le = E > 1 ? 32 - __clz(E - 1) : 0;
   const int e = threadIdx.x & ((1 << le) - 1), share = threadIdx.x >> le, shares = blockDim.x >> le;
   int* const s_start = scratch + 512;   // of every expert
-  int* const s_sum = scratch + 768;     // entries of the routed experts, and of those with several tiles
   int r0 = 0, cnt = 0;
   if (e < E && row_cap > 0) {
     r0 = expert_offsets[e];
@@ -50,29 +52,25 @@ __device__ __forceinline__ void fmoe_build_tiles(const int32_t* expert_offsets, 
   if (share == 0) {
     scratch[2 * e] = (e < E) ? (int)key : 0;
     scratch[2 * e + 1] = nt;
-    s_start[e] = 0;
-    if (e == 0) s_sum[0] = s_sum[1] = 0;
+    if constexpr (SPLIT) s_start[e] = 0;
   }
   __syncthreads();
   // first tile slot of expert e = tiles of all experts ahead of it in that order
+  int start = 0;
   {
-    int start = 0;
+    const int per = !SPLIT ? E : ((1 << le) > 8 * shares ? (1 << le) / shares : 8);
+    const int o0 = SPLIT ? share * per : 0, o1 = o0 + per < E ? o0 + per : E;
 #pragma unroll 8
-    for (int o = share; o < E; o += shares) {
+    for (int o = o0; o < o1; ++o) {
       const int2 kn = *reinterpret_cast<const int2*>(&scratch[2 * o]);
       start += ((unsigned)kn.x > key) ? kn.y : 0;
     }
-    if (start) atomicAdd(&s_start[e], start);
-    // totals by wavefront: one addition each, where one per share meant 256 to one address with a single expert (4 us)
-    const int all = share == 0 ? nt : 0;
-    const int routed = wave_scan(all), several = wave_scan(all > 1 ? all : 0);
-    if ((threadIdx.x & 63) == 63 && routed) {
-      atomicAdd(&s_sum[0], routed);
-      atomicAdd(&s_sum[1], several);
-    }
   }
-  __syncthreads();
-  const int start = s_start[e], routed = s_sum[0], several = s_sum[1];
+  if constexpr (SPLIT) {
+    if (start) atomicAdd(&s_start[e], start);
+    __syncthreads();
+    start = s_start[e];
+  }
 
   const int ns = (n_shared > 0) ? (n + bm - 1) / bm : 0;
   const int rep1 = (ns > 0 && cols1 > 0) ? (scols1 + cols1 - 1) / cols1 : 0;
@@ -111,13 +109,23 @@ __device__ __forceinline__ void fmoe_build_tiles(const int32_t* expert_offsets, 
       if (sh2 + start + j < tile_cap) tiles2[sh2 + start + j] = t;
     }
   }
-  if (threadIdx.x == 0) {
-    const int t1 = routed + sh1, t2 = routed + sh2;
-    counts[0] = t1 < tile_cap ? t1 : tile_cap;
-    counts[1] = t2 < tile_cap ? t2 : tile_cap;
-    const int s1 = several + (ns > 1 ? sh1 : 0), s2 = several + (ns > 1 ? sh2 : 0);
-    counts[2] = s1 < tile_cap ? s1 : tile_cap;
-    counts[3] = s2 < tile_cap ? s2 : tile_cap;
+  if (threadIdx.x >= blockDim.x - 64) {   // the last wavefront, which has the fewest tiles to write
+    const int lane = threadIdx.x & 63;
+    int all = 0, more = 0;   // entries of the routed experts, of those with several tiles
+    for (int o = lane; o < E; o += 64) {
+      const int v = scratch[2 * o + 1];
+      all += v;
+      more += v > 1 ? v : 0;
+    }
+    const int routed = wave_scan(all), several = wave_scan(more);
+    if (lane == 63) {
+      const int t1 = routed + sh1, t2 = routed + sh2;
+      counts[0] = t1 < tile_cap ? t1 : tile_cap;
+      counts[1] = t2 < tile_cap ? t2 : tile_cap;
+      const int s1 = several + (ns > 1 ? sh1 : 0), s2 = several + (ns > 1 ? sh2 : 0);
+      counts[2] = s1 < tile_cap ? s1 : tile_cap;
+      counts[3] = s2 < tile_cap ? s2 : tile_cap;
+    }
   }
 }
 #endif
