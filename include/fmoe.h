@@ -128,10 +128,11 @@ int fmoe_set_selection(fmoe_ctx* ctx, int32_t strategy, int32_t k_base, uint64_t
 
 /* Tuning knob of the bf16 expert GEMMs (Eq.4).  The kernel has two shapes for batches: the weight-stream shape (a
  * workgroup = 128 rows x 4 column blocks) for calls that route few rows per expert, and the dense
- * shape (128 rows x 8 column blocks, half the on-chip traffic per flop) from a capacity of 256 routed
- * rows per expert (T * Kmax / E) on.  Calls of at most 16 tokens take a third, thin shape (a wavefront per
+ * shape (128 rows x 8 column blocks, half the on-chip traffic per flop) from a capacity (T * Kmax / E) of 112,
+ * 144 or 256 routed rows per expert on: the less, the more work items the layer has with one row tile an expert,
+ * and 256 where d_model or S_m is below 736.  Calls of at most 16 tokens take a third, thin shape (a wavefront per
  * column block).  All add the products of a dot product in ascending k, so their
- * outputs are bit-identical.  shape 0 = choose by that rule (default), 1 = always weight-stream,
+ * outputs are bit-identical.  shape 0 = choose by size (default), 1 = always weight-stream,
  * 2 = always dense; anything else is FMOE_ERR_INVALID_ARG.  No effect on fp32 contexts. */
 int fmoe_set_ffn_shape(fmoe_ctx* ctx, int32_t shape);
 

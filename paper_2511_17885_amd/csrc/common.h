@@ -19,19 +19,28 @@
 // Routed-row capacity per expert from which the expert GEMMs take their dense shape, by how much there is to do with one
 // row tile an expert: work items (column groups of the narrower GEMM) and length of the shorter reduction.  The dense
 // shape's items are twice as long and half as many; where they leave the chip half idle the weight-stream shape wins
-// until experts have several row tiles.  Gate/up + down, stream / dense, us, half of the visual tokens kept, all kept:
-//   704 and 512 items (d 2048, 64 experts of 1408): capacity 98 172 / 181, 221 / 217; 121 213 / 216, 257 / 246; 188
-//     240 / 240, 310 / 277;  128 experts of 768: 125 134 / 135, 175 / 163
-//   448 and 320 (d 1280, 64 of 896): 117 80 / 86, 105 / 101; 150 89 / 91, 114 / 108; 197 105 / 104, 136 / 138
-//   512 and 512, but short (d 1024, 128 of 512): 166 56 / 63, 74 / 69; 230 71 / 67, 96 / 91
-//   256 (d 2048, 32 of 1024): 166 98 / 112, 122 / 118; 231 109 / 113, 137 / 127
-//   96 and 128 (d 4096, 8 of 1536): 167 78 / 99, 103 / 102; 232 103 / 100, 109 / 106
+// until experts have several row tiles.  Gate/up + down, stream / dense, us, layer after layer: half of the visual tokens
+// kept, all kept (both half of the experts a token), all kept with all experts; the lines lie between the layers measured:
+//   704 gate/up, 512 down items (d 2048, 64 experts of 1408, two shared): capacity 80 158/152, 199/195, 243/226;
+//     120 189/181, 234/218, 287/269
+//   768 and 1024 (d 2048, 128 of 768): 100 121/118, 146/148, 213/199; 120 125/123, 156/159, 232/207; 150 144/142, 188/181
+//   448 and 320 (d 1280, 64 of 896, two shared): 120 78/81, 102/96, 129/125; 150 85/83, 110/103, 145/140
+//   420 and 300 (d 1280, 60 of 896): 150 70/76, 84/82, 114/114; 215 75/81, 97/96, 141/135; 250 82/83, 105/103, 155/148
+//   288 (d 2048, 36 of 1024): 150 90/99, 117/107, 143/138; 180 103/101, 124/114; 256: 150 87/97, 105/101; 215 105/101
+//   96 and 128 (d 4096, 8 of 1536): 215 76/100, 103/101, 142/152; 300 101/102, 110/103, 145/151
+//   short reductions: 704 (d 2048, 112 experts, 672 and 896 items) 120 139/142, 168/167, 220/207; 150 153/163, 183/179;
+//     215 174/176, 212/199; 640 (128 experts) 150 155/158, 189/192, 267/237; 576 215 154/157, 198/185; 512 (d 1024) 180
+//     67/68, 85/84, 122/113; 250 77/75, 103/104, 149/136
+// One decision for both GEMMs: alone the down product of 64 experts of 896 at capacity 150, half kept, is faster in the
+// weight-stream shape (33 against 35 us), but behind a gate/up product in the dense shape that gains nothing (layer of
+// 1600 tokens, runs of 8 / 64 row tiles: half kept 114.4 -> 115.3 / 113.9 -> 113.1 us, three quarters with merging
+// 167.5 -> 169.7 / 168.1 -> 170.3).
 #define FMOE_DENSE_MIN_ROWS 112        // from FMOE_DENSE_ITEMS items on
 #define FMOE_DENSE_MIN_ROWS_SOME 144   // from FMOE_DENSE_ITEMS_SOME on
 #define FMOE_DENSE_MIN_ROWS_FEW 256    // fewer, or shorter reductions than FMOE_DENSE_MIN_K
-#define FMOE_DENSE_ITEMS 512
-#define FMOE_DENSE_ITEMS_SOME 320
-#define FMOE_DENSE_MIN_K 768
+#define FMOE_DENSE_ITEMS 480
+#define FMOE_DENSE_ITEMS_SOME 310
+#define FMOE_DENSE_MIN_K 736
 
 // ---- optional per-kernel timing (instrumentation; off by default)
 enum fmoe_kernel_slot {

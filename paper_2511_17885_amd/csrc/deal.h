@@ -12,8 +12,11 @@
 // eight contiguous shares, one per XCD (consecutive workgroups go round the XCDs), separately for the entries of
 // groups with several row tiles, the first n_several of the list, and for the single tiles behind them; a share
 // of each is walked by one XCD, evenly mixed.
-//  * Contiguous: a group of several row tiles sits on one XCD, or two where a cut falls into it, so that its rows and
-//    weights enter one L2; dealt out entry by entry over the XCDs they entered most of them.
+//  * Contiguous: a group of several row tiles sits on one XCD, or two where a cut falls into it, and every XCD has as
+//    much to do.  What the down GEMM reads past L2 fell by it (4096 tokens, 64 experts of 1408: 15 % less; 8192, 128 of
+//    768: 31 %).  Gate/up reads 10 % less at the latter, but 3 % more at the former and 11 % more with hundreds of rows
+//    per expert, since its items wait for each other less and walk the reduction out of step: there the gain
+//    in time is the balance.
 //  * Mixed: groups of many rows keep the matrix pipes busy, single tiles the memory; one kind after the other left
 //    the pipes idle in the second half.
 //  * Inside a run the items go down the row tiles in strips of DENSE_STRIP column groups: neighbours in time
@@ -32,6 +35,11 @@ constexpr int DENSE_STRIP = 3;
 // Up to so many items, a round and a half of two workgroups a CU, the launch takes as long as its fullest XCD: entries go
 // round the XCDs, long and short ones alike, and a run's items in strips of one column group, so that a weight
 // tile enters one or two L2s (layer of 1600 tokens, d 1280, 64 experts of 896, half kept: 118.1 -> 114.9 us).
+// Contiguous shares / entry by entry, us, gate/up and down; below the line: 1920 tokens of that layer 51/48 and 38/35;
+// 1440 tokens, d 2048, 32 experts of 1024, half kept 66/62 and 40/37; 1066 tokens, 64 experts of 1408, half kept 119/115
+// and 63/56; 960 tokens, d 1024, 72 of 768, all kept 38/36 and 22/22; above it: 2666 tokens, 64 of 1408, half kept 137/145
+// and 81/84, all kept 245/251 and 142/149; 4000 tokens, 128 of 768, half kept 100/107 and 63/63, all kept 204/221 and
+// 127/143; 3200 tokens of the first layer, all kept 123/125 and 80/84.
 constexpr int DENSE_ONE_ROUND = 768;
 
 // workgroups of a launch whose list has at most tile_cap entries (an XCD's share of either kind rounds up)
