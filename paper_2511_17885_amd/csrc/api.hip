@@ -363,7 +363,8 @@ int fmoe_combine(fmoe_ctx* ctx, const void* y, const void* y_shared, const int32
   if (!aligned16(y) || !aligned16(y_shared) || !aligned16(residual) || !aligned16(out))
     return fmoe_fail(FMOE_ERR_INVALID_ARG, "fmoe_combine: tensor pointers must be 16-byte aligned");
   return launch_combine(ctx, y, ctx->cfg.n_shared > 0 ? y_shared : nullptr, inv_perm, topk_gate,
-                        kept_idx, n_kept, n_kept_dev, residual, out, static_cast<hipStream_t>(stream));
+                        kept_idx, n_kept, n_kept_dev, n_kept_dev ? n_kept / 2 : n_kept, residual, out,
+                        static_cast<hipStream_t>(stream));
 }
 
 int fmoe_layer_forward(fmoe_ctx* ctx, const fmoe_prune_params* params, const void* x,
@@ -387,6 +388,7 @@ int fmoe_layer_forward(fmoe_ctx* ctx, const fmoe_prune_params* params, const voi
   const bool do_prune = params && params->prune_mode != 0 && params->retention < 1.0f;
   if (params && (rc = check_prune(params)) != FMOE_OK) return rc;
   if ((rc = check_ws(ctx, ws, ws_bytes, T, B)) != FMOE_OK) return rc;
+  const int n_expected = do_prune ? (int)(params->retention * (float)T) : T;   // about what combine gets to see
   hipStream_t s = static_cast<hipStream_t>(stream);
   const fmoe_ws_layout L = fmoe_layout(ctx, T, B);
   char* base = static_cast<char*>(ws);
@@ -421,7 +423,7 @@ int fmoe_layer_forward(fmoe_ctx* ctx, const fmoe_prune_params* params, const voi
       return rc;
     if ((rc = launch_expert_ffn(ctx, x, nullptr, T, nullptr, expert_offsets, perm_src, y, y_shared, ws, L, true, s)) != FMOE_OK)
       return rc;
-    return launch_combine(ctx, y, y_shared, inv_perm, topk_gate, nullptr, T, nullptr, add_residual ? x : nullptr, out, s);
+    return launch_combine(ctx, y, y_shared, inv_perm, topk_gate, nullptr, T, nullptr, T, add_residual ? x : nullptr, out, s);
   }
   if ((rc = launch_route(ctx, x, is_visual, T, do_prune ? probs : nullptr, topk_idx, topk_gate, ord, s)) != FMOE_OK)
     return rc;
@@ -439,7 +441,7 @@ int fmoe_layer_forward(fmoe_ctx* ctx, const fmoe_prune_params* params, const voi
     }
     if ((rc = launch_expert_ffn(ctx, x, kept, T, n_dev, expert_offsets, perm_src, y, y_shared, ws, L, true, s)) != FMOE_OK)
       return rc;
-    return launch_combine(ctx, y, y_shared, inv_perm, topk_gate, kept, T, n_dev, add_residual ? x : nullptr,
+    return launch_combine(ctx, y, y_shared, inv_perm, topk_gate, kept, T, n_dev, n_expected, add_residual ? x : nullptr,
                           out, s);
   }
   if (merge_after) {
@@ -454,7 +456,7 @@ int fmoe_layer_forward(fmoe_ctx* ctx, const fmoe_prune_params* params, const voi
       return rc;
     if ((rc = launch_expert_ffn(ctx, x, nullptr, T, nullptr, expert_offsets, perm_src, y, y_shared, ws, L, true, s)) != FMOE_OK)
       return rc;
-    if ((rc = launch_combine(ctx, y, y_shared, inv_perm, topk_gate, nullptr, T, nullptr, add_residual ? x : nullptr,
+    if ((rc = launch_combine(ctx, y, y_shared, inv_perm, topk_gate, nullptr, T, nullptr, T, add_residual ? x : nullptr,
                              full, s)) != FMOE_OK)
       return rc;
     return launch_prune(ctx, params, probs, is_visual, cu_seqlens, B, T, attn_importance, kept_idx,
@@ -483,7 +485,7 @@ int fmoe_layer_forward(fmoe_ctx* ctx, const fmoe_prune_params* params, const voi
     if (rc != FMOE_OK) return rc;
     if ((rc = launch_expert_ffn(ctx, xm, nullptr, T, n_dev, expert_offsets, perm_src, y, y_shared, ws, L, true, s)) != FMOE_OK)
       return rc;
-    return launch_combine(ctx, y, y_shared, inv_perm, topk_gate, nullptr, T, n_dev, add_residual ? xm : nullptr,
+    return launch_combine(ctx, y, y_shared, inv_perm, topk_gate, nullptr, T, n_dev, n_expected, add_residual ? xm : nullptr,
                           out, s);
   }
   if (do_prune) {
@@ -500,7 +502,7 @@ int fmoe_layer_forward(fmoe_ctx* ctx, const fmoe_prune_params* params, const voi
     return rc;
   if ((rc = launch_expert_ffn(ctx, x, kept, T, n_dev, expert_offsets, perm_src, y, y_shared, ws, L, true, s)) != FMOE_OK)
     return rc;
-  return launch_combine(ctx, y, y_shared, inv_perm, topk_gate, kept, T, n_dev, add_residual ? x : nullptr,
+  return launch_combine(ctx, y, y_shared, inv_perm, topk_gate, kept, T, n_dev, n_expected, add_residual ? x : nullptr,
                         out, s);
 }
 

@@ -51,15 +51,18 @@ template <> struct Vec<float> {
 // slots would not allow): 1600 tokens of d 2048 in fp32, sixteen slots, 43.8 -> 38.1 us.  8 tokens, d 2048, eight
 // slots, through LDS and now: 4.4 -> 4.0 us; 22016 tokens, d 2048, six slots, two shared experts: 165 us both,
 // 5.5 TB/s, which is what a large copy reaches.
-// TOGETHER: all rows of a token on their way before the first is added.  Otherwise a wavefront waits for each row
-// before it asks for the next (the test for a row that counts stands between), and only the other wavefronts of the
-// CU keep the memory busy: with eight to a SIMD and tens of megabytes they do, and the registers then count for more.
-// The line is drawn at the size of one row set (tokens x d), separate / together, us, bf16, six slots, two shared
-// experts: 832 tokens of d 1280 (2 MB) 8.5 / 7.7, 2176 of d 2048 (9 MB) 23.2 / 20.0, 4096 (17 MB) 27.8 / 29.2, 22016
-// 173 / 175; eight slots, none shared: 3838 of d 2048 (16 MB) 31.8 / 32.2; six, 20000 of d 128 (5 MB) 21.5 / 14.4;
-// fp32, 832 of d 1280 (4 MB) 11.6 / 10.5; sixteen, 1600 of d 2048 (13 MB) 50.4 / 52.1.  One or two fp32 rows a token
-// are nothing to gather: 8192 of d 128 (4 MB) 5.1 / 5.5, one token 2.8 / 3.0.
-constexpr size_t COMBINE_TOGETHER_BYTES = 10u << 20;
+// TOGETHER: all rows of a token on their way before the first is added (a row that does not count is not asked for:
+// reading something else in its place took 10 to 20 % where half of the slots are empty).  Otherwise a wavefront
+// waits for each row before it asks for the next (the test for a row that counts stands between), and only the other
+// wavefronts of the CU keep the memory busy: with eight to a SIMD and tens of megabytes they do as well.
+// The line is drawn at the size of one row set (tokens x d; where the device holds their number, n_expected: what the
+// retention leaves, or half of the capacity for a caller who gives none).  Inside a layer, bf16, separate / together,
+// us: six slots and two shared experts, d 1280, half of the slots empty 2457 tokens (6 MB) 13.0 / 11.4, 4915 22.1 / 18.6,
+// 8192 31.0 / 28.1, 12288 (30 MB) 44.0 / 42.0, none empty 17.8 / 14.8, 29.2 / 25.5, 41.4 / 40.4, 61.3 / 57.9; d 2048,
+// half of them empty 2304 (9 MB) 18.8 / 15.8, 3840 24.4 / 23.6, 7680 (30 MB) 43.4 / 44.0, 11520 62.2 / 62.6; a quarter of
+// 8000 tokens kept, 128 experts, eight slots 16.6 / 14.0.  One or two fp32 rows a token are nothing to gather: 8192 of d 128
+// (4 MB) 5.1 / 5.5, one token 2.8 / 3.0.
+constexpr size_t COMBINE_TOGETHER_BYTES = 32u << 20;
 template <typename T, int KM, bool TOGETHER>
 __global__ __launch_bounds__(256, TOGETHER ? 4 : 8) void combine_kernel(
     const T* __restrict__ y, const T* __restrict__ y_shared, const int32_t* __restrict__ inv_perm,
@@ -90,10 +93,9 @@ __global__ __launch_bounds__(256, TOGETHER ? 4 : 8) void combine_kernel(
           vs[s] = *reinterpret_cast<const uint4*>(y_shared + ((size_t)(s < n_shared ? s : 0) * n_cap + p) * d + c);
       }
 #pragma unroll
-      for (int s = 0; s < KM; ++s) {   // a row that does not count: what stands in the output, not added
-        const T* const src = rows[s] < 0 || rows[s] >= row_cap ? out + (size_t)p * d : y + (size_t)rows[s] * d;
-        vk[s] = *reinterpret_cast<const uint4*>(src + c);
-      }
+      for (int s = 0; s < KM; ++s)
+        if (rows[s] >= 0 && rows[s] < row_cap)   // uniform
+          vk[s] = *reinterpret_cast<const uint4*>(y + (size_t)rows[s] * d + c);
       if (residual) Vec<T>::widen(vr, acc);
       if (y_shared) {
         for (int s = 0; s < n_shared; ++s) {
@@ -140,17 +142,17 @@ __global__ __launch_bounds__(256, TOGETHER ? 4 : 8) void combine_kernel(
 template <typename T, int KM>
 void launch_combine_t(const fmoe_ctx* ctx, const void* y, const void* y_shared, const int32_t* inv_perm,
                       const float* topk_gate, const int32_t* kept_idx, int n_cap, const int32_t* n_dev,
-                      const void* residual, void* out, hipStream_t stream) {
+                      int n_expected, const void* residual, void* out, hipStream_t stream) {
   if constexpr (KM < FMOE_MAX_TOPK) {
     if (ctx->kmax > KM)
-      return launch_combine_t<T, KM + 1>(ctx, y, y_shared, inv_perm, topk_gate, kept_idx, n_cap, n_dev, residual, out, stream);
+      return launch_combine_t<T, KM + 1>(ctx, y, y_shared, inv_perm, topk_gate, kept_idx, n_cap, n_dev, n_expected, residual,
+                                         out, stream);
   }
 #define FMOE_COMBINE_LAUNCH(TOGETHER)                                                                            \
   hipLaunchKernelGGL((combine_kernel<T, KM, TOGETHER>), dim3(n_cap), dim3(256), 0, stream, static_cast<const T*>(y), \
                      static_cast<const T*>(y_shared), inv_perm, topk_gate, kept_idx, n_cap, n_dev, n_cap * KM,       \
                      ctx->cfg.d_model, ctx->cfg.n_shared, static_cast<const T*>(residual), static_cast<T*>(out))
-  // a count on the device is what pruning left of the capacity: half of it, say
-  const size_t bytes = (size_t)n_cap * ctx->cfg.d_model * sizeof(T) / (n_dev != nullptr ? 2 : 1);
+  const size_t bytes = (size_t)n_expected * ctx->cfg.d_model * sizeof(T);
   const bool few = sizeof(T) == 4 && KM <= 2 && y_shared == nullptr;
   if (bytes <= COMBINE_TOGETHER_BYTES && !few) FMOE_COMBINE_LAUNCH(true);
   else FMOE_COMBINE_LAUNCH(false);
@@ -161,13 +163,13 @@ void launch_combine_t(const fmoe_ctx* ctx, const void* y, const void* y_shared, 
 
 int launch_combine(const fmoe_ctx* ctx, const void* y, const void* y_shared, const int32_t* inv_perm,
                    const float* topk_gate, const int32_t* kept_idx, int n_cap, const int32_t* n_dev,
-                   const void* residual, void* out, hipStream_t stream) {
+                   int n_expected, const void* residual, void* out, hipStream_t stream) {
   if (n_cap == 0) return FMOE_OK;
   fmoe_prof_scope prof(ctx, SLOT_COMBINE, stream);
   if (ctx->cfg.dtype == FMOE_BF16)
-    launch_combine_t<bf16_t, 0>(ctx, y, y_shared, inv_perm, topk_gate, kept_idx, n_cap, n_dev, residual, out, stream);
+    launch_combine_t<bf16_t, 0>(ctx, y, y_shared, inv_perm, topk_gate, kept_idx, n_cap, n_dev, n_expected, residual, out, stream);
   else
-    launch_combine_t<float, 0>(ctx, y, y_shared, inv_perm, topk_gate, kept_idx, n_cap, n_dev, residual, out, stream);
+    launch_combine_t<float, 0>(ctx, y, y_shared, inv_perm, topk_gate, kept_idx, n_cap, n_dev, n_expected, residual, out, stream);
   FMOE_HIP_CHECK(hipGetLastError());
   return FMOE_OK;
 }

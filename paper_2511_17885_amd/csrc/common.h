@@ -198,7 +198,7 @@ int launch_expert_ffn(const fmoe_ctx* ctx, const void* x, const int32_t* kept_id
 
 int launch_combine(const fmoe_ctx* ctx, const void* y, const void* y_shared, const int32_t* inv_perm,
                    const float* topk_gate, const int32_t* kept_idx, int n_cap, const int32_t* n_dev,
-                   const void* residual, void* out, hipStream_t stream);
+                   int n_expected, const void* residual, void* out, hipStream_t stream);
 
 // ---- diagnostics (diag.hip)
 int launch_adjacent_similarity(const float* probs, const uint8_t* is_visual, const int32_t* cu, int B, int T,
