@@ -1649,9 +1649,9 @@ def test_expert_ffn_thin_shape(n, d, F):
 
 
 @pytest.mark.parametrize("k,n_shared", [(0, 2), (1, 1), (6, 3), (16, 0)])
-@pytest.mark.parametrize("dtype,n", [(W.F32, 1300), (W.BF16, 2600)])
+@pytest.mark.parametrize("dtype,n", [(W.F32, 1300), (W.BF16, 2600), (W.F32, 4200), (W.BF16, 8300)])
 def test_combine_forms_agree_bit_for_bit(dtype, n, k, n_shared):
-    """Rows fetched together (small calls) and one after the other (here from 10 MB a row set on) are added in one
+    """Rows fetched together and one after the other (from 32 MB a row set on: the two longer calls) are added in one
     order: a few tokens on their own give the bits they have in the large call, unused slots included."""
     td = torch.bfloat16 if dtype == W.BF16 else torch.float32
     d, few = 2056, 33
