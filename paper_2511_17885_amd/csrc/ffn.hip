@@ -1028,8 +1028,8 @@ struct GemmArgs {
 };
 
 template <bool SWIGLU, int NRB, int SLOTS>   // NRB: live 16-row blocks of the tile; SLOTS: k tiles in a register ring
-__device__ __forceinline__ void f32_tile(const GemmProblem& P, const fmoe_tile& tile, int group, bool shared, int nt,
-                                         float* As) {
+__device__ __forceinline__ void f32_products(const GemmProblem& P, const fmoe_tile& tile, int group, bool shared, int nt,
+                                             float* As, f32x4_t (&acc)[NRB][2]) {
   constexpr int A_IT = (NRB + 1) / 2;   // 16-byte pieces of a k tile per thread
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -1092,7 +1092,6 @@ __device__ __forceinline__ void f32_tile(const GemmProblem& P, const fmoe_tile& 
     for (int it = 0; it < A_IT; ++it) *reinterpret_cast<f32x4_t*>(&As[buf * (FBM * FBK) + a_dst[it]]) = areg[slot][it];
   };
 
-  f32x4_t acc[NRB][2];
 #pragma unroll
   for (int rb = 0; rb < NRB; ++rb)
 #pragma unroll
@@ -1186,6 +1185,13 @@ whole_tiles_done:
     multiply(0, 0);
   }
 
+}
+
+template <bool SWIGLU, int NRB>
+__device__ __forceinline__ void f32_store(const GemmProblem& P, const fmoe_tile& tile, int group, bool shared, int nt,
+                                          const f32x4_t (&acc)[NRB][2]) {
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int N = P.N;
   // accumulator register v of lane l holds row 4*(l/16) + v, column l%16 of a 16x16 block
   float* C = P.C + (shared ? (size_t)group * P.c_group_off : 0);
 #pragma unroll
@@ -1206,9 +1212,259 @@ whole_tiles_done:
     }
 }
 
-template <bool SWIGLU>
-__global__ __launch_bounds__(256, 2) void grouped_gemm_kernel(GemmArgs a) {
-  __shared__ __align__(16) float As[2 * FBM * FBK];
+template <bool SWIGLU, int NRB, int SLOTS>
+__device__ __forceinline__ void f32_tile(const GemmProblem& P, const fmoe_tile& tile, int group, bool shared, int nt,
+                                         float* As) {
+  f32x4_t acc[NRB][2];
+  f32_products<SWIGLU, NRB, SLOTS>(P, tile, group, shared, nt, As, acc);
+  f32_store<SWIGLU, NRB>(P, tile, group, shared, nt, acc);
+}
+
+// ---- the same products on the bf16 matrix instruction, for reductions of F_SPLIT_K and more.  An fp32 value is the sum
+// of three bf16 values x1 + x2 + x3 (8 + 8 + 8 significant bits and two signs, exactly), and of the nine products of two
+// such sums the three of lowest order are below 2^-26 of the whole.  The other six take 6 * 16 cycles of the matrix pipe
+// per 16 x 16 block and 32 k where the fp32 instruction takes 8 * 32, and round their sums less often: x1*w1 in one
+// accumulator, once per 32 k, and the five small ones in another.  Error of the layer against 64 bits (1600 tokens, d 1280,
+// 64 experts of 896, two shared) 3.1e-7 -> 1.3e-7.
+//  * What bounds it is instruction issue: a matrix instruction keeps the vector unit from issuing for 8 of its 16
+//    cycles, and splitting costs 11 vector instructions per pair of values (the exact remainder by a dot product of two
+//    bf16 would be 7, but it waits for the matrix pipe).  So a value is split once per workgroup: rows and weights both go
+//    through LDS as three planes.  This also lets eight threads fetch a weight row's 128 bytes together; straight into
+//    matrix order, four neighbouring lanes ask for four rows, 64 lookups per load instruction instead of 16, and the
+//    address unit is what the kernel waits for (1358 items of the layer above: busy 67 % of the time, 42 % now).
+//  * LDS rows of 64 bytes; a row's four 16-byte pieces change places with (row / 4) % 4 so that the lanes which an
+//    LDS instruction serves together (0..3, 12..15, 20..27 and so on, of 64) fall on different banks: no conflicts,
+//    where the plain exchange by row / 4 has them in a third of the cycles (180 -> 171 us).
+//  * Two forms.  Two LDS buffers and two workgroups a CU: the next tile is split while the present one is multiplied.  One
+//    buffer and three workgroups: they cover for each other; better where there are enough of them (see F_WIDE_ITEMS).
+// Measured, gate/up + down, us, fp32 instruction / split: that layer with half of the visual tokens kept 214 + 117 / 166 + 89,
+// 3000 tokens 341 + 181 / 256 + 137, 416 tokens 100 + 49 / 77 + 43, one token 32 + 23 / 31 + 24; d 4096, 8 experts of 1536,
+// 400 tokens 156 + 66 / 118 + 52, 8 tokens 86 + 39 / 78 + 37.
+// A result that is not finite (infinities split into infinity and NaN), or so small that parts below the range of
+// bf16 could count in it, is computed again on the fp32 instruction.
+constexpr int F_SPLIT_K = 896;
+constexpr int S_ROWS = FBM + 128;              // rows of a k tile in LDS: the tile's, then the weights'
+constexpr int S_PLANE = S_ROWS * FBK;          // one part of a k tile, in bf16 elements
+constexpr int S_BUF = 3 * S_PLANE;             // a buffer
+// Three workgroups a CU from this many rows an expert and work items on (capacities).  One buffer / two, us: 1600 tokens
+// of the layer above 255 / 264, 416 tokens 120 / 128, 250 tokens 114 / 116, 120 tokens 103 / 97; d 1288, 16 experts of 904
+// and a shared one, 2000 tokens 206 / 214, 600 tokens 113 / 110; d 4096, 8 experts of 1536, 400 tokens 203 / 170.
+constexpr int F_WIDE_ROWS = 20;
+constexpr int F_WIDE_ITEMS = 1024;
+constexpr float F_TINY = 0x1p-60f;             // parts lost are below 2^-125 of an operand
+// The three parts of four values: each the nearest bf16 to what the ones before leave over.
+__device__ __forceinline__ void split_bf16(f32x4_t v, uint2 (&part)[3]) {
+  typedef __attribute__((__vector_size__(2 * sizeof(__bf16)))) __bf16 bf16x2_t;
+  typedef __attribute__((__vector_size__(2 * sizeof(float)))) float f32x2_t;
+#pragma unroll
+  for (int p = 0; p < 3; ++p) {
+    uint32_t w[2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      w[i] = __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2_t{v[2 * i], v[2 * i + 1]}, bf16x2_t));
+      if (p < 2) {   // what is left over, exactly
+        v[2 * i] -= __uint_as_float(w[i] << 16);
+        v[2 * i + 1] -= __uint_as_float(w[i] & 0xffff0000u);
+      }
+    }
+    part[p] = make_uint2(w[0], w[1]);
+  }
+}
+
+// SLOTS: k tiles in a register ring, BUFS: LDS buffers
+template <bool SWIGLU, int NRB, int SLOTS, int BUFS>
+__device__ __forceinline__ void split_products(const GemmProblem& P, const fmoe_tile& tile, int group, bool shared, int nt,
+                                               bf16_t* As, f32x4_t (&acc)[NRB][2]) {
+  constexpr int A_IT = (NRB + 1) / 2, IT = A_IT + 4;   // 16-byte pieces of a k tile per thread: of the rows; with the weights
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int N = P.N, K = P.K;
+  const int NT = K / FBK;               // whole k tiles
+  const int chunk = tid & 7;            // every eight threads fetch the 128 bytes of a row's k tile
+  // weight row 32*it + tid/8 in LDS: wavefront it's fragment tid/128, column (tid/8)%16 (past N the last one again,
+  // never stored)
+  const int f_load = wave >> 1;         // scalar
+  const int n0 = SWIGLU ? nt * 64 : nt * 128 + f_load * 16;
+  const int base = n0 < N ? n0 : N - 1;
+  const float* B = (SWIGLU && f_load ? P.B1 : P.B0) + (size_t)group * P.group_stride + (size_t)base * P.ldb;
+  const __amdgpu_buffer_rsrc_t b_rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(B), 0, 0xffffffff, 0x00020000);
+  uint32_t b_off[4];
+#pragma unroll
+  for (int it = 0; it < 4; ++it) {
+    const int n = n0 + it * (SWIGLU ? 16 : 32) + ((tid >> 3) & 15);
+    b_off[it] = ((uint32_t)((n < N ? n : N - 1) - base) * (uint32_t)P.ldb + (uint32_t)chunk * 4u) * 4u;
+  }
+  f32x4_t raw[SLOTS][IT];
+  auto load_b = [&](int slot, int t) {   // past the last tile the last one again
+    const uint32_t off = (uint32_t)(t < NT ? t : NT - 1) * (FBK * 4);   // scalar
+#pragma unroll
+    for (int it = 0; it < 4; ++it)
+      raw[slot][A_IT + it] = __builtin_bit_cast(f32x4_t, __builtin_amdgcn_raw_buffer_load_b128(b_rsrc, b_off[it], off, 0));
+  };
+  if (NT > 0) {   // uniform; the weights do not wait for the row indices
+#pragma unroll
+    for (int t = 0; t < SLOTS; ++t) {
+      load_b(t, t);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  }
+  const float* a_src[A_IT];
+#pragma unroll
+  for (int it = 0; it < A_IT; ++it) {
+    const int r = 32 * it + (tid >> 3);
+    int src = tile.row0 + (r < tile.rows ? r : tile.rows - 1);
+    if (P.map1) {
+      src = P.map1[src];
+      if (P.map1_limit > 0) src = src < 0 ? 0 : (src >= P.map1_limit ? P.map1_limit - 1 : src);
+    }
+    if (P.map2) src = P.map2[src];
+    a_src[it] = P.A + (shared ? (size_t)group * P.a_group_off : 0) + (size_t)src * P.lda + chunk * 4;
+  }
+  auto load_a = [&](int slot, int t) {
+    const int off = (t < NT ? t : NT - 1) * FBK;   // scalar
+#pragma unroll
+    for (int it = 0; it < A_IT; ++it) raw[slot][it] = *reinterpret_cast<const f32x4_t*>(a_src[it] + off);
+  };
+  // LDS: quarter q of a row holds k = 4q..4q+3 and 16+4q..16+4q+3, on both sides
+  const int l_row = tid >> 3;
+  auto place = [](int q, int row) { return (q ^ (0x1320 >> (row & 12))) & 3; };
+  bf16_t* const dst = As + l_row * FBK + place(chunk & 3, l_row) * 8 + (chunk >> 2) * 4;
+  const bf16_t* const frag = As + (lane & 15) * FBK + place(lane >> 4, lane & 15) * 8;
+  auto store = [&](int buf, int slot) {
+#pragma unroll
+    for (int it = 0; it < IT; ++it) {
+      uint2 part[3];
+      split_bf16(raw[slot][it], part);
+      const int row = it < A_IT ? 32 * it : FBM + 32 * (it - A_IT);
+#pragma unroll
+      for (int p = 0; p < 3; ++p) *reinterpret_cast<uint2*>(dst + buf * S_BUF + p * S_PLANE + row * FBK) = part[p];
+    }
+  };
+  f32x4_t low[NRB][2];   // the products with lower parts
+#pragma unroll
+  for (int rb = 0; rb < NRB; ++rb)
+#pragma unroll
+    for (int f = 0; f < 2; ++f) acc[rb][f] = low[rb][f] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+  auto multiply = [&](int buf) {
+    bf16x8_t fa[3][NRB], fb[3][2];
+#pragma unroll
+    for (int p = 0; p < 3; ++p) {
+#pragma unroll
+      for (int f = 0; f < 2; ++f)
+        fb[p][f] = *reinterpret_cast<const bf16x8_t*>(frag + buf * S_BUF + p * S_PLANE + (FBM + wave * 32 + f * 16) * FBK);
+#pragma unroll
+      for (int rb = 0; rb < NRB; ++rb)
+        fa[p][rb] = *reinterpret_cast<const bf16x8_t*>(frag + buf * S_BUF + p * S_PLANE + rb * 16 * FBK);
+    }
+    auto products = [&](int pa, int pb, f32x4_t (&sum)[NRB][2]) {
+#pragma unroll
+      for (int rb = 0; rb < NRB; ++rb)
+#pragma unroll
+        for (int f = 0; f < 2; ++f)
+          sum[rb][f] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa[pa][rb], fb[pb][f], sum[rb][f], 0, 0, 0);
+    };
+    products(0, 0, acc);
+    products(0, 1, low);
+    products(1, 0, low);
+    products(1, 1, low);
+    products(0, 2, low);
+    products(2, 0, low);
+  };
+  if (NT > 0) {   // uniform
+#pragma unroll
+    for (int t = 0; t < SLOTS; ++t) {
+      load_a(t, t);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    if constexpr (BUFS == 2) {
+      store(0, 0);
+      load_b(0, SLOTS);
+      load_a(0, SLOTS);
+      __syncthreads();
+    }
+    auto step = [&](int u, int t) {
+      if constexpr (BUFS == 2) {   // products of tile t, parts of tile t+1 into the other buffer, loads of tile t+1+SLOTS
+        multiply(u & 1);
+        store((u + 1) & 1, (u + 1) % SLOTS);
+        load_b((u + 1) % SLOTS, t + 1 + SLOTS);
+        load_a((u + 1) % SLOTS, t + 1 + SLOTS);
+      } else {                     // parts of tile t, loads of tile t+SLOTS, products of tile t
+        store(0, u);
+        __builtin_amdgcn_sched_barrier(0);
+        load_b(u, t + SLOTS);
+        load_a(u, t + SLOTS);
+        __builtin_amdgcn_sched_barrier(0);
+        __syncthreads();
+        multiply(0);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+      __syncthreads();   // all are done with tile t (and tile t+1 is in LDS)
+    };
+    static_assert(BUFS == 1 || SLOTS % 2 == 0, "ring slots and LDS buffers are compile-time");
+    int t0 = 0;
+    for (; t0 + SLOTS <= NT; t0 += SLOTS) {   // no exit inside, so that the waits can count on the ring's order
+#pragma unroll
+      for (int u = 0; u < SLOTS; ++u) step(u, t0 + u);
+    }
+    static_for<0, SLOTS - 1>([&](auto u) {
+      if (t0 + decltype(u)::value < NT) step(decltype(u)::value, t0 + decltype(u)::value);   // uniform
+    });
+  }
+  if (NT * FBK < K) {   // uniform: the last, partial tile; what lies past K counts as zero on both sides
+    const f32x4_t zero = {0.f, 0.f, 0.f, 0.f};
+    const int k0 = NT * FBK;
+    const bool in = k0 + chunk * 4 < K;
+#pragma unroll
+    for (int it = 0; it < A_IT; ++it) {
+      const f32x4_t v = *reinterpret_cast<const f32x4_t*>(a_src[it] + (in ? k0 : K - 4 - chunk * 4));
+      raw[0][it] = in ? v : zero;
+    }
+#pragma unroll
+    for (int it = 0; it < 4; ++it) {
+      const uint32_t off = b_off[it] + (uint32_t)(in ? k0 : K - 4 - chunk * 4) * 4u;
+      const f32x4_t v = __builtin_bit_cast(f32x4_t, __builtin_amdgcn_raw_buffer_load_b128(b_rsrc, off, 0, 0));
+      raw[0][A_IT + it] = in ? v : zero;
+    }
+    store(0, 0);   // the loop's last barrier is behind every reader of the buffers
+    __syncthreads();
+    multiply(0);
+  }
+#pragma unroll
+  for (int rb = 0; rb < NRB; ++rb)
+#pragma unroll
+    for (int f = 0; f < 2; ++f) acc[rb][f] += low[rb][f];
+}
+
+template <bool SWIGLU, int NRB, int SLOTS, int BUFS>
+__device__ __forceinline__ void split_tile(const GemmProblem& P, const fmoe_tile& tile, int group, bool shared, int nt,
+                                           bf16_t* As) {
+  f32x4_t acc[NRB][2];
+  split_products<SWIGLU, NRB, SLOTS, BUFS>(P, tile, group, shared, nt, As, acc);
+  auto again = [](float v) { return !(fabsf(v) < __builtin_inff()) || (fabsf(v) < F_TINY && v != 0.0f); };
+  bool any = false;
+#pragma unroll
+  for (int rb = 0; rb < NRB; ++rb)
+#pragma unroll
+    for (int f = 0; f < 2; ++f)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) any |= again(acc[rb][f][v]);
+  if (__syncthreads_or(any)) {
+    f32x4_t whole[NRB][2];
+    f32_products<SWIGLU, NRB, 2>(P, tile, group, shared, nt, reinterpret_cast<float*>(As), whole);
+#pragma unroll
+    for (int rb = 0; rb < NRB; ++rb)
+#pragma unroll
+      for (int f = 0; f < 2; ++f)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) acc[rb][f][v] = again(acc[rb][f][v]) ? whole[rb][f][v] : acc[rb][f][v];
+  }
+  f32_store<SWIGLU, NRB>(P, tile, group, shared, nt, acc);
+}
+
+// SPLIT: 0 on the fp32 instruction, else split, with so many LDS buffers
+template <bool SWIGLU, int SPLIT>
+__global__ __launch_bounds__(256, SPLIT == 1 ? 3 : 2) void grouped_gemm_kernel(GemmArgs a) {
+  __shared__ __align__(16) float As[SPLIT ? SPLIT * S_BUF / 2 : 2 * FBM * FBK];
 
   // XCD-aware decode of the linear block id, as in the weight-stream kernel: row tiles dealt round-robin over
   // the XCDs, the blocks of a group with several row tiles re-dealt column-major so that one XCD fetches a
@@ -1244,7 +1500,19 @@ __global__ __launch_bounds__(256, 2) void grouped_gemm_kernel(GemmArgs a) {
   const int nt = tile.col0 + nt_launch;
   const int group = shared ? tile.group - a.E : tile.group;
   const bool deep = n_tiles * a.n_col_tiles_max <= F_DEEP_ITEMS && P.K >= F_DEEP_K;   // uniform
-  switch ((tile.rows + 15) >> 4) {   // live 16-row blocks of the tile, uniform per block
+  const int row_blocks = (tile.rows + 15) >> 4;   // live 16-row blocks of the tile, uniform per block
+  if constexpr (SPLIT != 0) {
+    constexpr int FEW = SPLIT == 2 ? 4 : 2, MORE = SPLIT == 2 ? 2 : 1;   // ring slots
+    bf16_t* const parts = reinterpret_cast<bf16_t*>(As);
+    switch (row_blocks) {
+      case 1: split_tile<SWIGLU, 1, FEW, SPLIT>(P, tile, group, shared, nt, parts); break;
+      case 2: split_tile<SWIGLU, 2, FEW, SPLIT>(P, tile, group, shared, nt, parts); break;
+      case 3: split_tile<SWIGLU, 3, MORE, SPLIT>(P, tile, group, shared, nt, parts); break;
+      default: split_tile<SWIGLU, 4, MORE, SPLIT>(P, tile, group, shared, nt, parts); break;
+    }
+    return;
+  }
+  switch (row_blocks) {
     case 1:
       if (deep) f32_tile<SWIGLU, 1, 4>(P, tile, group, shared, nt, As);
       else f32_tile<SWIGLU, 1, 2>(P, tile, group, shared, nt, As);
@@ -1382,15 +1650,24 @@ int run_ffn_f32(const fmoe_ctx* ctx, const void* x, const int32_t* kept_idx, int
     g2.n_col_tiles_max = geo.cols2;
   }
   const unsigned batches = (unsigned)((geo.tile_cap + 7) / 8);
+  // Split products: by the lengths of the reductions alone, so that a token's result does not depend on its batch.
+  const bool split = d >= F_SPLIT_K && F >= F_SPLIT_K && (Ft == 0 || Fs >= F_SPLIT_K);
+  const long long rows = (long long)n_cap * ctx->kmax;
+  const bool wide = rows >= (long long)F_WIDE_ROWS * E && (E + rows / FBM) * geo.cols1 >= F_WIDE_ITEMS;
+  auto launch = [&](auto swiglu, const GemmArgs& g) {
+    constexpr bool S = decltype(swiglu)::value;
+    const dim3 grid(batches * 8 * g.n_col_tiles_max), block(256);
+    if (!split) hipLaunchKernelGGL((grouped_gemm_kernel<S, 0>), grid, block, 0, stream, g);
+    else if (wide) hipLaunchKernelGGL((grouped_gemm_kernel<S, 1>), grid, block, 0, stream, g);
+    else hipLaunchKernelGGL((grouped_gemm_kernel<S, 2>), grid, block, 0, stream, g);
+  };
   {
     fmoe_prof_scope prof(ctx, SLOT_GEMM1, stream);
-    hipLaunchKernelGGL(grouped_gemm_kernel<true>, dim3(batches * 8 * g1.n_col_tiles_max),
-                       dim3(256), 0, stream, g1);
+    launch(std::true_type{}, g1);
   }
   {
     fmoe_prof_scope prof(ctx, SLOT_GEMM2, stream);
-    hipLaunchKernelGGL(grouped_gemm_kernel<false>, dim3(batches * 8 * g2.n_col_tiles_max),
-                       dim3(256), 0, stream, g2);
+    launch(std::false_type{}, g2);
   }
   return FMOE_OK;
 }

@@ -1619,6 +1619,58 @@ def test_expert_ffn_fp32_long_reductions_of_few_rows(d, F, E):
             assert max_rel_err(host(y)[lo:lo + c], ref) <= TOL[W.F32], (e, c)
 
 
+@pytest.mark.parametrize("d,F", [(896, 904), (1000, 912), (928, 896)])
+def test_expert_ffn_fp32_split_products(d, F):
+    """The fp32 expert GEMMs on the bf16 instruction (both reductions long) at every count of live 16-row blocks of a tile
+    and around its edges, whole and partial k tiles, column counts that end inside a block, in both forms (a call of
+    few tokens and one of many, which give the same bits); rows that the instruction cannot hold: an infinity that must
+    not become NaN, values near the largest, a row whose up projection is below the range of the lower parts; against
+    fp64 at the fp32 bound (TOL)."""
+    counts = [0, 1, 15, 16, 17, 31, 33, 48, 49, 63, 64, 65, 130]
+    E, n, n_many, M = len(counts), 150, 1200, sum(counts)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(d * 1000 + F)
+    rnd = lambda *s: torch.randn(s, generator=g, device="cuda")
+    x, wr = rnd(n_many, d), rnd(E, d)
+    w = [rnd(E, F, d) * 0.1, rnd(E, F, d) * 0.1, rnd(E, d, F) * 0.1]
+    sh = [rnd(1, F, d) * 0.1, rnd(1, F, d) * 0.1, rnd(1, d, F) * 0.1]
+    half = d // 2
+    w[0][8, :, half:], w[1][8, :, :half] = 0.0, 0.0      # expert 8: gates from the first half of a row, ups from the second
+    w[0][9], w[1][9], w[2][9] = (t[9].abs().clamp_min(1e-6) for t in w)   # expert 9: nothing cancels, infinity meets no zero
+    w[0][10], w[1][10], w[2][10] = w[0][10].abs() * 3e-22, w[1][10].abs() * 3e-22, w[2][10].abs() * 1e-6
+    x[1, half:] *= 1e-33
+    x[2, 7] = float("inf")
+    x[3] = 3.4e38
+    m = binding.FMoE(d_model=d, n_experts=E, d_ffn=F, n_shared=1, d_ffn_shared=F, k_text=4, k_visual=4, dtype="f32")
+    m.set_weights(wr, None, *w, *sh)
+    perm = torch.randint(4, n, (M,), generator=g, device="cuda").int()
+    first = np.cumsum([0] + counts)
+    special = {8: 1, 9: 2, 10: 3}
+    for e, row in special.items():
+        perm[int(first[e]) + 20] = row
+    offs = torch.tensor(np.concatenate([[0], np.cumsum(counts)]), dtype=torch.int32, device="cuda")
+    y, ysh = m.expert_ffn(x, None, n, offs, perm)
+    y_many, ysh_many = m.expert_ffn(x, None, n_many, offs, perm)
+    assert torch.equal(y[:M].view(torch.int32), y_many[:M].view(torch.int32))
+    assert torch.equal(ysh[0, :n].view(torch.int32), ysh_many[0, :n].view(torch.int32))
+
+    def ffn(v, a, b, c):
+        v, a, b, c = (t.double() for t in (v, a, b, c))
+        return ((torch.nn.functional.silu(v @ a.T) * (v @ b.T)) @ c.T).cpu().numpy()
+
+    for e, (lo, c) in enumerate(zip(first, counts)):
+        got, ref = host(y)[lo:lo + c], ffn(x[perm[lo:lo + c].long()], w[0][e], w[1][e], w[2][e])
+        if e in special:      # on its own scale
+            if e == 9:
+                assert np.isposinf(got[20]).all()
+            else:
+                assert max_rel_err(got[20], ref[20]) <= TOL[W.F32], e
+            got, ref = np.delete(got, 20, 0), np.delete(ref, 20, 0)
+        if c and e != 10:     # (ordinary rows times expert 10's weights are below fp32's range)
+            assert max_rel_err(got, ref) <= TOL[W.F32], (e, c)
+    assert max_rel_err(host(ysh)[0, 4:n], ffn(x[4:n], sh[0][0], sh[1][0], sh[2][0])) <= TOL[W.F32]
+
+
 @pytest.mark.parametrize("n,d,F", [(1, 8, 8), (3, 136, 40), (8, 712, 456), (15, 392, 776), (16, 1288, 264), (16, 616, 248)])
 def test_expert_ffn_thin_shape(n, d, F):
     """Calls of at most 16 tokens take a kernel shape of their own: the same bits as the weight-stream shape
