@@ -123,12 +123,6 @@ fmoe_ws_layout fmoe_layout(const fmoe_ctx* ctx, int32_t max_tokens, int32_t max_
   L.seq_nv = take(B * 4);
   L.win_s = take(T * 4);
   L.win_a = take(T * 4);
-  L.drop_from = take(T * 4);
-  L.keep_prefix = take((T + 1) * 4);
-  L.compact_blk = take((T / 1024 + 2) * 4);
-  L.rank_c = take(T * 4);
-  L.win_merged = take(T * 4);
-  L.merged_before = take(T * 4);
   L.is_merged = take(T);
   L.vis_out = take(T);
   L.x_merged = take(T * (size_t)c.d_model * es);
@@ -604,7 +598,7 @@ const char* fmoe_profile_name(int slot) {
   // kernel symbols (the two expert GEMMs: bf16 symbol; fp32 contexts run grouped_gemm_kernel, calls of at most 16
   // tokens ffn_thin_kernel; scan and scatter in one launch are timed as the scatter)
   static const char* names[SLOT_COUNT] = {
-      "route_kernel", "seq_ordinals_kernel", "window_score_kernel", "select_kernel", "compact_flag_kernel+compact_write_kernel",
+      "route_kernel", "seq_ordinals_kernel", "window_score_kernel", "compact_kernel",
       "prune_dispatch_small_kernel", "permute_count_kernel", "permute_scan_kernel",
       "permute_scatter_kernel", "build_tiles_kernel", "ffn_stream_kernel<true>",
       "ffn_stream_kernel<false>", "combine_kernel", "ffn_dense_kernel<true>", "ffn_dense_kernel<false>"};

@@ -44,7 +44,7 @@
 
 // ---- optional per-kernel timing (instrumentation; off by default)
 enum fmoe_kernel_slot {
-  SLOT_ROUTE = 0, SLOT_ORDINALS, SLOT_SCORES, SLOT_SELECT, SLOT_COMPACT, SLOT_DISPATCH,
+  SLOT_ROUTE = 0, SLOT_ORDINALS, SLOT_SCORES, SLOT_COMPACT, SLOT_DISPATCH,
   SLOT_PERM_COUNT, SLOT_PERM_SCAN, SLOT_PERM_SCATTER, SLOT_TILES, SLOT_GEMM1, SLOT_GEMM2,
   SLOT_COMBINE, SLOT_GEMM1_DENSE, SLOT_GEMM2_DENSE, SLOT_COUNT
 };
@@ -96,9 +96,7 @@ int fmoe_fail(int code, const char* fmt, ...);
 struct fmoe_ws_layout {
   size_t probs, topk_idx, topk_gate;            // layer_forward intermediates
   size_t vis_tok, vis_ord, seq_nv;              // prune
-  size_t win_s, win_a, drop_from, keep_prefix;  // prune
-  size_t compact_blk;                           // prune: kept tokens per block of the compaction
-  size_t rank_c, win_merged, merged_before;     // prune with window merging
+  size_t win_s, win_a;                          // prune
   size_t is_merged, vis_out, x_merged;          // layer_forward with window merging
   size_t slot_rank, blk_count;                  // permute
   size_t expert_offsets, perm_src, inv_perm;    // layer_forward intermediates

@@ -38,8 +38,19 @@ __device__ __forceinline__ float wave_sum_butterfly(float p) {
   return p + row_rotate<1>(p);
 }
 
+__device__ __forceinline__ uint32_t wave_or(uint32_t v) {   // over all lanes, in every lane
+  const auto h = __builtin_amdgcn_permlane32_swap(v, v, false, false);
+  v = h[0] | h[1];
+  const auto q = __builtin_amdgcn_permlane16_swap(v, v, false, false);
+  v = q[0] | q[1];
+  v |= __builtin_amdgcn_update_dpp(0, v, 0x128, 0xf, 0xf, false);
+  v |= __builtin_amdgcn_update_dpp(0, v, 0x124, 0xf, 0xf, false);
+  v |= __builtin_amdgcn_update_dpp(0, v, 0x122, 0xf, 0xf, false);
+  return v | __builtin_amdgcn_update_dpp(0, v, 0x121, 0xf, 0xf, false);
+}
+
 // ---- A: visual ordinals.  One block per sequence.
-// vis_ord[t] = number of visual tokens before t in its sequence (for visual t), -1 for text;
+// vis_ord[t] = number of visual tokens before t in its sequence, as ~(that number) < 0 for text;
 // vis_tok[cu[b] + j] = global index of the j-th visual token of sequence b; seq_nv[b] = N_v.
 __global__ __launch_bounds__(256) void seq_ordinals_kernel(
     const uint8_t* __restrict__ is_visual, const int32_t* __restrict__ cu, int T,
@@ -66,15 +77,9 @@ template <bool STAGED>
 __global__ __launch_bounds__(256) void window_score_kernel(
     const float* __restrict__ probs, const int32_t* __restrict__ cu, int B, int T, int E, int W,
     int sim_mode, const int32_t* __restrict__ vis_tok, const int32_t* __restrict__ seq_nv,
-    const float* __restrict__ attn, float* __restrict__ win_s, float* __restrict__ win_a,
-    int32_t* __restrict__ precede, int32_t* __restrict__ rank_c) {
+    const float* __restrict__ attn, float* __restrict__ win_s, float* __restrict__ win_a) {
   __shared__ float tile_all[STAGED ? 4 * WS_TILE : 1];
   const int lane = threadIdx.x & 63;
-  // counters of the drop order (accumulated by select_kernel), cleared for every slot
-  for (int g = blockIdx.x * 256 + threadIdx.x; g < T; g += gridDim.x * 256) {
-    precede[g] = 0;
-    if (rank_c != nullptr) rank_c[g] = 0;
-  }
   const int u = blockIdx.x * 4 + (threadIdx.x >> 6);
   int lo = 0, hi = B - 1;   // largest b with unit_base(b) <= u
   while (lo < hi) {
@@ -203,277 +208,533 @@ __global__ __launch_bounds__(256) void window_score_kernel(
   if (lane == 0) win_s[g] = S;
 }
 
-// ---- C: drop order.  The drop order (normalised attention asc, score desc, index asc) is total, so
-// "how many windows precede window i" fixes everything.  The count is an all-pairs comparison on
-// integer sort keys, split two ways over the grid: blockIdx.x owns 256 window slots (i), blockIdx.y
-// a run of 64 candidate windows (j) of the same sequence, staged through LDS; partial counts are
-// added with integer atomics (order-free).  Bit 30 of the sum records that the sequence's last
-// (possibly shorter) window precedes i.
-constexpr int SEL_JC = 64;
-
-__global__ __launch_bounds__(256) void select_kernel(
-    const int32_t* __restrict__ cu, int B, int T, int W, float alpha,
-    const int32_t* __restrict__ seq_nv, const float* __restrict__ win_s,
-    const float* __restrict__ win_a, int32_t* __restrict__ precede, float* __restrict__ scores_out,
-    int32_t* __restrict__ rank_c, const int32_t* __restrict__ only_merged) {
-  // rank_c (window merging): also count the predecessors in the merge order (C desc, index asc).
-  // only_merged (second pass of window merging): count only predecessors whose flag is set.
-  __shared__ __align__(16) unsigned long long tileK[SEL_JC];   // (~key(C) << 32) | index: ascending = drop order
-  __shared__ __align__(16) uint32_t tileA[SEL_JC];             // key(A)
-  __shared__ float red[4];
-  const int g0 = blockIdx.x * 256;
-  const int g = g0 + threadIdx.x;
-  const int g_last = (g0 + 255 < T - 1) ? g0 + 255 : T - 1;
-  const int jbase = blockIdx.y * SEL_JC;
-  const int b_first = find_seq(cu, B, g0), b_last = find_seq(cu, B, g_last);
-  const bool has_attn = (win_a != nullptr);
-  const float one_minus_alpha = 1.0f - alpha;
-  for (int b = b_first; b <= b_last; ++b) {   // uniform over the block
-    int s, e;
-    seq_range(cu, b, T, s, e);
-    const int nv = seq_nv[b];
-    const int n = (nv + W - 1) / W;
-    if (jbase >= n || s + n <= g0 || s > g_last) continue;
-    // per-sequence attention maximum (Eq.12)
-    float amax = 0.0f;
-    if (has_attn) {
-      float m = 0.0f;
-      for (int j = threadIdx.x; j < n; j += 256) {
-        const float a = win_a[s + j];
-        m = (a > m) ? a : m;
-      }
-#pragma unroll
-      for (int sh = 32; sh >= 1; sh >>= 1) {
-        const float o = __shfl_xor(m, sh, 64);
-        m = (o > m) ? o : m;
-      }
-      __syncthreads();
-      if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = m;
-      __syncthreads();
-      amax = red[0];
-#pragma unroll
-      for (int w = 1; w < 4; ++w) amax = (red[w] > amax) ? red[w] : amax;
-    }
-    auto score = [&](int j, float& Aj) -> float {   // Eq.13 (C = S exactly without attention)
-      return redundancy_score(win_s[s + j], has_attn, has_attn ? win_a[s + j] : 0.0f, amax, alpha,
-                              one_minus_alpha, Aj);
-    };
-    const int i = g - s;
-    const bool mine = (g < T) && i >= 0 && i < n;
-    unsigned long long Ki = 0ull;
-    uint32_t Ai = 0u;
-    if (mine) {
-      float a;
-      const float c = score(i, a);
-      if (scores_out != nullptr && blockIdx.y == 0) scores_out[g] = c;
-      Ki = ((unsigned long long)(~float_order_key(c)) << 32) | (uint32_t)i;
-      Ai = float_order_key(a);
-    }
-    int count = 0, last_first = 0, count_c = 0;
-    for (int j0 = jbase; j0 < n; j0 += (int)gridDim.y * SEL_JC) {   // uniform
-      __syncthreads();
-      if (threadIdx.x < SEL_JC) {
-        const int jl = j0 + threadIdx.x;
-        unsigned long long kj = ~0ull;   // sentinel: precedes nothing
-        uint32_t aj = ~0u;
-        if (jl < n && (only_merged == nullptr || only_merged[s + jl] != 0)) {
-          float a;
-          const float c = score(jl, a);
-          kj = ((unsigned long long)(~float_order_key(c)) << 32) | (uint32_t)jl;
-          aj = float_order_key(a);
-        }
-        tileK[threadIdx.x] = kj;
-        tileA[threadIdx.x] = aj;
-      }
-      __syncthreads();
-      if (mine) {
-#pragma unroll
-        for (int jj = 0; jj < SEL_JC; ++jj) {
-          const unsigned long long K = tileK[jj];
-          const uint32_t A = tileA[jj];
-          const int first = (int)(A < Ai) | ((int)(A == Ai) & (int)(K < Ki));
-          count += first;
-          last_first |= first & (int)(j0 + jj == n - 1);
-          count_c += (int)(K < Ki);
-        }
-      }
-    }
-    if (mine && (count | last_first)) atomicAdd(&precede[g], count + (last_first << 30));
-    if (mine && rank_c != nullptr && count_c) atomicAdd(&rank_c[g], count_c);
-  }
-}
-
-// ---- C2: window merging (Sec. 3.2.3, Eq.14-15): which windows merge.  One thread per window slot;
-// the greedy walk is evaluated in closed form from the window's place in the merge order and the
-// place of the sequence's last window (merge_plan).  Also clears the counter of the second counting
-// pass.
-__global__ __launch_bounds__(256) void merge_decide_kernel(
-    const int32_t* __restrict__ cu, int B, int T, int W, float retention, float gamma,
-    const int32_t* __restrict__ seq_nv, const int32_t* __restrict__ rank_c,
-    int32_t* __restrict__ win_merged, int32_t* __restrict__ merged_before) {
-  const int g = blockIdx.x * 256 + threadIdx.x;
-  if (g >= T) return;
-  merged_before[g] = 0;
-  win_merged[g] = 0;
-  const int b = find_seq(cu, B, g);
-  int s, e;
-  seq_range(cu, b, T, s, e);
-  const int nv = seq_nv[b];
-  const int n = (nv + W - 1) / W;
-  const int i = g - s;
-  if (i < 0 || i >= n) return;
-  const int w_last = nv - (n - 1) * W;
-  const bool short_last = w_last < W;
-  const int L = short_last ? rank_c[s + n - 1] : n;
-  const fmoe_merge_plan p = merge_plan(nv, W, retention, gamma, L);
-  int m;
-  if (short_last && i == n - 1) {
-    m = p.last_m;
-  } else {
-    const int r = rank_c[g];
-    const int k = r - ((short_last && L < r) ? 1 : 0);   // place among the full-size windows
-    m = k < p.q_full ? 1 : 0;
-  }
-  win_merged[g] = m;
-}
-
-// ---- D: budget + compaction, in two launches over blocks of CP_BLOCK positions (a position is a token
-// index, or T itself, which only carries the total).
-//   compact_flag_kernel:  every position decides keep / drop on its own (text tokens and the leading tokens
-//                         of each window stay) and stores (kept positions before it in its block) * 4 +
-//                         merged * 2 + keep in keep_code; every block stores its number of kept tokens.
-//   compact_write_kernel: a block's first output index is the sum of the counts of the blocks before it;
-//                         kept tokens write their ascending index lists; new_cu[b] = kept tokens before
-//                         cu[b], read off the same two arrays.
-// The decision is a chain of dependent loads per token (its visual ordinal -> its sequence -> its
-// window's counters), which is why it is spread over the chip instead of walked by one block.
-constexpr int CP_BLOCK = 1024;
+// ---- C: drop order, merged set, budget and compaction in one launch over blocks of CP_BLOCK positions.
+// The drop order (normalised attention asc, score desc, index asc) and the merge order (score desc, index asc) are
+// total, and of the places in them only two matters: where merging ends and where the drop budget ends.  So nobody
+// ranks the windows: every block finds, for the sequences that its positions belong to, those two windows by a radix
+// selection over integer keys, after which a window's fate is one comparison, and counts what is dropped ahead of its
+// first position; sequences before that have dropped exactly their budget.  Blocks need nothing from each other.
+// Bound: latency, a dozen barriers between LDS passes over a few keys a thread; the uniform arithmetic is paid once per
+// wavefront of a SIMD, hence 512 threads and not 1024 (12.6 -> 8.9 us inside the kernel at 4096 tokens; 256: 9.6).
+// In place of counting all pairs of windows, deciding, flagging and writing (three launches, five with merging and
+// attention), average kernel times: 4096 tokens, 1280 windows 17.0 -> 10.4 us; 8192 tokens, 1588 windows 17.5 -> 10.7; three
+// ragged sequences of 5003 tokens, one of them short, 14.9 -> 12.8; 1600 tokens, merging and attention 24.4 -> 15.4.
+// Sequences of up to CP_WAVE_N windows are decided by a wavefront each (lane = window, ranks by counting), so that a
+// block with many short ones does not walk them one barrier at a time.
+constexpr int CP_BLOCK = 512;
+constexpr int CP_WAVES = CP_BLOCK / 64;
+constexpr int CP_KEYS = 4096;     // windows of a sequence whose keys stay in LDS; those past it are formed again
+constexpr int CP_WAVE_N = 64;     // windows of a sequence that one wavefront decides
+constexpr int CP_RANK = 8;        // candidates of a selection that are ranked by counting
+constexpr int CP_SEQS = 512;      // sequences whose bounds stay in LDS
 
 struct CompactArgs {
   const uint8_t* is_visual;
   const int32_t* cu;
   int B, T, W;
-  float retention, gamma;
+  float retention, gamma, alpha;
   const int32_t* vis_ord;
   const int32_t* seq_nv;
-  const int32_t* precede;
-  const int32_t* rank_c;          // gamma > 0
-  const int32_t* win_merged;      // gamma > 0 with an attention term; nullptr: closed form (see below)
-  const int32_t* merged_before;
-  int32_t* keep_code;             // [T + 1]
-  int32_t* blk_kept;              // [ceil((T + 1) / CP_BLOCK)]
+  const float* win_s;
+  const float* win_a;             // nullptr without attention importance
+  float* scores_out;              // or nullptr
   int32_t* kept_idx;
   int32_t* new_cu;
   uint8_t* is_visual_out;         // or nullptr
   uint8_t* is_merged_out;         // or nullptr
+  unsigned long long window_rcp;  // ceil(2^37 / W)
 };
-
-// largest b in [0,n) with clamp(cu[b]) <= g
-__device__ __forceinline__ int find_seq_clamped(const int32_t* cu, int n, int T, int g) {
-  int lo = 0, hi = n - 1;
-  while (lo < hi) {
-    const int mid = (lo + hi + 1) >> 1;
-    if (clampi(cu[mid], 0, T) <= g) lo = mid; else hi = mid - 1;
-  }
-  return lo;
+// v / W, exactly: W <= 64 and 0 <= v < 2^24, so the error of the product is below 2^24 in 2^37, less than 1 / W
+__device__ __forceinline__ int per_window(const CompactArgs& a, int v) {
+  return (int)(((unsigned long long)(uint32_t)v * a.window_rcp) >> 37);
 }
 
-// bit 0: token t survives, bit 1: it is the token a merged window collapses into.
-// gamma > 0 (window merging): a merged window keeps exactly its first token; the others follow the
-// drop rule with the merged windows taken out of the walk and the budget merging left.
-// win_merged == nullptr (no attention term: drop order and merge order are the same order): which
-// windows merge and how many merged windows precede a window follow in closed form from the
-// window's place rank_c in that order and the place of the sequence's last window.
-__device__ __forceinline__ int keep_decision(const CompactArgs& a, int t, int t_end) {
-  // tokens past the last sequence have no ordinal and count as text
-  const int ord = t < t_end ? a.vis_ord[t] : -1;
-  if (ord < 0) return 1;
-  const int T = a.T, W = a.W;
-  const int b = find_seq_clamped(a.cu, a.B, T, t);
-  const int s = clampi(a.cu[b], 0, T);
-  const int nv = a.seq_nv[b];
-  const int n = (nv + W - 1) / W;
-  const int last = T - 1;
-  int slot = s + ord / W;
-  slot = slot < last ? slot : last;            // (always inside for the ordinals seq_ordinals writes)
-  int slot_last = s + n - 1;
-  slot_last = slot_last < 0 ? 0 : (slot_last < last ? slot_last : last);
-  const int pc = a.precede[slot];
-  const int in_win = ord % W;
-  const bool merging = a.gamma > 0.0f;
-  if (!merging) return in_win < window_keep_lead(ord, nv, W, a.retention, pc) ? 1 : 0;
-  const bool closed = a.win_merged == nullptr;
-  const int rl = a.rank_c[slot_last];
-  const bool short_last = nv - (n - 1) * W < W;
-  const int L = short_last ? rl : n;
-  const fmoe_merge_plan p = merge_plan(nv, W, a.retention, a.gamma, L);
-  int is_m, mb, last_m;
-  if (closed) {
-    const int r = a.rank_c[slot];                                  // place of this window
-    const int k = r - ((short_last && L < r) ? 1 : 0);             // full-size windows ahead of it
-    const bool is_last = short_last && (ord / W == n - 1);
-    is_m = is_last ? p.last_m : (k < p.q_full ? 1 : 0);
-    last_m = short_last ? p.last_m : (rl < p.q_full ? 1 : 0);
-    mb = (k < p.q_full ? k : p.q_full) + ((short_last && p.last_m && L < r) ? 1 : 0);
-  } else {
-    is_m = a.win_merged[slot];
-    mb = a.merged_before[slot];
-    last_m = a.win_merged[slot_last];
-  }
-  if (is_m) return in_win == 0 ? 3 : 0;
-  return in_win < window_keep_lead_merge(ord, nv, W, pc, mb, last_m != 0, p.u_rem) ? 1 : 0;
+// Sort key of a window: attention (0 without), then score; ascending = drop order.  The score alone, ascending = merge
+// order.  Ties by index.
+struct fmoe_window_key {
+  uint32_t att, sc;
+  __device__ __forceinline__ unsigned long long both() const { return (unsigned long long)att << 32 | sc; }
+};
+__device__ __forceinline__ bool key_before(fmoe_window_key a, int i, fmoe_window_key b, int j) {
+  return (a.both() < b.both()) | ((a.both() == b.both()) & (i < j));
 }
 
-__global__ __launch_bounds__(CP_BLOCK) void compact_flag_kernel(CompactArgs a) {
-  __shared__ int wave_tot[CP_BLOCK / 64];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int t = blockIdx.x * CP_BLOCK + threadIdx.x;
-  const int t_end = clampi(a.cu[a.B], 0, a.T);
-  const int bits = t < a.T ? keep_decision(a, t, t_end) : 0;
-  const unsigned long long mask = __ballot(bits & 1);
-  const int before = __popcll(mask & ((1ull << lane) - 1ull));
-  if (lane == 0) wave_tot[wave] = __popcll(mask);
-  __syncthreads();
-  int wave_base = 0, total = 0;
-#pragma unroll
-  for (int w = 0; w < CP_BLOCK / 64; ++w) {
-    if (w < wave) wave_base += wave_tot[w];
-    total += wave_tot[w];
+// What becomes of the windows of a sequence (uniform).
+struct fmoe_window_cut {
+  int n_full;                // windows of W tokens; one more if the last is shorter
+  int last_merged, last_keeps;
+  uint32_t merge_sc;         // of the full ones, merged: those ahead of this one in the merge order
+  int merge_i;
+  fmoe_window_key drop_key;  // of the others, dropped: those ahead of this one in the drop order, and the last `part` tokens
+  int drop_i, part;          // of this one
+  __device__ __forceinline__ bool merged(int i, fmoe_window_key K) const {
+    const bool m = (K.sc < merge_sc) | ((K.sc == merge_sc) & (i < merge_i));
+    return i < n_full ? m : last_merged != 0;
   }
-  if (t <= a.T) a.keep_code[t] = ((wave_base + before) << 2) | bits;
-  if (threadIdx.x == 0) a.blk_kept[blockIdx.x] = total;
+  __device__ __forceinline__ int lead(int i, fmoe_window_key K, int W) const {   // leading tokens of an unmerged one that stay
+    const int l = i == drop_i ? W - part : (key_before(K, i, drop_key, drop_i) ? 0 : W);
+    return i < n_full ? l : last_keeps;
+  }
+};
+constexpr int CP_ALL = 0x7fffffff;   // index of a cut behind all windows (with the largest key), -1 of one ahead of all (with 0)
+
+// The drop walk over the unmerged windows with a budget of u tokens: q full windows go whole and `part` tokens of the
+// next; a shorter last window that takes part in it (`last`) has its turn behind `ahead` full ones.
+__device__ __forceinline__ void drop_walk(const CompactArgs& a, int u, bool last, int w_last, int ahead, int& q, int& part,
+                                          int& last_keeps) {
+  q = per_window(a, u);
+  part = u - q * a.W;
+  last_keeps = w_last;
+  if (last && q >= ahead) {
+    const int v = u - ahead * a.W, rest = v < w_last ? 0 : v - w_last, more = per_window(a, rest);
+    last_keeps = v < w_last ? w_last - v : 0;
+    q = ahead + more;
+    part = rest - more * a.W;
+  }
 }
 
-__global__ __launch_bounds__(CP_BLOCK) void compact_write_kernel(CompactArgs a) {
-  __shared__ int part[CP_BLOCK / 64];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  // kept tokens in the blocks before this one
-  int sum = 0;
-  for (int k = threadIdx.x; k < (int)blockIdx.x; k += CP_BLOCK) sum += a.blk_kept[k];
-#pragma unroll
-  for (int d = 32; d >= 1; d >>= 1) sum += __shfl_xor(sum, d, 64);
-  if (lane == 0) part[wave] = sum;
-  __syncthreads();
-  int first = 0;
-#pragma unroll
-  for (int w = 0; w < CP_BLOCK / 64; ++w) first += part[w];
-  const int t = blockIdx.x * CP_BLOCK + threadIdx.x;
-  if (t < a.T) {
-    const int code = a.keep_code[t];
-    const int pos = first + (code >> 2);
-    if ((code & 1) && pos >= 0 && pos < a.T) {   // pos <= t by construction
-      a.kept_idx[pos] = t;
-      if (a.is_visual_out != nullptr) a.is_visual_out[pos] = a.is_visual[t];
-      if (a.is_merged_out != nullptr) a.is_merged_out[pos] = (code >> 1) & 1;
+template <bool MERGE, bool ATTN>
+__global__ __launch_bounds__(CP_BLOCK) void compact_kernel(CompactArgs a) {
+  __shared__ uint32_t s_sc[CP_KEYS], s_att[ATTN ? CP_KEYS : 1];
+  __shared__ unsigned long long s_red[2][CP_WAVES];
+  __shared__ __align__(16) int hist[3 * 256];
+  // fates of the short sequences' windows, leading tokens that stay or ~0 for merged: of the sequence that the block
+  // begins inside at i, of one that starts at position s at CP_WAVE_N + s - p0 + i (a sequence has no more windows
+  // than tokens, so they don't overlap)
+  __shared__ int s_fate[CP_WAVE_N + CP_BLOCK + CP_WAVE_N];
+  __shared__ int s_few[CP_BLOCK], s_many[CP_BLOCK / CP_WAVE_N + 2];
+  __shared__ int s_count[3], s_first;   // sequences in the two lists, candidates; dropped of the first sequence before p0
+  __shared__ uint32_t s_cand_att[CP_RANK], s_cand_sc[CP_RANK];
+  __shared__ int s_cand[CP_RANK];
+  __shared__ int s_cu[CP_SEQS + 1], s_nv[CP_SEQS];
+
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int T = a.T, W = a.W, B = a.B;
+  const int p0 = blockIdx.x * CP_BLOCK, t = p0 + tid;   // p0 < T
+  const int p1 = p0 + CP_BLOCK < T ? p0 + CP_BLOCK : T;
+  const int tc = t < T ? t : T - 1;
+  const float one_minus_alpha = 1.0f - a.alpha;
+  if (tid < 3) s_count[tid] = 0;
+  if (tid == 3) s_first = 0;
+  __syncthreads();   // (while the first loads are on their way)
+
+  // ---- the sequences: which of them have windows and positions in this block, what those before it have dropped
+  const int ord = a.vis_ord[tc], ord_p0 = a.vis_ord[p0];   // (meaningless outside the sequences)
+  const uint8_t vis = a.is_visual_out != nullptr ? a.is_visual[tc] : 0;
+  const bool cached = B <= CP_SEQS;
+  bool bad = false;
+  int gone = 0;
+  for (int b = tid; b < B; b += CP_BLOCK) {
+    const int s = clampi(a.cu[b], 0, T), e = clampi(a.cu[b + 1], 0, T), nv = clampi(a.seq_nv[b], 0, e - s);
+    bad |= e < s;
+    if (e <= p0) {
+      gone += nv - token_budget(nv, a.retention);
+    } else if (s < p1 && nv > 0) {
+      if (nv > W * CP_WAVE_N) {
+        const int at = atomicAdd(&s_count[1], 1);   // (a bound that decreases could make them more than there is room for)
+        if (at < CP_BLOCK / CP_WAVE_N + 2) s_many[at] = b;
+      } else {
+        const int at = atomicAdd(&s_count[0], 1);
+        if (at < CP_BLOCK) s_few[at] = b;
+      }
+    }
+    if (cached) {
+      s_cu[b] = s;
+      s_nv[b] = nv;
+      if (b == B - 1) s_cu[B] = e;
     }
   }
-  // sequence bounds of the kept tokens: kept tokens before cu[b]
-  for (int b = blockIdx.x * CP_BLOCK + threadIdx.x; b <= a.B; b += gridDim.x * CP_BLOCK) {
-    const int c = clampi(a.cu[b], 0, a.T);
-    const int blk = c / CP_BLOCK;
+  gone = wave_scan(gone);
+  const bool wave_bad = __ballot(bad) != 0ull;
+  if (lane == 63) s_red[0][wave] = (unsigned long long)(uint32_t)gone | (wave_bad ? 1ull << 63 : 0ull);
+  __syncthreads();
+  unsigned long long before_block = 0;
+#pragma unroll
+  for (int w = 0; w < CP_WAVES; ++w) {
+    before_block += s_red[0][w] & ~(1ull << 63);
+    bad |= (s_red[0][w] >> 63) != 0;
+  }
+  if (__builtin_expect(bad, 0)) {   // uniform: bounds that decrease are no partition into sequences; nothing is pruned
+    if (t < T) {
+      a.kept_idx[t] = t;
+      if (a.is_visual_out != nullptr) a.is_visual_out[t] = vis;
+      if (a.is_merged_out != nullptr) a.is_merged_out[t] = 0;
+    }
+    for (int b = t; b <= B; b += gridDim.x * CP_BLOCK) a.new_cu[b] = clampi(a.cu[b], 0, T);
+    return;
+  }
+  const int32_t* cu = cached ? s_cu : a.cu;
+  const int32_t* seq_nv = cached ? s_nv : a.seq_nv;
+  auto visual_tokens = [&](int b) {
+    int s, e;
+    seq_range(cu, b, T, s, e);
+    return clampi(seq_nv[b], 0, e - s);
+  };
+  // sums over the block: two sets of slots in turn, one barrier
+  int phase = 1;
+  auto block_sum = [&](int v) -> int {
+    v = wave_scan(v);
+    if (lane == 63) s_red[phase][wave] = (unsigned long long)(uint32_t)v;
+    __syncthreads();
+    int total = 0;
+#pragma unroll
+    for (int w = 0; w < CP_WAVES; ++w) total += (int)(uint32_t)s_red[phase][w];
+    phase ^= 1;
+    return total;
+  };
+  int bits = t < T ? 1 : 0;   // bit 0: the token stays, bit 1: a merged window collapses into it
+  const int n_few = s_count[0], n_many = s_count[1];
+  // visual tokens of the sequence from s on ahead of p0
+  auto ahead_of_block = [&](int s) { return s < p0 ? (ord_p0 >= 0 ? ord_p0 : ~ord_p0) : 0; };
+  auto key_from = [&](float ws, float wa, float amax) {
+    float A;
+    const float c = redundancy_score(ws, ATTN, wa, amax, a.alpha, one_minus_alpha, A);
+    return fmoe_window_key{ATTN ? float_order_key(A) : 0u, ~float_order_key(c)};
+  };
+  auto write_score = [&](int g, float ws, float wa, float amax) {
+    float A;
+    a.scores_out[g] = redundancy_score(ws, ATTN, wa, amax, a.alpha, one_minus_alpha, A);
+  };
+
+  // ---- sequences of more than CP_WAVE_N windows, one after the other over the whole block
+  for (int k = 0; k < n_many; ++k) {   // uniform
+    const int b = __builtin_amdgcn_readfirstlane(s_many[k]);
+    const int s = __builtin_amdgcn_readfirstlane(clampi(cu[b], 0, T)), nv = __builtin_amdgcn_readfirstlane(visual_tokens(b));
+    const int n = per_window(a, nv + W - 1);
+    const int w_last = nv - (n - 1) * W, o0 = ahead_of_block(s);
+    auto win_a = [&](int i) { return ATTN ? a.win_a[s + i] : 0.0f; };
+    float amax = 0.0f;
+    if constexpr (ATTN) {   // per-sequence attention maximum (Eq.12)
+      for (int i = tid; i < n; i += CP_BLOCK) {
+        const float v = a.win_a[s + i];
+        amax = v > amax ? v : amax;
+      }
+#pragma unroll
+      for (int sh = 32; sh >= 1; sh >>= 1) {
+        const float o = __shfl_xor(amax, sh, 64);
+        amax = o > amax ? o : amax;
+      }
+      if (lane == 0) s_red[phase][wave] = __float_as_uint(amax);
+      __syncthreads();
+#pragma unroll
+      for (int w = 0; w < CP_WAVES; ++w) {
+        const float o = __uint_as_float((uint32_t)s_red[phase][w]);
+        amax = o > amax ? o : amax;
+      }
+      phase ^= 1;
+    }
+    auto key_of = [&](int i) { return key_from(a.win_s[s + i], win_a(i), amax); };
+    const fmoe_window_key K_first = key_of(0), K_last = key_of(n - 1);
+    uint32_t diff_sc = 0, diff_att = 0;   // bits in which the keys are not all alike
+    for (int i0 = 0; i0 < n && i0 < CP_KEYS; i0 += 4 * CP_BLOCK) {   // four loads at a time (past the end the last window)
+      fmoe_window_key K[4];
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int i = i0 + r * CP_BLOCK + tid;
+        K[r] = key_of(i < n ? i : n - 1);
+      }
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        s_sc[i0 + r * CP_BLOCK + tid] = K[r].sc;
+        if (ATTN) s_att[i0 + r * CP_BLOCK + tid] = K[r].att;
+        diff_sc |= K[r].sc ^ K_first.sc;
+        diff_att |= K[r].att ^ K_first.att;
+      }
+    }
+    static_assert(CP_KEYS % (4 * CP_BLOCK) == 0, "whole rounds of keys");
+    for (int i = CP_KEYS + tid; i < n; i += CP_BLOCK) {
+      const fmoe_window_key K = key_of(i);
+      diff_sc |= K.sc ^ K_first.sc;
+      diff_att |= K.att ^ K_first.att;
+    }
+    diff_sc = wave_or(diff_sc);
+    if (ATTN) diff_att = wave_or(diff_att);
+    if (lane == 0) s_red[phase][wave] = (unsigned long long)diff_att << 32 | diff_sc;
+    for (int h = tid; h < 256; h += CP_BLOCK) hist[h] = 0;
+    fmoe_window_cut cut{};
+    const int n_full = w_last < W ? n - 1 : n;
+    cut.n_full = n_full;
+    const int eps = nv - token_budget(nv, a.retention);
+    __syncthreads();
+#pragma unroll
+    for (int w = 0; w < CP_WAVES; ++w) {
+      diff_sc |= (uint32_t)s_red[phase][w];
+      if (ATTN) diff_att |= (uint32_t)(s_red[phase][w] >> 32);
+    }
+    phase ^= 1;
+    // this thread's windows, and up to the end of a round some past the last; their keys are its own
+    auto each = [&](auto f) {
+      for (int i0 = 0; i0 < n && i0 < CP_KEYS; i0 += 4 * CP_BLOCK) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const int i = i0 + r * CP_BLOCK + tid;
+          const fmoe_window_key K{ATTN ? s_att[i] : 0u, s_sc[i]};
+          f(i, K);
+        }
+      }
+#pragma unroll 1
+      for (int i = CP_KEYS + tid; i < n; i += CP_BLOCK) f(i, key_of(i));
+    };
+    fmoe_merge_plan p{0, 0, eps};
+    if constexpr (MERGE) {
+      int L = n;
+      if (n_full < n) {   // uniform
+        int v = 0;
+        each([&](int i, fmoe_window_key K) { v += (int)(i < n_full) & (int)(K.sc <= K_last.sc); });
+        L = block_sum(v);
+      }
+      p = merge_plan(nv, W, a.retention, a.gamma, L);
+    }
+    cut.last_merged = p.last_m;
+    cut.last_keeps = w_last;
+    // stage 0: the full window at place q_full of the merge order; stage 1: of those not merged, the one at place q of
+    // the drop order
+#pragma unroll 1
+    for (int stage = MERGE ? 0 : 1; stage < 2; ++stage) {
+      int place, live = n_full;   // full windows that take part
+      if (stage == 0) {
+        place = p.q_full;
+        cut.merge_sc = place == 0 ? 0u : ~0u;
+        cut.merge_i = place == 0 ? -1 : CP_ALL;
+        if (place == 0 || place >= n_full) continue;
+      } else {
+        live -= p.q_full;
+        const bool last = n_full < n && !p.last_m;
+        int ahead = 0;
+        if (last) {   // uniform
+          int v = 0;
+          each([&](int i, fmoe_window_key K) { v += (int)((i < n_full) & !(MERGE && cut.merged(i, K)) & (K.both() <= K_last.both())); });
+          ahead = block_sum(v);
+        }
+        drop_walk(a, p.u_rem, last, w_last, ahead, place, cut.part, cut.last_keeps);
+        const bool none = place == 0 && cut.part == 0;
+        cut.drop_key = none ? fmoe_window_key{0u, 0u} : fmoe_window_key{ATTN ? ~0u : 0u, ~0u};
+        cut.drop_i = none ? -1 : CP_ALL;
+        if (none || place >= live) continue;
+      }
+      // The window at `place`: digits of eight bits of the attention key, then of the score's, then of the index, each
+      // from the highest bit on that is not the same in all, until the candidates are few enough to rank.  Counts of
+      // the candidates per digit are summed by every wavefront for itself; a barrier a digit, the tables take turns.
+      auto candidate = [&](int i, fmoe_window_key K) { return (i < n_full) & !(MERGE && stage == 1 && cut.merged(i, K)); };
+      const int index_bits = 32 - __clz(n);
+      int level = ATTN && stage == 1 && diff_att != 0 ? 0 : (diff_sc != 0 ? 1 : 2);
+      uint32_t chosen = level == 0 ? K_first.att : (level == 1 ? K_first.sc : 0u);
+      int fixed = level == 2 ? index_bits : 32 - __clz(level == 0 ? diff_att : diff_sc);   // bits from here on are those of `chosen`
+      // what the levels before have settled (the keys' common attention, if it takes part in the order at all)
+      fmoe_window_key tied = K_first;
+      uint32_t att_counts = ATTN && stage == 1 && level > 0 ? ~0u : 0u, sc_counts = level == 2 ? ~0u : 0u;
+      int table = 0;
+      for (;;) {   // uniform; ends because indices differ
+        const int shift = fixed > 8 ? fixed - 8 : 0;
+        int* const h = hist + table * 256;
+        table = table == 2 ? 0 : table + 1;
+        for (int z = tid; z < 256; z += CP_BLOCK) hist[table * 256 + z] = 0;
+        auto live_digit = [&](int i, fmoe_window_key K, uint32_t& digit) {
+          const uint32_t v = level == 1 ? K.sc : (level == 0 ? K.att : (uint32_t)i);
+          digit = (v >> shift) & 255u;
+          const uint32_t off = ((K.att ^ tied.att) & att_counts) | ((K.sc ^ tied.sc) & sc_counts) |
+                               (fixed < 32 ? (v ^ chosen) >> fixed : 0u);
+          return (off == 0u) & candidate(i, K);
+        };
+        each([&](int i, fmoe_window_key K) {
+          uint32_t digit;
+          if (live_digit(i, K, digit)) atomicAdd(&h[digit], 1);
+        });
+        __syncthreads();
+        const int4 c4 = *reinterpret_cast<const int4*>(&h[4 * lane]);
+        const int sum4 = c4.x + c4.y + c4.z + c4.w;
+        const int excl = wave_scan(sum4) - sum4;
+        const int src = __builtin_ctzll(__ballot(excl <= place && place < excl + sum4));   // exactly one lane
+        int before = excl, val = 4 * lane, here = c4.x;
+        if (before + here <= place) { before += here; here = c4.y; ++val; }
+        if (val > 4 * lane && before + here <= place) { before += here; here = c4.z; ++val; }
+        if (val > 4 * lane + 1 && before + here <= place) { before += here; here = c4.w; ++val; }
+        place -= __builtin_amdgcn_readlane(before, src);
+        const uint32_t digit_found = (uint32_t)__builtin_amdgcn_readlane(val, src);
+        here = __builtin_amdgcn_readlane(here, src);
+        if (here <= CP_RANK) {
+          each([&](int i, fmoe_window_key K) {
+            uint32_t digit;
+            if (live_digit(i, K, digit) & (digit == digit_found)) {
+              const int at = atomicAdd(&s_count[2], 1);
+              if (ATTN) s_cand_att[at] = K.att;
+              s_cand_sc[at] = K.sc;
+              s_cand[at] = i;
+            }
+          });
+          break;
+        }
+        const uint32_t mask = (0xffu << shift) & (fixed < 32 ? (1u << fixed) - 1u : ~0u);
+        chosen = (chosen & ~mask) | ((digit_found << shift) & mask);
+        fixed = shift;
+        if (fixed == 0) {   // alike so far: by what comes next
+          if (level == 0) {
+            tied.att = chosen;
+            att_counts = ~0u;
+          } else {
+            tied.sc = chosen;
+            sc_counts = ~0u;
+          }
+          level = level == 0 && diff_sc != 0 ? 1 : 2;
+          chosen = level == 1 ? K_first.sc : 0u;
+          fixed = level == 1 ? 32 - __clz(diff_sc) : index_bits;
+        }
+      }
+      __syncthreads();
+      const int here = s_count[2], mine = lane < here ? lane : 0;
+      const fmoe_window_key K{ATTN ? s_cand_att[mine] : 0u, s_cand_sc[mine]};
+      const int i = s_cand[mine];
+      int rank = 0;
+#pragma unroll 4
+      for (int j = 0; j < here; ++j) {   // uniform
+        const fmoe_window_key o{ATTN && stage == 1 ? (uint32_t)__builtin_amdgcn_readlane(K.att, j) : 0u,
+                                (uint32_t)__builtin_amdgcn_readlane(K.sc, j)};
+        rank += (int)key_before(o, __builtin_amdgcn_readlane(i, j), fmoe_window_key{ATTN && stage == 1 ? K.att : 0u, K.sc}, i);
+      }
+      const int src = __builtin_ctzll(__ballot(lane < here && rank == place));   // exactly one
+      const fmoe_window_key found{ATTN ? (uint32_t)__builtin_amdgcn_readlane(K.att, src) : 0u,
+                                  (uint32_t)__builtin_amdgcn_readlane(K.sc, src)};
+      const int found_i = __builtin_amdgcn_readlane(i, src);
+      if (stage == 0) {
+        cut.merge_sc = found.sc;
+        cut.merge_i = found_i;
+        for (int z = tid; z < 256; z += CP_BLOCK) hist[z] = 0;   // for the next search
+        __syncthreads();   // all have read the number of candidates
+        if (tid == 0) s_count[2] = 0;
+      } else {
+        cut.drop_key = found;
+        cut.drop_i = found_i;
+      }
+    }
+    if (ord >= 0 && ord < nv && t >= s && t < clampi(cu[b + 1], 0, T)) {
+      const int i = per_window(a, ord);
+      const fmoe_window_key K = i < CP_KEYS ? fmoe_window_key{ATTN ? s_att[i] : 0u, s_sc[i]} : key_of(i);   // (barriers behind the writers)
+      const int in_win = ord - i * W;
+      if (MERGE && cut.merged(i, K)) bits = in_win == 0 ? 3 : 0;
+      else bits = in_win < cut.lead(i, K, W) ? 1 : 0;
+    }
+    if (a.scores_out != nullptr && t >= s && t < s + n) write_score(t, a.win_s[t], win_a(t - s), amax);
+    if (s < p0) {   // uniform: what is dropped of it ahead of this block
+      const int i0 = per_window(a, o0), j0 = o0 - i0 * W;
+      int v = 0;
+      each([&](int i, fmoe_window_key K) {
+        const int lead = cut.lead(i, K, W), stays = MERGE && cut.merged(i, K) ? 1 : lead;
+        const int size = i < i0 ? (i < n_full ? W : w_last) : (i == i0 ? j0 : 0);
+        v += size > stays ? size - stays : 0;
+      });
+      v = block_sum(v);
+      if (tid == 0) s_first = v;
+    }
+    __syncthreads();   // keys, candidates and their number are read no more
+    if (tid == 0) s_count[2] = 0;   // (the next use is behind another barrier)
+  }
+
+  // ---- the others, a wavefront each (lane = window)
+  if (__builtin_expect(n_few > 0, 0)) {   // uniform
+    for (int k = wave; k < n_few; k += CP_WAVES) {   // uniform over the wavefront
+      const int b = __builtin_amdgcn_readfirstlane(s_few[k]);
+      const int s = clampi(cu[b], 0, T), nv = visual_tokens(b), n = per_window(a, nv + W - 1);
+      const int w_last = nv - (n - 1) * W, n_full = w_last < W ? n - 1 : n;
+      const int i = lane < n ? lane : n - 1;   // lanes past the windows repeat the last one and are not counted
+      const float ws = a.win_s[s + i], wa = ATTN ? a.win_a[s + i] : 0.0f;
+      float amax = wa > 0.0f ? wa : 0.0f;
+      if constexpr (ATTN) {
+#pragma unroll
+        for (int sh = 32; sh >= 1; sh >>= 1) {
+          const float o = __shfl_xor(amax, sh, 64);
+          amax = o > amax ? o : amax;
+        }
+      }
+      const fmoe_window_key K = key_from(ws, wa, amax);
+      auto key_at = [&](int j) {
+        return fmoe_window_key{ATTN ? (uint32_t)__builtin_amdgcn_readlane(K.att, j) : 0u, (uint32_t)__builtin_amdgcn_readlane(K.sc, j)};
+      };
+      const fmoe_window_key K_last = key_at(n - 1);
+      const bool full = lane < n_full;
+      fmoe_merge_plan p{0, 0, nv - token_budget(nv, a.retention)};
+      bool merged = false;
+      if constexpr (MERGE) {
+        const int L = n_full < n ? __popcll(__ballot(full && K.sc <= K_last.sc)) : n;
+        p = merge_plan(nv, W, a.retention, a.gamma, L);
+        int place = 0;
+#pragma unroll 4
+        for (int j = 0; j < n_full; ++j) {
+          const uint32_t o = __builtin_amdgcn_readlane(K.sc, j);
+          place += (int)((o < K.sc) | ((o == K.sc) & (j < lane)));
+        }
+        merged = full ? place < p.q_full : p.last_m != 0;
+      }
+      const bool takes_part = full && !merged;
+      const unsigned long long part_mask = __ballot(takes_part);
+      const int ahead = __popcll(__ballot(takes_part && K.both() <= K_last.both()));
+      int q, part, last_keeps;
+      drop_walk(a, p.u_rem, n_full < n && !p.last_m, w_last, ahead, q, part, last_keeps);
+      int place = 0;
+#pragma unroll 4
+      for (int j = 0; j < n_full; ++j) {
+        place += (int)key_before(key_at(j), j, K, lane) & (int)((part_mask >> j) & 1);
+      }
+      const int lead = full ? (place < q ? 0 : (place == q ? W - part : W)) : last_keeps;
+      if (lane < n) {
+        s_fate[(s < p0 ? 0 : CP_WAVE_N + s - p0) + lane] = merged ? ~0 : lead;
+        const int g = s + lane;
+        if (a.scores_out != nullptr && g >= p0 && g < p1) write_score(g, ws, wa, amax);
+      }
+      if (s < p0) {   // uniform: what is dropped of it ahead of this block
+        const int o0 = ahead_of_block(s), i0 = per_window(a, o0), j0 = o0 - i0 * W;
+        const int stays = merged ? 1 : lead, size = full ? W : w_last;
+        int v = 0;
+        if (lane < n) v = lane < i0 ? size - stays : (lane == i0 && j0 > stays ? j0 - stays : 0);
+        v = wave_scan(v);
+        if (lane == 63) s_first = v;
+      }
+    }
+    __syncthreads();
+    if (ord >= 0 && t >= clampi(cu[0], 0, T) && t < clampi(cu[B], 0, T)) {
+      const int b = find_seq(cu, B, t), s = clampi(cu[b], 0, T), nv = visual_tokens(b);
+      if (ord < nv && nv <= W * CP_WAVE_N) {
+        const int i = per_window(a, ord), fate = s_fate[(s < p0 ? 0 : CP_WAVE_N + s - p0) + i];
+        const int in_win = ord - i * W;
+        bits = fate < 0 ? (in_win == 0 ? 3 : 0) : (in_win < fate ? 1 : 0);
+      }
+    }
+  }
+
+  // ---- positions of the kept tokens
+  const unsigned long long kept = __ballot(bits & 1);
+  if (lane == 0) s_red[phase][wave] = (unsigned long long)__popcll(kept);
+  __syncthreads();
+  int pos = p0 - (int)before_block - s_first + __popcll(kept & ((1ull << lane) - 1ull));
+#pragma unroll
+  for (int w = 0; w < CP_WAVES; ++w) pos += w < wave ? (int)s_red[phase][w] : 0;
+  phase ^= 1;
+  if ((bits & 1) && pos >= 0 && pos < T) {   // pos <= t by construction
+    a.kept_idx[pos] = t;
+    if (a.is_visual_out != nullptr) a.is_visual_out[pos] = vis;
+    if (a.is_merged_out != nullptr) a.is_merged_out[pos] = (bits >> 1) & 1;
+  }
+  if (blockIdx.x == gridDim.x - 1) {   // sequence bounds of the kept tokens
     int before = 0;
-    for (int k = 0; k < blk; ++k) before += a.blk_kept[k];
-    a.new_cu[b] = before + (a.keep_code[c] >> 2);
+    for (int b0 = 0; b0 <= B; b0 += CP_BLOCK) {   // uniform
+      const int b = b0 + tid;
+      int v = 0;
+      if (b < B) {   // a sequence loses its budget exactly
+        const int nv = visual_tokens(b);
+        v = nv - token_budget(nv, a.retention);
+      }
+      const int incl = wave_scan(v);
+      if (lane == 63) s_red[phase][wave] = (unsigned long long)(uint32_t)incl;
+      __syncthreads();
+      int mine = before + incl - v;
+#pragma unroll
+      for (int w = 0; w < CP_WAVES; ++w) {
+        const int c = (int)(uint32_t)s_red[phase][w];
+        mine += w < wave ? c : 0;
+        before += c;
+      }
+      phase ^= 1;
+      if (b <= B) a.new_cu[b] = clampi(cu[b], 0, T) - mine;
+    }
   }
 }
 
@@ -956,15 +1217,15 @@ __global__ __launch_bounds__(SB_THREADS) void prune_dispatch_small_kernel(SmallA
 // One wavefront per window unit (floor(T/W) + B units cover every window), four per block.
 void launch_window_scores(const float* probs, const int32_t* cu_seqlens, int B, int T, int E, int W,
                           int sim_mode, const int32_t* vis_tok, const int32_t* seq_nv, const float* attn,
-                          float* win_s, float* win_a, int32_t* precede, int32_t* rank_c, hipStream_t stream) {
+                          float* win_s, float* win_a, hipStream_t stream) {
   const int n_units = T / W + B;
   const dim3 grid((n_units + 3) / 4);
   if ((long long)W * E <= WS_TILE)
     hipLaunchKernelGGL(window_score_kernel<true>, grid, dim3(256), 0, stream, probs, cu_seqlens, B, T, E, W,
-                       sim_mode, vis_tok, seq_nv, attn, win_s, win_a, precede, rank_c);
+                       sim_mode, vis_tok, seq_nv, attn, win_s, win_a);
   else
     hipLaunchKernelGGL(window_score_kernel<false>, grid, dim3(256), 0, stream, probs, cu_seqlens, B, T, E, W,
-                       sim_mode, vis_tok, seq_nv, attn, win_s, win_a, precede, rank_c);
+                       sim_mode, vis_tok, seq_nv, attn, win_s, win_a);
 }
 
 }  // namespace
@@ -980,12 +1241,7 @@ int launch_prune(const fmoe_ctx* ctx, const fmoe_prune_params* pp, const float* 
   int32_t* seq_nv = reinterpret_cast<int32_t*>(base + L.seq_nv);
   float* win_s = reinterpret_cast<float*>(base + L.win_s);
   float* win_a = attn ? reinterpret_cast<float*>(base + L.win_a) : nullptr;
-  int32_t* drop_from = reinterpret_cast<int32_t*>(base + L.drop_from);
-  int32_t* keep_prefix = reinterpret_cast<int32_t*>(base + L.keep_prefix);
   const bool merging = pp->gamma > 0.0f;
-  int32_t* rank_c = merging ? reinterpret_cast<int32_t*>(base + L.rank_c) : nullptr;
-  int32_t* win_merged = merging ? reinterpret_cast<int32_t*>(base + L.win_merged) : nullptr;
-  int32_t* merged_before = merging ? reinterpret_cast<int32_t*>(base + L.merged_before) : nullptr;
   uint8_t* is_merged = is_merged_out;
   if (merging && is_merged == nullptr) is_merged = reinterpret_cast<uint8_t*>(base + L.is_merged);
   const int E = ctx->cfg.n_experts;
@@ -1000,38 +1256,22 @@ int launch_prune(const fmoe_ctx* ctx, const fmoe_prune_params* pp, const float* 
   {
     fmoe_prof_scope prof(ctx, SLOT_SCORES, stream);
     launch_window_scores(probs, cu_seqlens, B, T, E, pp->window, pp->sim_mode, vis_tok, seq_nv, attn, win_s,
-                         win_a, drop_from, rank_c, stream);
-  }
-  const int n_max = (T + pp->window - 1) / pp->window;   // no sequence has more windows
-  const int gy = (n_max + SEL_JC - 1) / SEL_JC;
-  const dim3 sel_grid((T + 255) / 256, gy < 4096 ? gy : 4096);
-  {
-    fmoe_prof_scope prof(ctx, SLOT_SELECT, stream);
-    hipLaunchKernelGGL(select_kernel, sel_grid, dim3(256), 0, stream, cu_seqlens, B, T, pp->window,
-                       pp->alpha, seq_nv, win_s, win_a, drop_from, scores_out, rank_c,
-                       static_cast<const int32_t*>(nullptr));
-  }
-  const bool closed_form = merging && attn == nullptr;   // one order: the compaction derives the merged set
-  if (merging && !closed_form) {   // which windows merge, then how many merged windows precede each window in drop order
-    hipLaunchKernelGGL(merge_decide_kernel, dim3((T + 255) / 256), dim3(256), 0, stream, cu_seqlens, B, T,
-                       pp->window, pp->retention, pp->gamma, seq_nv, rank_c, win_merged, merged_before);
-    hipLaunchKernelGGL(select_kernel, sel_grid, dim3(256), 0, stream, cu_seqlens, B, T, pp->window,
-                       pp->alpha, seq_nv, win_s, win_a, merged_before, static_cast<float*>(nullptr),
-                       static_cast<int32_t*>(nullptr), static_cast<const int32_t*>(win_merged));
+                         win_a, stream);
   }
   {
     fmoe_prof_scope prof(ctx, SLOT_COMPACT, stream);
     CompactArgs ca;
     ca.is_visual = is_visual; ca.cu = cu_seqlens; ca.B = B; ca.T = T; ca.W = pp->window;
-    ca.retention = pp->retention; ca.gamma = pp->gamma;
-    ca.vis_ord = vis_ord; ca.seq_nv = seq_nv; ca.precede = drop_from; ca.rank_c = rank_c;
-    ca.win_merged = closed_form ? nullptr : win_merged; ca.merged_before = merged_before;
-    ca.keep_code = keep_prefix; ca.blk_kept = reinterpret_cast<int32_t*>(base + L.compact_blk);
-    ca.kept_idx = kept_idx; ca.new_cu = new_cu_seqlens; ca.is_visual_out = is_visual_out;
+    ca.retention = pp->retention; ca.gamma = pp->gamma; ca.alpha = pp->alpha;
+    ca.vis_ord = vis_ord; ca.seq_nv = seq_nv; ca.win_s = win_s; ca.win_a = win_a;
+    ca.scores_out = scores_out; ca.kept_idx = kept_idx; ca.new_cu = new_cu_seqlens; ca.is_visual_out = is_visual_out;
     ca.is_merged_out = merging ? is_merged : nullptr;
-    const dim3 cgrid((T + 1 + CP_BLOCK - 1) / CP_BLOCK);
-    hipLaunchKernelGGL(compact_flag_kernel, cgrid, dim3(CP_BLOCK), 0, stream, ca);
-    hipLaunchKernelGGL(compact_write_kernel, cgrid, dim3(CP_BLOCK), 0, stream, ca);
+    ca.window_rcp = ((1ull << 37) + pp->window - 1) / pp->window;
+    const dim3 grid((T + CP_BLOCK - 1) / CP_BLOCK), block(CP_BLOCK);
+    if (merging && attn) hipLaunchKernelGGL((compact_kernel<true, true>), grid, block, 0, stream, ca);
+    else if (merging) hipLaunchKernelGGL((compact_kernel<true, false>), grid, block, 0, stream, ca);
+    else if (attn) hipLaunchKernelGGL((compact_kernel<false, true>), grid, block, 0, stream, ca);
+    else hipLaunchKernelGGL((compact_kernel<false, false>), grid, block, 0, stream, ca);
   }
   if (merging) {
     if (ctx->cfg.dtype == FMOE_BF16)
@@ -1077,12 +1317,11 @@ int launch_prune_dispatch_small(const fmoe_ctx* ctx, const fmoe_prune_params* pp
   int32_t* seq_nv = reinterpret_cast<int32_t*>(base + L.seq_nv);
   float* win_s = reinterpret_cast<float*>(base + L.win_s);
   float* win_a = attn ? reinterpret_cast<float*>(base + L.win_a) : nullptr;
-  int32_t* drop_from = reinterpret_cast<int32_t*>(base + L.drop_from);
   const int E = ctx->cfg.n_experts;
   if (prune) {   // the visual ordinals were produced in the router's launch
     fmoe_prof_scope prof(ctx, SLOT_SCORES, stream);
     launch_window_scores(probs, cu_seqlens, B, T, E, pp->window, pp->sim_mode, vis_tok, seq_nv, attn, win_s,
-                         win_a, drop_from, nullptr, stream);
+                         win_a, stream);
   }
   SmallArgs a;
   a.prune = prune ? 1 : 0;

@@ -24,7 +24,7 @@ __device__ __forceinline__ int find_seq(const int32_t* cu, int B, int g) {
 }
 
 // Visual ordinals of sequence b, by one 256-thread block (wave_tot: 4 * ORD_ROWS ints of LDS).
-// vis_ord[t] = number of visual tokens before t in its sequence (for visual t), -1 for text;
+// vis_ord[t] = number of visual tokens before t in its sequence, as ~(that number) < 0 for text;
 // vis_tok[cu[b] + j] = global index of the j-th visual token of sequence b; seq_nv[b] = N_v.
 // ORD_ROWS rows of 256 tokens are fetched and counted together: the scan is a chain of memory latencies,
 // and it shares a launch with the router, which it must not outlast.
@@ -63,7 +63,7 @@ __device__ __forceinline__ void seq_ordinals_block(const uint8_t* __restrict__ i
       const int t = base + r * 256 + (int)threadIdx.x;
       if (t < e) {
         const int ord = running + wave_base + __popcll(mask[r] & ((1ull << lane) - 1ull));
-        vis_ord[t] = vis[r] ? ord : -1;
+        vis_ord[t] = vis[r] ? ord : ~ord;
         if (vis[r]) vis_tok[s + ord] = t;
       }
       running += total;
@@ -157,39 +157,5 @@ __device__ __forceinline__ fmoe_merge_plan merge_plan(int nv, int W, float reten
   p.q_full = L + more;
   p.u_rem = u - more * c;
   return p;
-}
-
-// Number of leading tokens of visual ordinal `ord`'s window that survive (Sec. 3.2.3 budget and the
-// drop rule): windows are dropped whole in drop order while they fit in eps = N_v - eta and the
-// next one loses its last tokens.  pc = number of windows ahead of this window in drop order, bit
-// 30 set when the sequence's last (possibly shorter) window is one of them.
-__device__ __forceinline__ int window_keep_lead(int ord, int nv, int W, float retention, int pc) {
-  const int n = (nv + W - 1) / W;
-  const int i = ord / W;
-  const int eps = nv - token_budget(nv, retention);
-  const int count = pc & 0x3fffffff, last_first = pc >> 30;
-  const int w_last = nv - (n - 1) * W;
-  const int before = count * W - (last_first ? (W - w_last) : 0);
-  const int wi = (i == n - 1) ? w_last : W;
-  if (before + wi <= eps) return 0;
-  if (before < eps) return wi - (eps - before);
-  return wi;
-}
-
-// The same with window merging: `merged_before` merged windows are among the `pc` predecessors (they
-// are no longer part of the drop walk), the last window counts as a predecessor only if it was not
-// merged, and the budget is what merging left.
-__device__ __forceinline__ int window_keep_lead_merge(int ord, int nv, int W, int pc, int merged_before,
-                                                      bool last_merged, int u_rem) {
-  const int n = (nv + W - 1) / W;
-  const int i = ord / W;
-  const int count = (pc & 0x3fffffff) - (merged_before & 0x3fffffff);
-  const int last_first = (pc >> 30) && !last_merged;
-  const int w_last = nv - (n - 1) * W;
-  const int before = count * W - (last_first ? (W - w_last) : 0);
-  const int wi = (i == n - 1) ? w_last : W;
-  if (before + wi <= u_rem) return 0;
-  if (before < u_rem) return wi - (u_rem - before);
-  return wi;
 }
 #endif

@@ -465,6 +465,60 @@ def test_prune_merge_many_windows_several_blocks():
         _check_merged_rows(host(x_m)[:n], o_xm, o_mrg, wl.dtype)
 
 
+@pytest.mark.parametrize("gamma", [0.0, 0.15])
+@pytest.mark.parametrize("with_attn", [False, True])
+@pytest.mark.parametrize("T_v,T_t,window,distinct", [
+    ([126, 128, 129, 130, 131, 64, 65], [0, 3, 0, 1, 900, 0, 2], 2, 0),      # 63 .. 66 windows: one wavefront or the block
+    ([8191, 700], [5, 0], 2, 0), ([4097], [0], 1, 0),                        # around and past the keys that stay in LDS
+    ([8199], [30], 2, 5),                                                    # windows that tie: the index decides
+    ([100, 2048, 70, 1500], [924, 0, 954, 3], 3, 4)])
+def test_prune_selection_edges(T_v, T_t, window, distinct, with_attn, gamma):
+    """Compaction at the edges of its forms (windows of a sequence, blocks of 1024 positions), visual and text tokens
+    mixed, with and without ties, the attention term and window merging; tokens behind the last sequence stay.  Kept set,
+    merged flags, bounds and scores bit for bit."""
+    rng = np.random.default_rng(sum(T_v) + window)
+    E, tail = 8, 37
+    vis = np.concatenate([rng.permutation(np.repeat([1, 0], [a, b])) for a, b in zip(T_v, T_t)]).astype(np.uint8)
+    cu = np.concatenate([[0], np.cumsum(np.add(T_v, T_t))]).astype(np.int32)
+    T = int(cu[-1])
+    probs = rng.random((distinct or T, E)).astype(np.float32) ** 3
+    if distinct:      # runs as long as two windows
+        probs = probs[np.repeat(rng.integers(0, distinct, T), 2 * window)[:T]]
+    probs /= probs.sum(1, keepdims=True)
+    attn = (rng.integers(0, 4, T) if distinct else rng.random(T)).astype(np.float32) if with_attn else None
+    x = rng.standard_normal((T, 8)).astype(np.float32)
+    alpha = 0.6 if with_attn else 1.0
+    res = oracle.prune(probs, vis, cu, 0.45, window, alpha=alpha, gamma=gamma, attn=attn, x=x if gamma else None)
+    m = binding.FMoE(d_model=8, n_experts=E, d_ffn=8, k_text=2, k_visual=1, dtype="f32")
+    m.set_weights(torch.zeros(E, 8).cuda(), None, *(torch.zeros(E, 8, 8).cuda() for _ in range(3)))
+    end = lambda a: None if a is None else dev(np.concatenate([a, a[:tail]]))      # tokens of no sequence
+    kw = dict(x=end(x)) if gamma else {}
+    pp = binding.prune_params(retention=0.45, window=window, alpha=alpha, gamma=gamma)
+    kept, new_cu, scores, *merged = m.prune(pp, end(probs), end(vis), dev(cu), attn=end(attn), want_scores=True, **kw)
+    n = int(new_cu[-1])
+    assert np.array_equal(host(new_cu), res[1])
+    assert np.array_equal(host(kept)[:n + tail], np.concatenate([res[0], np.arange(T, T + tail)]))
+    got, windows = host(scores), [(v + window - 1) // window for v in T_v]
+    assert np.array_equal(np.concatenate([got[c:c + w] for c, w in zip(cu, windows)]), res[2])
+    if gamma:
+        assert np.array_equal(host(merged[0])[:n], res[3])
+        assert res[3].sum() > 20 or window == 1      # (a window of one token never merges)
+        _check_merged_rows(host(merged[1])[:n], res[4], res[3], W.F32)
+    plain, new_cu2, *_ = m.prune(pp, end(probs), end(vis), dev(cu), attn=end(attn), **kw)      # nobody asks for the scores
+    assert np.array_equal(host(new_cu2), res[1]) and torch.equal(plain[:n + tail], kept[:n + tail])
+
+
+def test_prune_bounds_that_decrease_keep_every_token():
+    """Sequence bounds that are no partition: nothing is pruned and nothing is read or written out of range."""
+    T, E = 3000, 8
+    m = binding.FMoE(d_model=8, n_experts=E, d_ffn=8, k_text=2, k_visual=1, dtype="f32")
+    m.set_weights(torch.zeros(E, 8).cuda(), None, *(torch.zeros(E, 8, 8).cuda() for _ in range(3)))
+    cu = np.array([0, 2000, 1000, 5000], np.int32)
+    kept, new_cu, _ = m.prune(binding.prune_params(retention=0.5, window=3), torch.full((T, E), 1 / E).cuda(),
+                              torch.ones(T, dtype=torch.uint8).cuda(), dev(cu))
+    assert np.array_equal(host(new_cu), [0, 2000, 1000, 3000]) and np.array_equal(host(kept), np.arange(T))
+
+
 # ---------------------------------------------------------------- permute
 @pytest.mark.parametrize("seed,kw", SMALL)
 def test_permute(seed, kw):
