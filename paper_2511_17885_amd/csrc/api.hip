@@ -487,12 +487,13 @@ int fmoe_layer_forward(fmoe_ctx* ctx, const fmoe_prune_params* params, const voi
                       new_cu_seqlens, nullptr, is_visual_out, nullptr, nullptr, nullptr, ws, L, s, true);
     kept = kept_idx;
     n_dev = new_cu_seqlens + B;
-  } else {
-    rc = launch_identity_kept(is_visual, cu_seqlens, B, T, kept_idx, new_cu_seqlens, is_visual_out, s);
+    if (rc != FMOE_OK) return rc;
   }
-  if (rc != FMOE_OK) return rc;
-  if (T == 0) return FMOE_OK;
-  if ((rc = launch_permute(ctx, topk_idx, kept, T, n_dev, expert_offsets, perm_src, inv_perm, ws, L, true, s)) != FMOE_OK)
+  if (T == 0)
+    return do_prune ? FMOE_OK : launch_identity_kept(is_visual, cu_seqlens, B, T, kept_idx, new_cu_seqlens, is_visual_out, s);
+  const fmoe_keep_all_job all{is_visual, cu_seqlens, B, kept_idx, new_cu_seqlens, is_visual_out};
+  if ((rc = launch_permute(ctx, topk_idx, kept, T, n_dev, expert_offsets, perm_src, inv_perm, ws, L, true, s,
+                           do_prune ? nullptr : &all)) != FMOE_OK)
     return rc;
   if ((rc = launch_expert_ffn(ctx, x, kept, T, n_dev, expert_offsets, perm_src, y, y_shared, ws, L, true, s)) != FMOE_OK)
     return rc;

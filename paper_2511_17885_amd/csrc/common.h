@@ -181,11 +181,20 @@ int launch_identity_kept(const uint8_t* is_visual, const int32_t* cu_seqlens, in
                          int32_t* kept_idx, int32_t* new_cu_seqlens, uint8_t* is_visual_out,
                          hipStream_t stream);
 
-// build_tiles: also write the grouped-GEMM tile lists (geometry from fmoe_geom(ctx, n_cap))
+// What the pruning writes where every token is kept (kept list, sequence bounds, modality mask; any output may be null).
+struct fmoe_keep_all_job {
+  const uint8_t* is_visual;
+  const int32_t* cu;
+  int B;
+  int32_t *kept_idx, *new_cu;
+  uint8_t* is_visual_out;
+};
+// build_tiles: also write the grouped-GEMM tile lists (geometry from fmoe_geom(ctx, n_cap)).  all (nullable; with its
+// kept_idx): all n_cap positions are kept, write that as well.
 int launch_permute(const fmoe_ctx* ctx, const int32_t* topk_idx, const int32_t* kept_idx, int n_cap,
                    const int32_t* n_dev, int32_t* expert_offsets, int32_t* perm_src,
                    int32_t* inv_perm, void* ws, const fmoe_ws_layout& L, bool build_tiles,
-                   hipStream_t stream);
+                   hipStream_t stream, const fmoe_keep_all_job* all = nullptr);
 
 
 

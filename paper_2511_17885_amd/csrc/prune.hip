@@ -843,16 +843,8 @@ __global__ __launch_bounds__(256) void merge_gather_kernel(
   for (int c = threadIdx.x + MG_COLS * 256; c < d; c += 256) dst[c] = from_f64<T>(column_mean(c) * scale);
 }
 
-__global__ void identity_kept_kernel(const uint8_t* __restrict__ is_visual,
-                                     const int32_t* __restrict__ cu, int B, int T,
-                                     int32_t* __restrict__ kept_idx, int32_t* __restrict__ new_cu,
-                                     uint8_t* __restrict__ is_visual_out) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < T) {
-    if (kept_idx != nullptr) kept_idx[i] = i;
-    if (is_visual_out != nullptr) is_visual_out[i] = is_visual[i];
-  }
-  if (i <= B && new_cu != nullptr) new_cu[i] = clampi(cu[i], 0, T);
+__global__ void identity_kept_kernel(fmoe_keep_all_job job, int T) {
+  keep_all(job, T, blockIdx.x * blockDim.x + threadIdx.x, gridDim.x * blockDim.x);
 }
 
 // ---- E: small batches.  One 1024-thread block takes the whole chain after the window scores:
@@ -1293,8 +1285,8 @@ int launch_identity_kept(const uint8_t* is_visual, const int32_t* cu_seqlens, in
                          int32_t* kept_idx, int32_t* new_cu_seqlens, uint8_t* is_visual_out,
                          hipStream_t stream) {
   const int n = (T > B + 1) ? T : B + 1;
-  hipLaunchKernelGGL(identity_kept_kernel, dim3((n + 255) / 256), dim3(256), 0, stream, is_visual,
-                     cu_seqlens, B, T, kept_idx, new_cu_seqlens, is_visual_out);
+  hipLaunchKernelGGL(identity_kept_kernel, dim3((n + 255) / 256), dim3(256), 0, stream,
+                     fmoe_keep_all_job{is_visual, cu_seqlens, B, kept_idx, new_cu_seqlens, is_visual_out}, T);
   FMOE_HIP_CHECK(hipGetLastError());
   return FMOE_OK;
 }

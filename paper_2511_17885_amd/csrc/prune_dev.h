@@ -23,6 +23,15 @@ __device__ __forceinline__ int find_seq(const int32_t* cu, int B, int g) {
   return lo;
 }
 
+// What the pruning writes where every one of T tokens is kept, by the threads i, i + step, ... of a launch.
+__device__ __forceinline__ void keep_all(const fmoe_keep_all_job& job, int T, int first, int step) {
+  for (int i = first; i < T; i += step) {
+    if (job.kept_idx != nullptr) job.kept_idx[i] = i;
+    if (job.is_visual_out != nullptr) job.is_visual_out[i] = job.is_visual[i];
+  }
+  for (int i = first; i <= job.B && job.new_cu != nullptr; i += step) job.new_cu[i] = clampi(job.cu[i], 0, T);
+}
+
 // Visual ordinals of sequence b, by one 256-thread block (wave_tot: 4 * ORD_ROWS ints of LDS).
 // vis_ord[t] = number of visual tokens before t in its sequence, as ~(that number) < 0 for text;
 // vis_tok[cu[b] + j] = global index of the j-th visual token of sequence b; seq_nv[b] = N_v.

@@ -1505,6 +1505,33 @@ def test_layer_forward_general_chain_over_many_sequences():
     assert_residual_outputs_close(host(out)[:n], o["out_f64"], _x_rows(wl, o), wl.dtype, "1500 sequences")
 
 
+@pytest.mark.parametrize("n_seq", [1, 9000])
+@pytest.mark.parametrize("k_text,k_visual", [(2, 1), (0, 0)])
+def test_layer_forward_that_keeps_every_token_above_the_small_batch(k_text, k_visual, n_seq):
+    """The kept list, the bounds (more of them than tokens, most sequences empty) and the mask come from the permutation's
+    count, or from a launch of their own where no slot is routed; the rows against fp64."""
+    T, d, E, F = 4099, 64, 4, 32
+    g = torch.Generator(device="cuda")
+    g.manual_seed(n_seq + k_text)
+    rnd = lambda *s: torch.randn(s, generator=g, device="cuda")
+    m = binding.FMoE(d_model=d, n_experts=E, d_ffn=F, n_shared=1, d_ffn_shared=F, k_text=k_text, k_visual=k_visual, dtype="f32")
+    wr, w, sh = rnd(E, d), [rnd(E, F, d), rnd(E, F, d), rnd(E, d, F)], [rnd(1, F, d), rnd(1, F, d), rnd(1, d, F)]
+    m.set_weights(wr, None, *w, *sh)
+    x, vis = rnd(T, d), (rnd(T) > 0).to(torch.uint8)
+    cu = torch.from_numpy(np.sort(np.concatenate([[0, T], np.random.default_rng(n_seq).integers(0, T, n_seq - 1)]))).int().cuda()
+    out, kept, new_cu, mask = m.layer_forward(x, vis, cu, None, want_mask=True)
+    assert torch.equal(kept, torch.arange(T, dtype=torch.int32, device="cuda")) and torch.equal(new_cu, cu)
+    assert torch.equal(mask, vis)
+    ffn = lambda v, a, b, c: (torch.nn.functional.silu(v @ a.double().T) * (v @ b.double().T)) @ c.double().T
+    v = x.double()
+    ref = ffn(v, *(t[0] for t in sh))
+    if k_text:
+        _, idx, gate = m.route(x, vis)
+        for e in range(E):
+            ref += (gate.double() * (idx == e)).sum(1, keepdim=True) * ffn(v, *(t[e] for t in w))
+    assert max_rel_err(host(out), ref.cpu().numpy()) <= TOL[W.F32]
+
+
 @pytest.mark.parametrize("with_attention", [False, True])
 def test_layer_forward_merge_after_the_layer_over_several_compaction_blocks(with_attention):
     """Merging on the layer output at a size where the experts run in several row tiles per expert, the
