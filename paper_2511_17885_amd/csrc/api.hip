@@ -399,7 +399,7 @@ int fmoe_layer_forward(fmoe_ctx* ctx, const fmoe_prune_params* params, const voi
   const bool merge_after = merging && params->prune_mode == 2;
   const bool small = !merging && T > 0 && dispatch_small_fits(T, do_prune ? params->window : 1, do_prune);
   // with merging the pruning decisions take the general kernels, but a small batch still gets its
-  // permutation and tile lists from the single-workgroup kernel
+  // permutation and tile lists from the small-batch kernel
   const bool small_merge = merging && T > 0 && dispatch_small_fits(T, 1, false);
   // whenever the layer prunes, the router's launch carries the per-sequence ordinal blocks
   fmoe_ordinals_job ord{};
@@ -424,7 +424,7 @@ int fmoe_layer_forward(fmoe_ctx* ctx, const fmoe_prune_params* params, const voi
   const int32_t* kept = nullptr;
   const int32_t* n_dev = nullptr;
   if (small) {
-    // a few thousand tokens: scores, then one block for the whole prune/permute chain
+    // a few thousand tokens: scores, then one launch for the whole prune/permute chain
     if ((rc = launch_prune_dispatch_small(ctx, params, do_prune, probs, is_visual, cu_seqlens, B, T,
                                           attn_importance, topk_idx, kept_idx, new_cu_seqlens,
                                           is_visual_out, expert_offsets, perm_src, inv_perm, ws, L, s)) != FMOE_OK)

@@ -164,7 +164,7 @@ int launch_prune(const fmoe_ctx* ctx, const fmoe_prune_params* pp, const float* 
                  uint8_t* is_visual_out, const void* x_in, void* x_merged, uint8_t* is_merged_out,
                  void* ws, const fmoe_ws_layout& L, hipStream_t stream, bool ordinals_ready = false);
 
-// Small batches: window scores, then ONE block for drop order, compaction, permutation by expert and
+// Small batches: window scores, then ONE launch for drop order, compaction, permutation by expert and
 // the grouped-GEMM tile lists (prune == false: every token is kept).  Expects the visual ordinals in
 // the workspace (fmoe_ordinals_job) when pruning.  T_dev (nullable): device count of the tokens present;
 // write_kept = false: permutation and tile lists only (kept_idx / new_cu_seqlens / is_visual_out untouched).
