@@ -219,6 +219,8 @@ __global__ __launch_bounds__(256) void window_score_kernel(
 // In place of counting all pairs of windows, deciding, flagging and writing (three launches, five with merging and
 // attention), average kernel times: 4096 tokens, 1280 windows 17.0 -> 10.4 us; 8192 tokens, 1588 windows 17.5 -> 10.7; three
 // ragged sequences of 5003 tokens, one of them short, 14.9 -> 12.8; 1600 tokens, merging and attention 24.4 -> 15.4.
+// A block takes the sequences that it touches one after the other: three of 7000 tokens, merging without attention (three
+// launches before), cost their layer 6 us more than they did.
 // Sequences of up to CP_WAVE_N windows are decided by a wavefront each (lane = window, ranks by counting), so that a
 // block with many short ones does not walk them one barrier at a time.
 constexpr int CP_BLOCK = 512;
