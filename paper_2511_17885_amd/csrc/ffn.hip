@@ -1240,8 +1240,14 @@ __device__ __forceinline__ void f32_tile(const GemmProblem& P, const fmoe_tile& 
 // Measured, gate/up + down, us, fp32 instruction / split: that layer with half of the visual tokens kept 214 + 117 / 166 + 89,
 // 3000 tokens 341 + 181 / 256 + 137, 416 tokens 100 + 49 / 77 + 43, one token 32 + 23 / 31 + 24; d 4096, 8 experts of 1536,
 // 400 tokens 156 + 66 / 118 + 52, 8 tokens 86 + 39 / 78 + 37.
-// A result that is not finite (infinities split into infinity and NaN), or so small that parts below the range of
-// bf16 could count in it, is computed again on the fp32 instruction.
+// Range: rows are split times 2^96, so that every part of every row value down to fp32's smallest is a normal bf16, and
+// results are divided by it.  Row values from 2^32, results from 2^32 and weights that round to infinity in bf16 come out
+// as infinity or NaN; those results are computed again on the fp32 instruction.  Weights keep their bits down to 2^-133,
+// the smallest bf16 (the instruction takes subnormals, checked on the card); against rows below 2^32 what they lose is
+// below K * 2^-102, so results below F_TINY are computed again too, and a result of zero unless its row or its weights
+// are zero.  Scaling instead of a test on the operands while splitting: one multiplication per row value (a third of
+// the values or less), where finding the largest or the smallest operand takes one instruction per pair of them all,
+// and whether a result is computed again depends on that result alone, not on the others of its tile.
 constexpr int F_SPLIT_K = 896;
 constexpr int S_ROWS = FBM + 128;              // rows of a k tile in LDS: the tile's, then the weights'
 constexpr int S_PLANE = S_ROWS * FBK;          // one part of a k tile, in bf16 elements
@@ -1251,7 +1257,8 @@ constexpr int S_BUF = 3 * S_PLANE;             // a buffer
 // and a shared one, 2000 tokens 206 / 214, 600 tokens 113 / 110; d 4096, 8 experts of 1536, 400 tokens 203 / 170.
 constexpr int F_WIDE_ROWS = 20;
 constexpr int F_WIDE_ITEMS = 1024;
-constexpr float F_TINY = 0x1p-60f;             // parts lost are below 2^-125 of an operand
+constexpr float S_ROW_SCALE = 0x1p96f;         // exact, as every power of two
+constexpr float F_TINY = 0x1p-60f;             // K * 2^-102 is below 2^-25 of it up to K = 2^17
 // The three parts of four values: each the nearest bf16 to what the ones before leave over.
 __device__ __forceinline__ void split_bf16(f32x4_t v, uint2 (&part)[3]) {
   typedef __attribute__((__vector_size__(2 * sizeof(__bf16)))) __bf16 bf16x2_t;
@@ -1269,6 +1276,18 @@ __device__ __forceinline__ void split_bf16(f32x4_t v, uint2 (&part)[3]) {
     }
     part[p] = make_uint2(w[0], w[1]);
   }
+}
+
+// Row r of the tile; past its end the last one again.
+__device__ __forceinline__ const float* gathered_row(const GemmProblem& P, const fmoe_tile& tile, int group, bool shared,
+                                                     int r) {
+  int src = tile.row0 + (r < tile.rows ? r : tile.rows - 1);
+  if (P.map1) {
+    src = P.map1[src];
+    if (P.map1_limit > 0) src = src < 0 ? 0 : (src >= P.map1_limit ? P.map1_limit - 1 : src);
+  }
+  if (P.map2) src = P.map2[src];
+  return P.A + (shared ? (size_t)group * P.a_group_off : 0) + (size_t)src * P.lda;
 }
 
 // SLOTS: k tiles in a register ring, BUFS: LDS buffers
@@ -1310,16 +1329,7 @@ __device__ __forceinline__ void split_products(const GemmProblem& P, const fmoe_
   }
   const float* a_src[A_IT];
 #pragma unroll
-  for (int it = 0; it < A_IT; ++it) {
-    const int r = 32 * it + (tid >> 3);
-    int src = tile.row0 + (r < tile.rows ? r : tile.rows - 1);
-    if (P.map1) {
-      src = P.map1[src];
-      if (P.map1_limit > 0) src = src < 0 ? 0 : (src >= P.map1_limit ? P.map1_limit - 1 : src);
-    }
-    if (P.map2) src = P.map2[src];
-    a_src[it] = P.A + (shared ? (size_t)group * P.a_group_off : 0) + (size_t)src * P.lda + chunk * 4;
-  }
+  for (int it = 0; it < A_IT; ++it) a_src[it] = gathered_row(P, tile, group, shared, 32 * it + (tid >> 3)) + chunk * 4;
   auto load_a = [&](int slot, int t) {
     const int off = (t < NT ? t : NT - 1) * FBK;   // scalar
 #pragma unroll
@@ -1334,7 +1344,7 @@ __device__ __forceinline__ void split_products(const GemmProblem& P, const fmoe_
 #pragma unroll
     for (int it = 0; it < IT; ++it) {
       uint2 part[3];
-      split_bf16(raw[slot][it], part);
+      split_bf16(it < A_IT ? raw[slot][it] * S_ROW_SCALE : raw[slot][it], part);
       const int row = it < A_IT ? 32 * it : FBM + 32 * (it - A_IT);
 #pragma unroll
       for (int p = 0; p < 3; ++p) *reinterpret_cast<uint2*>(dst + buf * S_BUF + p * S_PLANE + row * FBK) = part[p];
@@ -1432,7 +1442,48 @@ __device__ __forceinline__ void split_products(const GemmProblem& P, const fmoe_
 #pragma unroll
   for (int rb = 0; rb < NRB; ++rb)
 #pragma unroll
-    for (int f = 0; f < 2; ++f) acc[rb][f] += low[rb][f];
+    for (int f = 0; f < 2; ++f) acc[rb][f] = (acc[rb][f] + low[rb][f]) * (1.0f / S_ROW_SCALE);
+}
+
+// Is a result zero although neither its row nor its weights are?  Uniform.  A thread stops at its first value that is not
+// zero, so only zero rows are read to their end.  (As: no longer read)
+template <bool SWIGLU, int NRB>
+__device__ __forceinline__ bool lost_in_zero(const GemmProblem& P, const fmoe_tile& tile, int group, bool shared, int nt,
+                                             int* As, const f32x4_t (&acc)[NRB][2]) {
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, K = P.K;
+  if (tid < S_ROWS) As[tid] = 0;   // rows of LDS as in the products; 1: something there
+  __syncthreads();
+  auto look = [&](const float* row, int at) {
+    constexpr int AHEAD = 8;       // loads in flight
+    const int first = (tid & 7) * 4;
+    uint32_t any = 0;
+    for (int k = first; k < K && any == 0; k += AHEAD * FBK) {
+      u32x4_t v[AHEAD];
+#pragma unroll
+      for (int u = 0; u < AHEAD; ++u) v[u] = *reinterpret_cast<const u32x4_t*>(row + (k + u * FBK < K ? k + u * FBK : first));
+#pragma unroll
+      for (int u = 0; u < AHEAD; ++u) any |= (v[u][0] | v[u][1] | v[u][2] | v[u][3]) & 0x7fffffffu;
+    }
+    if (any) As[at] = 1;
+  };
+#pragma unroll 1
+  for (int r = tid >> 3; r < NRB * 16; r += 32) look(gathered_row(P, tile, group, shared, r), r);
+#pragma unroll 1
+  for (int r = tid >> 3; r < 128; r += 32) {
+    const int f = (r >> 4) & 1, w = r >> 5;
+    const int n = SWIGLU ? nt * 64 + w * 16 + (r & 15) : nt * 128 + r;
+    look((SWIGLU && f ? P.B1 : P.B0) + (size_t)group * P.group_stride + (size_t)(n < P.N ? n : P.N - 1) * P.ldb, FBM + r);
+  }
+  __syncthreads();
+  bool lost = false;
+#pragma unroll
+  for (int rb = 0; rb < NRB; ++rb)
+#pragma unroll
+    for (int f = 0; f < 2; ++f)
+#pragma unroll
+      for (int v = 0; v < 4; ++v)
+        lost |= acc[rb][f][v] == 0.0f && As[rb * 16 + 4 * (lane >> 4) + v] != 0 && As[FBM + wave * 32 + f * 16 + (lane & 15)] != 0;
+  return __syncthreads_or(lost) != 0;
 }
 
 template <bool SWIGLU, int NRB, int SLOTS, int BUFS>
@@ -1440,15 +1491,20 @@ __device__ __forceinline__ void split_tile(const GemmProblem& P, const fmoe_tile
                                            bf16_t* As) {
   f32x4_t acc[NRB][2];
   split_products<SWIGLU, NRB, SLOTS, BUFS>(P, tile, group, shared, nt, As, acc);
-  auto again = [](float v) { return !(fabsf(v) < __builtin_inff()) || (fabsf(v) < F_TINY && v != 0.0f); };
-  bool any = false;
+  auto again = [](float v) { return !(fabsf(v) < __builtin_inff()) || fabsf(v) < F_TINY; };
+  bool any = false, certain = false;   // (zeros: only if there is something in both operands)
 #pragma unroll
   for (int rb = 0; rb < NRB; ++rb)
 #pragma unroll
     for (int f = 0; f < 2; ++f)
 #pragma unroll
-      for (int v = 0; v < 4; ++v) any |= again(acc[rb][f][v]);
-  if (__syncthreads_or(any)) {
+      for (int v = 0; v < 4; ++v) {
+        const bool a = again(acc[rb][f][v]);
+        any |= a;
+        certain |= a && acc[rb][f][v] != 0.0f;
+      }
+  if (__syncthreads_or(any) && (__syncthreads_or(certain) || lost_in_zero<SWIGLU, NRB>(P, tile, group, shared, nt,
+                                                                                       reinterpret_cast<int*>(As), acc))) {
     f32x4_t whole[NRB][2];
     f32_products<SWIGLU, NRB, 2>(P, tile, group, shared, nt, reinterpret_cast<float*>(As), whole);
 #pragma unroll

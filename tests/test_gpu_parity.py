@@ -1674,6 +1674,48 @@ def test_expert_ffn_fp32_tile_edges(d, F):
         assert max_rel_err(host(ysh)[s], ffn(rows, sh[0][s], sh[1][s], sh[2][s])) <= TOL[W.F32], s
 
 
+@pytest.mark.parametrize("d,F", [(904, 896), (928, 912)])
+def test_expert_ffn_fp32_split_operands_far_apart(d, F):
+    """Operands whose lower parts lie below the range of bf16, and such that vanish in it, where the other operand brings
+    the result back to an ordinary size: rows (up projection from the second half of a row), weights, and activations
+    between the two products; zero rows and zero weights beside them.  A row's bits do not depend on the rows beside it,
+    nor on the form; against fp64 at the fp32 bound (TOL)."""
+    scales = [(1, 1, 1), (1e-35, 1e30, 1), (1e-38, 1e33, 1), (1e-42, 1e37, 1), (1e30, 1e-35, 1), (1e33, 1e-40, 1e4),
+              (1, 1e-35, 1e32), (1, 1e-38, 1e35), (1e6, 1e-42, 1e30), (1e12, 1e-42, 1e30)]   # rows, up, down
+    E, each, n_many = len(scales), 21, 1200
+    n, half = E * each, d // 2
+    g = torch.Generator(device="cuda")
+    g.manual_seed(d + F)
+    rnd = lambda *s: torch.randn(s, generator=g, device="cuda")
+    x, w = rnd(n_many, d), [rnd(E, F, d) * 0.1, rnd(E, F, d), rnd(E, d, F) * 0.1]
+    w[0][:, :, half:], w[1][:, :, :half] = 0.0, 0.0
+    for e, (a, b, c) in enumerate(scales):
+        x[e * each:(e + 1) * each, half:] *= a
+        w[1][e] *= b
+        w[2][e] *= c
+    zero = torch.arange(E, device="cuda") * each + 7
+    x[zero] = 0.0
+    w[1][:, 5], w[2][:, 9] = 0.0, 0.0
+    m = binding.FMoE(d_model=d, n_experts=E, d_ffn=F, k_text=1, k_visual=1, dtype="f32")
+    m.set_weights(rnd(E, d), None, *w)
+    perm = torch.arange(n, dtype=torch.int32, device="cuda")
+    offs = torch.arange(E + 1, dtype=torch.int32, device="cuda") * each
+    y, _ = m.expert_ffn(x, None, n, offs, perm)
+    y_many, _ = m.expert_ffn(x, None, n_many, offs, perm)
+    assert torch.equal(y[:n].view(torch.int32), y_many[:n].view(torch.int32))
+    alone, _ = m.expert_ffn(x, None, n, torch.arange(E + 1, dtype=torch.int32, device="cuda"),
+                            (torch.arange(E, device="cuda") * each + 3).int())
+    assert torch.equal(y[:n].view(E, each, d)[:, 3].view(torch.int32), alone[:E].view(torch.int32))
+    assert not y[zero].any() and not y[:n, 9].any()
+    err = {}
+    for e in range(E):
+        v, a, b, c = (t.double() for t in (x[e * each:(e + 1) * each], w[0][e], w[1][e], w[2][e]))
+        ref = (torch.nn.functional.silu(v @ a.T) * (v @ b.T)) @ c.T
+        assert ref.abs().max() > 1e-12
+        err[scales[e]] = max_rel_err(host(y)[e * each:(e + 1) * each], ref.cpu().numpy())
+    assert max(err.values()) <= TOL[W.F32], err
+
+
 @pytest.mark.parametrize("E", [8, 72])   # fewer and more work items than CUs: the deep and the shallow register rings
 @pytest.mark.parametrize("d,F", [(512, 544), (520, 576), (616, 608), (640, 584)])
 def test_expert_ffn_fp32_long_reductions_of_few_rows(d, F, E):
