@@ -854,7 +854,8 @@ __global__ void identity_kept_kernel(fmoe_keep_all_job job, int T) {
 // intermediate arrays in LDS.  At a few thousand tokens each of those steps is a few microseconds
 // of work and the launches between them cost more than the steps themselves.
 //   * both blocks come to the same expert offsets; then one writes the token lists and the other the tile lists, neither
-//     behind the other (1600 tokens 15.3 -> 13.5 us, permutation only 10.7 -> 9.8, a 64-token batch 8.9 -> 8.4);
+//     behind the other (1600 tokens 15.3 -> 13.5 us, permutation only 10.7 -> 9.8, a 64-token batch 8.9 -> 8.4).  Where
+//     the new sequence bounds replace the old ones in place, one block does both: two would race on them;
 //   * every global input is fetched up front (thread i owns tokens i, i+1024, ...), every global
 //     output is stored at the very end, so no barrier in between waits on memory;
 //   * drop order: the order (normalised attention asc, score desc, index asc) is total, and of the places in it
@@ -1173,13 +1174,13 @@ __global__ __launch_bounds__(SB_THREADS) void prune_dispatch_small_kernel(SmallA
   }
   __syncthreads();
 
-  // ---- grouped-GEMM tile lists
-  if (blockIdx.x != 0) {
+  // ---- grouped-GEMM tile lists, by the last block
+  if (blockIdx.x + 1 == gridDim.x) {
     fmoe_build_tiles<true>(s_off, E, a.row_cap, n, a.n_shared, a.geom.bm, a.geom.run, a.geom.tile_cap, a.geom.cols1,
                            a.geom.scols1, a.tiles1, a.tiles2, a.tile_count, s_scr);
     if (tid <= E) a.expert_offsets[tid] = s_off[tid];
-    return;
   }
+  if (blockIdx.x != 0) return;
 
   // ---- token lists
   for (int b = tid; b <= B && !PERM_ONLY; b += SB_THREADS) {   // new_cu[b] = kept tokens before the sequence start
@@ -1207,6 +1208,12 @@ __global__ __launch_bounds__(SB_THREADS) void prune_dispatch_small_kernel(SmallA
       }
     }
   }
+}
+
+// Do the sequence bounds before and after share memory?
+bool same_bounds(const int32_t* cu, const int32_t* new_cu, int B) {
+  const uintptr_t a = reinterpret_cast<uintptr_t>(cu), b = reinterpret_cast<uintptr_t>(new_cu), n = ((uintptr_t)B + 1) * 4;
+  return a < b + n && b < a + n;
 }
 
 // One wavefront per window unit (floor(T/W) + B units cover every window), four per block.
@@ -1341,12 +1348,13 @@ int launch_prune_dispatch_small(const fmoe_ctx* ctx, const fmoe_prune_params* pp
     fmoe_prof_scope prof(ctx, SLOT_DISPATCH, stream);
     if (!write_kept && (prune || T_dev == nullptr))
       return fmoe_fail(FMOE_ERR_INVALID_ARG, "small dispatch: the permutation-only form needs a device token count and no pruning");
-#define FMOE_DISPATCH_LAUNCH(TP, KM)                                                                            \
-  do {                                                                                                          \
-    if (write_kept)                                                                                             \
-      hipLaunchKernelGGL((prune_dispatch_small_kernel<TP, KM, false>), dim3(2), dim3(SB_THREADS), 0, stream, a); \
-    else                                                                                                        \
-      hipLaunchKernelGGL((prune_dispatch_small_kernel<TP, KM, true>), dim3(2), dim3(SB_THREADS), 0, stream, a);  \
+    const dim3 grid(write_kept && same_bounds(cu_seqlens, new_cu_seqlens, B) ? 1 : 2);
+#define FMOE_DISPATCH_LAUNCH(TP, KM)                                                                         \
+  do {                                                                                                       \
+    if (write_kept)                                                                                          \
+      hipLaunchKernelGGL((prune_dispatch_small_kernel<TP, KM, false>), grid, dim3(SB_THREADS), 0, stream, a); \
+    else                                                                                                     \
+      hipLaunchKernelGGL((prune_dispatch_small_kernel<TP, KM, true>), grid, dim3(SB_THREADS), 0, stream, a);  \
   } while (0)
     // the register arrays as small as the call allows: with those for sixteen experts per token a batch of 3000
     // tokens and six took 34.6 us (pruning, the drop order then still sorted) and 25.8 us (not), with those for eight

@@ -1532,6 +1532,27 @@ def test_layer_forward_that_keeps_every_token_above_the_small_batch(k_text, k_vi
     assert max_rel_err(host(out), ref.cpu().numpy()) <= TOL[W.F32]
 
 
+IN_PLACE_SMALL = [([1500], [90], 0.5, 0.0), ([1500], [90], 1.0, 0.0), ([700, 3, 900, 0], [9, 0, 200, 1], 0.6, 0.0),
+                  ([4, 0, 3] * 200, [1, 2, 0] * 200, 0.5, 0.0)]      # more sequences than have their bounds in LDS
+
+
+@pytest.mark.parametrize("T_v,T_t,retention,gamma", IN_PLACE_SMALL)
+def test_layer_forward_updates_the_bounds_in_place(T_v, T_t, retention, gamma):
+    """new_cu_seqlens = cu_seqlens: the same results, three times over, as with bounds of their own."""
+    wl = W.small_random(sum(T_v), T_v=T_v, T_t=T_t, d=64, E=16, F=32, k_text=3, k_visual=2, retention=retention, window=3,
+                        n_shared=1, F_shared=32)
+    m = make_layer(wl)
+    x, vis, cu = inputs(wl)
+    pp = binding.prune_params(retention=retention, window=3, gamma=gamma)
+    out, kept, new_cu, mask = m.layer_forward(x, vis, cu, pp, want_mask=True)
+    n = int(new_cu[-1])
+    for _ in range(3):
+        again = cu.clone()
+        out2, kept2, new_cu2, mask2 = m.layer_forward(x, vis, again, pp, new_cu=again, want_mask=True)
+        assert torch.equal(new_cu2, new_cu) and torch.equal(kept2[:n], kept[:n]) and torch.equal(mask2[:n], mask[:n])
+        assert torch.equal(out2[:n], out[:n])
+
+
 @pytest.mark.parametrize("with_attention", [False, True])
 def test_layer_forward_merge_after_the_layer_over_several_compaction_blocks(with_attention):
     """Merging on the layer output at a size where the experts run in several row tiles per expert, the
