@@ -183,7 +183,8 @@ int fmoe_route(fmoe_ctx* ctx, const void* x, const uint8_t* is_visual, int32_t T
  * survive (at least 1 if N_v > 0): whole windows are dropped in order while they fit and the
  * next window loses its last tokens.  Text tokens always survive.
  * kept_idx [T capacity] int32: ascending global indices of surviving tokens (first T' valid).
- * new_cu_seqlens [B+1] int32: per-sequence boundaries after pruning; new_cu_seqlens[B] = T'.
+ * new_cu_seqlens [B+1] int32: per-sequence boundaries after pruning; new_cu_seqlens[B] = T'.  Here and in
+ * fmoe_layer_forward it may be cu_seqlens itself; the other outputs share no memory with the inputs.
  * scores [T capacity] fp32 or NULL: the score C of window i of sequence b at
  * scores[cu_seqlens[b] + i].
  * Window merging (Sec. 3.2.3, Eq.14-18), params->gamma > 0: before the drop walk at most

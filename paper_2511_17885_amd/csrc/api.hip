@@ -123,6 +123,7 @@ fmoe_ws_layout fmoe_layout(const fmoe_ctx* ctx, int32_t max_tokens, int32_t max_
   L.seq_nv = take(B * 4);
   L.win_s = take(T * 4);
   L.win_a = take(T * 4);
+  L.new_cu = take((B + 1) * 4);
   L.is_merged = take(T);
   L.vis_out = take(T);
   L.x_merged = take(T * (size_t)c.d_model * es);

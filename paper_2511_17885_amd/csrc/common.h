@@ -96,7 +96,7 @@ int fmoe_fail(int code, const char* fmt, ...);
 struct fmoe_ws_layout {
   size_t probs, topk_idx, topk_gate;            // layer_forward intermediates
   size_t vis_tok, vis_ord, seq_nv;              // prune
-  size_t win_s, win_a;                          // prune
+  size_t win_s, win_a, new_cu;                  // prune
   size_t is_merged, vis_out, x_merged;          // layer_forward with window merging
   size_t slot_rank, blk_count;                  // permute
   size_t expert_offsets, perm_src, inv_perm;    // layer_forward intermediates

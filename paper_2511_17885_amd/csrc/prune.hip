@@ -1246,6 +1246,10 @@ int launch_prune(const fmoe_ctx* ctx, const fmoe_prune_params* pp, const float* 
   const bool merging = pp->gamma > 0.0f;
   uint8_t* is_merged = is_merged_out;
   if (merging && is_merged == nullptr) is_merged = reinterpret_cast<uint8_t*>(base + L.is_merged);
+  // blocks of the compaction and the gather behind it read the bounds while one block writes the new ones: if these are
+  // to take their place, they wait in the workspace
+  const bool in_place = same_bounds(cu_seqlens, new_cu_seqlens, B);
+  int32_t* const new_cu = in_place ? reinterpret_cast<int32_t*>(base + L.new_cu) : new_cu_seqlens;
   const int E = ctx->cfg.n_experts;
   if (T == 0 || B == 0) return launch_identity_kept(is_visual, cu_seqlens, B, T, kept_idx,
                                                     new_cu_seqlens, is_visual_out, stream);
@@ -1266,7 +1270,7 @@ int launch_prune(const fmoe_ctx* ctx, const fmoe_prune_params* pp, const float* 
     ca.is_visual = is_visual; ca.cu = cu_seqlens; ca.B = B; ca.T = T; ca.W = pp->window;
     ca.retention = pp->retention; ca.gamma = pp->gamma; ca.alpha = pp->alpha;
     ca.vis_ord = vis_ord; ca.seq_nv = seq_nv; ca.win_s = win_s; ca.win_a = win_a;
-    ca.scores_out = scores_out; ca.kept_idx = kept_idx; ca.new_cu = new_cu_seqlens; ca.is_visual_out = is_visual_out;
+    ca.scores_out = scores_out; ca.kept_idx = kept_idx; ca.new_cu = new_cu; ca.is_visual_out = is_visual_out;
     ca.is_merged_out = merging ? is_merged : nullptr;
     ca.window_rcp = ((1ull << 37) + pp->window - 1) / pp->window;
     const dim3 grid((T + CP_BLOCK - 1) / CP_BLOCK), block(CP_BLOCK);
@@ -1278,16 +1282,17 @@ int launch_prune(const fmoe_ctx* ctx, const fmoe_prune_params* pp, const float* 
   if (merging) {
     if (ctx->cfg.dtype == FMOE_BF16)
       hipLaunchKernelGGL(merge_gather_kernel<bf16_t>, dim3(T), dim3(256), 0, stream,
-                         static_cast<const bf16_t*>(x_in), ctx->cfg.d_model, kept_idx, new_cu_seqlens + B,
+                         static_cast<const bf16_t*>(x_in), ctx->cfg.d_model, kept_idx, new_cu + B,
                          is_merged, cu_seqlens, B, T, pp->window, vis_ord, vis_tok, seq_nv,
                          static_cast<bf16_t*>(x_merged), pp->merge_mode);
     else
       hipLaunchKernelGGL(merge_gather_kernel<float>, dim3(T), dim3(256), 0, stream,
-                         static_cast<const float*>(x_in), ctx->cfg.d_model, kept_idx, new_cu_seqlens + B,
+                         static_cast<const float*>(x_in), ctx->cfg.d_model, kept_idx, new_cu + B,
                          is_merged, cu_seqlens, B, T, pp->window, vis_ord, vis_tok, seq_nv,
                          static_cast<float*>(x_merged), pp->merge_mode);
   }
   FMOE_HIP_CHECK(hipGetLastError());
+  if (in_place) return launch_identity_kept(nullptr, new_cu, B, T, nullptr, new_cu_seqlens, nullptr, stream);
   return FMOE_OK;
 }
 

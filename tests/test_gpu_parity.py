@@ -1532,11 +1532,12 @@ def test_layer_forward_that_keeps_every_token_above_the_small_batch(k_text, k_vi
     assert max_rel_err(host(out), ref.cpu().numpy()) <= TOL[W.F32]
 
 
-IN_PLACE_SMALL = [([1500], [90], 0.5, 0.0), ([1500], [90], 1.0, 0.0), ([700, 3, 900, 0], [9, 0, 200, 1], 0.6, 0.0),
-                  ([4, 0, 3] * 200, [1, 2, 0] * 200, 0.5, 0.0)]      # more sequences than have their bounds in LDS
-
-
-@pytest.mark.parametrize("T_v,T_t,retention,gamma", IN_PLACE_SMALL)
+@pytest.mark.parametrize("T_v,T_t,retention,gamma", [
+    ([1500], [90], 0.5, 0.0), ([1500], [90], 1.0, 0.0), ([700, 3, 900, 0], [9, 0, 200, 1], 0.6, 0.0),
+    ([4, 0, 3] * 200, [1, 2, 0] * 200, 0.5, 0.0),      # more sequences than have their bounds in LDS
+    ([700, 3, 900, 0], [9, 0, 200, 1], 0.6, 0.1), ([4100], [90], 0.5, 0.0), ([4100], [90], 1.0, 0.0),
+    ([3700, 3, 1900, 0], [9, 0, 200, 1], 0.6, 0.0), ([3700, 3, 1900, 0], [9, 0, 200, 1], 0.6, 0.1),
+    ([4, 0, 30] * 200, [1, 2, 0] * 200, 0.5, 0.0)])
 def test_layer_forward_updates_the_bounds_in_place(T_v, T_t, retention, gamma):
     """new_cu_seqlens = cu_seqlens: the same results, three times over, as with bounds of their own."""
     wl = W.small_random(sum(T_v), T_v=T_v, T_t=T_t, d=64, E=16, F=32, k_text=3, k_visual=2, retention=retention, window=3,
