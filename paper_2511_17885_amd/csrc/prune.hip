@@ -219,8 +219,15 @@ __global__ __launch_bounds__(256) void window_score_kernel(
 // In place of counting all pairs of windows, deciding, flagging and writing (three launches, five with merging and
 // attention), average kernel times: 4096 tokens, 1280 windows 17.0 -> 10.4 us; 8192 tokens, 1588 windows 17.5 -> 10.7; three
 // ragged sequences of 5003 tokens, one of them short, 14.9 -> 12.8; 1600 tokens, merging and attention 24.4 -> 15.4.
-// A block takes the sequences that it touches one after the other: three of 7000 tokens, merging without attention (three
-// launches before), cost their layer 6 us more than they did.
+// Without attention both orders are one: the two windows are found together.  fmoe_prune of one sequence of 7000 tokens in
+// windows of two, merging: two searches 35.7 us, one 32.8, three launches 32.7.
+// A block takes the sequences that it touches one after the other, so in batches of up to CP_CUT_SEQS sequences no block
+// has positions of two: its place is looked up first, in one load of a wavefront.  fmoe_prune in us, three to five
+// launches / blocks of CP_BLOCK positions throughout / ending with their sequence: 7000 tokens in three sequences, windows
+// of two, 22.4 / 22.6 / 20.1, with merging 31.7 / 38.5 / 31.8, with attention 25.1 / 26.9 / 23.0; in sixteen 23.0 / 25.2 /
+// 16.6, 32.2 / 44.9 / 28.0, 25.1 / 30.7 / 18.6; 1000 tokens in eight 22.6 / 24.6 / 14.7, 30.1 / 43.7 / 22.2, 25.9 / 29.5 / 15.3.
+// Larger batches gain more from the one launch than that costs (4000 tokens in 64 sequences 36.1 -> 20.7, 12000 in 150
+// 43.1 -> 22.8).
 // Sequences of up to CP_WAVE_N windows are decided by a wavefront each (lane = window, ranks by counting), so that a
 // block with many short ones does not walk them one barrier at a time.
 constexpr int CP_BLOCK = 512;
@@ -229,6 +236,7 @@ constexpr int CP_KEYS = 4096;     // windows of a sequence whose keys stay in LD
 constexpr int CP_WAVE_N = 64;     // windows of a sequence that one wavefront decides
 constexpr int CP_RANK = 8;        // candidates of a selection that are ranked by counting
 constexpr int CP_SEQS = 512;      // sequences whose bounds stay in LDS
+constexpr int CP_CUT_SEQS = 62;   // sequences of a batch whose blocks end with them: with what lies ahead and behind a lane each
 
 struct CompactArgs {
   const uint8_t* is_visual;
@@ -245,6 +253,7 @@ struct CompactArgs {
   uint8_t* is_visual_out;         // or nullptr
   uint8_t* is_merged_out;         // or nullptr
   unsigned long long window_rcp;  // ceil(2^37 / W)
+  bool cut;                       // blocks end where a sequence ends (B <= CP_CUT_SEQS)
 };
 // v / W, exactly: W <= 64 and 0 <= v < 2^24, so the error of the product is below 2^24 in 2^37, less than 1 / W
 __device__ __forceinline__ int per_window(const CompactArgs& a, int v) {
@@ -299,29 +308,38 @@ template <bool MERGE, bool ATTN>
 __global__ __launch_bounds__(CP_BLOCK) void compact_kernel(CompactArgs a) {
   __shared__ uint32_t s_sc[CP_KEYS], s_att[ATTN ? CP_KEYS : 1];
   __shared__ unsigned long long s_red[2][CP_WAVES];
-  __shared__ __align__(16) int hist[3 * 256];
+  constexpr int NT = MERGE && !ATTN ? 2 : 1;   // windows that one search finds
+  constexpr int TABLE = NT * 256;
+  __shared__ __align__(16) int hist[3 * TABLE];
   // fates of the short sequences' windows, leading tokens that stay or ~0 for merged: of the sequence that the block
   // begins inside at i, of one that starts at position s at CP_WAVE_N + s - p0 + i (a sequence has no more windows
   // than tokens, so they don't overlap)
   __shared__ int s_fate[CP_WAVE_N + CP_BLOCK + CP_WAVE_N];
   __shared__ int s_few[CP_BLOCK], s_many[CP_BLOCK / CP_WAVE_N + 2];
-  __shared__ int s_count[3], s_first;   // sequences in the two lists, candidates; dropped of the first sequence before p0
-  __shared__ uint32_t s_cand_att[CP_RANK], s_cand_sc[CP_RANK];
-  __shared__ int s_cand[CP_RANK];
-  __shared__ int s_cu[CP_SEQS + 1], s_nv[CP_SEQS];
+  __shared__ int s_count[2 + NT], s_first;   // sequences in the two lists, candidates; dropped of the first sequence before p0
+  __shared__ uint32_t s_cand_att[NT * CP_RANK], s_cand_sc[NT * CP_RANK];
+  __shared__ int s_cand[NT * CP_RANK];
+  __shared__ int s_cu[CP_SEQS + 1], s_nv[CP_SEQS], s_ahead[CP_WAVES];
 
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int T = a.T, W = a.W, B = a.B;
-  const int p0 = blockIdx.x * CP_BLOCK, t = p0 + tid;   // p0 < T
-  const int p1 = p0 + CP_BLOCK < T ? p0 + CP_BLOCK : T;
-  const int tc = t < T ? t : T - 1;
+  int p0 = blockIdx.x * CP_BLOCK, p1 = p0 + CP_BLOCK < T ? p0 + CP_BLOCK : T;
+  if (a.cut) {   // lane = part of the batch: ahead of the sequences, each of them, behind them; a block's is the last to begin by it
+    const int begin = lane == 0 ? 0 : clampi(a.cu[lane <= B + 1 ? lane - 1 : B], 0, T);
+    const int first = begin / CP_BLOCK + lane;   // block; ascending in a partition (of bounds that decrease nothing below is used)
+    const int j = __popcll(__ballot(lane <= B + 1 && first <= (int)blockIdx.x)) - 1;
+    p0 = __builtin_amdgcn_readlane(begin, j) + ((int)blockIdx.x - __builtin_amdgcn_readlane(first, j)) * CP_BLOCK;
+    const int end = j == B + 1 ? T : __builtin_amdgcn_readlane(begin, j + 1);
+    p1 = p0 + CP_BLOCK < end ? p0 + CP_BLOCK : end;
+  }
+  const int t = p0 + tid, tc = t < T ? (t < 0 ? 0 : t) : T - 1;
   const float one_minus_alpha = 1.0f - a.alpha;
-  if (tid < 3) s_count[tid] = 0;
-  if (tid == 3) s_first = 0;
+  if (tid < 2 + NT) s_count[tid] = 0;
+  if (tid == 2 + NT) s_first = 0;
   __syncthreads();   // (while the first loads are on their way)
 
   // ---- the sequences: which of them have windows and positions in this block, what those before it have dropped
-  const int ord = a.vis_ord[tc], ord_p0 = a.vis_ord[p0];   // (meaningless outside the sequences)
+  const int ord = a.vis_ord[tc], ord_p0 = a.vis_ord[clampi(p0, 0, T - 1)];   // (meaningless outside the sequences)
   const uint8_t vis = a.is_visual_out != nullptr ? a.is_visual[tc] : 0;
   const bool cached = B <= CP_SEQS;
   bool bad = false;
@@ -331,7 +349,7 @@ __global__ __launch_bounds__(CP_BLOCK) void compact_kernel(CompactArgs a) {
     bad |= e < s;
     if (e <= p0) {
       gone += nv - token_budget(nv, a.retention);
-    } else if (s < p1 && nv > 0) {
+    } else if (s < p1 && p0 < p1 && nv > 0) {
       if (nv > W * CP_WAVE_N) {
         const int at = atomicAdd(&s_count[1], 1);   // (a bound that decreases could make them more than there is room for)
         if (at < CP_BLOCK / CP_WAVE_N + 2) s_many[at] = b;
@@ -357,14 +375,16 @@ __global__ __launch_bounds__(CP_BLOCK) void compact_kernel(CompactArgs a) {
     bad |= (s_red[0][w] >> 63) != 0;
   }
   if (__builtin_expect(bad, 0)) {   // uniform: bounds that decrease are no partition into sequences; nothing is pruned
-    if (t < T) {
-      a.kept_idx[t] = t;
-      if (a.is_visual_out != nullptr) a.is_visual_out[t] = vis;
-      if (a.is_merged_out != nullptr) a.is_merged_out[t] = 0;
+    const int own = blockIdx.x * CP_BLOCK + tid;
+    if (own < T) {
+      a.kept_idx[own] = own;
+      if (a.is_visual_out != nullptr) a.is_visual_out[own] = a.is_visual[own];
+      if (a.is_merged_out != nullptr) a.is_merged_out[own] = 0;
     }
-    for (int b = t; b <= B; b += gridDim.x * CP_BLOCK) a.new_cu[b] = clampi(a.cu[b], 0, T);
+    for (int b = own; b <= B; b += gridDim.x * CP_BLOCK) a.new_cu[b] = clampi(a.cu[b], 0, T);
     return;
   }
+  if (p0 >= p1 && blockIdx.x + 1 != gridDim.x) return;   // uniform: no positions, and the bounds are the last block's
   const int32_t* cu = cached ? s_cu : a.cu;
   const int32_t* seq_nv = cached ? s_nv : a.seq_nv;
   auto visual_tokens = [&](int b) {
@@ -384,7 +404,7 @@ __global__ __launch_bounds__(CP_BLOCK) void compact_kernel(CompactArgs a) {
     phase ^= 1;
     return total;
   };
-  int bits = t < T ? 1 : 0;   // bit 0: the token stays, bit 1: a merged window collapses into it
+  int bits = t < p1 ? 1 : 0;   // bit 0: the token stays, bit 1: a merged window collapses into it
   const int n_few = s_count[0], n_many = s_count[1];
   // visual tokens of the sequence from s on ahead of p0
   auto ahead_of_block = [&](int s) { return s < p0 ? (ord_p0 >= 0 ? ord_p0 : ~ord_p0) : 0; };
@@ -428,6 +448,12 @@ __global__ __launch_bounds__(CP_BLOCK) void compact_kernel(CompactArgs a) {
     auto key_of = [&](int i) { return key_from(a.win_s[s + i], win_a(i), amax); };
     const fmoe_window_key K_first = key_of(0), K_last = key_of(n - 1);
     uint32_t diff_sc = 0, diff_att = 0;   // bits in which the keys are not all alike
+    int ahead_of_last = 0;                // windows ahead of the last one in the merge order, without merging in the drop order
+    auto take_in = [&](int i, fmoe_window_key K) {
+      diff_sc |= K.sc ^ K_first.sc;
+      diff_att |= K.att ^ K_first.att;
+      ahead_of_last += (int)(i < n - 1) & (int)(MERGE ? K.sc <= K_last.sc : K.both() <= K_last.both());
+    };
     for (int i0 = 0; i0 < n && i0 < CP_KEYS; i0 += 4 * CP_BLOCK) {   // four loads at a time (past the end the last window)
       fmoe_window_key K[4];
 #pragma unroll
@@ -439,20 +465,20 @@ __global__ __launch_bounds__(CP_BLOCK) void compact_kernel(CompactArgs a) {
       for (int r = 0; r < 4; ++r) {
         s_sc[i0 + r * CP_BLOCK + tid] = K[r].sc;
         if (ATTN) s_att[i0 + r * CP_BLOCK + tid] = K[r].att;
-        diff_sc |= K[r].sc ^ K_first.sc;
-        diff_att |= K[r].att ^ K_first.att;
+        take_in(i0 + r * CP_BLOCK + tid, K[r]);
       }
     }
     static_assert(CP_KEYS % (4 * CP_BLOCK) == 0, "whole rounds of keys");
-    for (int i = CP_KEYS + tid; i < n; i += CP_BLOCK) {
-      const fmoe_window_key K = key_of(i);
-      diff_sc |= K.sc ^ K_first.sc;
-      diff_att |= K.att ^ K_first.att;
-    }
+    for (int i = CP_KEYS + tid; i < n; i += CP_BLOCK) take_in(i, key_of(i));
     diff_sc = wave_or(diff_sc);
     if (ATTN) diff_att = wave_or(diff_att);
-    if (lane == 0) s_red[phase][wave] = (unsigned long long)diff_att << 32 | diff_sc;
-    for (int h = tid; h < 256; h += CP_BLOCK) hist[h] = 0;
+    ahead_of_last = wave_scan(ahead_of_last);
+    if (lane == 63) {
+      s_red[phase][wave] = (unsigned long long)diff_att << 32 | diff_sc;
+      s_ahead[wave] = ahead_of_last;
+    }
+    ahead_of_last = 0;
+    for (int h = tid; h < TABLE; h += CP_BLOCK) hist[h] = 0;
     fmoe_window_cut cut{};
     const int n_full = w_last < W ? n - 1 : n;
     cut.n_full = n_full;
@@ -462,6 +488,7 @@ __global__ __launch_bounds__(CP_BLOCK) void compact_kernel(CompactArgs a) {
     for (int w = 0; w < CP_WAVES; ++w) {
       diff_sc |= (uint32_t)s_red[phase][w];
       if (ATTN) diff_att |= (uint32_t)(s_red[phase][w] >> 32);
+      ahead_of_last += s_ahead[w];
     }
     phase ^= 1;
     // this thread's windows, and up to the end of a round some past the last; their keys are its own
@@ -478,134 +505,184 @@ __global__ __launch_bounds__(CP_BLOCK) void compact_kernel(CompactArgs a) {
       for (int i = CP_KEYS + tid; i < n; i += CP_BLOCK) f(i, key_of(i));
     };
     fmoe_merge_plan p{0, 0, eps};
-    if constexpr (MERGE) {
-      int L = n;
-      if (n_full < n) {   // uniform
-        int v = 0;
-        each([&](int i, fmoe_window_key K) { v += (int)(i < n_full) & (int)(K.sc <= K_last.sc); });
-        L = block_sum(v);
-      }
-      p = merge_plan(nv, W, a.retention, a.gamma, L);
-    }
+    if constexpr (MERGE) p = merge_plan(nv, W, a.retention, a.gamma, n_full < n ? ahead_of_last : n);
     cut.last_merged = p.last_m;
     cut.last_keeps = w_last;
-    // stage 0: the full window at place q_full of the merge order; stage 1: of those not merged, the one at place q of
-    // the drop order
-#pragma unroll 1
-    for (int stage = MERGE ? 0 : 1; stage < 2; ++stage) {
-      int place, live = n_full;   // full windows that take part
-      if (stage == 0) {
-        place = p.q_full;
-        cut.merge_sc = place == 0 ? 0u : ~0u;
-        cut.merge_i = place == 0 ? -1 : CP_ALL;
-        if (place == 0 || place >= n_full) continue;
-      } else {
-        live -= p.q_full;
-        const bool last = n_full < n && !p.last_m;
-        int ahead = 0;
-        if (last) {   // uniform
-          int v = 0;
-          each([&](int i, fmoe_window_key K) { v += (int)(i < n_full) & (int)!(MERGE && cut.merged(i, K)) & (int)(K.both() <= K_last.both()); });
-          ahead = block_sum(v);
-        }
-        drop_walk(a, p.u_rem, last, w_last, ahead, place, cut.part, cut.last_keeps);
-        const bool none = place == 0 && cut.part == 0;
-        cut.drop_key = none ? fmoe_window_key{0u, 0u} : fmoe_window_key{ATTN ? ~0u : 0u, ~0u};
-        cut.drop_i = none ? -1 : CP_ALL;
-        if (none || place >= live) continue;
+    const int index_bits = 32 - __clz(n);
+    // The windows at `place` of the drop order (by_att: with the attention keys) among the candidates: digits of eight bits of
+    // the attention key, then of the score's, then of the index, each from the highest bit on that is not the same in all,
+    // until the candidates are few enough to rank.  Counts of the candidates per digit are summed by every wavefront for
+    // itself; a barrier a digit, the tables take turns.  Two windows of one order share a table until their digits part.
+    auto find = [&](bool by_att, int (&place)[NT], const bool (&wanted)[NT], auto candidate, fmoe_window_key (&found)[NT],
+                    int (&found_i)[NT]) {
+      struct { int level, fixed; uint32_t chosen, tied_sc, tied_att, att_counts, sc_counts; bool open; } st[NT];
+      bool shared = NT == 2;
+#pragma unroll
+      for (int q = 0; q < NT; ++q) {
+        const int level = by_att && diff_att != 0 ? 0 : (diff_sc != 0 ? 1 : 2);
+        st[q].level = level;
+        st[q].chosen = level == 0 ? K_first.att : (level == 1 ? K_first.sc : 0u);
+        st[q].fixed = level == 2 ? index_bits : 32 - __clz(level == 0 ? diff_att : diff_sc);   // bits from here on are those of `chosen`
+        // what the levels before have settled (the keys' common attention, if it takes part in the order at all)
+        st[q].tied_att = K_first.att;
+        st[q].tied_sc = K_first.sc;
+        st[q].att_counts = by_att && level > 0 ? ~0u : 0u;
+        st[q].sc_counts = level == 2 ? ~0u : 0u;
+        st[q].open = wanted[q];
+        shared = shared && wanted[q];
       }
-      // The window at `place`: digits of eight bits of the attention key, then of the score's, then of the index, each
-      // from the highest bit on that is not the same in all, until the candidates are few enough to rank.  Counts of
-      // the candidates per digit are summed by every wavefront for itself; a barrier a digit, the tables take turns.
-      auto candidate = [&](int i, fmoe_window_key K) { return (int)(i < n_full) & (int)!(MERGE && stage == 1 && cut.merged(i, K)); };
-      const int index_bits = 32 - __clz(n);
-      int level = ATTN && stage == 1 && diff_att != 0 ? 0 : (diff_sc != 0 ? 1 : 2);
-      uint32_t chosen = level == 0 ? K_first.att : (level == 1 ? K_first.sc : 0u);
-      int fixed = level == 2 ? index_bits : 32 - __clz(level == 0 ? diff_att : diff_sc);   // bits from here on are those of `chosen`
-      // what the levels before have settled (the keys' common attention, if it takes part in the order at all)
-      fmoe_window_key tied = K_first;
-      uint32_t att_counts = ATTN && stage == 1 && level > 0 ? ~0u : 0u, sc_counts = level == 2 ? ~0u : 0u;
       int table = 0;
       for (;;) {   // uniform; ends because indices differ
-        const int shift = fixed > 8 ? fixed - 8 : 0;
-        int* const h = hist + table * 256;
+        int* const h = hist + table * TABLE;
         table = table == 2 ? 0 : table + 1;
-        for (int z = tid; z < 256; z += CP_BLOCK) hist[table * 256 + z] = 0;
-        auto live_digit = [&](int i, fmoe_window_key K, uint32_t& digit) {
-          const uint32_t v = level == 1 ? K.sc : (level == 0 ? K.att : (uint32_t)i);
+        for (int z = tid; z < TABLE; z += CP_BLOCK) hist[table * TABLE + z] = 0;
+        auto live_digit = [&](int q, int i, fmoe_window_key K, uint32_t& digit) {
+          const int shift = st[q].fixed > 8 ? st[q].fixed - 8 : 0;
+          const uint32_t v = st[q].level == 1 ? K.sc : (st[q].level == 0 ? K.att : (uint32_t)i);
           digit = (v >> shift) & 255u;
-          const uint32_t off = ((K.att ^ tied.att) & att_counts) | ((K.sc ^ tied.sc) & sc_counts) |
-                               (fixed < 32 ? (v ^ chosen) >> fixed : 0u);
+          const uint32_t off = ((K.att ^ st[q].tied_att) & st[q].att_counts) | ((K.sc ^ st[q].tied_sc) & st[q].sc_counts) |
+                               (st[q].fixed < 32 ? (v ^ st[q].chosen) >> st[q].fixed : 0u);
           return (int)(off == 0u) & candidate(i, K);
         };
         each([&](int i, fmoe_window_key K) {
-          uint32_t digit;
-          if (live_digit(i, K, digit)) atomicAdd(&h[digit], 1);
+#pragma unroll
+          for (int q = 0; q < NT; ++q) {
+            uint32_t digit;
+            if (st[q].open && !(q == 1 && shared) && live_digit(q, i, K, digit)) atomicAdd(&h[q * 256 + digit], 1);
+          }
         });
         __syncthreads();
-        const int4 c4 = *reinterpret_cast<const int4*>(&h[4 * lane]);
-        const int sum4 = c4.x + c4.y + c4.z + c4.w;
-        const int excl = wave_scan(sum4) - sum4;
-        const int src = __builtin_ctzll(__ballot(excl <= place && place < excl + sum4));   // exactly one lane
-        int before = excl, val = 4 * lane, here = c4.x;
-        if (before + here <= place) { before += here; here = c4.y; ++val; }
-        if (val > 4 * lane && before + here <= place) { before += here; here = c4.z; ++val; }
-        if (val > 4 * lane + 1 && before + here <= place) { before += here; here = c4.w; ++val; }
-        place -= __builtin_amdgcn_readlane(before, src);
-        const uint32_t digit_found = (uint32_t)__builtin_amdgcn_readlane(val, src);
-        here = __builtin_amdgcn_readlane(here, src);
-        if (here <= CP_RANK) {
-          each([&](int i, fmoe_window_key K) {
-            uint32_t digit;
-            if (live_digit(i, K, digit) & (int)(digit == digit_found)) {
-              const int at = atomicAdd(&s_count[2], 1);
-              if (ATTN) s_cand_att[at] = K.att;
-              s_cand_sc[at] = K.sc;
-              s_cand[at] = i;
-            }
-          });
-          break;
-        }
-        const uint32_t mask = (0xffu << shift) & (fixed < 32 ? (1u << fixed) - 1u : ~0u);
-        chosen = (chosen & ~mask) | ((digit_found << shift) & mask);
-        fixed = shift;
-        if (fixed == 0) {   // alike so far: by what comes next
-          if (level == 0) {
-            tied.att = chosen;
-            att_counts = ~0u;
-          } else {
-            tied.sc = chosen;
-            sc_counts = ~0u;
+        uint32_t digits[NT];
+        int4 c4{};
+        int sum4 = 0, excl = 0;
+#pragma unroll
+        for (int q = 0; q < NT; ++q) {
+          digits[q] = 0;
+          if (!st[q].open) continue;   // uniform
+          if (q == 0 || !shared) {     // uniform
+            c4 = *reinterpret_cast<const int4*>(&h[q * 256 + 4 * lane]);
+            sum4 = c4.x + c4.y + c4.z + c4.w;
+            excl = wave_scan(sum4) - sum4;
           }
-          level = level == 0 && diff_sc != 0 ? 1 : 2;
-          chosen = level == 1 ? K_first.sc : 0u;
-          fixed = level == 1 ? 32 - __clz(diff_sc) : index_bits;
+          const int src = __builtin_ctzll(__ballot(excl <= place[q] && place[q] < excl + sum4));   // exactly one lane
+          int before = excl, val = 4 * lane, here = c4.x;
+          if (before + here <= place[q]) { before += here; here = c4.y; ++val; }
+          if (val > 4 * lane && before + here <= place[q]) { before += here; here = c4.z; ++val; }
+          if (val > 4 * lane + 1 && before + here <= place[q]) { before += here; here = c4.w; ++val; }
+          place[q] -= __builtin_amdgcn_readlane(before, src);
+          digits[q] = (uint32_t)__builtin_amdgcn_readlane(val, src);
+          here = __builtin_amdgcn_readlane(here, src);
+          if (here <= CP_RANK) {
+            each([&](int i, fmoe_window_key K) {
+              uint32_t digit;
+              if (live_digit(q, i, K, digit) & (int)(digit == digits[q])) {
+                const int at = q * CP_RANK + atomicAdd(&s_count[2 + q], 1);
+                if (ATTN) s_cand_att[at] = K.att;
+                s_cand_sc[at] = K.sc;
+                s_cand[at] = i;
+              }
+            });
+            st[q].open = false;
+            continue;
+          }
+          const int shift = st[q].fixed > 8 ? st[q].fixed - 8 : 0;
+          const uint32_t mask = (0xffu << shift) & (st[q].fixed < 32 ? (1u << st[q].fixed) - 1u : ~0u);
+          st[q].chosen = (st[q].chosen & ~mask) | ((digits[q] << shift) & mask);
+          st[q].fixed = shift;
+          if (shift == 0) {   // alike so far: by what comes next
+            if (st[q].level == 0) {
+              st[q].tied_att = st[q].chosen;
+              st[q].att_counts = ~0u;
+            } else {
+              st[q].tied_sc = st[q].chosen;
+              st[q].sc_counts = ~0u;
+            }
+            st[q].level = st[q].level == 0 && diff_sc != 0 ? 1 : 2;
+            st[q].chosen = st[q].level == 1 ? K_first.sc : 0u;
+            st[q].fixed = st[q].level == 1 ? 32 - __clz(diff_sc) : index_bits;
+          }
         }
+        bool open = false;
+#pragma unroll
+        for (int q = 0; q < NT; ++q) open |= st[q].open;
+        if (!open) break;
+        if (NT == 2) shared = shared && digits[0] == digits[NT - 1];
       }
       __syncthreads();
-      const int here = s_count[2], mine = lane < here ? lane : 0;
-      const fmoe_window_key K{ATTN ? s_cand_att[mine] : 0u, s_cand_sc[mine]};
-      const int i = s_cand[mine];
-      int rank = 0;
+#pragma unroll
+      for (int q = 0; q < NT; ++q) {
+        if (!wanted[q]) continue;   // uniform
+        const int here = s_count[2 + q], mine = q * CP_RANK + (lane < here ? lane : 0);
+        const fmoe_window_key K{ATTN ? s_cand_att[mine] : 0u, s_cand_sc[mine]};
+        const int i = s_cand[mine];
+        int rank = 0;
 #pragma unroll 4
-      for (int j = 0; j < here; ++j) {   // uniform
-        const fmoe_window_key o{ATTN && stage == 1 ? (uint32_t)__builtin_amdgcn_readlane(K.att, j) : 0u,
-                                (uint32_t)__builtin_amdgcn_readlane(K.sc, j)};
-        rank += (int)key_before(o, __builtin_amdgcn_readlane(i, j), fmoe_window_key{ATTN && stage == 1 ? K.att : 0u, K.sc}, i);
+        for (int j = 0; j < here; ++j) {   // uniform
+          const fmoe_window_key o{by_att ? (uint32_t)__builtin_amdgcn_readlane(K.att, j) : 0u,
+                                  (uint32_t)__builtin_amdgcn_readlane(K.sc, j)};
+          rank += (int)key_before(o, __builtin_amdgcn_readlane(i, j), fmoe_window_key{by_att ? K.att : 0u, K.sc}, i);
+        }
+        const int src = __builtin_ctzll(__ballot(lane < here && rank == place[q]));   // exactly one
+        found[q] = fmoe_window_key{ATTN ? (uint32_t)__builtin_amdgcn_readlane(K.att, src) : 0u,
+                                   (uint32_t)__builtin_amdgcn_readlane(K.sc, src)};
+        found_i[q] = __builtin_amdgcn_readlane(i, src);
       }
-      const int src = __builtin_ctzll(__ballot(lane < here && rank == place));   // exactly one
-      const fmoe_window_key found{ATTN ? (uint32_t)__builtin_amdgcn_readlane(K.att, src) : 0u,
-                                  (uint32_t)__builtin_amdgcn_readlane(K.sc, src)};
-      const int found_i = __builtin_amdgcn_readlane(i, src);
-      if (stage == 0) {
-        cut.merge_sc = found.sc;
-        cut.merge_i = found_i;
-        for (int z = tid; z < 256; z += CP_BLOCK) hist[z] = 0;   // for the next search
+    };
+    // where merging ends: the full window at place q_full of the merge order
+    const bool find_merge = MERGE && p.q_full > 0 && p.q_full < n_full;
+    if constexpr (MERGE) {
+      cut.merge_sc = p.q_full == 0 ? 0u : ~0u;
+      cut.merge_i = p.q_full == 0 ? -1 : CP_ALL;
+    }
+    if constexpr (MERGE && ATTN) {
+      if (find_merge) {   // uniform; a search of its own, the drop order is another one
+        int place[NT] = {p.q_full}, i[NT];
+        const bool wanted[NT] = {true};
+        fmoe_window_key found[NT];
+        find(false, place, wanted, [&](int w, fmoe_window_key) { return (int)(w < n_full); }, found, i);
+        cut.merge_sc = found[0].sc;
+        cut.merge_i = i[0];
+        for (int z = tid; z < TABLE; z += CP_BLOCK) hist[z] = 0;   // for the next search
         __syncthreads();   // all have read the number of candidates
         if (tid == 0) s_count[2] = 0;
-      } else {
-        cut.drop_key = found;
-        cut.drop_i = found_i;
+      }
+    }
+    // where the budget ends: of the full windows that are not merged, the one at place q of the drop order
+    {
+      const bool last = n_full < n && !p.last_m;
+      int ahead = 0, q, place[NT], i[NT];
+      if (last) {   // uniform
+        if constexpr (MERGE && ATTN) {
+          int v = 0;
+          each([&](int w, fmoe_window_key K) { v += (int)(w < n_full) & (int)!cut.merged(w, K) & (int)(K.both() <= K_last.both()); });
+          ahead = block_sum(v);
+        } else {   // one order, in which the merged ones come first
+          ahead = ahead_of_last > p.q_full ? ahead_of_last - p.q_full : 0;
+        }
+      }
+      drop_walk(a, p.u_rem, last, w_last, ahead, q, cut.part, cut.last_keeps);
+      const bool none = q == 0 && cut.part == 0, find_drop = !none && q < n_full - p.q_full;
+      cut.drop_key = none ? fmoe_window_key{0u, 0u} : fmoe_window_key{ATTN ? ~0u : 0u, ~0u};
+      cut.drop_i = none ? -1 : CP_ALL;
+      bool wanted[NT];
+      wanted[NT - 1] = find_drop;
+      place[NT - 1] = NT == 2 ? p.q_full + q : q;
+      if constexpr (NT == 2) {
+        wanted[0] = find_merge;
+        place[0] = p.q_full;
+      }
+      if (find_drop || (NT == 2 && find_merge)) {   // uniform
+        fmoe_window_key found[NT];
+        find(ATTN, place, wanted,
+             [&](int w, fmoe_window_key K) { return (int)(w < n_full) & (int)!(MERGE && ATTN && cut.merged(w, K)); }, found, i);
+        if (find_drop) {
+          cut.drop_key = found[NT - 1];
+          cut.drop_i = i[NT - 1];
+        }
+        if (NT == 2 && find_merge) {
+          cut.merge_sc = found[0].sc;
+          cut.merge_i = i[0];
+        }
       }
     }
     if (ord >= 0 && ord < nv && t >= s && t < clampi(cu[b + 1], 0, T)) {
@@ -628,7 +705,7 @@ __global__ __launch_bounds__(CP_BLOCK) void compact_kernel(CompactArgs a) {
       if (tid == 0) s_first = v;
     }
     __syncthreads();   // keys, candidates and their number are read no more
-    if (tid == 0) s_count[2] = 0;   // (the next use is behind another barrier)
+    if (tid < NT) s_count[2 + tid] = 0;   // (the next use is behind another barrier)
   }
 
   // ---- the others, a wavefront each (lane = window)
@@ -655,10 +732,10 @@ __global__ __launch_bounds__(CP_BLOCK) void compact_kernel(CompactArgs a) {
       const bool full = lane < n_full;
       fmoe_merge_plan p{0, 0, nv - token_budget(nv, a.retention)};
       bool merged = false;
+      int place = 0;
       if constexpr (MERGE) {
         const int L = n_full < n ? __popcll(__ballot(full && K.sc <= K_last.sc)) : n;
         p = merge_plan(nv, W, a.retention, a.gamma, L);
-        int place = 0;
 #pragma unroll 4
         for (int j = 0; j < n_full; ++j) {
           const uint32_t o = __builtin_amdgcn_readlane(K.sc, j);
@@ -671,10 +748,14 @@ __global__ __launch_bounds__(CP_BLOCK) void compact_kernel(CompactArgs a) {
       const int ahead = __popcll(__ballot(takes_part && K.both() <= K_last.both()));
       int q, part, last_keeps;
       drop_walk(a, p.u_rem, n_full < n && !p.last_m, w_last, ahead, q, part, last_keeps);
-      int place = 0;
+      if constexpr (MERGE && !ATTN) {
+        place -= p.q_full;   // one order, in which the merged ones come first
+      } else {
+        place = 0;
 #pragma unroll 4
-      for (int j = 0; j < n_full; ++j) {
-        place += (int)key_before(key_at(j), j, K, lane) & (int)((part_mask >> j) & 1);
+        for (int j = 0; j < n_full; ++j) {
+          place += (int)key_before(key_at(j), j, K, lane) & (int)((part_mask >> j) & 1);
+        }
       }
       const int lead = full ? (place < q ? 0 : (place == q ? W - part : W)) : last_keeps;
       if (lane < n) {
@@ -692,7 +773,7 @@ __global__ __launch_bounds__(CP_BLOCK) void compact_kernel(CompactArgs a) {
       }
     }
     __syncthreads();
-    if (ord >= 0 && t >= clampi(cu[0], 0, T) && t < clampi(cu[B], 0, T)) {
+    if (ord >= 0 && t < p1 && t >= clampi(cu[0], 0, T) && t < clampi(cu[B], 0, T)) {
       const int b = find_seq(cu, B, t), s = clampi(cu[b], 0, T), nv = visual_tokens(b);
       if (ord < nv && nv <= W * CP_WAVE_N) {
         const int i = per_window(a, ord), fate = s_fate[(s < p0 ? 0 : CP_WAVE_N + s - p0) + i];
@@ -1273,7 +1354,9 @@ int launch_prune(const fmoe_ctx* ctx, const fmoe_prune_params* pp, const float* 
     ca.scores_out = scores_out; ca.kept_idx = kept_idx; ca.new_cu = new_cu; ca.is_visual_out = is_visual_out;
     ca.is_merged_out = merging ? is_merged : nullptr;
     ca.window_rcp = ((1ull << 37) + pp->window - 1) / pp->window;
-    const dim3 grid((T + CP_BLOCK - 1) / CP_BLOCK), block(CP_BLOCK);
+    ca.cut = B > 1 && B <= CP_CUT_SEQS;
+    // cut: part j of the batch begins at block (its first position) / CP_BLOCK + j
+    const dim3 grid(ca.cut ? T / CP_BLOCK + B + 2 : (T + CP_BLOCK - 1) / CP_BLOCK), block(CP_BLOCK);
     if (merging && attn) hipLaunchKernelGGL((compact_kernel<true, true>), grid, block, 0, stream, ca);
     else if (merging) hipLaunchKernelGGL((compact_kernel<true, false>), grid, block, 0, stream, ca);
     else if (attn) hipLaunchKernelGGL((compact_kernel<false, true>), grid, block, 0, stream, ca);

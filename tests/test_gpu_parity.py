@@ -471,10 +471,12 @@ def test_prune_merge_many_windows_several_blocks():
     ([126, 128, 129, 130, 131, 64, 65], [0, 3, 0, 1, 900, 0, 2], 2, 0),      # 63 .. 66 windows: one wavefront or the block
     ([8191, 700], [5, 0], 2, 0), ([4097], [0], 1, 0),                        # around and past the keys that stay in LDS
     ([8199], [30], 2, 5),                                                    # windows that tie: the index decides
-    ([100, 2048, 70, 1500], [924, 0, 954, 3], 3, 4)])
+    ([100, 2048, 70, 1500], [924, 0, 954, 3], 3, 4),
+    ([0, 5, 800, 1, 512, 511, 513, 0, 300, 90] * 6 + [0, 640], [2, 0, 212, 1, 0, 1, 0, 512, 0, 7] * 6 + [0, 0], 2, 0),   # 62 sequences:
+    ([0, 5, 800, 1, 512, 511, 513, 0, 300, 90] * 6 + [0, 640, 3], [2, 0, 212, 1, 0, 1, 0, 512, 0, 7] * 6 + [0, 0, 1], 2, 6)])  # blocks end with them; 63: not
 def test_prune_selection_edges(T_v, T_t, window, distinct, with_attn, gamma):
-    """Compaction at the edges of its forms (windows of a sequence, blocks of 1024 positions), visual and text tokens
-    mixed, with and without ties, the attention term and window merging; tokens behind the last sequence stay.  Kept set,
+    """Compaction at the edges of its forms (windows of a sequence, blocks of 512 positions, sequences of a batch), visual and
+    text tokens mixed, with and without ties, the attention term and window merging; tokens behind the last sequence stay.  Kept set,
     merged flags, bounds and scores bit for bit."""
     rng = np.random.default_rng(sum(T_v) + window)
     E, tail = 8, 37
