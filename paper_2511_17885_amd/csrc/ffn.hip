@@ -1237,6 +1237,9 @@ __device__ __forceinline__ void f32_tile(const GemmProblem& P, const fmoe_tile& 
 //    where the plain exchange by row / 4 has them in a third of the cycles (180 -> 171 us).
 //  * Two forms.  Two LDS buffers and two workgroups a CU: the next tile is split while the present one is multiplied.  One
 //    buffer and three workgroups: they cover for each other; better where there are enough of them (see F_WIDE_ITEMS).
+//    Rings of two k tiles: with four in the first form, calls of a few rows fetched more code than the tiles in flight
+//    gained (both GEMMs of 4 tokens, d 2048, 128 experts of 1024 170 -> 154 us; 12 of d 1280, 64 of 896 134 -> 128; 416 of
+//    either equal), with six it was slower still.
 // Measured, gate/up + down, us, fp32 instruction / split: that layer with half of the visual tokens kept 214 + 117 / 166 + 89,
 // 3000 tokens 341 + 181 / 256 + 137, 416 tokens 100 + 49 / 77 + 43, one token 32 + 23 / 31 + 24; d 4096, 8 experts of 1536,
 // 400 tokens 156 + 66 / 118 + 52, 8 tokens 86 + 39 / 78 + 37.
@@ -1558,7 +1561,7 @@ __global__ __launch_bounds__(256, SPLIT == 1 ? 3 : 2) void grouped_gemm_kernel(G
   const bool deep = n_tiles * a.n_col_tiles_max <= F_DEEP_ITEMS && P.K >= F_DEEP_K;   // uniform
   const int row_blocks = (tile.rows + 15) >> 4;   // live 16-row blocks of the tile, uniform per block
   if constexpr (SPLIT != 0) {
-    constexpr int FEW = SPLIT == 2 ? 4 : 2, MORE = SPLIT == 2 ? 2 : 1;   // ring slots
+    constexpr int FEW = 2, MORE = SPLIT == 2 ? 2 : 1;   // ring slots
     bf16_t* const parts = reinterpret_cast<bf16_t*>(As);
     switch (row_blocks) {
       case 1: split_tile<SWIGLU, 1, FEW, SPLIT>(P, tile, group, shared, nt, parts); break;
