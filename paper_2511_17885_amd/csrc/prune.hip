@@ -1024,6 +1024,10 @@ __global__ __launch_bounds__(SB_THREADS) void prune_dispatch_small_kernel(SmallA
       ex[k][sl] = (e >= 0 && e < E) ? e : -1;
     }
   }
+  // Under bounds that decrease a token's ordinal can be another sequence's and name a window that none has.  What stands
+  // there has to be the same in both blocks, or their lists would not fit together.
+  static_assert(SB_MAX_T * 4 == SB_THREADS * 16 && SB_MAX_T * 4 <= U_BYTES, "2 * SB_MAX_T entries");
+  if (a.prune) *reinterpret_cast<uint4*>(s_u + tid * 16) = make_uint4(0, 0, 0, 0);
   const bool cached = B <= SB_MAX_B;
   if (cached) {
     for (int b = tid; b <= B; b += SB_THREADS) s_cu[b] = clampi(a.cu[b], 0, T);
@@ -1167,7 +1171,8 @@ __global__ __launch_bounds__(SB_THREADS) void prune_dispatch_small_kernel(SmallA
       } else {
         const int b = find_seq(cu, B, t);
         const int s = clampi(cu[b], 0, T);
-        keep = (ord % W) < s_pre[s + ord / W];
+        const unsigned w = (unsigned)(s + ord / W);
+        keep = (ord % W) < s_pre[w < 2 * SB_MAX_T ? w : 0];
       }
     }
     keep_r[k] = keep;

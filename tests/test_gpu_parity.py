@@ -1534,6 +1534,30 @@ def test_layer_forward_that_keeps_every_token_above_the_small_batch(k_text, k_vi
     assert max_rel_err(host(out), ref.cpu().numpy()) <= TOL[W.F32]
 
 
+@pytest.mark.parametrize("cu", [[0, 2000, 1000, 5000], [0, 700, 2900, 1500, 3000, 3000], [0, 3000, 40, 2999, 7, 3000]])
+@pytest.mark.parametrize("with_attention", [False, True])
+def test_layer_forward_bounds_that_decrease_in_a_small_batch(cu, with_attention):
+    """Which tokens stay is not defined, but the lists fit together: ascending tokens, each with the output that it has in
+    a layer that drops nothing, and nothing is written behind the buffers."""
+    wl = W.small_random(len(cu), T_v=[3000], T_t=[0], d=64, E=16, F=32, k_text=3, k_visual=2, retention=0.5, window=3)
+    m = make_layer(wl)
+    x, vis, _ = inputs(wl)
+    T, guard = wl.T, 4096
+    full, *_ = m.layer_forward(x, vis, dev(wl.cu_seqlens), None)
+    attn = torch.rand(T, device="cuda") if with_attention else None
+    buf = [torch.full((T * 64 + guard,), 7.0, device="cuda"), torch.full((T + guard,), -7, dtype=torch.int32, device="cuda"),
+           torch.full((len(cu) + guard,), -7, dtype=torch.int32, device="cuda")]
+    out, kept, new_cu = buf[0][:T * 64].view(T, 64), buf[1][:T], buf[2][:len(cu)]
+    m.layer_forward(x, vis, torch.tensor(cu, dtype=torch.int32, device="cuda"),
+                    binding.prune_params(retention=0.5, window=3, alpha=0.5 if with_attention else 1.0), attn=attn, out=out,
+                    kept_idx=kept, new_cu=new_cu)
+    n = int(new_cu[-1])
+    k = kept[:n].long()
+    assert 0 < n <= T and (k[1:] > k[:-1]).all() and k[0] >= 0 and k[-1] < T
+    assert torch.equal(out[:n], full[k])
+    assert all((b[-guard:] == b[-1]).all() for b in buf) and buf[0][-1] == 7.0 and buf[1][-1] == -7 and buf[2][-1] == -7
+
+
 @pytest.mark.parametrize("T_v,T_t,retention,gamma", [
     ([1500], [90], 0.5, 0.0), ([1500], [90], 1.0, 0.0), ([700, 3, 900, 0], [9, 0, 200, 1], 0.6, 0.0),
     ([4, 0, 3] * 200, [1, 2, 0] * 200, 0.5, 0.0),      # more sequences than have their bounds in LDS
