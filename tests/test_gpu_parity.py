@@ -447,7 +447,7 @@ def test_prune_merge_with_attention_and_short_last_window(gamma):
 
 
 def test_prune_merge_many_windows_several_blocks():
-    # more windows than one counting tile and one compaction pass hold
+    # windows and tokens of several compaction blocks
     wl = W.small_random(117, T_v=[2600, 1301], T_t=[40, 9], d=64, E=16, F=32, k_text=2, k_visual=1,
                         retention=0.5, window=3, n_components=20)
     o_probs, _, _ = oracle.route(wl.x, wl.is_visual, wl.weights.router_w, None, 2, 1)
@@ -510,15 +510,30 @@ def test_prune_selection_edges(T_v, T_t, window, distinct, with_attn, gamma):
     assert np.array_equal(host(new_cu2), res[1]) and torch.equal(plain[:n + tail], kept[:n + tail])
 
 
-def test_prune_bounds_that_decrease_keep_every_token():
-    """Sequence bounds that are no partition: nothing is pruned and nothing is read or written out of range."""
-    T, E = 3000, 8
-    m = binding.FMoE(d_model=8, n_experts=E, d_ffn=8, k_text=2, k_visual=1, dtype="f32")
-    m.set_weights(torch.zeros(E, 8).cuda(), None, *(torch.zeros(E, 8, 8).cuda() for _ in range(3)))
-    cu = np.array([0, 2000, 1000, 5000], np.int32)
-    kept, new_cu, _ = m.prune(binding.prune_params(retention=0.5, window=3), torch.full((T, E), 1 / E).cuda(),
-                              torch.ones(T, dtype=torch.uint8).cuda(), dev(cu))
-    assert np.array_equal(host(new_cu), [0, 2000, 1000, 3000]) and np.array_equal(host(kept), np.arange(T))
+@pytest.mark.parametrize("cu", [[0, 2000, 1000, 9000], [0] + [5000, 10] * 40 + [5000]])   # in a batch of few sequences and of many
+@pytest.mark.parametrize("gamma", [0.0, 0.1])
+def test_prune_bounds_that_decrease_keep_every_token(gamma, cu):
+    """Sequence bounds that are no partition, outside the small batch: nothing is pruned, by fmoe_prune and in a layer, and
+    nothing is written behind the layer's buffers."""
+    T, E, d, guard = 5000, 8, 64, 4096
+    m = binding.FMoE(d_model=d, n_experts=E, d_ffn=32, k_text=2, k_visual=1, dtype="f32")
+    rnd = lambda *s: torch.randn(s, device="cuda")
+    m.set_weights(rnd(E, d), None, rnd(E, 32, d), rnd(E, 32, d), rnd(E, d, 32))
+    x, vis, bounds = rnd(T, d), torch.ones(T, dtype=torch.uint8, device="cuda"), np.clip(cu, 0, T)
+    pp = binding.prune_params(retention=0.5, window=3, gamma=gamma)
+    kept, new_cu, _, *merged = m.prune(pp, torch.full((T, E), 1 / E).cuda(), vis, dev(np.array(cu, np.int32)),
+                                       **(dict(x=x) if gamma else {}))
+    assert np.array_equal(host(new_cu), bounds) and np.array_equal(host(kept), np.arange(T))
+    if gamma:
+        assert not merged[0].any() and torch.equal(merged[1], x)
+    full, *_ = m.layer_forward(x, vis, dev(np.array([0, T], np.int32)), None)
+    fill = lambda n, v, t: torch.full((n + guard,), v, dtype=t, device="cuda")
+    buf = [fill(T * d, 7, torch.float32), fill(T, -7, torch.int32), fill(len(cu), -7, torch.int32), fill(T, 7, torch.uint8)]
+    out, kept, new_cu, mask = buf[0][:T * d].view(T, d), buf[1][:T], buf[2][:len(cu)], buf[3][:T]
+    m.layer_forward(x, vis, dev(np.array(cu, np.int32)), pp, out=out, kept_idx=kept, new_cu=new_cu, is_visual_out=mask)
+    assert np.array_equal(host(new_cu), bounds) and np.array_equal(host(kept), np.arange(T)) and mask.all()
+    assert torch.equal(out, full)
+    assert all((b[-guard:] == v).all() for b, v in zip(buf, (7, -7, -7, 7)))
 
 
 # ---------------------------------------------------------------- permute
@@ -869,9 +884,9 @@ def test_expert_gemm_shapes_agree_bit_for_bit(cfg):
     ([333], [0], 64, 0.01, 1, True),
 ])
 def test_one_block_prune_keeps_what_the_general_chain_keeps(T_v, T_t, win, retention, copies, attn):
-    """The single-workgroup form finds the window at which the budget ends by selection, the general chain counts the
-    predecessors of every window: the same tokens, with equal scores, short last windows, attention (with equal
-    sums), and up to as many windows as it takes."""
+    """The small-batch form and the general chain find the window at which the budget ends by selections of their own:
+    the same tokens, with equal scores, short last windows, attention (with equal sums), and up to as many windows as
+    the small batch takes."""
     wl = W.small_random(4100 + sum(T_v) + win, T_v=T_v, T_t=T_t, d=64, E=12, F=16, k_text=2, k_visual=1,
                             retention=0.5, window=win, dtype=W.F32, n_components=4)
     x = wl.x.copy()
@@ -1459,14 +1474,14 @@ def test_randomized_layer_sweep(seed, shape):
 
 
 @pytest.mark.parametrize("T_v,T_t,window", [
-    ([4096], [0], 4),        # 4096 tokens, 1024 windows: the largest batch of the single-workgroup dispatch kernel
+    ([4096], [0], 4),        # 4096 tokens, 1024 windows: the largest batch of the small-batch dispatch kernel
     ([4095], [1], 4),        # 1024 windows, the last one short
     ([4092], [4], 3),        # 1364 windows in one sequence: the general kernels, although T = 4096
-    ([4096], [1], 4),        # one token more than the single-workgroup kernel takes
+    ([4096], [1], 4),        # one token more than the small-batch kernel takes
     ([1024, 1024, 1024, 1020], [1, 1, 1, 1], 1),   # W = 1: every visual token is a window of its own
 ])
 def test_layer_forward_at_the_small_batch_limits(T_v, T_t, window):
-    """Both sides of the size limits that decide between the single-workgroup prune/dispatch kernel and the
+    """Both sides of the size limits that decide between the small-batch prune/dispatch kernel and the
     general kernel chain give the oracle's kept set, permutation and outputs."""
     wl = W.small_random(4242, T_v=T_v, T_t=T_t, d=64, E=16, F=32, k_text=3, k_visual=2, retention=0.6,
                         window=window, dtype=W.F32, bias_std=1.0, n_components=24)
@@ -1613,12 +1628,12 @@ def test_layer_forward_merge_after_the_layer_over_several_compaction_blocks(with
 
 @pytest.mark.parametrize("dtype", [W.F32, W.BF16])
 @pytest.mark.parametrize("T_v,T_t,window,prune", [
-    ([4070], [40], 3, None),                                        # more tokens than the single-workgroup kernel takes
+    ([4070], [40], 3, None),                                        # more tokens than the small-batch kernel takes
     ([4070], [40], 3, dict()),
     ([2600, 2, 1900], [30, 0, 9], 5, dict(gamma=0.1)),
     ([1400, 7], [11, 3], 1, dict()),                                # more windows than it takes
     ([90, 30], [6, 2], 3, dict(gamma=0.1, prune_mode=2)),           # merging after the layer
-    ([90, 30], [6, 2], 3, dict()),                                  # the single-workgroup kernel
+    ([90, 30], [6, 2], 3, dict()),                                  # the small-batch kernel
     ([4], [5], 3, None),                                            # dispatch from the router's launch
 ])
 def test_layer_forward_shared_experts_only(dtype, T_v, T_t, window, prune):
@@ -1645,7 +1660,7 @@ def test_layer_forward_shared_experts_only(dtype, T_v, T_t, window, prune):
 @pytest.mark.parametrize("shape", SHAPES)
 def test_layer_forward_general_chain_at_the_widest_routing(shape):
     """The largest expert count and top-k the library takes (256 experts, 16 per text token), shared experts,
-    bf16, several ragged sequences and more tokens than the single-workgroup kernel handles."""
+    bf16, several ragged sequences and more tokens than the small-batch kernel handles."""
     wl = W.small_random(5151, T_v=[2500, 1, 1800, 700], T_t=[40, 3, 0, 77], d=96, E=256, F=40, k_text=16, k_visual=7,
                         retention=0.4, window=5, dtype=W.BF16, n_shared=2, F_shared=24, bias_std=1.0, n_components=40)
     assert wl.T > 4096
@@ -1730,7 +1745,7 @@ def test_expert_ffn_fp32_split_operands_far_apart(d, F):
     nor on the form; against fp64 at the fp32 bound (TOL)."""
     scales = [(1, 1, 1), (1e-35, 1e30, 1), (1e-38, 1e33, 1), (1e-42, 1e37, 1), (1e30, 1e-35, 1), (1e33, 1e-40, 1e4),
               (1, 1e-35, 1e32), (1, 1e-38, 1e35), (1e6, 1e-42, 1e30), (1e12, 1e-42, 1e30)]   # rows, up, down
-    E, each, n_many = len(scales), 21, 1200
+    E, each, n_many = len(scales), 21, 4200
     n, half = E * each, d // 2
     g = torch.Generator(device="cuda")
     g.manual_seed(d + F)
@@ -1992,7 +2007,7 @@ def test_permute_every_number_of_slots(k):
                                        ([2900, 1100], [60, 36], 9)])
 @pytest.mark.parametrize("gamma", [0.0, 0.1])
 def test_small_dispatch_register_sizes(T_v, T_t, k, gamma):
-    """The single-workgroup dispatch at the edges of its register-array sizes: 2048 and 2049 tokens, 4096 tokens,
+    """The small-batch dispatch at the edges of its register-array sizes: 2048 and 2049 tokens, 4096 tokens,
     eight and nine experts per token, with pruning inside it and (merging) as permutation only."""
     wl = W.small_random(700 + k, T_v=T_v, T_t=T_t, d=32, E=24, F=16, k_text=k, k_visual=3, retention=0.5, window=5,
                         bias_std=1.0, n_components=12)
