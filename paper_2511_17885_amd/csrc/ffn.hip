@@ -1220,7 +1220,7 @@ __device__ __forceinline__ void f32_tile(const GemmProblem& P, const fmoe_tile& 
   f32_store<SWIGLU, NRB>(P, tile, group, shared, nt, acc);
 }
 
-// ---- the same products on the bf16 matrix instruction, for reductions of F_SPLIT_K and more.  An fp32 value is the sum
+// ---- the same products on the bf16 matrix instruction, in layers whose reductions are all F_SPLIT_K and more.  An fp32 value is the sum
 // of three bf16 values x1 + x2 + x3 (8 + 8 + 8 significant bits and two signs, exactly), and of the nine products of two
 // such sums the three of lowest order are below 2^-26 of the whole.  The other six take 6 * 16 cycles of the matrix pipe
 // per 16 x 16 block and 32 k where the fp32 instruction takes 8 * 32, and round their sums less often: x1*w1 in one
@@ -1240,9 +1240,11 @@ __device__ __forceinline__ void f32_tile(const GemmProblem& P, const fmoe_tile& 
 //    Rings of two k tiles: with four in the first form, calls of a few rows fetched more code than the tiles in flight
 //    gained (both GEMMs of 4 tokens, d 2048, 128 experts of 1024 170 -> 154 us; 12 of d 1280, 64 of 896 134 -> 128; 416 of
 //    either equal), with six it was slower still.
-// Measured, gate/up + down, us, fp32 instruction / split: that layer with half of the visual tokens kept 214 + 117 / 166 + 89,
-// 3000 tokens 341 + 181 / 256 + 137, 416 tokens 100 + 49 / 77 + 43, one token 32 + 23 / 31 + 24; d 4096, 8 experts of 1536,
-// 400 tokens 156 + 66 / 118 + 52, 8 tokens 86 + 39 / 78 + 37.
+// Measured, fmoe_expert_ffn with weights that are not in the memory-side cache, us, fp32 instruction / split: d 1280, 64
+// experts of 896, two shared, 3000 tokens 1076 / 707, 1600 682 / 447, 416 248 / 224, 64 206 / 190, 16 174 / 164, 8 126 /
+// 122, one 51 / 54; d 4096, 8 experts of 1536, 800 tokens 527 / 368, 8 131 / 123, one 105 / 113; d 2048, 128 experts of 1024,
+// 1600 tokens 1023 / 727, 100 546 / 542, 4 149 / 157.  With one token, and with up to four in the last layer and in the
+// smallest (d 896, 8 experts of 896 42 / 44), it is slower: few workgroups, each a chain of LDS passes and barriers.
 // Range: rows are split times 2^96, so that every part of every row value down to fp32's smallest is a normal bf16, and
 // results are divided by it.  Row values from 2^32, results from 2^32 and weights that round to infinity in bf16 come out
 // as infinity or NaN; those results are computed again on the fp32 instruction.  Weights keep their bits down to 2^-133,
@@ -1250,7 +1252,14 @@ __device__ __forceinline__ void f32_tile(const GemmProblem& P, const fmoe_tile& 
 // below K * 2^-102, so results below F_TINY are computed again too, and a result of zero unless its row or its weights
 // are zero.  Scaling instead of a test on the operands while splitting: one multiplication per row value (a third of
 // the values or less), where finding the largest or the smallest operand takes one instruction per pair of them all,
-// and whether a result is computed again depends on that result alone, not on the others of its tile.
+// and whether a result is computed again depends on that result alone, not on the others of its tile.  It costs 0 to 3 %
+// from 400 tokens on (the layer of 1600 tokens with half of its visual tokens kept 286 -> 292 us).
+// 896 is where it was measured first and not where the two cross.  Since then, d = d_ffn = K, 64 experts, one / 64 / 416 / 3000
+// tokens, us, fp32 instruction / split: K 128 13.8 / 15.1, 15.9 / 17.4, 21.3 / 20.5, 33.7 / 32.5; 256 17.8 / 19.6, 21.4 / 23.0,
+// 29.2 / 28.7, 73 / 51; 384 24.8 / 25.6, 36.8 / 36.7, 45.7 / 41.8, 143 / 93; 512 28.6 / 29.9, 47.4 / 47.3, 58.6 / 53.3, 205 / 133;
+// 768 39.3 / 41.2, 109 / 97, 121 / 104, 400 / 272.  So it could be 384, at 3 to 7 % of the calls of one to eight tokens.  One
+// line for all reductions of a layer: a shorter down reduction keeps gate/up on the fp32 instruction as well (d 2048, 64
+// experts of 768, 3000 tokens 972 / 647 if both were split); apart they were not measured.
 constexpr int F_SPLIT_K = 896;
 constexpr int S_ROWS = FBM + 128;              // rows of a k tile in LDS: the tile's, then the weights'
 constexpr int S_PLANE = S_ROWS * FBK;          // one part of a k tile, in bf16 elements
