@@ -1027,9 +1027,12 @@ struct GemmArgs {
   int n_col_tiles_max;
 };
 
-template <bool SWIGLU, int NRB, int SLOTS>   // NRB: live 16-row blocks of the tile; SLOTS: k tiles in a register ring
+// NRB: live 16-row blocks of the tile; SLOTS: k tiles in a register ring.  The sums go to `sink` and do not come back in a
+// reference: with that the compiler keeps 254 registers instead of 160, two workgroups a CU instead of three (both GEMMs of
+// 3000 tokens, d 512, 64 experts of 512 173 -> 191 us; of 1600, d 1024, 64 of 768 and two shared 461 -> 475).
+template <bool SWIGLU, int NRB, int SLOTS, class Sink>
 __device__ __forceinline__ void f32_products(const GemmProblem& P, const fmoe_tile& tile, int group, bool shared, int nt,
-                                             float* As, f32x4_t (&acc)[NRB][2]) {
+                                             float* As, Sink sink) {
   constexpr int A_IT = (NRB + 1) / 2;   // 16-byte pieces of a k tile per thread
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -1092,6 +1095,7 @@ __device__ __forceinline__ void f32_products(const GemmProblem& P, const fmoe_ti
     for (int it = 0; it < A_IT; ++it) *reinterpret_cast<f32x4_t*>(&As[buf * (FBM * FBK) + a_dst[it]]) = areg[slot][it];
   };
 
+  f32x4_t acc[NRB][2];
 #pragma unroll
   for (int rb = 0; rb < NRB; ++rb)
 #pragma unroll
@@ -1184,7 +1188,7 @@ whole_tiles_done:
     __syncthreads();
     multiply(0, 0);
   }
-
+  sink(acc);
 }
 
 template <bool SWIGLU, int NRB>
@@ -1215,9 +1219,9 @@ __device__ __forceinline__ void f32_store(const GemmProblem& P, const fmoe_tile&
 template <bool SWIGLU, int NRB, int SLOTS>
 __device__ __forceinline__ void f32_tile(const GemmProblem& P, const fmoe_tile& tile, int group, bool shared, int nt,
                                          float* As) {
-  f32x4_t acc[NRB][2];
-  f32_products<SWIGLU, NRB, SLOTS>(P, tile, group, shared, nt, As, acc);
-  f32_store<SWIGLU, NRB>(P, tile, group, shared, nt, acc);
+  f32_products<SWIGLU, NRB, SLOTS>(P, tile, group, shared, nt, As, [&](const f32x4_t (&acc)[NRB][2]) {
+    f32_store<SWIGLU, NRB>(P, tile, group, shared, nt, acc);
+  });
 }
 
 // ---- the same products on the bf16 matrix instruction, in layers whose reductions are all F_SPLIT_K and more.  An fp32 value is the sum
@@ -1255,11 +1259,11 @@ __device__ __forceinline__ void f32_tile(const GemmProblem& P, const fmoe_tile& 
 // and whether a result is computed again depends on that result alone, not on the others of its tile.  It costs 0 to 3 %
 // from 400 tokens on (the layer of 1600 tokens with half of its visual tokens kept 286 -> 292 us).
 // 896 is where it was measured first and not where the two cross.  Since then, d = d_ffn = K, 64 experts, one / 64 / 416 / 3000
-// tokens, us, fp32 instruction / split: K 128 13.8 / 15.1, 15.9 / 17.4, 21.3 / 20.5, 33.7 / 32.5; 256 17.8 / 19.6, 21.4 / 23.0,
-// 29.2 / 28.7, 73 / 51; 384 24.8 / 25.6, 36.8 / 36.7, 45.7 / 41.8, 143 / 93; 512 28.6 / 29.9, 47.4 / 47.3, 58.6 / 53.3, 205 / 133;
-// 768 39.3 / 41.2, 109 / 97, 121 / 104, 400 / 272.  So it could be 384, at 3 to 7 % of the calls of one to eight tokens.  One
+// tokens, us, fp32 instruction / split: K 128 13.9 / 15.3, 16.0 / 17.6, 21.1 / 20.8, 34.7 / 33.2; 256 17.8 / 19.7, 21.6 / 23.3,
+// 30.0 / 30.6, 68 / 52; 384 24.8 / 25.8, 36.8 / 36.5, 41.0 / 41.0, 131 / 89; 512 28.8 / 30.2, 48.9 / 47.8, 58.9 / 53.7, 179 / 125;
+// 768 39.7 / 41.7, 97 / 96, 114 / 105, 388 / 264.  So it could be 384, at 3 to 6 % of the calls of one to eight tokens.  One
 // line for all reductions of a layer: a shorter down reduction keeps gate/up on the fp32 instruction as well (d 2048, 64
-// experts of 768, 3000 tokens 972 / 647 if both were split); apart they were not measured.
+// experts of 768, 3000 tokens 960 / 638 if both were split); apart they were not measured.
 constexpr int F_SPLIT_K = 896;
 constexpr int S_ROWS = FBM + 128;              // rows of a k tile in LDS: the tile's, then the weights'
 constexpr int S_PLANE = S_ROWS * FBK;          // one part of a k tile, in bf16 elements
@@ -1517,14 +1521,14 @@ __device__ __forceinline__ void split_tile(const GemmProblem& P, const fmoe_tile
       }
   if (__syncthreads_or(any) && (__syncthreads_or(certain) || lost_in_zero<SWIGLU, NRB>(P, tile, group, shared, nt,
                                                                                        reinterpret_cast<int*>(As), acc))) {
-    f32x4_t whole[NRB][2];
-    f32_products<SWIGLU, NRB, 2>(P, tile, group, shared, nt, reinterpret_cast<float*>(As), whole);
+    f32_products<SWIGLU, NRB, 2>(P, tile, group, shared, nt, reinterpret_cast<float*>(As), [&](const f32x4_t (&whole)[NRB][2]) {
 #pragma unroll
-    for (int rb = 0; rb < NRB; ++rb)
+      for (int rb = 0; rb < NRB; ++rb)
 #pragma unroll
-      for (int f = 0; f < 2; ++f)
+        for (int f = 0; f < 2; ++f)
 #pragma unroll
-        for (int v = 0; v < 4; ++v) acc[rb][f][v] = again(acc[rb][f][v]) ? whole[rb][f][v] : acc[rb][f][v];
+          for (int v = 0; v < 4; ++v) acc[rb][f][v] = again(acc[rb][f][v]) ? whole[rb][f][v] : acc[rb][f][v];
+    });
   }
   f32_store<SWIGLU, NRB>(P, tile, group, shared, nt, acc);
 }
