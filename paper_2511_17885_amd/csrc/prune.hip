@@ -217,8 +217,9 @@ __global__ __launch_bounds__(256) void window_score_kernel(
 // Bound: latency, a dozen barriers between LDS passes over a few keys a thread; the uniform arithmetic is paid once per
 // wavefront of a SIMD, hence 512 threads and not 1024 (12.6 -> 8.9 us inside the kernel at 4096 tokens; 256: 9.6).
 // In place of counting all pairs of windows, deciding, flagging and writing (three launches, five with merging and
-// attention), average kernel times: 4096 tokens, 1280 windows 17.0 -> 10.4 us; 8192 tokens, 1588 windows 17.5 -> 10.7; three
-// ragged sequences of 5003 tokens, one of them short, 14.9 -> 12.8; 1600 tokens, merging and attention 24.4 -> 15.4.
+// attention), average kernel times: 4096 tokens, 1280 windows 17.0 -> 10.4 us; 8192 tokens, 1588 windows 17.5 -> 9.8; three
+// ragged sequences of 5003 tokens, one of them short, 15.0 -> 9.8; eight of 22016 24.4 -> 10.1; 1600 tokens, merging and
+// attention 24.8 -> 14.0.
 // Without attention both orders are one: the two windows are found together.  fmoe_prune of one sequence of 7000 tokens in
 // windows of two, merging: two searches 35.7 us, one 32.8, three launches 32.7.
 // A block takes the sequences that it touches one after the other, so in batches of up to CP_CUT_SEQS sequences no block
