@@ -1246,7 +1246,7 @@ __device__ __forceinline__ void f32_tile(const GemmProblem& P, const fmoe_tile& 
 //    either equal), with six it was slower still.
 // Measured, fmoe_expert_ffn with weights that are not in the memory-side cache, us, fp32 instruction / split: d 1280, 64
 // experts of 896, two shared, 3000 tokens 1076 / 707, 1600 682 / 447, 416 248 / 224, 64 206 / 190, 16 174 / 164, 8 126 /
-// 122, one 51 / 54; d 4096, 8 experts of 1536, 800 tokens 527 / 368, 8 131 / 123, one 105 / 113; d 2048, 128 experts of 1024,
+// 122, one 51 / 54; d 4096, 8 experts of 1536, 800 tokens 527 / 368, 8 131 / 123, one 105 / 117; d 2048, 128 experts of 1024,
 // 1600 tokens 1023 / 727, 100 546 / 542, 4 149 / 157.  With one token, and with up to four in the last layer and in the
 // smallest (d 896, 8 experts of 896 42 / 44), it is slower: few workgroups, each a chain of LDS passes and barriers.
 // Range: rows are split times 2^96, so that every part of every row value down to fp32's smallest is a normal bf16, and
@@ -1256,8 +1256,9 @@ __device__ __forceinline__ void f32_tile(const GemmProblem& P, const fmoe_tile& 
 // below K * 2^-102, so results below F_TINY are computed again too, and a result of zero unless its row or its weights
 // are zero.  Scaling instead of a test on the operands while splitting: one multiplication per row value (a third of
 // the values or less), where finding the largest or the smallest operand takes one instruction per pair of them all,
-// and whether a result is computed again depends on that result alone, not on the others of its tile.  It costs 0 to 3 %
-// from 400 tokens on (the layer of 1600 tokens with half of its visual tokens kept 286 -> 292 us).
+// and whether a result is computed again depends on that result alone, not on the others of its tile.  Which rows are zero
+// is gathered while splitting (reading them again took 16 tokens of which 14 are zero 57 -> 65 us).  All of it costs 0 to 4 %
+// with one or two tokens and nothing from eight on.
 // 896 is where it was measured first and not where the two cross.  Since then, d = d_ffn = K, 64 experts, one / 64 / 416 / 3000
 // tokens, us, fp32 instruction / split: K 128 13.9 / 15.3, 16.0 / 17.6, 21.1 / 20.8, 34.7 / 33.2; 256 17.8 / 19.7, 21.6 / 23.3,
 // 30.0 / 30.6, 68 / 52; 384 24.8 / 25.8, 36.8 / 36.5, 41.0 / 41.0, 131 / 89; 512 28.8 / 30.2, 48.9 / 47.8, 58.9 / 53.7, 179 / 125;
@@ -1309,8 +1310,11 @@ __device__ __forceinline__ const float* gathered_row(const GemmProblem& P, const
 // SLOTS: k tiles in a register ring, BUFS: LDS buffers
 template <bool SWIGLU, int NRB, int SLOTS, int BUFS>
 __device__ __forceinline__ void split_products(const GemmProblem& P, const fmoe_tile& tile, int group, bool shared, int nt,
-                                               bf16_t* As, f32x4_t (&acc)[NRB][2]) {
+                                               bf16_t* As, f32x4_t (&acc)[NRB][2], uint32_t (&in_row)[(NRB + 1) / 2]) {
   constexpr int A_IT = (NRB + 1) / 2, IT = A_IT + 4;   // 16-byte pieces of a k tile per thread: of the rows; with the weights
+  // in_row: bits of this thread's values of its rows (32*it + tid/8): signs aside, 0 where they are all zero
+#pragma unroll
+  for (int it = 0; it < A_IT; ++it) in_row[it] = 0;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int N = P.N, K = P.K;
@@ -1361,6 +1365,10 @@ __device__ __forceinline__ void split_products(const GemmProblem& P, const fmoe_
     for (int it = 0; it < IT; ++it) {
       uint2 part[3];
       split_bf16(it < A_IT ? raw[slot][it] * S_ROW_SCALE : raw[slot][it], part);
+      if (it < A_IT) {
+        const u32x4_t b = __builtin_bit_cast(u32x4_t, raw[slot][it]);
+        in_row[it] |= (b[0] | b[1]) | (b[2] | b[3]);
+      }
       const int row = it < A_IT ? 32 * it : FBM + 32 * (it - A_IT);
 #pragma unroll
       for (int p = 0; p < 3; ++p) *reinterpret_cast<uint2*>(dst + buf * S_BUF + p * S_PLANE + row * FBK) = part[p];
@@ -1461,15 +1469,34 @@ __device__ __forceinline__ void split_products(const GemmProblem& P, const fmoe_
     for (int f = 0; f < 2; ++f) acc[rb][f] = (acc[rb][f] + low[rb][f]) * (1.0f / S_ROW_SCALE);
 }
 
-// Is a result zero although neither its row nor its weights are?  Uniform.  A thread stops at its first value that is not
-// zero, so only zero rows are read to their end.  (As: no longer read)
+// Is a result zero although neither its row nor its weights are?  Uniform.  Weights are read only for a zero in a row that is
+// not, by a thread up to its first value that is not zero, so that only zero weights are read to their end.  (As: no longer read)
 template <bool SWIGLU, int NRB>
-__device__ __forceinline__ bool lost_in_zero(const GemmProblem& P, const fmoe_tile& tile, int group, bool shared, int nt,
-                                             int* As, const f32x4_t (&acc)[NRB][2]) {
+__device__ __forceinline__ bool lost_in_zero(const GemmProblem& P, int group, int nt, int* As, const f32x4_t (&acc)[NRB][2],
+                                             const uint32_t (&in_row)[(NRB + 1) / 2]) {
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, K = P.K;
   if (tid < S_ROWS) As[tid] = 0;   // rows of LDS as in the products; 1: something there
   __syncthreads();
-  auto look = [&](const float* row, int at) {
+#pragma unroll
+  for (int it = 0; it < (NRB + 1) / 2; ++it)
+    if (in_row[it] & 0x7fffffffu) As[32 * it + (tid >> 3)] = 1;
+  __syncthreads();
+  uint32_t open = 0;   // this lane's zeros in such rows, a bit each; the bits of a fragment
+  constexpr uint32_t FRAG = 0x0f0f0f0fu;
+  static_assert(NRB <= 4, "bits");
+#pragma unroll
+  for (int rb = 0; rb < NRB; ++rb)
+#pragma unroll
+    for (int f = 0; f < 2; ++f)
+#pragma unroll
+      for (int v = 0; v < 4; ++v)
+        open |= (uint32_t)(acc[rb][f][v] == 0.0f && As[rb * 16 + 4 * (lane >> 4) + v] != 0) << (rb * 8 + f * 4 + v);
+  if (!__syncthreads_or(open != 0)) return false;
+#pragma unroll 1
+  for (int r = tid >> 3; r < 128; r += 32) {
+    const int f = (r >> 4) & 1, w = r >> 5;
+    const int n = SWIGLU ? nt * 64 + w * 16 + (r & 15) : nt * 128 + r;
+    const float* row = (SWIGLU && f ? P.B1 : P.B0) + (size_t)group * P.group_stride + (size_t)(n < P.N ? n : P.N - 1) * P.ldb;
     constexpr int AHEAD = 8;       // loads in flight
     const int first = (tid & 7) * 4;
     uint32_t any = 0;
@@ -1480,33 +1507,19 @@ __device__ __forceinline__ bool lost_in_zero(const GemmProblem& P, const fmoe_ti
 #pragma unroll
       for (int u = 0; u < AHEAD; ++u) any |= (v[u][0] | v[u][1] | v[u][2] | v[u][3]) & 0x7fffffffu;
     }
-    if (any) As[at] = 1;
-  };
-#pragma unroll 1
-  for (int r = tid >> 3; r < NRB * 16; r += 32) look(gathered_row(P, tile, group, shared, r), r);
-#pragma unroll 1
-  for (int r = tid >> 3; r < 128; r += 32) {
-    const int f = (r >> 4) & 1, w = r >> 5;
-    const int n = SWIGLU ? nt * 64 + w * 16 + (r & 15) : nt * 128 + r;
-    look((SWIGLU && f ? P.B1 : P.B0) + (size_t)group * P.group_stride + (size_t)(n < P.N ? n : P.N - 1) * P.ldb, FBM + r);
+    if (any) As[FBM + r] = 1;
   }
   __syncthreads();
-  bool lost = false;
-#pragma unroll
-  for (int rb = 0; rb < NRB; ++rb)
-#pragma unroll
-    for (int f = 0; f < 2; ++f)
-#pragma unroll
-      for (int v = 0; v < 4; ++v)
-        lost |= acc[rb][f][v] == 0.0f && As[rb * 16 + 4 * (lane >> 4) + v] != 0 && As[FBM + wave * 32 + f * 16 + (lane & 15)] != 0;
-  return __syncthreads_or(lost) != 0;
+  const int c = FBM + wave * 32 + (lane & 15);
+  return __syncthreads_or((As[c] != 0 && (open & FRAG) != 0) || (As[c + 16] != 0 && (open & ~FRAG) != 0)) != 0;
 }
 
 template <bool SWIGLU, int NRB, int SLOTS, int BUFS>
 __device__ __forceinline__ void split_tile(const GemmProblem& P, const fmoe_tile& tile, int group, bool shared, int nt,
                                            bf16_t* As) {
   f32x4_t acc[NRB][2];
-  split_products<SWIGLU, NRB, SLOTS, BUFS>(P, tile, group, shared, nt, As, acc);
+  uint32_t in_row[(NRB + 1) / 2];
+  split_products<SWIGLU, NRB, SLOTS, BUFS>(P, tile, group, shared, nt, As, acc, in_row);
   auto again = [](float v) { return !(fabsf(v) < __builtin_inff()) || fabsf(v) < F_TINY; };
   bool any = false, certain = false;   // (zeros: only if there is something in both operands)
 #pragma unroll
@@ -1519,8 +1532,8 @@ __device__ __forceinline__ void split_tile(const GemmProblem& P, const fmoe_tile
         any |= a;
         certain |= a && acc[rb][f][v] != 0.0f;
       }
-  if (__syncthreads_or(any) && (__syncthreads_or(certain) || lost_in_zero<SWIGLU, NRB>(P, tile, group, shared, nt,
-                                                                                       reinterpret_cast<int*>(As), acc))) {
+  if (__syncthreads_or(any) &&
+      (__syncthreads_or(certain) || lost_in_zero<SWIGLU, NRB>(P, group, nt, reinterpret_cast<int*>(As), acc, in_row))) {
     f32_products<SWIGLU, NRB, 2>(P, tile, group, shared, nt, reinterpret_cast<float*>(As), [&](const f32x4_t (&whole)[NRB][2]) {
 #pragma unroll
       for (int rb = 0; rb < NRB; ++rb)
