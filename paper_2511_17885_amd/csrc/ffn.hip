@@ -1246,7 +1246,7 @@ __device__ __forceinline__ void f32_tile(const GemmProblem& P, const fmoe_tile& 
 //    either equal), with six it was slower still.
 // Measured, fmoe_expert_ffn with weights that are not in the memory-side cache, us, fp32 instruction / split: d 1280, 64
 // experts of 896, two shared, 3000 tokens 1076 / 707, 1600 682 / 447, 416 248 / 224, 64 206 / 190, 16 174 / 164, 8 126 /
-// 122, one 51 / 54; d 4096, 8 experts of 1536, 800 tokens 527 / 368, 8 131 / 123, one 105 / 117; d 2048, 128 experts of 1024,
+// 122, one 51 / 54; d 4096, 8 experts of 1536, 800 tokens 527 / 368, 8 131 / 123, one 105 / 114; d 2048, 128 experts of 1024,
 // 1600 tokens 1023 / 727, 100 546 / 542, 4 149 / 157.  With one token, and with up to four in the last layer and in the
 // smallest (d 896, 8 experts of 896 42 / 44), it is slower: few workgroups, each a chain of LDS passes and barriers.
 // Range: rows are split times 2^96, so that every part of every row value down to fp32's smallest is a normal bf16, and
@@ -1257,8 +1257,9 @@ __device__ __forceinline__ void f32_tile(const GemmProblem& P, const fmoe_tile& 
 // are zero.  Scaling instead of a test on the operands while splitting: one multiplication per row value (a third of
 // the values or less), where finding the largest or the smallest operand takes one instruction per pair of them all,
 // and whether a result is computed again depends on that result alone, not on the others of its tile.  Which rows are zero
-// is gathered while splitting (reading them again took 16 tokens of which 14 are zero 57 -> 65 us).  All of it costs 0 to 4 %
-// with one or two tokens and nothing from eight on.
+// is gathered while splitting, one instruction a piece, in tiles of more than one block: with a second read of the rows 1600
+// tokens of the layer above took 2 % longer.  Against the split alone all of it is within 2 %, and within 4 % for 4 to 150
+// tokens of d 4096, 8 experts of 1536.
 // 896 is where it was measured first and not where the two cross.  Since then, d = d_ffn = K, 64 experts, one / 64 / 416 / 3000
 // tokens, us, fp32 instruction / split: K 128 13.9 / 15.3, 16.0 / 17.6, 21.1 / 20.8, 34.7 / 33.2; 256 17.8 / 19.7, 21.6 / 23.3,
 // 30.0 / 30.6, 68 / 52; 384 24.8 / 25.8, 36.8 / 36.5, 41.0 / 41.0, 131 / 89; 512 28.8 / 30.2, 48.9 / 47.8, 58.9 / 53.7, 179 / 125;
@@ -1365,10 +1366,7 @@ __device__ __forceinline__ void split_products(const GemmProblem& P, const fmoe_
     for (int it = 0; it < IT; ++it) {
       uint2 part[3];
       split_bf16(it < A_IT ? raw[slot][it] * S_ROW_SCALE : raw[slot][it], part);
-      if (it < A_IT) {
-        const u32x4_t b = __builtin_bit_cast(u32x4_t, raw[slot][it]);
-        in_row[it] |= (b[0] | b[1]) | (b[2] | b[3]);
-      }
+      if (NRB > 1 && it < A_IT) in_row[it] |= part[0].x | part[0].y;   // (a scaled value that is not zero has a first part)
       const int row = it < A_IT ? 32 * it : FBM + 32 * (it - A_IT);
 #pragma unroll
       for (int p = 0; p < 3; ++p) *reinterpret_cast<uint2*>(dst + buf * S_BUF + p * S_PLANE + row * FBK) = part[p];
@@ -1469,17 +1467,38 @@ __device__ __forceinline__ void split_products(const GemmProblem& P, const fmoe_
     for (int f = 0; f < 2; ++f) acc[rb][f] = (acc[rb][f] + low[rb][f]) * (1.0f / S_ROW_SCALE);
 }
 
+// Is there something in a row of memory?  Every STEP-th 16 bytes of it from `first` on, up to the first that are not zero.
+template <int STEP>
+__device__ __forceinline__ bool any_bits(const float* row, int first, int K) {
+  constexpr int AHEAD = 16;   // loads in flight
+  uint32_t any = 0;
+  for (int k = first; k < K && any == 0; k += AHEAD * STEP) {
+    u32x4_t v[AHEAD];
+#pragma unroll
+    for (int u = 0; u < AHEAD; ++u) v[u] = *reinterpret_cast<const u32x4_t*>(row + (k + u * STEP < K ? k + u * STEP : first));
+#pragma unroll
+    for (int u = 0; u < AHEAD; ++u) any |= (v[u][0] | v[u][1] | v[u][2] | v[u][3]) & 0x7fffffffu;
+  }
+  return any != 0;
+}
+
 // Is a result zero although neither its row nor its weights are?  Uniform.  Weights are read only for a zero in a row that is
-// not, by a thread up to its first value that is not zero, so that only zero weights are read to their end.  (As: no longer read)
+// not.  The rows of a tile of one block are read here: gathering their bits in its short steps made one token 3 to 4 % slower
+// (d 4096, 8 experts of 1536 112 -> 116 us), reading them makes 16 tokens of which 14 are zero 57 -> 59 (d 1280, 64 of 896).
+// (As: no longer read)
 template <bool SWIGLU, int NRB>
-__device__ __forceinline__ bool lost_in_zero(const GemmProblem& P, int group, int nt, int* As, const f32x4_t (&acc)[NRB][2],
-                                             const uint32_t (&in_row)[(NRB + 1) / 2]) {
+__device__ __forceinline__ bool lost_in_zero(const GemmProblem& P, const fmoe_tile& tile, int group, bool shared, int nt,
+                                             int* As, const f32x4_t (&acc)[NRB][2], const uint32_t (&in_row)[(NRB + 1) / 2]) {
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, K = P.K;
   if (tid < S_ROWS) As[tid] = 0;   // rows of LDS as in the products; 1: something there
   __syncthreads();
+  if constexpr (NRB > 1) {
 #pragma unroll
-  for (int it = 0; it < (NRB + 1) / 2; ++it)
-    if (in_row[it] & 0x7fffffffu) As[32 * it + (tid >> 3)] = 1;
+    for (int it = 0; it < (NRB + 1) / 2; ++it)
+      if (in_row[it] & 0x7fff7fffu) As[32 * it + (tid >> 3)] = 1;
+  } else if (any_bits<64>(gathered_row(P, tile, group, shared, tid >> 4), (tid & 15) * 4, K)) {
+    As[tid >> 4] = 1;
+  }
   __syncthreads();
   uint32_t open = 0;   // this lane's zeros in such rows, a bit each; the bits of a fragment
   constexpr uint32_t FRAG = 0x0f0f0f0fu;
@@ -1497,17 +1516,7 @@ __device__ __forceinline__ bool lost_in_zero(const GemmProblem& P, int group, in
     const int f = (r >> 4) & 1, w = r >> 5;
     const int n = SWIGLU ? nt * 64 + w * 16 + (r & 15) : nt * 128 + r;
     const float* row = (SWIGLU && f ? P.B1 : P.B0) + (size_t)group * P.group_stride + (size_t)(n < P.N ? n : P.N - 1) * P.ldb;
-    constexpr int AHEAD = 8;       // loads in flight
-    const int first = (tid & 7) * 4;
-    uint32_t any = 0;
-    for (int k = first; k < K && any == 0; k += AHEAD * FBK) {
-      u32x4_t v[AHEAD];
-#pragma unroll
-      for (int u = 0; u < AHEAD; ++u) v[u] = *reinterpret_cast<const u32x4_t*>(row + (k + u * FBK < K ? k + u * FBK : first));
-#pragma unroll
-      for (int u = 0; u < AHEAD; ++u) any |= (v[u][0] | v[u][1] | v[u][2] | v[u][3]) & 0x7fffffffu;
-    }
-    if (any) As[FBM + r] = 1;
+    if (any_bits<FBK>(row, (tid & 7) * 4, K)) As[FBM + r] = 1;
   }
   __syncthreads();
   const int c = FBM + wave * 32 + (lane & 15);
@@ -1533,7 +1542,7 @@ __device__ __forceinline__ void split_tile(const GemmProblem& P, const fmoe_tile
         certain |= a && acc[rb][f][v] != 0.0f;
       }
   if (__syncthreads_or(any) &&
-      (__syncthreads_or(certain) || lost_in_zero<SWIGLU, NRB>(P, group, nt, reinterpret_cast<int*>(As), acc, in_row))) {
+      (__syncthreads_or(certain) || lost_in_zero<SWIGLU, NRB>(P, tile, group, shared, nt, reinterpret_cast<int*>(As), acc, in_row))) {
     f32_products<SWIGLU, NRB, 2>(P, tile, group, shared, nt, reinterpret_cast<float*>(As), [&](const f32x4_t (&whole)[NRB][2]) {
 #pragma unroll
       for (int rb = 0; rb < NRB; ++rb)
